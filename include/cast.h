@@ -401,9 +401,9 @@ typedef struct {
     uint64_t zmask;
 } cast_pauli_term;
 
-/* out[0] = sum_m coeff_m <psi|P_m|psi> (real part) and out[1] its imaginary
- * part (round-off for Hermitian sums), accumulated in FP64 for both dtypes
- * with a fixed reduction order.  Synchronous. */
+/* out[0] = sum_m coeff_m <psi|P_m|psi> (real part), accumulated in FP64 for
+ * both dtypes with a fixed reduction order, and out[1] its imaginary part,
+ * which is 0 (real coefficients, Hermitian strings).  Synchronous. */
 cast_status expval(const cast_sv *sv, const cast_pauli_term *terms, size_t n_terms, double *out);
 
 /* Most terms expval_noalloc takes. */
@@ -412,7 +412,7 @@ cast_status expval(const cast_sv *sv, const cast_pauli_term *terms, size_t n_ter
 /* expval for callers that cannot allocate device memory (code under stream
  * capture, tight serving loops, harnesses that forbid hipMalloc): the same
  * result, bit for bit, from the same kernels, with the device scratch
- * (reduction partials and per-term results, 192 KiB) in a fixed array that
+ * (reduction partials and the result, 128 KiB) in a fixed array that
  * each GPU holds from the first call until the process ends.  Calls no
  * hipMalloc/hipFree; on success it allocates no host memory either (fixed
  * arrays on the stack).  n_terms above

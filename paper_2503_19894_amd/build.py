@@ -21,7 +21,11 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-
 # in which registers they read; LLVM's sinking of common code would fold the
 # variants into one body fed by register copies (16 moves per inner product),
 # so it is turned off for that file.
-FILE_FLAGS = {"batch_kernels.hip": ["-mllvm", "-simplifycfg-sink-common=false"]}
+# The expectation-value kernel reads its argument tables at run-time indices
+# from many unrolled places; past LLVM's default of 300 such reads the 3 KiB
+# argument struct would be copied to scratch memory by every lane.
+FILE_FLAGS = {"batch_kernels.hip": ["-mllvm", "-simplifycfg-sink-common=false"],
+              "reduce.hip": ["-mllvm", "-instcombine-max-copied-from-constant-users=100000"]}
 
 
 def sources():

@@ -2,8 +2,8 @@
 // memory (code under stream capture, tight serving loops, harnesses that
 // forbid hipMalloc).
 //
-// expval needs device scratch for the reduction partials of k_pauli_inner
-// and for the per-term results; expval takes it from the reuse pool.  Here it
+// expval needs device scratch for the reduction partials and the result;
+// expval takes it from the reuse pool.  Here it
 // is one file-scope device array per GPU, whose device address is looked up
 // once per device with hipGetSymbolAddress (in host code the array's name is
 // not a device address) and passed to the same kernels expval uses.  Every
@@ -12,7 +12,6 @@
 #include <hip/hip_runtime.h>
 
 #include <cmath>
-#include <complex>
 #include <mutex>
 
 #include "internal.hpp"
@@ -22,10 +21,7 @@ namespace cast {
 
 namespace {
 
-constexpr size_t kNoAllocPartials = 1024 * 2 * kMaxZ;   // reduce_scratch_doubles(), checked below
-constexpr size_t kNoAllocDoubles = kNoAllocPartials + 2 * (size_t)CAST_EXPVAL_NOALLOC_MAX_TERMS;
-
-static __device__ __align__(256) double scratch[kNoAllocDoubles];
+static __device__ __align__(256) double scratch[kReduceScratch + 1];
 
 constexpr int kMaxDevices = 64;
 std::mutex g_sym_mu;
@@ -50,8 +46,6 @@ cast_status scratch_ptr(double **out) {
     return CAST_OK;
 }
 
-const std::complex<double> kIp[4] = {{1, 0}, {0, 1}, {-1, 0}, {0, -1}};
-
 }  // namespace
 
 }  // namespace cast
@@ -67,7 +61,6 @@ cast_status expval_noalloc(const cast_sv *sv, const cast_pauli_term *terms, size
     if (n_terms > (size_t)CAST_EXPVAL_NOALLOC_MAX_TERMS)
         return fail(CAST_EINVAL, "expval_noalloc: more terms than the fixed scratch holds (" +
                                      std::to_string(CAST_EXPVAL_NOALLOC_MAX_TERMS) + ")");
-    if (reduce_scratch_doubles() != kNoAllocPartials) return fail(CAST_EUNSUPPORTED, "reduction scratch size changed");
     const uint64_t full = sv->n >= 64 ? ~0ull : ((1ull << sv->n) - 1);
     for (size_t i = 0; i < n_terms; ++i)
         if ((terms[i].xmask | terms[i].zmask) & ~full) return fail(CAST_EINVAL, "Pauli term acts outside the state");
@@ -75,44 +68,15 @@ cast_status expval_noalloc(const cast_sv *sv, const cast_pauli_term *terms, size
     if (!n_terms) return CAST_OK;
     double *base = nullptr;
     if (cast_status rc = scratch_ptr(&base)) return rc;
-    double *partials = base, *res = base + kNoAllocPartials;
-
-    // Terms sharing an x mask go to one pass, up to kMaxZ z masks at a time;
-    // results land in slot order, slot[i] = the term's place in that order.
-    // Fixed-size host arrays: nothing is allocated, on the host either.
-    uint16_t slot[CAST_EXPVAL_NOALLOC_MAX_TERMS];
-    bool done[CAST_EXPVAL_NOALLOC_MAX_TERMS] = {false};
-    uint32_t next = 0;
-    for (size_t i = 0; i < n_terms; ++i) {
-        if (done[i]) continue;
-        const uint64_t x = terms[i].xmask;
-        size_t j = i;
-        while (j < n_terms) {
-            uint64_t zs[kMaxZ];
-            int nz = 0;
-            const uint32_t first = next;
-            for (; j < n_terms && nz < kMaxZ; ++j) {
-                if (done[j] || terms[j].xmask != x) continue;
-                done[j] = true;
-                slot[j] = (uint16_t)next++;
-                zs[nz++] = terms[j].zmask;
-            }
-            if (!nz) break;
-            if (cast_status rc = pauli_inner(sv->data, sv->data, sv->n, sv->dt, x, zs, nz, partials, res + 2 * first,
-                                             sv->stream))
-                return rc;
-        }
-    }
-    double h[2 * CAST_EXPVAL_NOALLOC_MAX_TERMS];
-    CAST_HIP_TRY(hipMemcpyAsync(h, res, 2 * n_terms * sizeof(double), hipMemcpyDeviceToHost, sv->stream));
+    // fixed-size host array: nothing is allocated, on the host either
+    uint16_t order[CAST_EXPVAL_NOALLOC_MAX_TERMS];
+    if (cast_status rc = expval_sum(sv->data, sv->n, sv->dt, terms, n_terms, order, base, base + kReduceScratch,
+                                    sv->stream))
+        return rc;
+    double e = 0.0;
+    CAST_HIP_TRY(hipMemcpyAsync(&e, base + kReduceScratch, sizeof e, hipMemcpyDeviceToHost, sv->stream));
     CAST_HIP_TRY(hipStreamSynchronize(sv->stream));
-    std::complex<double> e = 0;
-    for (size_t i = 0; i < n_terms; ++i) {
-        const std::complex<double> S(h[2 * slot[i]], h[2 * slot[i] + 1]);
-        e += terms[i].coeff * kIp[__builtin_popcountll(terms[i].xmask & terms[i].zmask) & 3] * S;
-    }
-    out[0] = e.real();
-    out[1] = e.imag();
+    out[0] = e;
     return CAST_OK;
 }
 

@@ -14,6 +14,8 @@ namespace cast {
 
 static const cplx kIpow[4] = {cplx(1, 0), cplx(0, 1), cplx(-1, 0), cplx(0, -1)};
 
+constexpr size_t kExpvalTerms = 65536;   // terms per expval_sum call
+
 // Terms grouped by x mask, in first-appearance order of the x masks.
 struct Grouped {
     std::vector<uint64_t> x;
@@ -62,18 +64,6 @@ struct DevBuf {
     template <typename T> T *as() const { return (T *)p; }
 };
 
-// Queues all z-groups of one x-mask; results (re, im per term) land in
-// dev_out[2 * slot(term)].
-static cast_status queue_pauli_inner(const void *a, const void *b, int n, cast_dtype dt, uint64_t x,
-                                     const std::vector<uint64_t> &zs, double *scratch, double *dev_out,
-                                     hipStream_t s) {
-    for (size_t j0 = 0; j0 < zs.size(); j0 += kMaxZ) {
-        const int nz = (int)std::min<size_t>(kMaxZ, zs.size() - j0);
-        if (cast_status rc = pauli_inner(a, b, n, dt, x, zs.data() + j0, nz, scratch, dev_out + 2 * j0, s)) return rc;
-    }
-    return CAST_OK;
-}
-
 static void gen_masks(const int *qubits, int k, int generator, uint64_t *x, uint64_t *z) {
     *x = 0;
     *z = 0;
@@ -96,34 +86,21 @@ cast_status expval(const cast_sv *sv, const cast_pauli_term *terms, size_t n_ter
     if (cast_status rc = check_terms(sv->n, terms, n_terms)) return rc;
     out[0] = out[1] = 0.0;
     if (!n_terms) return CAST_OK;
-    Grouped g = group_by_x(terms, n_terms);
-    DevBuf scratch(sv->stream), res(sv->stream);
-    if (cast_status rc = scratch.alloc(reduce_scratch_doubles() * sizeof(double))) return rc;
-    if (cast_status rc = res.alloc(2 * n_terms * sizeof(double))) return rc;
-    std::vector<size_t> slot_of(n_terms);
-    size_t slot = 0;
-    for (size_t gi = 0; gi < g.x.size(); ++gi) {
-        std::vector<uint64_t> zs;
-        for (size_t i : g.idx[gi]) {
-            zs.push_back(terms[i].zmask);
-            slot_of[i] = slot++;
-        }
-        const size_t first = slot_of[g.idx[gi][0]];
-        if (cast_status rc = queue_pauli_inner(sv->data, sv->data, sv->n, sv->dt, g.x[gi], zs, scratch.as<double>(),
-                                               res.as<double>() + 2 * first, sv->stream))
+    DevBuf scratch(sv->stream);
+    if (cast_status rc = scratch.alloc((kReduceScratch + 1) * sizeof(double))) return rc;
+    double *res = scratch.as<double>() + kReduceScratch, sum = 0.0;
+    std::vector<uint16_t> order(std::min(n_terms, kExpvalTerms));
+    for (size_t i = 0; i < n_terms; i += kExpvalTerms) {
+        const size_t m = std::min(n_terms - i, kExpvalTerms);
+        if (cast_status rc = expval_sum(sv->data, sv->n, sv->dt, terms + i, m, order.data(), scratch.as<double>(), res,
+                                        sv->stream))
             return rc;
+        double part = 0.0;
+        CAST_HIP_TRY(hipMemcpyAsync(&part, res, sizeof part, hipMemcpyDeviceToHost, sv->stream));
+        CAST_HIP_TRY(hipStreamSynchronize(sv->stream));
+        sum += part;
     }
-    std::vector<double> h(2 * n_terms);
-    CAST_HIP_TRY(hipMemcpyAsync(h.data(), res.p, h.size() * sizeof(double), hipMemcpyDeviceToHost, sv->stream));
-    CAST_HIP_TRY(hipStreamSynchronize(sv->stream));
-    cplx e = 0;
-    for (size_t i = 0; i < n_terms; ++i) {
-        const size_t s = slot_of[i];
-        const cplx S(h[2 * s], h[2 * s + 1]);
-        e += terms[i].coeff * kIpow[__builtin_popcountll(terms[i].xmask & terms[i].zmask) & 3] * S;
-    }
-    out[0] = e.real();
-    out[1] = e.imag();
+    out[0] = sum;
     return CAST_OK;
 }
 
@@ -184,7 +161,7 @@ cast_status adjoint_grad(const cast_sv *init, const cast_gate *gates, size_t n_g
     DevBuf psi(s), lam(s), scratch(s), res(s), tgroups(s), tterms(s);
     if (cast_status rc = psi.alloc(sbytes)) return rc;
     if (cast_status rc = lam.alloc(sbytes)) return rc;
-    if (cast_status rc = scratch.alloc(reduce_scratch_doubles() * sizeof(double))) return rc;
+    if (cast_status rc = scratch.alloc(kReduceScratch * sizeof(double))) return rc;
     if (cast_status rc = res.alloc((2 + 2 * (size_t)nslots) * sizeof(double))) return rc;
     CAST_HIP_TRY(hipMemcpyAsync(psi.p, init->data, sbytes, hipMemcpyDeviceToDevice, s));
     // ---- forward
@@ -212,8 +189,7 @@ cast_status adjoint_grad(const cast_sv *init, const cast_gate *gates, size_t n_g
     } else {
         CAST_HIP_TRY(hipMemsetAsync(lam.p, 0, sbytes, s));
     }
-    const uint64_t z0 = 0;
-    if (cast_status rc = pauli_inner(psi.p, lam.p, n, dt, 0, &z0, 1, scratch.as<double>(), res.as<double>(), s))
+    if (cast_status rc = pauli_inner(psi.p, lam.p, n, dt, 0, 0, scratch.as<double>(), res.as<double>(), s))
         return rc;
     // ---- reverse sweep
     std::vector<uint64_t> gx(n_gates), gz(n_gates);
@@ -221,7 +197,7 @@ cast_status adjoint_grad(const cast_sv *init, const cast_gate *gates, size_t n_g
         const cast_gate &gg = gates[li];
         if (slot[li] >= 0) {
             gen_masks(gg.qubits, gg.k, gg.generator, &gx[li], &gz[li]);
-            if (cast_status rc = pauli_inner(lam.p, psi.p, n, dt, gx[li], &gz[li], 1, scratch.as<double>(),
+            if (cast_status rc = pauli_inner(lam.p, psi.p, n, dt, gx[li], gz[li], scratch.as<double>(),
                                              res.as<double>() + 2 + 2 * slot[li], s))
                 return rc;
         }

@@ -8,8 +8,6 @@
 
 namespace cast {
 
-constexpr int kMaxZ = 8;  // z-masks evaluated per pass of k_pauli_inner
-
 struct PauliSumGroup {
     uint64_t x;
     int first, count;
@@ -19,13 +17,19 @@ struct PauliSumTerm {
     double cre, cim;  // coefficient times i^{|x&z|}
 };
 
-// Doubles of device scratch pauli_inner needs.
-size_t reduce_scratch_doubles();
+// Doubles of device scratch pauli_inner and expval_sum need.
+constexpr size_t kReduceScratch = 16384;
 
-// dev_out[2j], dev_out[2j+1] = re, im of S(x, z_j) = sum_y conj(a[y^x]) (-1)^{|z_j & y|} b[y]
-// for j < nz (1 <= nz <= 8), FP64, fixed reduction order.  Stream-ordered.
-cast_status pauli_inner(const void *a, const void *b, int n, cast_dtype dt, uint64_t x, const uint64_t *z, int nz,
-                        double *scratch, double *dev_out, hipStream_t s);
+// dev_out[0], dev_out[1] = re, im of S(x, z) = sum_y conj(a[y^x]) (-1)^{|z & y|} b[y],
+// FP64, fixed reduction order.  Stream-ordered.
+cast_status pauli_inner(const void *a, const void *b, int n, cast_dtype dt, uint64_t x, uint64_t z, double *scratch,
+                        double *dev_out, hipStream_t s);
+
+// dev_out[0] = sum_m coeff_m <psi|P_m|psi> (1 <= n_terms <= 65536; real, since every P_m is Hermitian),
+// FP64, fixed reduction order.  `order`: host scratch, n_terms entries.  Stream-ordered; the terms are consumed
+// before it returns.
+cast_status expval_sum(const void *psi, int n, cast_dtype dt, const cast_pauli_term *terms, size_t n_terms,
+                       uint16_t *order, double *scratch, double *dev_out, hipStream_t s);
 
 // out = (sum of Pauli terms) psi; term tables in device memory.  out != psi.
 cast_status apply_pauli_sum(const void *psi, void *out, int n, cast_dtype dt, const PauliSumGroup *dgroups,
