@@ -17,14 +17,18 @@ COMMON = ["--offload-arch=gfx950", "-O3", "-fPIC", "-std=c++17", "-Wall", "-Wno-
 
 
 # Per-file compiler options.  The register sweeps of the batched kernels
-# dispatch on a gate's sweep bits to fully unrolled variants that differ only
-# in which registers they read; LLVM's sinking of common code would fold the
-# variants into one body fed by register copies (16 moves per inner product),
-# so it is turned off for that file.
+# dispatch on an operation's code to fully unrolled variants.  LLVM's sinking
+# of common code would fold variants that differ only in the registers they
+# read into one body fed by register copies (16 moves per inner product), so
+# it is turned off for that file; and its control-flow structuriser, which
+# divergent branches need, would also linearise the dispatch, which is
+# uniform, with a copy of all amplitudes at each join (34 moves per
+# operation), so it is told to leave uniform regions alone.
 # The expectation-value kernel reads its argument tables at run-time indices
 # from many unrolled places; past LLVM's default of 300 such reads the 3 KiB
 # argument struct would be copied to scratch memory by every lane.
-FILE_FLAGS = {"batch_kernels.hip": ["-mllvm", "-simplifycfg-sink-common=false"],
+FILE_FLAGS = {"batch_kernels.hip": ["-mllvm", "-simplifycfg-sink-common=false",
+                                    "-mllvm", "-structurizecfg-skip-uniform-regions"],
               "reduce.hip": ["-mllvm", "-instcombine-max-copied-from-constant-users=100000"]}
 
 

@@ -15,12 +15,17 @@
 
 namespace cast {
 
-static const cplx kIpowB[4] = {cplx(1, 0), cplx(0, 1), cplx(-1, 0), cplx(0, -1)};
-
 struct HostOp {
     uint32_t kind;
-    int gate;            // gate index (FWD/ADJ)
-    int slot;
+    std::vector<int> gates;   // FWD/ADJ: gates in processing order
+};
+
+// Coefficients of a rotation operation, rewritten for every run: the angle
+// is the sum over its gates (equal rotations that met in a segment).
+struct BoundOp {
+    uint64_t mat;             // offset in reals
+    bool dagger, diag;        // U^dag; diagonal generator (phase form)
+    std::vector<int> gates;
 };
 
 struct InstPlan {
@@ -28,16 +33,12 @@ struct InstPlan {
     std::vector<cast_gate> gates;          // copied descriptors
     std::vector<std::vector<cplx>> fixed;  // fixed matrices (sorted-qubit order), per gate
     std::vector<int> sq0, sq1;             // sorted targets per gate
-    std::vector<int> form;                 // BatchForm of each gate's matrix (all parameter values)
-    std::vector<uint32_t> neg;             // BF_SIGN: local indices of the -1 diagonal entries
-    std::vector<uint32_t> xl, zl;          // local generator masks per gate
-    std::vector<int> gen_sorted;           // generator letters in sorted local order
-    std::vector<uint64_t> gx, gz;          // global generator masks per gate
+    std::vector<char> diag;                // diagonal for every parameter value
+    std::vector<uint64_t> gx, gz;          // generator masks per gate (qubits)
     std::vector<int> gslot;                // result slot per gate (-1: none)
     std::vector<HostOp> ops;
+    std::vector<BoundOp> bound;
     int tb = 0;                            // tile bits of this instance's segments
-    std::vector<std::vector<int>> seg_gates;   // per op (FWD/ADJ): gates in processing order
-    std::vector<uint64_t> mat_fwd, mat_adj;  // matrix offsets (complex entries) per gate
     size_t nparams = 0;
     int nslots = 0;
     uint32_t wgs = 1;
@@ -54,20 +55,21 @@ struct cast_batch {
     // device
     void *states = nullptr;
     cast::BatchRec *d_recs = nullptr;
-    cast::SegGate *d_segs = nullptr;
+    cast::SegOp *d_ops = nullptr;
+    uint32_t *d_slots = nullptr;
     cast::SegSweep *d_sweeps = nullptr;
     size_t lds_bytes = 0;
     uint64_t *d_step_rec = nullptr, *d_step_item = nullptr;
     cast::BatchInst *d_insts = nullptr;
     void *d_mats = nullptr;
-    cast::PauliSumGroup *d_tg = nullptr;
-    cast::PauliSumTerm *d_tt = nullptr;
+    cast::BatchHGroup *d_tg = nullptr;
+    cast::BatchHTerm *d_tt = nullptr;
     double *d_partials = nullptr, *d_results = nullptr;
     unsigned long long *d_counters = nullptr;
     // host
     void *h_mats = nullptr;      // pinned, matrices in the state dtype
     double *h_results = nullptr; // pinned
-    size_t mat_entries = 0, result_doubles = 0;
+    size_t mat_reals = 0, result_doubles = 0;
     std::vector<uint64_t> step_rec, step_item;
     std::vector<uint64_t> step_items;   // items per step
     std::vector<size_t> step_lds;       // LDS bytes of each step's launch
@@ -90,39 +92,6 @@ static void sorted_matrix(int k, const int *qubits, const std::vector<cplx> &m, 
     *q0 = p.q[0];
     *q1 = k == 2 ? p.q[1] : -1;
     *out = p.full;
-}
-
-// Writes a gate's matrix entry into the pinned table in the state dtype: its
-// 2^k x 2^k entries row-major (dagger: those of the adjoint), or compactly
-// for the forms the batched kernels read so: a two-qubit diagonal its four
-// diagonal entries; a Pauli pair (BF_PAULI, masks xm / zm) a and b of
-// y_r = a x_r + b (-1)^{popc(zm & (r ^ xm))} x_{r ^ xm}.
-static void put_matrix(cast_batch *b, uint64_t off, const cplx *m, bool dagger, int k, int form, uint32_t xm,
-                       uint32_t zm) {
-    const int D = 1 << k;
-    auto put = [&](uint64_t e, cplx z) {
-        if (b->dt == CAST_C128) {
-            ((double *)b->h_mats)[2 * e] = z.real();
-            ((double *)b->h_mats)[2 * e + 1] = z.imag();
-        } else {
-            ((float *)b->h_mats)[2 * e] = (float)z.real();
-            ((float *)b->h_mats)[2 * e + 1] = (float)z.imag();
-        }
-    };
-    auto at = [&](int r, int c) { return dagger ? std::conj(m[(size_t)c * D + r]) : m[(size_t)r * D + c]; };
-    if (k == 2 && (form == BF_DIAG || form == BF_PAULI)) {
-        if (form == BF_DIAG) {
-            for (int r = 0; r < D; ++r) put(off + r, at(r, r));
-        } else {
-            put(off, at(0, 0));
-            put(off + 1, at(0, (int)xm) * ((__builtin_popcount(zm & xm) & 1) ? -1.0 : 1.0));
-            for (int e = 2; e < D; ++e) put(off + e, 0.0);
-        }
-        for (int e = D; e < D * D; ++e) put(off + e, 0.0);
-        return;
-    }
-    for (int r = 0; r < D; ++r)
-        for (int c = 0; c < D; ++c) put(off + (uint64_t)r * D + c, at(r, c));
 }
 
 // Whether a two-qubit matrix is a I + b P for one Pauli string P that flips
@@ -156,38 +125,110 @@ static bool pauli_pair(const std::vector<cplx> &m, uint32_t *xm, uint32_t *zm) {
     return false;
 }
 
-// exp(-i a P / 2) = cos(a/2) I - i sin(a/2) P with P a Pauli string (2-bit
-// letters in local bit order): P has one nonzero per row, at column r ^ x.
-static void bind_rotation(cast_batch *b, uint64_t off, int k, int gen, double angle, bool dagger, int form,
-                          uint32_t xm, uint32_t zm) {
-    const int D = 1 << k;
-    const double c = std::cos(angle / 2), s = std::sin(angle / 2) * (dagger ? -1.0 : 1.0);
-    uint32_t x = 0;
-    for (int i = 0; i < k; ++i) {
-        const int L = (gen >> (2 * i)) & 3;
-        if (L == 1 || L == 2) x |= 1u << i;
-    }
-    cplx m[16];
-    for (int e = 0; e < D * D; ++e) m[e] = 0.0;
-    for (int r = 0; r < D; ++r) {
-        // P[r][r ^ x] = prod_i f(letter_i, bit_i(r)); Y: [[0,-i],[i,0]], Z: diag(1,-1)
-        cplx p = 1.0;
-        for (int i = 0; i < k; ++i) {
-            const int L = (gen >> (2 * i)) & 3, bit = (r >> i) & 1;
-            if (L == 2) p *= bit ? cplx(0, 1) : cplx(0, -1);
-            else if (L == 3 && bit) p = -p;
+// (cos, sin) of a rotation -> (t, sin) of its three shears, up to a common
+// sign: cos >= 0 keeps |t| <= 1.
+static void shear_coefs(double *cs) {
+    if (cs[0] < 0) cs[0] = -cs[0], cs[1] = -cs[1];
+    cs[0] = -cs[1] / (1.0 + cs[0]);
+}
+
+// Operation code and coefficients (FP64; dagger: of the adjoint) of a fixed
+// gate on sweep bits t0 < t1 (t1 = -1: one qubit), local bit i of its matrix
+// index belonging to t_i.
+static uint32_t fixed_op(const std::vector<cplx> &mat, int t0, int t1, bool dagger, bool c128,
+                         std::vector<double> *out) {
+    const int D = t1 < 0 ? 2 : 4, bit = t0, pair = t1 < 0 ? 0 : t0 + t1 - 1;
+    auto at = [&](int r, int c) { return dagger ? std::conj(mat[(size_t)c * D + r]) : mat[(size_t)r * D + c]; };
+    auto put = [&](cplx z) { out->push_back(z.real()), out->push_back(z.imag()); };
+    bool diag = true, real = true, sign = true;
+    for (int r = 0; r < D; ++r)
+        for (int c = 0; c < D; ++c) {
+            const cplx z = mat[(size_t)r * D + c];
+            if (r != c && z != cplx(0, 0)) diag = false;
+            if (z.imag() != 0.0) real = false;
+            if (r == c && z != cplx(1, 0) && z != cplx(-1, 0)) sign = false;
         }
-        m[r * D + r] += c;
-        m[r * D + (r ^ (int)x)] += cplx(0, -1) * s * p;  // dagger: conj of a Hermitian P's coefficient
+    const cplx one(1, 0);
+    // local masks of a one- or two-qubit Pauli string -> sweep bits
+    auto spread = [&](uint32_t m) { return ((m & 1u) << t0) | (t1 < 0 ? 0u : ((m >> 1) & 1u) << t1); };
+    if (diag && sign) {
+        uint32_t neg = 0;
+        for (int r = 0; r < D; ++r)
+            if (mat[(size_t)r * D + r] == -one) neg |= 1u << r;
+        if (D == 4 && neg == 8u) return SO_CZ + pair;
+        uint32_t neg8 = 0;
+        for (uint32_t j = 0; j < 8; ++j) {
+            const uint32_t loc = ((j >> t0) & 1u) | (t1 < 0 ? 0u : ((j >> t1) & 1u) << 1);
+            neg8 |= ((neg >> loc) & 1u) << j;
+        }
+        return SO_SIGN | neg8 << 8;
     }
-    // U^dag = cos I + i sin P; the loop above used -s for it, and P is Hermitian
-    put_matrix(b, off, m, false, k, form, xm, zm);
+    if (diag && D == 2) {
+        if (c128 && mat[0] == one) {   // a phase on bit 1: the diagonal rotation's form
+            put(at(1, 1));
+            return spread(1);
+        }
+        for (int r = 0; r < D; ++r) put(at(r, r));
+        return SO_DIAG1 + bit;
+    }
+    if (diag) {
+        if (mat[0] == one && mat[5] == one && mat[10] == one) {
+            put(at(3, 3));
+            return SO_CP + pair;
+        }
+        for (int r = 0; r < D; ++r) put(at(r, r));
+        return SO_DIAG2 + pair;
+    }
+    if (real) {
+        for (int r = 0; r < D; ++r)
+            for (int c = 0; c < D; ++c) out->push_back(at(r, c).real());
+        return (D == 2 ? SO_REAL1 + bit : SO_REAL2 + pair);
+    }
+    // c I - i s P: the rotation's form (complex128: its shears are orthogonal
+    // whatever c and s, so they need a unitary matrix)
+    auto rotation = [&](double c, double s) {
+        if (c128 && std::fabs(c * c + s * s - 1.0) > 4e-16) return false;
+        double cs[2] = {c, s};
+        if (c128) shear_coefs(cs);
+        out->insert(out->end(), cs, cs + 2);
+        return true;
+    };
+    if (D == 2 && mat[0] == mat[3] && mat[1] == mat[2] && mat[0].imag() == 0.0 && mat[1].real() == 0.0 &&
+        rotation(mat[0].real(), -at(0, 1).imag()))
+        return 8 * spread(1);
+    uint32_t xm, zm;
+    if (D == 4 && pauli_pair(mat, &xm, &zm)) {
+        const cplx a = at(0, 0), b = at(0, (int)xm) * ((__builtin_popcount(zm & xm) & 1) ? -1.0 : 1.0);
+        const int pw = __builtin_popcount(xm & zm);
+        // every row agrees with b exactly, so that the pair stands for the matrix
+        bool same = true;
+        for (int r = 0; r < D; ++r)
+            same &= at(r, r ^ (int)xm) == b * ((__builtin_popcount(zm & (r ^ xm)) & 1) ? -1.0 : 1.0);
+        const bool two_qubit = (xm | zm) == 3u;
+        if (same && two_qubit && a.imag() == 0.0 && (pw & 1 ? b.imag() : b.real()) == 0.0 &&
+            rotation(a.real(), pw == 0 ? -b.imag() : pw == 1 ? b.real() : b.imag()))
+            return 8 * spread(xm) + spread(zm);
+        put(a);
+        put(b);
+        return (SO_PAULI + spread(xm)) | spread(zm) << 8;
+    }
+    for (int r = 0; r < D; ++r)
+        for (int c = 0; c < D; ++c) put(at(r, c));
+    return D == 2 ? SO_GEN1 + bit : SO_GEN2 + pair;
+}
+
+// Writes coefficients into the pinned table in the state dtype.
+static void put_reals(cast_batch *b, uint64_t off, const double *v, size_t n) {
+    for (size_t i = 0; i < n; ++i) {
+        if (b->dt == CAST_C128) ((double *)b->h_mats)[off + i] = v[i];
+        else ((float *)b->h_mats)[off + i] = (float)v[i];
+    }
 }
 
 static cast_status queue_program(cast_batch *b) {
     hipStream_t s = b->stream;
     const size_t rsz = b->dt == CAST_C128 ? 8 : 4;
-    CAST_HIP_TRY(hipMemcpyAsync(b->d_mats, b->h_mats, b->mat_entries * 2 * rsz, hipMemcpyHostToDevice, s));
+    CAST_HIP_TRY(hipMemcpyAsync(b->d_mats, b->h_mats, b->mat_reals * rsz, hipMemcpyHostToDevice, s));
     if (cast_status rc = batch_init_states(b->dev, b->dt, s)) return rc;
     if (b->mode == 2) {
         if (cast_status rc = batch_zero(b->d_counters, 2 + (size_t)b->ninst, s)) return rc;
@@ -214,7 +255,8 @@ static void free_batch(cast_batch *b) {
     if (b->graph) (void)hipGraphDestroy(b->graph);
     dev_free(b->states);
     dev_free(b->d_recs);
-    dev_free(b->d_segs);
+    dev_free(b->d_ops);
+    dev_free(b->d_slots);
     dev_free(b->d_sweeps);
     dev_free(b->d_step_rec);
     dev_free(b->d_step_item);
@@ -433,8 +475,8 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
     b->dt = dt;
     b->mode = mode;
     b->inst.resize(n_inst);
-    std::vector<PauliSumGroup> tg;
-    std::vector<PauliSumTerm> tt;
+    std::vector<BatchHGroup> tg;
+    std::vector<BatchHTerm> tt;
     std::vector<BatchInst> hinst(n_inst);
     size_t state_elems = 0;
     // amplitudes per work item, and the cache budget of an instance group
@@ -447,7 +489,7 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         if (mode != 2) group_bytes = atof(e) * (1 << 20);
     if (const char *e = std::getenv("CAST_PERSISTENT_GROUP_MB"))
         if (mode == 2) group_bytes = atof(e) * (1 << 20);
-    uint64_t mat_entries = 0, part = 0, res = 0;
+    uint64_t part = 0, res = 0;
     auto bail = [&](cast_status rc) {
         free_batch(b);
         return rc;
@@ -462,18 +504,12 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         ip.gates.assign(circuits[i], circuits[i] + n_gates[i]);
         const size_t L = ip.gates.size();
         ip.fixed.resize(L);
-        ip.form.assign(L, BF_GENERAL);
-        ip.neg.assign(L, 0);
+        ip.diag.assign(L, 0);
         ip.sq0.resize(L);
         ip.sq1.resize(L);
-        ip.xl.assign(L, 0);
-        ip.zl.assign(L, 0);
-        ip.gen_sorted.assign(L, 0);
         ip.gx.assign(L, 0);
         ip.gz.assign(L, 0);
         ip.gslot.assign(L, -1);
-        ip.mat_fwd.resize(L);
-        ip.mat_adj.resize(L);
         int slot = 1;  // slot 0: energy
         for (size_t l = 0; l < L; ++l) {
             const cast_gate &g = ip.gates[l];
@@ -484,87 +520,42 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
                     if (g.qubits[a] == g.qubits[c]) return bail(fail(CAST_EINVAL, "duplicate gate qubit"));
             }
             const int D = 1 << g.k;
-            std::vector<cplx> m((size_t)D * D);
             if (g.param_id >= 0) {
                 if ((size_t)g.param_id >= ip.nparams) return bail(fail(CAST_EINVAL, "param_id out of range"));
                 if (g.generator <= 0 || g.generator >= (1 << (2 * g.k)))
                     return bail(fail(CAST_EINVAL, "parametrised gate needs a Pauli generator"));
-                m = rotation_matrix(g.k, g.generator, 0.0);  // placeholder; bound in batch_run
                 ip.gslot[l] = slot++;
-            } else {
-                if (!g.matrix) return bail(fail(CAST_EINVAL, "fixed gate without a matrix"));
-                for (int e = 0; e < D * D; ++e) m[e] = cplx(g.matrix[2 * e], g.matrix[2 * e + 1]);
-            }
-            sorted_matrix(g.k, g.qubits, m, &ip.sq0[l], &ip.sq1[l], &ip.fixed[l]);
-            // generator masks: global and in sorted local bits
-            for (int a = 0; a < g.k && g.param_id >= 0; ++a) {
-                const int letter = (g.generator >> (2 * a)) & 3;
-                const int q = g.qubits[a];
-                const int lb = (q == ip.sq0[l]) ? 0 : 1;
-                if (letter == 1 || letter == 2) ip.gx[l] |= 1ull << q, ip.xl[l] |= 1u << lb;
-                if (letter == 2 || letter == 3) ip.gz[l] |= 1ull << q, ip.zl[l] |= 1u << lb;
-                ip.gen_sorted[l] |= letter << (2 * lb);
-            }
-            // form: exp(-i a P / 2) = cos I - i sin P is diagonal when P has no X or Y
-            // letter and real when P has an odd number of Y letters (P imaginary);
-            // a fixed gate's form is read off its matrix
-            if (g.param_id >= 0) {
-                int nx = 0, ny = 0;
                 for (int a = 0; a < g.k; ++a) {
                     const int letter = (g.generator >> (2 * a)) & 3;
-                    nx += letter == 1;
-                    ny += letter == 2;
+                    if (letter == 1 || letter == 2) ip.gx[l] |= 1ull << g.qubits[a];
+                    if (letter == 2 || letter == 3) ip.gz[l] |= 1ull << g.qubits[a];
                 }
-                if (nx == 0 && ny == 0) ip.form[l] = BF_DIAG;
-                else if (ny % 2 == 1) ip.form[l] = BF_REAL;
-                else if (g.k == 2) ip.form[l] = BF_PAULI;   // masks: the generator's
-            } else {
-                bool diag = true, real = true, sign = true;
-                for (int r = 0; r < D; ++r)
-                    for (int c = 0; c < D; ++c) {
-                        const cplx z = ip.fixed[l][(size_t)r * D + c];
-                        if (r != c && z != cplx(0, 0)) diag = false;
-                        if (z.imag() != 0.0) real = false;
-                        if (r == c && z != cplx(1, 0) && z != cplx(-1, 0)) sign = false;
-                    }
-                ip.form[l] = diag ? (sign ? BF_SIGN : BF_DIAG) : real ? BF_REAL : BF_GENERAL;
-                for (int r = 0; r < D && ip.form[l] == BF_SIGN; ++r)
-                    if (ip.fixed[l][(size_t)r * D + r] == cplx(-1, 0)) ip.neg[l] |= 1u << r;
-                uint32_t xm, zm;
-                if (ip.form[l] == BF_GENERAL && g.k == 2 && pauli_pair(ip.fixed[l], &xm, &zm)) {
-                    ip.form[l] = BF_PAULI;
-                    ip.xl[l] = xm;   // a fixed gate has no generator: its Pauli pair's masks
-                    ip.zl[l] = zm;
-                }
+                ip.sq0[l] = g.k == 2 ? std::min(g.qubits[0], g.qubits[1]) : g.qubits[0];
+                ip.sq1[l] = g.k == 2 ? std::max(g.qubits[0], g.qubits[1]) : -1;
+                ip.diag[l] = ip.gx[l] == 0;
+                continue;
             }
-            ip.mat_fwd[l] = mat_entries;
-            mat_entries += (uint64_t)D * D;
-            ip.mat_adj[l] = mat_entries;
-            mat_entries += (uint64_t)D * D;
+            if (!g.matrix) return bail(fail(CAST_EINVAL, "fixed gate without a matrix"));
+            std::vector<cplx> m((size_t)D * D);
+            for (int e = 0; e < D * D; ++e) m[e] = cplx(g.matrix[2 * e], g.matrix[2 * e + 1]);
+            sorted_matrix(g.k, g.qubits, m, &ip.sq0[l], &ip.sq1[l], &ip.fixed[l]);
+            ip.diag[l] = 1;
+            for (int e = 0; e < D * D; ++e)
+                if (e / D != e % D && ip.fixed[l][e] != cplx(0, 0)) ip.diag[l] = 0;
         }
         ip.nslots = slot;
         // segments (forward order, then reverse order) whose qubits together
         // fit one tile of 2^tb amplitudes
         ip.tb = std::min(n, tile_bits);
         std::vector<uint64_t> gmask(L, 0);
-        std::vector<char> gdiag(L, 0);
-        for (size_t l = 0; l < L; ++l) {
+        for (size_t l = 0; l < L; ++l)
             for (int a = 0; a < ip.gates[l].k; ++a) gmask[l] |= 1ull << ip.gates[l].qubits[a];
-            gdiag[l] = ip.form[l] == BF_DIAG || ip.form[l] == BF_SIGN;
-        }
         auto segment = [&](bool reverse) {
-            return segment_gates(gmask, gdiag, ip.tb, reverse, batch_reorder(), batch_min_window(dt, ip.tb));
+            return segment_gates(gmask, ip.diag, ip.tb, reverse, batch_reorder(), batch_min_window(dt, ip.tb));
         };
-        for (auto &sg : segment(false)) {
-            ip.ops.push_back(HostOp{BK_FWD, -1, -1});
-            ip.seg_gates.push_back(sg);
-        }
-        ip.ops.push_back(HostOp{BK_HPSI, -1, 0});
-        ip.seg_gates.emplace_back();
-        for (auto &sg : segment(true)) {
-            ip.ops.push_back(HostOp{BK_ADJ, -1, -1});
-            ip.seg_gates.push_back(sg);
-        }
+        for (auto &sg : segment(false)) ip.ops.push_back(HostOp{BK_FWD, sg});
+        ip.ops.push_back(HostOp{BK_HPSI, {}});
+        for (auto &sg : segment(true)) ip.ops.push_back(HostOp{BK_ADJ, sg});
         ip.wgs = 1u << (n - ip.tb);
         // Hamiltonian, grouped by x mask
         if (n_terms[i] && !hams[i]) return bail(fail(CAST_EINVAL, "Hamiltonian is NULL"));
@@ -574,30 +565,31 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         bi.wgs = ip.wgs;
         bi.tg_off = (uint32_t)tg.size();
         bi.tt_off = (uint32_t)tt.size();
-        std::map<uint64_t, std::vector<size_t>> byx;
-        std::vector<uint64_t> order;
+        std::map<std::pair<uint64_t, int>, std::vector<size_t>> byx;   // x mask, parity of |x & z|
+        std::vector<std::pair<uint64_t, int>> order;
         const uint64_t full = (1ull << n) - 1;
         for (size_t t = 0; t < n_terms[i]; ++t) {
             const cast_pauli_term &pt = hams[i][t];
             if ((pt.xmask | pt.zmask) & ~full) return bail(fail(CAST_EINVAL, "Pauli term acts outside the state"));
-            if (!byx.count(pt.xmask)) order.push_back(pt.xmask);
-            byx[pt.xmask].push_back(t);
+            const std::pair<uint64_t, int> key(pt.xmask, __builtin_popcountll(pt.xmask & pt.zmask) & 1);
+            if (!byx.count(key)) order.push_back(key);
+            byx[key].push_back(t);
         }
-        int first = 0;
-        for (uint64_t x : order) {
-            tg.push_back(PauliSumGroup{x, first, (int)byx[x].size()});
-            for (size_t t : byx[x]) {
+        uint32_t first = 0;
+        for (auto &key : order) {
+            tg.push_back(BatchHGroup{key.first, first, (uint32_t)byx[key].size(), (uint32_t)key.second, 0});
+            for (size_t t : byx[key]) {
                 const cast_pauli_term &pt = hams[i][t];
-                const cplx c = pt.coeff * kIpowB[__builtin_popcountll(pt.xmask & pt.zmask) & 3];
-                tt.push_back(PauliSumTerm{pt.zmask, c.real(), c.imag()});
+                // i^{|x & z|}: 1, i, -1, -i
+                tt.push_back(BatchHTerm{pt.zmask, __builtin_popcountll(pt.xmask & pt.zmask) & 2 ? -pt.coeff : pt.coeff});
                 ++first;
             }
         }
         bi.ngroups = (uint32_t)order.size();
         bi.part_off = part;
-        part += 2ull * ip.nslots * ip.wgs;
+        part += (uint64_t)ip.nslots * ip.wgs;
         bi.res_off = res;
-        res += 2ull * ip.nslots;
+        res += (uint64_t)ip.nslots;
         bi.init_kind = init_kind ? init_kind[i] : 0;
         if (bi.init_kind < 0 || bi.init_kind > 2) return bail(fail(CAST_EINVAL, "bad init kind"));
         if (bi.init_kind == 2) {
@@ -608,8 +600,6 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         }
         state_elems += 2ull << n;  // psi and lambda
     }
-    if (mat_entries > 0xffffffffull) return bail(fail(CAST_EUNSUPPORTED, "batch matrix table exceeds 2^32 entries"));
-    b->mat_entries = mat_entries;
     b->result_doubles = res;
     // ---- instance groups (consecutive instances whose psi and lambda fit the
     // cache budget run their whole programs before the next group), then
@@ -642,8 +632,10 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         }
     }
     std::vector<BatchRec> recs;
-    std::vector<SegGate> segs;
+    std::vector<SegOp> segs;
+    std::vector<uint32_t> slots;
     std::vector<SegSweep> sweeps;
+    std::vector<double> coefs;   // fixed gates' coefficients; rotations are bound per run
     uint64_t item_base = 0;
     for (auto &gr : groups) {
     size_t max_ops = 0;
@@ -653,7 +645,7 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         b->step_item.push_back(item_base);
         uint64_t items = 0;
         for (int i = gr.first; i < gr.second; ++i) {
-            const InstPlan &ip = b->inst[i];
+            InstPlan &ip = b->inst[i];
             if (s >= ip.ops.size()) continue;
             const HostOp &op = ip.ops[s];
             BatchRec r;
@@ -662,12 +654,11 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
             r.inst = (uint32_t)i;
             r.item0 = (uint32_t)items;
             r.wgs = ip.wgs;
-            r.slot = op.slot;
             r.need = (uint64_t)s * ip.wgs;
             r.tb = ip.tb;
             if (op.kind != BK_HPSI) {
                 // tile geometry: smallest khi with #{segment qubits >= tb - khi} == khi
-                const std::vector<int> &gl = ip.seg_gates[s];
+                const std::vector<int> &gl = op.gates;
                 uint64_t qm = 0;
                 for (int l : gl)
                     for (int a = 0; a < ip.gates[l].k; ++a) qm |= 1ull << ip.gates[l].qubits[a];
@@ -677,25 +668,52 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
                     const uint64_t above = lim >= 64 ? 0 : (qm & ~((1ull << lim) - 1));
                     if (__builtin_popcountll(above) == khi) break;
                 }
-                r.khi = khi;
                 r.W = ip.tb - khi;
                 int pos[64];
                 int h = 0;
-                for (int q = 0; q < ip.n; ++q) {
-                    if (!((qm >> q) & 1ull)) continue;
-                    if (q < r.W) pos[q] = q;
-                    else { r.qhi[h] = (uint8_t)q; pos[q] = r.W + h; ++h; }
-                }
+                for (int q = 0; q < r.W; ++q) pos[q] = q, r.bit[q] = 1ull << q;
+                for (int q = r.W; q < ip.n; ++q)
+                    if ((qm >> q) & 1ull) pos[q] = r.W + h, r.bit[r.W + h] = 1ull << q, ++h;
                 // sweeps: consecutive gates on at most three tile bits (padded
                 // with the lowest other tile bits to exactly three)
-                r.sg0 = (uint32_t)segs.size();
                 r.sw0 = (uint32_t)sweeps.size();
-                int nparam = 0;
+                r.ps0 = (uint32_t)slots.size();
+                // a rotation equal to an earlier one of the segment, with no
+                // gate in between on its qubits, joins it: one inner product
+                // (they commute) and one application with the summed angle.
+                // complex64 keeps every rotation: each rounds the state, and
+                // its results stay those of the gates one by one.
+                std::vector<int> head(gl.size(), -1);     // gate position it joins
+                std::vector<std::vector<int>> joined(gl.size());
+                {
+                    std::vector<int> last(64, -1);        // last position on each qubit
+                    for (size_t q = 0; q < gl.size(); ++q) {
+                        const int l = gl[q];
+                        const int p0 = last[ip.sq0[l]], p1 = ip.sq1[l] < 0 ? p0 : last[ip.sq1[l]];
+                        const int lp = p0 >= 0 ? gl[p0] : -1;
+                        if (dt == CAST_C128 && lp >= 0 && p0 == p1 && ip.gates[l].param_id >= 0 && ip.gates[lp].param_id >= 0 &&
+                            ip.gx[l] == ip.gx[lp] && ip.gz[l] == ip.gz[lp] && ip.sq0[l] == ip.sq0[lp] &&
+                            ip.sq1[l] == ip.sq1[lp]) {
+                            head[q] = p0;
+                            joined[p0].push_back(l);
+                            if (op.kind == BK_ADJ) ip.gslot[l] = ip.gslot[lp];
+                            continue;
+                        }
+                        joined[q].push_back(l);
+                        last[ip.sq0[l]] = (int)q;
+                        if (ip.sq1[l] >= 0) last[ip.sq1[l]] = (int)q;
+                    }
+                }
                 size_t gi = 0;
                 while (gi < gl.size()) {
+                    if (head[gi] >= 0) {
+                        ++gi;
+                        continue;
+                    }
                     uint32_t bits = 0;
                     size_t gj = gi;
                     for (; gj < gl.size(); ++gj) {
+                        if (head[gj] >= 0) continue;
                         const int l = gl[gj];
                         uint32_t gb = 1u << pos[ip.sq0[l]];
                         if (ip.gates[l].k == 2) gb |= 1u << pos[ip.sq1[l]];
@@ -707,38 +725,40 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
                     memset(&sw, 0, sizeof sw);
                     int loc[32];
                     for (int t = 0, c = 0; t < ip.tb; ++t)
-                        if ((bits >> t) & 1u) sw.b[c] = t, loc[t] = c++;
+                        if ((bits >> t) & 1u) sw.bits |= (uint32_t)t << (8 * c), loc[t] = c++;
                     sw.g0 = (uint32_t)segs.size();
-                    sw.p0 = nparam;
+                    sw.p0 = (uint32_t)slots.size() - r.ps0;
                     for (size_t q = gi; q < gj; ++q) {
+                        if (head[q] >= 0) continue;
                         const int l = gl[q];
-                        SegGate sgt;
-                        memset(&sgt, 0, sizeof sgt);
-                        const int k = ip.gates[l].k;
                         const int t0 = loc[pos[ip.sq0[l]]];
-                        const int t1 = k == 2 ? loc[pos[ip.sq1[l]]] : -1;
-                        sgt.slot = op.kind == BK_ADJ ? ip.gslot[l] : -1;
-                        // generator masks: gate-local bit 0 / 1 -> sweep bits t0 / t1
-                        uint32_t xl = 0, zl = 0;
-                        for (int bb = 0; bb < k; ++bb) {
-                            const int sb = bb == 0 ? t0 : t1;
-                            if ((ip.xl[l] >> bb) & 1u) xl |= 1u << sb;
-                            if ((ip.zl[l] >> bb) & 1u) zl |= 1u << sb;
+                        const int t1 = ip.gates[l].k == 2 ? loc[pos[ip.sq1[l]]] : -1;
+                        SegOp o;
+                        o.mat = (uint32_t)coefs.size();
+                        if (ip.gates[l].param_id >= 0) {
+                            auto mask = [&](uint64_t m) {
+                                uint32_t v = (uint32_t)((m >> ip.sq0[l]) & 1ull) << t0;
+                                if (t1 >= 0) v |= (uint32_t)((m >> ip.sq1[l]) & 1ull) << t1;
+                                return v;
+                            };
+                            o.info = 8 * mask(ip.gx[l]) + mask(ip.gz[l]);
+                            ip.bound.push_back(BoundOp{coefs.size(), op.kind == BK_ADJ, ip.diag[l] != 0, joined[q]});
+                            coefs.resize(coefs.size() + 2, 0.0);
+                            if (op.kind == BK_ADJ) {
+                                o.info |= kSegParam;
+                                slots.push_back((uint32_t)ip.gslot[l]);
+                            }
+                        } else {
+                            o.info = fixed_op(ip.fixed[l], t0, t1, op.kind == BK_ADJ, dt == CAST_C128, &coefs);
                         }
-                        // sign pattern: gate-local index -> sweep bits t0 / t1 stay in
-                        // the same order (bit 0 <-> t0 < t1 <-> bit 1)
-                        sgt.info = seg_info(k, t0, t1, ip.form[l], xl, zl, sgt.slot >= 0, ip.neg[l]);
-                        sgt.mat = (uint32_t)(op.kind == BK_FWD ? ip.mat_fwd[l] : ip.mat_adj[l]);
-                        if (sgt.slot >= 0) ++nparam;
-                        segs.push_back(sgt);
+                        segs.push_back(o);
                     }
                     sw.g1 = (uint32_t)segs.size();
                     sweeps.push_back(sw);
                     gi = gj;
                 }
-                r.sg1 = (uint32_t)segs.size();
                 r.sw1 = (uint32_t)sweeps.size();
-                r.slot = -1;
+                r.np = (uint32_t)slots.size() - r.ps0;
             }
             recs.push_back(r);
             items += ip.wgs;
@@ -759,6 +779,11 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         item_base += items;
     }
     }
+    // the kernel reads two operations and two coefficients ahead
+    segs.resize(segs.size() + 2, SegOp{0, 0});
+    coefs.resize(coefs.size() + 2, 0.0);
+    if (coefs.size() > 0xffffffffull) return bail(fail(CAST_EUNSUPPORTED, "batch matrix table exceeds 2^32 entries"));
+    b->mat_reals = coefs.size();
     b->nsteps = (int)b->step_items.size();
     b->step_rec.push_back(recs.size());
     b->step_item.push_back(item_base);
@@ -775,7 +800,8 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         off += 2 * N;
     }
     if (cast_status rc = upload(&b->d_recs, recs)) return bail(rc);
-    if (cast_status rc = upload(&b->d_segs, segs)) return bail(rc);
+    if (cast_status rc = upload(&b->d_ops, segs)) return bail(rc);
+    if (cast_status rc = upload(&b->d_slots, slots)) return bail(rc);
     if (cast_status rc = upload(&b->d_sweeps, sweeps)) return bail(rc);
     {
         int tbm = 0;
@@ -787,27 +813,24 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
     if (cast_status rc = upload(&b->d_insts, hinst)) return bail(rc);
     if (cast_status rc = upload(&b->d_tg, tg)) return bail(rc);
     if (cast_status rc = upload(&b->d_tt, tt)) return bail(rc);
-    if (cast_status rc = dev_alloc(&b->d_mats, std::max<size_t>(1, mat_entries) * 2 * rsz)) return bail(rc);
+    if (cast_status rc = dev_alloc(&b->d_mats, b->mat_reals * rsz)) return bail(rc);
     if (cast_status rc = dev_alloc((void **)&b->d_partials, std::max<uint64_t>(1, part) * sizeof(double)))
         return bail(rc);
     if (cast_status rc = dev_alloc((void **)&b->d_results, std::max<uint64_t>(1, res) * sizeof(double)))
         return bail(rc);
     if (cast_status rc = dev_alloc((void **)&b->d_counters, (2 + (size_t)n_inst) * sizeof(unsigned long long)))
         return bail(rc);
-    if (hipHostMalloc(&b->h_mats, std::max<size_t>(1, mat_entries) * 2 * rsz) != hipSuccess)
+    if (hipHostMalloc(&b->h_mats, b->mat_reals * rsz) != hipSuccess)
         return bail(fail(CAST_ENOMEM, "pinned matrix buffer"));
     if (hipHostMalloc((void **)&b->h_results, (res + 1) * sizeof(double)) != hipSuccess)
         return bail(fail(CAST_ENOMEM, "pinned result buffer"));
-    for (auto &ip : b->inst)
-        for (size_t l = 0; l < ip.gates.size(); ++l) {
-            put_matrix(b, ip.mat_fwd[l], ip.fixed[l].data(), false, ip.gates[l].k, ip.form[l], ip.xl[l], ip.zl[l]);
-            put_matrix(b, ip.mat_adj[l], ip.fixed[l].data(), true, ip.gates[l].k, ip.form[l], ip.xl[l], ip.zl[l]);
-        }
+    put_reals(b, 0, coefs.data(), coefs.size());
     if (hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking) != hipSuccess)
         return bail(fail(CAST_EHIP, "hipStreamCreate failed"));
     BatchDev &d = b->dev;
     d.recs = b->d_recs;
-    d.segs = b->d_segs;
+    d.ops = b->d_ops;
+    d.slots = b->d_slots;
     d.sweeps = b->d_sweeps;
     d.step_rec = b->d_step_rec;
     d.step_item = b->d_step_item;
@@ -856,16 +879,15 @@ cast_status batch_run(cast_batch *b, const double *const *theta, double *energie
             return fail(CAST_EINVAL, "theta/grads missing for an instance with parameters");
     }
     // bind parameters (host FP64, cast once into the pinned buffer)
-    for (int i = 0; i < b->ninst; ++i) {
-        const InstPlan &ip = b->inst[i];
-        for (size_t l = 0; l < ip.gates.size(); ++l) {
-            const cast_gate &g = ip.gates[l];
-            if (g.param_id < 0) continue;
-            const double a = g.param_coeff * theta[i][g.param_id];
-            bind_rotation(b, ip.mat_fwd[l], g.k, ip.gen_sorted[l], a, false, ip.form[l], ip.xl[l], ip.zl[l]);
-            bind_rotation(b, ip.mat_adj[l], g.k, ip.gen_sorted[l], a, true, ip.form[l], ip.xl[l], ip.zl[l]);
+    for (int i = 0; i < b->ninst; ++i)
+        for (const BoundOp &o : b->inst[i].bound) {
+            double angle = 0.0;
+            for (int l : o.gates) angle += b->inst[i].gates[l].param_coeff * theta[i][b->inst[i].gates[l].param_id];
+            if (!o.diag || b->dt == CAST_C64) angle *= 0.5;
+            double cs[2] = {std::cos(angle), o.dagger ? -std::sin(angle) : std::sin(angle)};
+            if (!o.diag && b->dt == CAST_C128) shear_coefs(cs);
+            put_reals(b, o.mat, cs, 2);
         }
-    }
     if (b->mode >= 1) {
         CAST_HIP_TRY(hipGraphLaunch(b->exec, b->stream));
     } else {
@@ -877,20 +899,20 @@ cast_status batch_run(cast_batch *b, const double *const *theta, double *energie
         memcpy(&err, b->h_results + b->result_doubles, sizeof err);
         if (err) return fail(CAST_EHIP, "persistent batch: a dependency wait exceeded its bound");
     }
+    size_t off = 0;
     for (int i = 0; i < b->ninst; ++i) {
         const InstPlan &ip = b->inst[i];
-        size_t off = 0;
-        for (int j = 0; j < i; ++j) off += 2 * (size_t)b->inst[j].nslots;
         const double *r = b->h_results + off;
+        off += (size_t)ip.nslots;
         energies[i] = r[0];
         if (!ip.nparams) continue;
         for (size_t p = 0; p < ip.nparams; ++p) grads[i][p] = 0.0;
         for (size_t l = ip.gates.size(); l-- > 0;) {
             const int s = ip.gslot[l];
             if (s < 0) continue;
-            const cplx S(r[2 * s], r[2 * s + 1]);
-            const cplx v = kIpowB[__builtin_popcountll(ip.gx[l] & ip.gz[l]) & 3] * S;
-            grads[i][ip.gates[l].param_id] += ip.gates[l].param_coeff * v.imag();
+            // Im i^{|x & z|} S from the part of S the kernel takes
+            const double v = __builtin_popcountll(ip.gx[l] & ip.gz[l]) & 2 ? -r[s] : r[s];
+            grads[i][ip.gates[l].param_id] += ip.gates[l].param_coeff * v;
         }
     }
     return CAST_OK;

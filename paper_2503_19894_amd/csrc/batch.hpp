@@ -19,61 +19,75 @@
 
 #include <cstdint>
 
-#include "reduce.hpp"
+#include "../../include/cast.h"
 
 namespace cast {
 
 enum BatchKind : uint32_t { BK_FWD = 0, BK_HPSI = 1, BK_ADJ = 2 };
 
 constexpr int kSegMaxGates = 64;   // gates per segment (bounds the LDS reduction area)
-// LDS of a segment item beyond its two tiles: address tables + partial sums
-constexpr size_t kSegLdsExtra = 128 * sizeof(uint64_t) + (size_t)kSegMaxGates * 4 * 2 * sizeof(double);
+// LDS of a segment item beyond its two tiles: the inner products' per-wave sums
+constexpr size_t kSegLdsExtra = (size_t)kSegMaxGates * 4 * sizeof(double);
 
-struct SegGate {            // one gate of a sweep, in sweep coordinates
-    // packed: bit 0 k - 1; bits 1-2 t0 and 3-4 t1, the sweep bits (0..2) of
-    // the sorted targets (t1 unused for k = 1); bits 5-7 the matrix form for
-    // every parameter value (BatchForm); bits 8-10 xl and 11-13 zl, the x / z
-    // masks over the sweep bits of the generator (ADJ inner products) or of
-    // a BF_PAULI gate's Pauli string; bit 14 set when the gate has a result
-    // slot; bits 15-18 (BF_SIGN) the local indices whose diagonal entry is -1
-    uint32_t info;
-    uint32_t mat;           // offset (complex entries) of U (FWD) or U^dag (ADJ): its 2^k x 2^k
-                            // entries, or for a two-qubit diagonal form its diagonal first
-    int slot;               // ADJ: result slot, or -1
-    int pad;
+// Operations of a register sweep, in sweep coordinates (a thread holds eight
+// amplitudes x[j], bit i of j <-> the sweep's tile bit i).  Codes below 64
+// are Pauli rotations, code = 8 X + Z with the string's x / z masks over the
+// sweep bits: exp(-i a P / 2), two reals.  complex64: cos and +-sin of a / 2.
+// complex128 leaves out a global phase, which energies and gradients do not
+// see: for X = 0 (diagonal) the phase e^{+-i a} on the amplitudes with odd Z
+// parity, (cos, +-sin) of a; for X != 0 the rotation by a / 2 up to a sign
+// that makes cos >= 0, as three shears, t = -sin / (1 + cos) and sin.  The
+// others are fixed gates; `pair` counts the sweep-bit pairs (0,1), (0,2),
+// (1,2).
+enum SegCode : uint32_t {
+    SO_CZ = 64,      // + pair: x[11] = -x[11]; no coefficients
+    SO_CP = 67,      // + pair: x[11] *= p; 2 reals
+    SO_DIAG1 = 70,   // + bit: 4 reals
+    SO_DIAG2 = 73,   // + pair: 8 reals
+    SO_REAL1 = 76,   // + bit: 4 reals
+    SO_GEN1 = 79,    // + bit: 8 reals
+    SO_REAL2 = 82,   // + pair: 16 reals
+    SO_GEN2 = 85,    // + pair: 32 reals
+    SO_SIGN = 88,    // x[j] = -x[j] where bit j of info bits 8-15 is set; no coefficients
+    SO_PAULI = 88,   // + X (1..7): y_j = a x_j + b (-1)^{popc(z & (j ^ X))} x_{j ^ X}, z = info bits 8-10;
+                     // 4 reals
 };
-inline uint32_t seg_info(int k, int t0, int t1, int form, uint32_t xl, uint32_t zl, bool param, uint32_t neg) {
-    return (uint32_t)(k - 1) | (uint32_t)t0 << 1 | (uint32_t)(t1 < 0 ? 0 : t1) << 3 | (uint32_t)form << 5 |
-           xl << 8 | zl << 11 | (uint32_t)param << 14 | (neg & 15u) << 15;
-}
-
-// Matrix forms the register sweeps specialise (fewer multiplies): diagonal
-// (e.g. RZ, RZZ, CZ) and real (e.g. RY).
-// A fixed diagonal gate whose entries are all +1 or -1 (e.g. CZ) is a sign
-// pattern: BF_SIGN, its -1 entries in info bits 14-17, no matrix read.
-// A two-qubit gate a I + b' P with P one Pauli string that flips bits (e.g.
-// RXX, RYY, or a fixed XX coupling) is BF_PAULI: y_r = a x_r + b s(r) x_{r^xm}
-// with s(r) = (-1)^{popc(zm & (r ^ xm))}, the masks in the record's xl / zl
-// fields and (a, b) the first two complex entries of its matrix slot.
-enum BatchForm : int { BF_GENERAL = 0, BF_DIAG = 1, BF_REAL = 2, BF_SIGN = 3, BF_PAULI = 4 };
+struct SegOp {
+    uint32_t info;          // bits 0-6 SegCode; bit 7: take the inner product first; bits 8-15 see SegCode
+    uint32_t mat;           // offset (reals) of its coefficients
+};
+constexpr uint32_t kSegParam = 128;
 
 struct SegSweep {           // consecutive gates of a segment on at most three tile bits
-    int b[3];               // the sweep's tile bits, ascending
-    uint32_t g0, g1;        // its gates [g0, g1) of the SegGate table
-    int p0;                 // index of its first inner product within the segment
+    uint32_t bits;          // the sweep's tile bits, ascending, 8 bits each
+    uint32_t g0, g1;        // its operations [g0, g1) of the SegOp table
+    uint32_t p0;            // index of its first inner product within the segment
 };
 
+// Read at wave-uniform addresses: 32- and 64-bit fields only (the scalar unit
+// loads no smaller ones).
 struct BatchRec {           // op `s` of one instance
     uint32_t kind;
     uint32_t inst;
     uint32_t item0;         // first item of this record within its step
     uint32_t wgs;           // items (workgroups) of this record
-    int slot;               // HPSI result slot
-    uint32_t sg0, sg1;      // FWD/ADJ: gates [sg0, sg1) of the SegGate table
     uint32_t sw0, sw1;      // FWD/ADJ: sweeps [sw0, sw1) of the SegSweep table
-    int tb, W, khi;         // tile: 2^tb amplitudes, window [0, W), khi high qubits
-    uint8_t qhi[12];        // high qubits of the tile, ascending
+    uint32_t ps0, np;       // ADJ: result slots [ps0, ps0 + np) of the slot table, one per inner product
+    int tb, W;              // tile: 2^tb amplitudes, window [0, W)
+    uint64_t bit[16];       // amplitude-index bit of tile bit i (0 past tb)
     uint64_t need;          // persistent mode: items of this instance that must be done first
+};
+
+// H's terms by x mask and parity of |x & z|: coefficients are real (even) or
+// imaginary (odd), c the nonzero part including i^{|x&z|}.
+struct BatchHGroup {
+    uint64_t x;
+    uint32_t first, count;
+    uint32_t odd, pad;
+};
+struct BatchHTerm {
+    uint64_t z;
+    double c;
 };
 
 struct BatchInst {
@@ -83,10 +97,10 @@ struct BatchInst {
     int nslots;
     uint32_t wgs;
     uint32_t ngroups;       // Pauli-term groups of H
-    uint64_t part_off;      // doubles: partial sums, nslots x wgs x 2
-    uint64_t res_off;       // doubles: results, nslots x 2
-    uint32_t tg_off;        // first PauliSumGroup of H
-    uint32_t tt_off;        // first PauliSumTerm of H (groups' `first` are relative to it)
+    uint64_t part_off;      // doubles: partial sums, nslots x wgs
+    uint64_t res_off;       // doubles: results, nslots
+    uint32_t tg_off;        // first BatchHGroup of H
+    uint32_t tt_off;        // first BatchHTerm of H (groups' `first` are relative to it)
     int init_kind;          // 0 |0...0>, 1 |+...+>, 2 copy of init_src
     int pad;
     const void *init_src;
@@ -94,14 +108,15 @@ struct BatchInst {
 
 struct BatchDev {           // device pointers of one program
     const BatchRec *recs;   // all records, step-major
-    const SegGate *segs;
+    const SegOp *ops;
+    const uint32_t *slots;
     const SegSweep *sweeps;
     const uint64_t *step_rec;    // nsteps + 1: first record of each step
     const uint64_t *step_item;   // nsteps + 1: first global item of each step (persistent mode)
     const BatchInst *insts;
     const void *mats;
-    const PauliSumGroup *tg;
-    const PauliSumTerm *tt;
+    const BatchHGroup *tg;
+    const BatchHTerm *tt;
     double *partials;
     double *results;
     int nsteps;

@@ -18,10 +18,6 @@ template <typename R> struct BAmp;
 template <> struct BAmp<double> { using T = double2; };
 template <> struct BAmp<float> { using T = float2; };
 
-__device__ __forceinline__ uint64_t ins0(uint64_t g, int q) {
-    const uint64_t lm = (1ull << q) - 1;
-    return ((g & ~lm) << 1) | (g & lm);
-}
 __device__ __forceinline__ uint32_t ins0_32(uint32_t g, int q) {
     const uint32_t lm = (1u << q) - 1;
     return ((g & ~lm) << 1) | (g & lm);
@@ -37,30 +33,6 @@ __device__ __forceinline__ uint32_t ins0_32(uint32_t g, int q) {
 template <typename T> using CPtr = const __attribute__((address_space(4))) T *;
 template <typename T> __device__ __forceinline__ CPtr<T> cptr(const T *p) { return (CPtr<T>)p; }
 
-template <typename V, typename R>
-__device__ __forceinline__ V cmul_acc(V acc, R mr, R mi, V v) {
-    acc.x = fma(mr, v.x, acc.x);
-    acc.x = fma(-mi, v.y, acc.x);
-    acc.y = fma(mr, v.y, acc.y);
-    acc.y = fma(mi, v.x, acc.y);
-    return acc;
-}
-
-// y = M x for a 2^K-vector held in registers (M row-major, uniform).
-template <int K, typename V, typename R>
-__device__ __forceinline__ void small_matvec(CPtr<R> m, const V *x, V *y) {
-    constexpr int D = 1 << K;
-#pragma unroll
-    for (int r = 0; r < D; ++r) {
-        V acc;
-        acc.x = 0;
-        acc.y = 0;
-#pragma unroll
-        for (int c = 0; c < D; ++c) acc = cmul_acc(acc, m[2 * (r * D + c)], m[2 * (r * D + c) + 1], x[c]);
-        y[r] = acc;
-    }
-}
-
 __device__ __forceinline__ double block_sum(double v, double *red) {
     for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -72,94 +44,264 @@ __device__ __forceinline__ double block_sum(double v, double *red) {
     return s;
 }
 
-// Gates on a thread's 8 register amplitudes x[j], j over the sweep's three
-// tile bits.  Bit positions are template parameters so every register index
-// is a compile-time constant.
-// The first eight reals of a gate's matrix entry, read ahead of the gate
-// (every one-qubit form and the two-qubit diagonal need no more).
-template <typename R> struct Coef8 {
-    R c[8];
-    __device__ __forceinline__ R operator[](int i) const { return c[i]; }
-};
-template <typename R>
-__device__ __forceinline__ Coef8<R> load_coef(CPtr<R> m) {
-    Coef8<R> k;
-#pragma unroll
-    for (int i = 0; i < 8; ++i) k.c[i] = m[i];
-    return k;
+// ------------------------------------------------------------------ operations
+// On a thread's eight register amplitudes x[j], j over the sweep's three tile
+// bits.  Masks and bit positions are template parameters, so every register
+// index and sign is known at compile time.
+constexpr int par(int v) { return __builtin_popcount(v) & 1; }
+
+// c a + b (NEG: b - c a) with c wave-uniform, in the three-address form: left
+// to itself the compiler takes v_fmac, whose result sits in b's register, and
+// copies it to a's place after every operation, since all cases of seg_op
+// have to leave x[] in the same registers (34 copies per operation).
+template <bool NEG>
+__device__ __forceinline__ double fma3(double c, double a, double b) {
+    double d;
+    if (NEG) asm("v_fma_f64 %0, -%1, %2, %3" : "=v"(d) : "s"(c), "v"(a), "v"(b));
+    else asm("v_fma_f64 %0, %1, %2, %3" : "=v"(d) : "s"(c), "v"(a), "v"(b));
+    return d;
+}
+template <bool NEG>
+__device__ __forceinline__ float fma3(float c, float a, float b) {
+    float d;
+    if (NEG) asm("v_fma_f32 %0, -%1, %2, %3" : "=v"(d) : "s"(c), "v"(a), "v"(b));
+    else asm("v_fma_f32 %0, %1, %2, %3" : "=v"(d) : "s"(c), "v"(a), "v"(b));
+    return d;
 }
 
-template <int B, typename V, typename M>
-__device__ __forceinline__ void reg_apply1(V *x, const M &m) {
+// (p, q) <- (c p - s q, s p + c q) (NEG: the inverse) as three shears,
+// t = -s / (1 + c), 0 <= c: in place and three fused operations instead of
+// four.
+template <bool NEG>
+__device__ __forceinline__ void shear(double &p, double &q, double t, double s) {
+    p = fma(NEG ? -t : t, q, p);
+    q = fma(NEG ? -s : s, p, q);
+    p = fma(NEG ? -t : t, q, p);
+}
+
+// Pauli rotation (SegCode below 64) with coefficients c, s.  complex128: see
+// SegCode.  complex64: the products of an output are rounded in a fixed order
+// (contraction off, fused operations written out), so that results do not
+// depend on how the compiler contracts them.
+template <int X, int Z>
+__device__ __forceinline__ void rot(double2 *x, double c, double s) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if (X == 0) {
+            if (!par(Z & j)) continue;
+            const double u = s * x[j].y, v = s * x[j].x;
+            x[j].x = fma3<false>(c, x[j].x, -u);
+            x[j].y = fma3<false>(c, x[j].y, v);
+            continue;
+        }
+        // x_j <- c x_j - i s P[j][j ^ X] x_{j ^ X},
+        // -i P[j][j ^ X] = -i i^{|X & Z|} (-1)^{Z . (j ^ X)}
+        constexpr bool flip = __builtin_popcount(X & Z) == 2;
+        const int k = j ^ X;
+        if (k < j) continue;   // each pair once
+        if (par(X & Z)) {
+            if (par(Z & j)) shear<true>(x[j].x, x[k].x, c, s), shear<true>(x[j].y, x[k].y, c, s);
+            else shear<false>(x[j].x, x[k].x, c, s), shear<false>(x[j].y, x[k].y, c, s);
+        } else if (par(Z & k) != (int)flip) {
+            shear<false>(x[j].x, x[k].y, c, s), shear<true>(x[j].y, x[k].x, c, s);
+        } else {
+            shear<true>(x[j].x, x[k].y, c, s), shear<false>(x[j].y, x[k].x, c, s);
+        }
+    }
+}
+
+template <int X, int Z>
+__device__ __forceinline__ void rot(float2 *x, float c, float s) {
+#pragma clang fp contract(off)
+    constexpr bool flip = __builtin_popcount(X & Z) == 2;
+    constexpr bool two = __builtin_popcount(X | Z) == 2;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if (X == 0) {
+            const float u = s * x[j].y, v = s * x[j].x;
+            x[j].x = fma3<false>(c, x[j].x, par(Z & j) ? -u : u);
+            x[j].y = fma3<false>(c, x[j].y, par(Z & j) ? v : -v);
+            continue;
+        }
+        const int k = j ^ X;
+        if (k < j) continue;   // each pair once
+        const float2 a = x[j], b = x[k];
+        // signs of s in x_j (from x_k) and x_k (from x_j)
+        constexpr bool real = par(X & Z);
+        const bool nj = par(Z & k) != (int)flip, nk = par(Z & j) != (int)flip;
+        if (real && !two) {          // Y
+            const float ux = s * b.x, uy = s * b.y, vx = c * b.x, vy = c * b.y;
+            x[j].x = fma3<false>(c, a.x, nj ? -ux : ux);
+            x[j].y = fma3<false>(c, a.y, nj ? -uy : uy);
+            x[k].x = nk ? fma3<true>(s, a.x, vx) : fma3<false>(s, a.x, vx);
+            x[k].y = nk ? fma3<true>(s, a.y, vy) : fma3<false>(s, a.y, vy);
+        } else if (real) {           // XY, YZ, ...
+            const float ux = c * a.x, uy = c * a.y, vx = s * a.x, vy = s * a.y;
+            x[j].x = nj ? fma3<true>(s, b.x, ux) : fma3<false>(s, b.x, ux);
+            x[j].y = nj ? fma3<true>(s, b.y, uy) : fma3<false>(s, b.y, uy);
+            x[k].x = fma3<false>(c, b.x, nk ? -vx : vx);
+            x[k].y = fma3<false>(c, b.y, nk ? -vy : vy);
+        } else if (!two) {           // X
+            const float ux = c * a.x, uy = c * a.y, vx = s * a.x, vy = s * a.y;
+            x[j].x = fma3<false>(s, b.y, ux);
+            x[j].y = fma3<true>(s, b.x, uy);
+            x[k].x = fma3<false>(c, b.x, vy);
+            x[k].y = fma3<false>(c, b.y, -vx);
+        } else {                     // XX, YY, XZ, ...
+            const float sj = nj ? -s : s, sk = nk ? -s : s;
+            x[j].x = c * a.x + sj * b.y;
+            x[j].y = c * a.y - sj * b.x;
+            x[k].x = c * b.x + sk * a.y;
+            x[k].y = c * b.y - sk * a.x;
+        }
+    }
+}
+
+// sum_j conj(l[j ^ X]) (-1)^{Z . j} x[j]: its imaginary part, or for odd
+// |X & Z| its real part, the one d E / d theta needs.  FP64 products.
+template <int X, int Z, typename V>
+__device__ __forceinline__ double inner(const V *l, const V *x) {
+    double s0 = 0.0, s1 = 0.0;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const V a = l[j ^ X];
+        const double u = par(X & Z) ? (double)x[j].x : (double)x[j].y;
+        const double v = par(X & Z) ? (double)x[j].y : -(double)x[j].x;
+        const double ar = par(Z & j) ? -(double)a.x : (double)a.x, ai = par(Z & j) ? -(double)a.y : (double)a.y;
+        s0 = fma(ar, u, s0);
+        s1 = fma(ai, v, s1);
+    }
+    return s0 + s1;
+}
+
+template <int B, typename V, typename R>
+__device__ __forceinline__ void gen1(V *x, CPtr<R> m) {
+    const R r00 = m[0], i00 = m[1], r01 = m[2], i01 = m[3], r10 = m[4], i10 = m[5], r11 = m[6], i11 = m[7];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         if (j & (1 << B)) continue;
-        const int j1 = j | (1 << B);
-        const V a = x[j], b = x[j1];
+        const V a = x[j], b = x[j | (1 << B)];
         V y0, y1;
-        y0.x = y0.y = y1.x = y1.y = 0;
-        y0 = cmul_acc(y0, m[0], m[1], a);
-        y0 = cmul_acc(y0, m[2], m[3], b);
-        y1 = cmul_acc(y1, m[4], m[5], a);
-        y1 = cmul_acc(y1, m[6], m[7], b);
+        y0.x = fma(-i01, b.y, fma(r01, b.x, fma(-i00, a.y, r00 * a.x)));
+        y0.y = fma(i01, b.x, fma(r01, b.y, fma(i00, a.x, r00 * a.y)));
+        y1.x = fma(-i11, b.y, fma(r11, b.x, fma(-i10, a.y, r10 * a.x)));
+        y1.y = fma(i11, b.x, fma(r11, b.y, fma(i10, a.x, r10 * a.y)));
         x[j] = y0;
-        x[j1] = y1;
+        x[j | (1 << B)] = y1;
     }
+}
+
+template <int B, typename V, typename R>
+__device__ __forceinline__ void real1(V *x, CPtr<R> m) {
+    const R m00 = m[0], m01 = m[1], m10 = m[2], m11 = m[3];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        if (j & (1 << B)) continue;
+        const V a = x[j], b = x[j | (1 << B)];
+        x[j].x = fma(m00, a.x, m01 * b.x);
+        x[j].y = fma(m00, a.y, m01 * b.y);
+        x[j | (1 << B)].x = fma(m10, a.x, m11 * b.x);
+        x[j | (1 << B)].y = fma(m10, a.y, m11 * b.y);
+    }
+}
+
+// Local index of j on sweep bits (B0, B1).
+template <int B0, int B1>
+__device__ __forceinline__ constexpr int loc2(int j) { return ((j >> B0) & 1) | ((j >> B1) & 1) << 1; }
+
+// Two-qubit dense gates, a row of coefficients at a time (all of them would
+// take 64 scalar registers in complex128).
+template <int B0, int B1, typename V, typename R>
+__device__ __forceinline__ void gen2(V *x, CPtr<R> m) {
+    V y[8];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            if (loc2<B0, B1>(j)) continue;
+            V a;
+            a.x = a.y = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                const R mr = m[2 * (r * 4 + c)], mi = m[2 * (r * 4 + c) + 1];
+                const V in = x[j | (c & 1) << B0 | (c >> 1) << B1];
+                a.x = fma(-mi, in.y, fma(mr, in.x, a.x));
+                a.y = fma(mi, in.x, fma(mr, in.y, a.y));
+            }
+            y[j | (r & 1) << B0 | (r >> 1) << B1] = a;
+        }
+    }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = y[j];
 }
 
 template <int B0, int B1, typename V, typename R>
-__device__ __forceinline__ void reg_apply2(V *x, CPtr<R> m) {
+__device__ __forceinline__ void real2(V *x, CPtr<R> m) {
+    V y[8];
 #pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        if (j & ((1 << B0) | (1 << B1))) continue;
-        const int idx[4] = {j, j | (1 << B0), j | (1 << B1), j | (1 << B0) | (1 << B1)};
-        V in[4], out[4];
+    for (int r = 0; r < 4; ++r) {
+        __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-        for (int c = 0; c < 4; ++c) in[c] = x[idx[c]];
-        small_matvec<2>(m, in, out);
+        for (int j = 0; j < 8; ++j) {
+            if (loc2<B0, B1>(j)) continue;
+            R yr = 0, yi = 0;
 #pragma unroll
-        for (int r = 0; r < 4; ++r) x[idx[r]] = out[r];
+            for (int c = 0; c < 4; ++c) {
+                const V in = x[j | (c & 1) << B0 | (c >> 1) << B1];
+                yr = fma(m[r * 4 + c], in.x, yr);
+                yi = fma(m[r * 4 + c], in.y, yi);
+            }
+            y[j | (r & 1) << B0 | (r >> 1) << B1].x = yr;
+            y[j | (r & 1) << B0 | (r >> 1) << B1].y = yi;
+        }
     }
+#pragma unroll
+    for (int j = 0; j < 8; ++j) x[j] = y[j];
 }
 
-// Diagonal gate on sweep bits (B0, B1; B1 < 0 for one qubit): x[j] *= D[j's bits].
-// A one-qubit diagonal is read from its 2 x 2 matrix (entries 0 and 3), a
-// two-qubit one from its compact diagonal (the host stores its four entries
-// first).
-template <int B0, int B1, typename V, typename M>
-__device__ __forceinline__ void reg_diag(V *x, const M &m) {
-    constexpr int K = B1 < 0 ? 1 : 2;
+// Diagonal on sweep bits (B0, B1; B1 = B0 for one qubit): x[j] *= m[j's bits].
+template <int B0, int B1, typename V, typename R>
+__device__ __forceinline__ void diag(V *x, CPtr<R> m) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const int loc = ((j >> B0) & 1) | (B1 < 0 ? 0 : ((j >> (B1 < 0 ? 0 : B1)) & 1) << 1);
-        const int e = K == 1 ? 3 * loc : loc;
-        const auto dr = m[2 * e], di = m[2 * e + 1];
+        const int e = B0 == B1 ? (j >> B0) & 1 : loc2<B0, B1>(j);
+        const R dr = m[2 * e], di = m[2 * e + 1];
         const V a = x[j];
         x[j].x = dr * a.x - di * a.y;
         x[j].y = dr * a.y + di * a.x;
     }
 }
 
-// Sign pattern on sweep bits (B0, B1; B1 < 0 for one qubit): x[j] = -x[j]
-// where the gate's diagonal entry for j's bits is -1 (`neg`, wave-uniform).
-template <int B0, int B1, typename V>
-__device__ __forceinline__ void reg_sign(V *x, uint32_t neg) {
+// x[11] *= (c, s) / x[11] = -x[11]
+template <int B0, int B1, typename V, typename R>
+__device__ __forceinline__ void cphase(V *x, R c, R s) {
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
-        const int loc = ((j >> B0) & 1) | (B1 < 0 ? 0 : ((j >> (B1 < 0 ? 0 : B1)) & 1) << 1);
-        if ((neg >> loc) & 1u) {
-            x[j].x = -x[j].x;
-            x[j].y = -x[j].y;
-        }
+        if (loc2<B0, B1>(j) != 3) continue;
+        const V a = x[j];
+        x[j].x = c * a.x - s * a.y;
+        x[j].y = c * a.y + s * a.x;
     }
 }
+template <int B0, int B1, typename V>
+__device__ __forceinline__ void cz(V *x) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if (loc2<B0, B1>(j) == 3) x[j].x = -x[j].x, x[j].y = -x[j].y;
+}
 
-// Pauli pair y_j = a x_j + b s(j) x_{j^X}, s(j) = (-1)^{popc(zl & (j ^ X))}
-// (X over the sweep bits, compile time; zl wave-uniform): two complex
-// products per amplitude where the dense two-qubit form takes four.
+template <typename V>
+__device__ __forceinline__ void sign8(V *x, uint32_t neg) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+        if ((neg >> j) & 1u) x[j].x = -x[j].x, x[j].y = -x[j].y;
+}
+
+// y_j = a x_j + b (-1)^{popc(z & (j ^ X))} x_{j ^ X}
 template <int X, typename V, typename R>
-__device__ __forceinline__ void reg_pauli(V *x, const Coef8<R> &c, uint32_t zl) {
-    const R ar = c[0], ai = c[1], br = c[2], bi = c[3];
+__device__ __forceinline__ void pauli_pair(V *x, CPtr<R> m, uint32_t z) {
+    const R ar = m[0], ai = m[1], br = m[2], bi = m[3];
 #pragma unroll
     for (int j = 0; j < 8; ++j) {
         const int k = j ^ X;
@@ -170,8 +312,8 @@ __device__ __forceinline__ void reg_pauli(V *x, const Coef8<R> &c, uint32_t zl) 
         pj.y = br * xk.y + bi * xk.x;
         pk.x = br * xj.x - bi * xj.y;
         pk.y = br * xj.y + bi * xj.x;
-        if (__popc(zl & (uint32_t)k) & 1) pj.x = -pj.x, pj.y = -pj.y;
-        if (__popc(zl & (uint32_t)j) & 1) pk.x = -pk.x, pk.y = -pk.y;
+        if (__popc(z & (uint32_t)k) & 1) pj.x = -pj.x, pj.y = -pj.y;
+        if (__popc(z & (uint32_t)j) & 1) pk.x = -pk.x, pk.y = -pk.y;
         x[j].x = ar * xj.x - ai * xj.y + pj.x;
         x[j].y = ar * xj.y + ai * xj.x + pj.y;
         x[k].x = ar * xk.x - ai * xk.y + pk.x;
@@ -179,233 +321,104 @@ __device__ __forceinline__ void reg_pauli(V *x, const Coef8<R> &c, uint32_t zl) 
     }
 }
 
-// Real matrix: only the real parts of the entries are read (two multiplies per entry).
-template <int B, typename V, typename M>
-__device__ __forceinline__ void reg_real1(V *x, const M &m) {
-    const auto m00 = m[0], m01 = m[2], m10 = m[4], m11 = m[6];
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        if (j & (1 << B)) continue;
-        const int j1 = j | (1 << B);
-        const V a = x[j], b = x[j1];
-        x[j].x = fma(m00, a.x, m01 * b.x);
-        x[j].y = fma(m00, a.y, m01 * b.y);
-        x[j1].x = fma(m10, a.x, m11 * b.x);
-        x[j1].y = fma(m10, a.y, m11 * b.y);
+// One operation on x and, with `two`, on l; c, s its first two coefficients
+// (read ahead), m all of them.  With the parameter flag, first the inner
+// product, whose value is returned.  One dispatch per operation: every case
+// is straight code for its masks.
+#define CAST_ROT(X, Z)                                                 \
+    case 8 * (X) + (Z):                                                \
+        if (info & kSegParam) v = inner<X, Z>(l, x);                   \
+        rot<X, Z>(x, c, s);                                            \
+        if (two) rot<X, Z>(l, c, s);                                   \
+        break;
+#define CAST_ROT1(B) CAST_ROT(0, B) CAST_ROT(B, 0) CAST_ROT(B, B)
+#define CAST_ROT2(P, Q)                                                \
+    CAST_ROT(0, P | Q) CAST_ROT(P, Q) CAST_ROT(Q, P) CAST_ROT(P, P | Q) CAST_ROT(Q, P | Q) \
+    CAST_ROT(P | Q, 0) CAST_ROT(P | Q, P) CAST_ROT(P | Q, Q) CAST_ROT(P | Q, P | Q)
+#define CAST_FIXED(CODE, CALL)                                         \
+    case (CODE): {                                                     \
+        { V *y = x; CALL; }                                            \
+        if (two) { V *y = l; CALL; }                                   \
+        break;                                                         \
     }
-}
-
-template <int B0, int B1, typename V, typename R>
-__device__ __forceinline__ void reg_real2(V *x, CPtr<R> m) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        if (j & ((1 << B0) | (1 << B1))) continue;
-        const int idx[4] = {j, j | (1 << B0), j | (1 << B1), j | (1 << B0) | (1 << B1)};
-        V in[4];
-#pragma unroll
-        for (int c = 0; c < 4; ++c) in[c] = x[idx[c]];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            R ar = 0, ai = 0;
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                ar = fma(m[2 * (r * 4 + c)], in[c].x, ar);
-                ai = fma(m[2 * (r * 4 + c)], in[c].y, ai);
-            }
-            x[idx[r]].x = ar;
-            x[idx[r]].y = ai;
-        }
-    }
-}
-
-// Fields of a packed gate record (SegGate::info).
-__device__ __forceinline__ int gi_k(uint32_t i) { return 1 + (int)(i & 1u); }
-__device__ __forceinline__ int gi_t0(uint32_t i) { return (int)((i >> 1) & 3u); }
-__device__ __forceinline__ int gi_t1(uint32_t i) { return (int)((i >> 3) & 3u); }
-__device__ __forceinline__ int gi_form(uint32_t i) { return (int)((i >> 5) & 7u); }
-__device__ __forceinline__ uint32_t gi_xl(uint32_t i) { return (i >> 8) & 7u; }
-__device__ __forceinline__ uint32_t gi_zl(uint32_t i) { return (i >> 11) & 7u; }
-__device__ __forceinline__ bool gi_param(uint32_t i) { return (i >> 14) & 1u; }
-
-// One gate of a sweep: `c` holds the first eight reals of its matrix entry
-// (read ahead), `m` points at the whole entry (two-qubit dense forms).
 template <typename V, typename R>
-__device__ __forceinline__ void reg_apply(uint32_t info, V *x, const Coef8<R> &c, CPtr<R> m) {
-    const int k = gi_k(info), t0 = gi_t0(info), t1 = gi_t1(info), form = gi_form(info);
-    if (form == BF_PAULI) {
-        const uint32_t zl = gi_zl(info);
-        switch (gi_xl(info)) {
-            case 1: reg_pauli<1>(x, c, zl); break;
-            case 2: reg_pauli<2>(x, c, zl); break;
-            case 3: reg_pauli<3>(x, c, zl); break;
-            case 4: reg_pauli<4>(x, c, zl); break;
-            case 5: reg_pauli<5>(x, c, zl); break;
-            case 6: reg_pauli<6>(x, c, zl); break;
-            default: reg_pauli<7>(x, c, zl); break;
-        }
-        return;
-    }
-    if (form == BF_SIGN) {
-        const uint32_t neg = (info >> 15) & 15u;
-        if (k == 1) {
-            switch (t0) {
-                case 0: reg_sign<0, -1>(x, neg); break;
-                case 1: reg_sign<1, -1>(x, neg); break;
-                default: reg_sign<2, -1>(x, neg); break;
-            }
-        } else if (t0 == 0) {
-            if (t1 == 1) reg_sign<0, 1>(x, neg);
-            else reg_sign<0, 2>(x, neg);
-        } else {
-            reg_sign<1, 2>(x, neg);
-        }
-        return;
-    }
-    if (form == BF_DIAG) {
-        if (k == 1) {
-            switch (t0) {
-                case 0: reg_diag<0, -1>(x, c); break;
-                case 1: reg_diag<1, -1>(x, c); break;
-                default: reg_diag<2, -1>(x, c); break;
-            }
-        } else if (t0 == 0) {
-            if (t1 == 1) reg_diag<0, 1>(x, c);
-            else reg_diag<0, 2>(x, c);
-        } else {
-            reg_diag<1, 2>(x, c);
-        }
-        return;
-    }
-    if (form == BF_REAL) {
-        if (k == 1) {
-            switch (t0) {
-                case 0: reg_real1<0>(x, c); break;
-                case 1: reg_real1<1>(x, c); break;
-                default: reg_real1<2>(x, c); break;
-            }
-        } else if (t0 == 0) {
-            if (t1 == 1) reg_real2<0, 1>(x, m);
-            else reg_real2<0, 2>(x, m);
-        } else {
-            reg_real2<1, 2>(x, m);
-        }
-        return;
-    }
-    if (k == 1) {
-        switch (t0) {
-            case 0: reg_apply1<0>(x, c); break;
-            case 1: reg_apply1<1>(x, c); break;
-            default: reg_apply1<2>(x, c); break;
-        }
-    } else if (t0 == 0) {
-        if (t1 == 1) reg_apply2<0, 1>(x, m);
-        else reg_apply2<0, 2>(x, m);
-    } else {
-        reg_apply2<1, 2>(x, m);
-    }
-}
-
-// sum_j conj(l[j ^ X]) (-1)^{|z & j|} x[j] over the 8 register amplitudes
-template <int X, typename V>
-__device__ __forceinline__ void reg_inner_x(const V *l, const V *x, uint32_t zl, double *re, double *im) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const V a = l[j ^ X];
-        const double pr = (double)a.x * x[j].x + (double)a.y * x[j].y;
-        const double pi = (double)a.x * x[j].y - (double)a.y * x[j].x;
-        const bool neg = __popc(zl & (uint32_t)j) & 1;
-        *re += neg ? -pr : pr;
-        *im += neg ? -pi : pi;
-    }
-}
-
-// The same sum with the generator's x and z masks known at compile time:
-// signs and partner registers are fixed, so it is straight-line adds and
-// subtracts.
-template <int X, int Z, typename V>
-__device__ __forceinline__ void reg_inner_xz(const V *l, const V *x, double *re, double *im) {
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const V a = l[j ^ X];
-        const double pr = (double)a.x * x[j].x + (double)a.y * x[j].y;
-        const double pi = (double)a.x * x[j].y - (double)a.y * x[j].x;
-        if (__builtin_popcount(Z & j) & 1) {
-            *re -= pr;
-            *im -= pi;
-        } else {
-            *re += pr;
-            *im += pi;
-        }
-    }
-}
-
-template <typename V>
-__device__ __forceinline__ void reg_inner(const V *l, const V *x, uint32_t xl, uint32_t zl, double *re, double *im) {
-    // one-qubit generators on a sweep bit b: Z (0, b), X (b, 0), Y (b, b)
-    switch (xl * 8 + zl) {
-        case 0 * 8 + 1: reg_inner_xz<0, 1>(l, x, re, im); return;
-        case 0 * 8 + 2: reg_inner_xz<0, 2>(l, x, re, im); return;
-        case 0 * 8 + 4: reg_inner_xz<0, 4>(l, x, re, im); return;
-        case 1 * 8 + 0: reg_inner_xz<1, 0>(l, x, re, im); return;
-        case 2 * 8 + 0: reg_inner_xz<2, 0>(l, x, re, im); return;
-        case 4 * 8 + 0: reg_inner_xz<4, 0>(l, x, re, im); return;
-        case 1 * 8 + 1: reg_inner_xz<1, 1>(l, x, re, im); return;
-        case 2 * 8 + 2: reg_inner_xz<2, 2>(l, x, re, im); return;
-        case 4 * 8 + 4: reg_inner_xz<4, 4>(l, x, re, im); return;
+__device__ __forceinline__ double seg_op(uint32_t info, V *x, V *l, bool two, R c, R s, CPtr<R> m) {
+    double v = 0.0;
+    switch (info & 127u) {
+        CAST_ROT1(1) CAST_ROT1(2) CAST_ROT1(4)
+        CAST_ROT2(1, 2) CAST_ROT2(1, 4) CAST_ROT2(2, 4)
+        CAST_FIXED(SO_CZ, (cz<0, 1>(y)))
+        CAST_FIXED(SO_CZ + 1, (cz<0, 2>(y)))
+        CAST_FIXED(SO_CZ + 2, (cz<1, 2>(y)))
+        CAST_FIXED(SO_CP, (cphase<0, 1>(y, c, s)))
+        CAST_FIXED(SO_CP + 1, (cphase<0, 2>(y, c, s)))
+        CAST_FIXED(SO_CP + 2, (cphase<1, 2>(y, c, s)))
+        CAST_FIXED(SO_DIAG1, (diag<0, 0, V, R>(y, m)))
+        CAST_FIXED(SO_DIAG1 + 1, (diag<1, 1, V, R>(y, m)))
+        CAST_FIXED(SO_DIAG1 + 2, (diag<2, 2, V, R>(y, m)))
+        CAST_FIXED(SO_DIAG2, (diag<0, 1, V, R>(y, m)))
+        CAST_FIXED(SO_DIAG2 + 1, (diag<0, 2, V, R>(y, m)))
+        CAST_FIXED(SO_DIAG2 + 2, (diag<1, 2, V, R>(y, m)))
+        CAST_FIXED(SO_REAL1, (real1<0, V, R>(y, m)))
+        CAST_FIXED(SO_REAL1 + 1, (real1<1, V, R>(y, m)))
+        CAST_FIXED(SO_REAL1 + 2, (real1<2, V, R>(y, m)))
+        CAST_FIXED(SO_GEN1, (gen1<0, V, R>(y, m)))
+        CAST_FIXED(SO_GEN1 + 1, (gen1<1, V, R>(y, m)))
+        CAST_FIXED(SO_GEN1 + 2, (gen1<2, V, R>(y, m)))
+        CAST_FIXED(SO_REAL2, (real2<0, 1, V, R>(y, m)))
+        CAST_FIXED(SO_REAL2 + 1, (real2<0, 2, V, R>(y, m)))
+        CAST_FIXED(SO_REAL2 + 2, (real2<1, 2, V, R>(y, m)))
+        CAST_FIXED(SO_GEN2, (gen2<0, 1, V, R>(y, m)))
+        CAST_FIXED(SO_GEN2 + 1, (gen2<0, 2, V, R>(y, m)))
+        CAST_FIXED(SO_GEN2 + 2, (gen2<1, 2, V, R>(y, m)))
+        CAST_FIXED(SO_SIGN, (sign8(y, info >> 8)))
+        CAST_FIXED(SO_PAULI + 1, (pauli_pair<1, V, R>(y, m, info >> 8)))
+        CAST_FIXED(SO_PAULI + 2, (pauli_pair<2, V, R>(y, m, info >> 8)))
+        CAST_FIXED(SO_PAULI + 3, (pauli_pair<3, V, R>(y, m, info >> 8)))
+        CAST_FIXED(SO_PAULI + 4, (pauli_pair<4, V, R>(y, m, info >> 8)))
+        CAST_FIXED(SO_PAULI + 5, (pauli_pair<5, V, R>(y, m, info >> 8)))
+        CAST_FIXED(SO_PAULI + 6, (pauli_pair<6, V, R>(y, m, info >> 8)))
+        CAST_FIXED(SO_PAULI + 7, (pauli_pair<7, V, R>(y, m, info >> 8)))
         default: break;
     }
-    switch (xl) {
-        case 0: reg_inner_x<0>(l, x, zl, re, im); break;
-        case 1: reg_inner_x<1>(l, x, zl, re, im); break;
-        case 2: reg_inner_x<2>(l, x, zl, re, im); break;
-        case 3: reg_inner_x<3>(l, x, zl, re, im); break;
-        case 4: reg_inner_x<4>(l, x, zl, re, im); break;
-        case 5: reg_inner_x<5>(l, x, zl, re, im); break;
-        case 6: reg_inner_x<6>(l, x, zl, re, im); break;
-        default: reg_inner_x<7>(l, x, zl, re, im); break;
-    }
-}
-
-// Sum over a wave's 64 lanes with DPP moves, which stay in the vector unit
-// (cross-lane shuffles go through the LDS crossbar and wait on it): pairs and
-// quads by quad permutations, rows of 16 by shifts right by 4 and 8 (lanes
-// with no source add 0), then lane 15 of each row into the next row and
-// lane 31 into the upper half.  Lane 63 ends with the total.
-template <int CTRL, int ROWS>
-__device__ __forceinline__ double dpp_move(double v) {
-    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, ROWS, 0xf, true);
-    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, ROWS, 0xf, true);
-    return __hiloint2double(hi, lo);
-}
-__device__ __forceinline__ double wave_total63(double v) {
-    v += dpp_move<0xb1, 0xf>(v);    // quad_perm [1, 0, 3, 2]
-    v += dpp_move<0x4e, 0xf>(v);    // quad_perm [2, 3, 0, 1]
-    v += dpp_move<0x114, 0xf>(v);   // row_shr:4
-    v += dpp_move<0x118, 0xf>(v);   // row_shr:8
-    v += dpp_move<0x142, 0xa>(v);   // row_bcast:15 into rows 1 and 3
-    v += dpp_move<0x143, 0xc>(v);   // row_bcast:31 into rows 2 and 3
     return v;
 }
+#undef CAST_ROT
+#undef CAST_ROT1
+#undef CAST_ROT2
+#undef CAST_FIXED
 
-__device__ __forceinline__ SegSweep load_sweep(CPtr<SegSweep> p) {
-    SegSweep w;
-    w.b[0] = p->b[0];
-    w.b[1] = p->b[1];
-    w.b[2] = p->b[2];
-    w.g0 = p->g0;
-    w.g1 = p->g1;
-    w.p0 = p->p0;
-    return w;
+// ------------------------------------------------------------------ inner-product sums
+// The matrix core sums the inner products over lanes.  With A[m][k] = 1 for
+// m = p mod 16 and 0 elsewhere, D = A B + D adds B's four rows (the lanes'
+// values, lane l at row l / 16, column l % 16) into row p mod 16 of D: one
+// v_mfma_f64_16x16x4 per product instead of six cross-lane adds of two moves
+// each, and sixteen products share one accumulator.  flush() adds the
+// accumulator's sixteen columns and leaves the sums with the workgroup's.
+typedef double acc_v4 __attribute__((ext_vector_type(4)));
+
+template <int CTRL>
+__device__ __forceinline__ double dpp_ror(double v) {
+    const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(v), CTRL, 0xf, 0xf, true);
+    const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(v), CTRL, 0xf, 0xf, true);
+    return __hiloint2double(hi, lo);
 }
-
-struct GateOp {             // what the sweep loop reads of a gate record
-    uint32_t info, mat;
-};
-__device__ __forceinline__ GateOp load_op(CPtr<SegGate> p) {
-    GateOp o;
-    o.info = p->info;
-    o.mat = p->mat;
-    return o;
+__device__ __forceinline__ double row_total(double v) {
+    v += dpp_ror<0x128>(v);   // rotate within rows of 16 lanes
+    v += dpp_ror<0x124>(v);
+    v += dpp_ror<0x122>(v);
+    v += dpp_ror<0x121>(v);
+    return v;
+}
+// D value v of lane l is row l / 16 + 4 v, column l % 16.
+__device__ __forceinline__ void flush_sums(acc_v4 &acc, double *gsum, uint32_t p0, int lane, int wave) {
+    const double r0 = row_total(acc[0]), r1 = row_total(acc[1]), r2 = row_total(acc[2]), r3 = row_total(acc[3]);
+    const int v = lane & 15;
+    if (v < 4) {
+        const double r = v == 0 ? r0 : v == 1 ? r1 : v == 2 ? r2 : r3;
+        gsum[(p0 + (uint32_t)(lane >> 4) + 4u * (uint32_t)v) * 4 + wave] += r;   // each wave its own entries
+    }
+    acc[0] = acc[1] = acc[2] = acc[3] = 0.0;
 }
 
 __device__ __forceinline__ BatchInst load_inst(CPtr<BatchInst> p) {
@@ -433,117 +446,127 @@ __device__ __forceinline__ uint32_t bswz(uint32_t c) { return c ^ (((c >> 4) ^ (
 template <int S>
 __device__ __forceinline__ uint32_t bat(uint32_t e) { return (bswz(e >> S) << S) | (e & ((1u << S) - 1)); }
 
-// FWD / ADJ segment on tile w of an instance.  LDS layout: two 64-entry
-// tables that deposit the 12 bits of a run index onto the tile's high qubits,
-// per-gate, per-wave partial sums of the segment's inner products (at most
-// kSegMaxGates gates), then the psi tile and (ADJ only) the lambda tile, 2^tb
-// amplitudes each, swizzled as above.  A forward step's launch carries one
-// tile's LDS, so more of its workgroups share a compute unit.  `pair` (FWD in
-// the persistent launch, whose workgroups hold two tiles of LDS anyway):
-// tiles w and w + 1 of psi go through the segment together in the two tile
-// slots, the second one taking the lambda tile's place.
+// FWD / ADJ segment on tile w of an instance.  LDS layout: per-wave sums of
+// the segment's inner products (at most kSegMaxGates), then the psi tile and
+// (ADJ only) the lambda tile, 2^tb amplitudes each, swizzled as above.  A
+// forward step's launch carries one tile's LDS, so more of its workgroups
+// share a compute unit.  `pair` (FWD in the persistent launch, whose
+// workgroups hold two tiles of LDS anyway): tiles w and w + 1 of psi go
+// through the segment together in the two tile slots, the second one taking
+// the lambda tile's place.
 template <typename R>
-__device__ void seg_item(const BatchDev &d, CPtr<BatchRec> rec, const BatchInst &in, uint32_t w, double *red,
+__device__ __forceinline__ void seg_item(const BatchDev &d, CPtr<BatchRec> rec, const BatchInst &in, uint32_t w,
                          typename BAmp<R>::T *lds, bool pair) {
     using V = typename BAmp<R>::T;
+    typedef unsigned int nu4 __attribute__((ext_vector_type(4)));
     constexpr int S = sizeof(V) == 16 ? 0 : 1;      // log2(amplitudes per 16-byte chunk)
     const bool adj = rec->kind == BK_ADJ;
     const bool two = adj || pair;                    // a second tile in the lambda slot
-    const uint32_t T = 1u << rec->tb;
-    uint64_t *hid = reinterpret_cast<uint64_t *>(lds);            // [2][64]
-    double *gsum = reinterpret_cast<double *>(hid + 128);         // [kSegMaxGates][4 waves][2]
+    const int tb = rec->tb, W = rec->W;
+    const uint32_t T = 1u << tb, tid = threadIdx.x;
+    double *gsum = reinterpret_cast<double *>(lds);               // [kSegMaxGates][4 waves]
     V *tp = reinterpret_cast<V *>(reinterpret_cast<char *>(lds) + kSegLdsExtra), *tl = tp + T;
     V *psi = reinterpret_cast<V *>(in.psi);
     V *lam = reinterpret_cast<V *>(in.lam);
-    uint64_t tbase = (uint64_t)w << rec->W, tbase2 = (uint64_t)(w + 1) << rec->W;
-    for (int j = 0; j < rec->khi; ++j) tbase = ins0(tbase, rec->qhi[j]), tbase2 = ins0(tbase2, rec->qhi[j]);
+    // amplitude index of a tile position: an OR of tile, lane and chunk parts
+    uint64_t tbase = (uint64_t)w << W, tbase2 = (uint64_t)(w + 1) << W;
+    for (int i = W; i < tb; ++i) {
+        const uint64_t lm = rec->bit[i] - 1;
+        tbase = ((tbase & ~lm) << 1) | (tbase & lm);
+        tbase2 = ((tbase2 & ~lm) << 1) | (tbase2 & lm);
+    }
     // the second tile: lambda's tile w, or psi's tile w + 1 (its amplitude
     // index differs from tile w's by the XOR of the two tile bases, which
     // lie above the tile's low window)
     V *sec = pair ? psi : lam;
     const uint64_t dsec = pair ? (tbase ^ tbase2) : 0;
-    for (int i = threadIdx.x; i < kSegMaxGates * 4 * 2; i += blockDim.x) gsum[i] = 0.0;
-    if (threadIdx.x < 128) {
-        const uint32_t h = threadIdx.x >> 6, r = threadIdx.x & 63;
-        uint64_t x = 0;
-        for (int j = 0; j < 6; ++j) {
-            const int bit = 6 * (int)h + j;
-            if (bit < rec->khi && ((r >> j) & 1u)) x |= 1ull << rec->qhi[bit];
-        }
-        hid[threadIdx.x] = x;
-    }
-    __syncthreads();
+    if (adj) gsum[tid] = 0.0;                        // kSegMaxGates * 4 = 256 entries
     // 16-byte chunks of the tile (a run holds at least one chunk when W >= S)
-    const bool chunked = rec->W >= S;
+    const bool chunked = W >= S;
     const uint32_t nchunk = chunked ? (T >> S) : T;
-    const uint32_t wmask = (1u << rec->W) - 1;
-    auto addr = [&](uint32_t e) {
-        const uint32_t r = e >> rec->W;
-        return tbase | (e & wmask) | hid[r & 63] | hid[64 + (r >> 6)];
+    const int s0 = chunked ? S : 0;
+    uint64_t xl = 0;
+#pragma unroll
+    for (int i = 0; i < 8; ++i)
+        if ((tid >> i) & 1u) xl |= rec->bit[s0 + i];
+    const uint64_t b8 = rec->bit[s0 + 8], b9 = rec->bit[s0 + 9], b10 = rec->bit[s0 + 10], b11 = rec->bit[s0 + 11];
+    auto chunk_part = [&](uint32_t u) {   // u < 16
+        return ((u & 1) ? b8 : 0) | ((u & 2) ? b9 : 0) | ((u & 4) ? b10 : 0) | ((u & 8) ? b11 : 0);
     };
+    const uint64_t x0 = tbase | xl;
+    const uint32_t zl = bswz(tid);
     if (chunked) {
         // eight chunks of each state in flight per lane (a whole 2^11-amplitude
         // complex128 or 2^12-amplitude complex64 tile per 256 lanes): the item
         // waits on its loads once instead of twice
         constexpr int DEPTH = 8;
-        typedef unsigned int nu4 __attribute__((ext_vector_type(4)));
         nu4 *t16p = reinterpret_cast<nu4 *>(tp), *t16l = reinterpret_cast<nu4 *>(tl);
         const nu4 *p16 = reinterpret_cast<const nu4 *>(psi), *l16 = reinterpret_cast<const nu4 *>(sec);
-        for (uint32_t c0 = threadIdx.x; c0 < nchunk; c0 += DEPTH * blockDim.x) {
+        for (uint32_t u0 = 0; u0 * 256 < nchunk; u0 += DEPTH) {
             nu4 bp[DEPTH], bl[DEPTH];
 #pragma unroll
             for (int u = 0; u < DEPTH; ++u) {
-                const uint32_t c = c0 + u * blockDim.x;
-                if (c < nchunk) {
-                    const uint64_t x = addr(c << S) >> S;
-                    bp[u] = p16[x];
-                    if (two) bl[u] = l16[x ^ (dsec >> S)];
+                if ((u0 + u) * 256 + tid < nchunk) {
+                    const uint64_t x = x0 | chunk_part(u0 + u);
+                    bp[u] = p16[x >> S];
+                    if (two) bl[u] = l16[(x ^ dsec) >> S];
                 }
             }
 #pragma unroll
             for (int u = 0; u < DEPTH; ++u) {
-                const uint32_t c = c0 + u * blockDim.x;
-                if (c < nchunk) {
-                    t16p[bswz(c)] = bp[u];
-                    if (two) t16l[bswz(c)] = bl[u];
+                if ((u0 + u) * 256 + tid < nchunk) {
+                    const uint32_t z = zl ^ bswz((u0 + u) * 256);
+                    t16p[z] = bp[u];
+                    if (two) t16l[z] = bl[u];
                 }
             }
         }
     } else {
-        for (uint32_t e = threadIdx.x; e < T; e += blockDim.x) {
-            const uint64_t x = addr(e);
-            tp[bat<S>(e)] = psi[x];
-            if (two) tl[bat<S>(e)] = sec[x ^ dsec];
+        for (uint32_t u = 0; u * 256 + tid < nchunk; ++u) {
+            const uint64_t x = x0 | chunk_part(u);
+            const uint32_t e = bat<S>(u * 256 + tid);
+            tp[e] = psi[x];
+            if (two) tl[e] = sec[x ^ dsec];
         }
     }
     __syncthreads();
     CPtr<R> mats = cptr(reinterpret_cast<const R *>(d.mats));
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    int nred = 0;
+    CPtr<SegOp> ops = cptr(d.ops);
+    const int lane = tid & 63, wave = tid >> 6;
+    acc_v4 acc = {0.0, 0.0, 0.0, 0.0};
+    uint32_t p = 0;
     // sweeps: each thread loads 8-amplitude groups over the sweep's three
-    // tile bits once, applies the sweep's gates in registers in order (taking
-    // each inner product right before its gate), and writes the group back
-    const uint32_t groups = 1u << (rec->tb - 3);
+    // tile bits once, applies the sweep's operations in registers in order
+    // (taking each inner product right before its gate), and writes the group back
+    const uint32_t groups = 1u << (tb - 3);
     char *tpb = reinterpret_cast<char *>(tp), *tlb = reinterpret_cast<char *>(tl);
-    for (uint32_t sw = rec->sw0; sw < rec->sw1; ++sw) {
-        const SegSweep SW = load_sweep(cptr(d.sweeps) + sw);
+    const uint32_t sw1 = rec->sw1;
+    for (uint32_t sw = rec->sw0; sw < sw1; ++sw) {
+        CPtr<SegSweep> sp = cptr(d.sweeps) + sw;
+        const uint32_t bits = sp->bits, g0 = sp->g0, g1 = sp->g1, p0 = sp->p0;
+        const int q0 = bits & 255, q1 = (bits >> 8) & 255, q2 = bits >> 16;
         // bat<S> is linear over GF(2) (shifts, masks and XORs) and a group's
         // base and the sweep offsets have disjoint bits, so the LDS slot of
         // base | off[j] is bat(base) ^ bat(off[j]): the eight swizzled
         // offsets are wave-uniform and each access costs one XOR
         // (byte offsets: the XOR of two multiples of sizeof(V) is one)
+        const uint32_t o0 = bat<S>(1u << q0) * (uint32_t)sizeof(V), o1 = bat<S>(1u << q1) * (uint32_t)sizeof(V),
+                       o2 = bat<S>(1u << q2) * (uint32_t)sizeof(V);
         uint32_t so[8];
 #pragma unroll
-        for (int j = 0; j < 8; ++j)
-            so[j] = bat<S>(((j & 1) ? (1u << SW.b[0]) : 0u) | ((j & 2) ? (1u << SW.b[1]) : 0u) |
-                           ((j & 4) ? (1u << SW.b[2]) : 0u)) * (uint32_t)sizeof(V);
-        for (uint32_t g0 = 0; g0 < groups; g0 += blockDim.x) {
-            const uint32_t g = g0 + threadIdx.x;
+        for (int j = 0; j < 8; ++j) so[j] = ((j & 1) ? o0 : 0u) ^ ((j & 2) ? o1 : 0u) ^ ((j & 4) ? o2 : 0u);
+        for (uint32_t gb = 0; gb < groups; gb += 256) {
+            const uint32_t g = gb + tid;
             const bool act = g < groups;
+            // lanes past the last group compute on zeros: the operations stay in
+            // uniform control flow (within a divergent branch the compiler would
+            // linearise the dispatch and copy x and l at each of its joins)
             uint32_t bb = 0;
             V x[8], l[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) x[j].x = x[j].y = l[j].x = l[j].y = 0;
             if (act) {
-                bb = bat<S>(ins0_32(ins0_32(ins0_32(g, SW.b[0]), SW.b[1]), SW.b[2])) * (uint32_t)sizeof(V);
+                bb = bat<S>(ins0_32(ins0_32(ins0_32(g, q0), q1), q2)) * (uint32_t)sizeof(V);
 #pragma unroll
                 for (int j = 0; j < 8; ++j) x[j] = *reinterpret_cast<const V *>(tpb + (bb ^ so[j]));
                 if (two) {
@@ -551,38 +574,33 @@ __device__ void seg_item(const BatchDev &d, CPtr<BatchRec> rec, const BatchInst 
                     for (int j = 0; j < 8; ++j) l[j] = *reinterpret_cast<const V *>(tlb + (bb ^ so[j]));
                 }
             }
-            int p = SW.p0;
-            // read ahead: the record two gates on and the coefficients of the
-            // next gate are requested while this gate is applied, so the
-            // scalar loads of a gate never wait on each other
-            CPtr<SegGate> sg = cptr(d.segs);
-            GateOp o0 = load_op(sg + SW.g0);
-            GateOp o1 = SW.g0 + 1 < SW.g1 ? load_op(sg + SW.g0 + 1) : o0;
-            Coef8<R> cn = load_coef(mats + 2 * (uint64_t)o0.mat);
-            for (uint32_t gi = SW.g0; gi < SW.g1; ++gi) {
-                const GateOp G = o0;
-                const Coef8<R> c = cn;
-                o0 = o1;
-                if (gi + 2 < SW.g1) o1 = load_op(sg + gi + 2);
-                if (gi + 1 < SW.g1) cn = load_coef(mats + 2 * (uint64_t)o0.mat);
-                if (adj && gi_param(G.info)) {
-                    double re = 0.0, im = 0.0;
-                    if (act) reg_inner(l, x, gi_xl(G.info), gi_zl(G.info), &re, &im);
-                    re = wave_total63(re);
-                    im = wave_total63(im);
-                    // one wave adds into its own slot, in program order
-                    if (lane == 63) {
-                        atomicAdd(&gsum[(p * 4 + wave) * 2], re);
-                        atomicAdd(&gsum[(p * 4 + wave) * 2 + 1], im);
-                    }
+            p = p0;
+            // read ahead: the record two operations on and the first
+            // coefficients of the next one are requested while this one is
+            // applied, so an operation's scalar loads never wait on each other
+            // (the tables are padded by two entries)
+            uint32_t info = ops[g0].info, mat = ops[g0].mat, info1 = ops[g0 + 1].info, mat1 = ops[g0 + 1].mat;
+            R c1 = mats[mat], s1 = mats[mat + 1];
+            for (uint32_t gi = g0; gi < g1; ++gi) {
+                const uint32_t op = info;
+                const R c = c1, s = s1;
+                CPtr<R> m = mats + mat;
+                info = info1;
+                mat = mat1;
+                c1 = mats[mat];
+                s1 = mats[mat + 1];
+                info1 = ops[gi + 2].info;
+                mat1 = ops[gi + 2].mat;
+                const double v = seg_op<V, R>(op, x, l, two, c, s, m);
+                if (op & kSegParam) {
+                    acc = __builtin_amdgcn_mfma_f64_16x16x4f64((uint32_t)(lane & 15) == (p & 15u) ? 1.0 : 0.0, v, acc,
+                                                               0, 0, 0);
                     ++p;
-                }
-                if (act) {
-                    CPtr<R> m = mats + 2 * (uint64_t)G.mat;
-                    reg_apply(G.info, x, c, m);
-                    if (two) reg_apply(G.info, l, c, m);
+                    if ((p & 15u) == 0) flush_sums(acc, gsum, p - 16, lane, wave);
                 }
             }
+            // more groups follow: they start again at p0
+            if (adj && groups > 256 && (p & 15u)) flush_sums(acc, gsum, p & ~15u, lane, wave);
             if (act) {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) *reinterpret_cast<V *>(tpb + (bb ^ so[j])) = x[j];
@@ -594,106 +612,117 @@ __device__ void seg_item(const BatchDev &d, CPtr<BatchRec> rec, const BatchInst 
         }
         __syncthreads();
     }
-    for (uint32_t sg = rec->sg0; sg < rec->sg1; ++sg) nred += (adj && cptr(d.segs)[sg].slot >= 0);
-    // one partial per inner product: its four waves in a fixed order
-    if (adj && nred) {
-        int idx = 0;
-        for (uint32_t sg = rec->sg0; sg < rec->sg1; ++sg) {
-            const int slot = cptr(d.segs)[sg].slot;
-            if (slot < 0) continue;
-            if ((int)threadIdx.x == (idx & 255)) {
-                double sre = 0.0, sim = 0.0;
-                for (int v = 0; v < 4; ++v) {
-                    sre += gsum[(idx * 4 + v) * 2];
-                    sim += gsum[(idx * 4 + v) * 2 + 1];
-                }
-                double *p = d.partials + in.part_off + 2 * ((uint64_t)slot * in.wgs + w);
-                p[0] = sre;
-                p[1] = sim;
-            }
-            ++idx;
+    if (adj && rec->np) {
+        if (groups <= 256 && (p & 15u)) flush_sums(acc, gsum, p & ~15u, lane, wave);
+        __syncthreads();
+        // one partial per inner product: its four waves in a fixed order
+        if (tid < rec->np) {
+            const double sum = ((gsum[tid * 4] + gsum[tid * 4 + 1]) + gsum[tid * 4 + 2]) + gsum[tid * 4 + 3];
+            d.partials[in.part_off + (uint64_t)d.slots[rec->ps0 + tid] * in.wgs + w] = sum;
         }
     }
     if (chunked) {
-        const uint4 *t16p = reinterpret_cast<const uint4 *>(tp), *t16l = reinterpret_cast<const uint4 *>(tl);
-        uint4 *p16 = reinterpret_cast<uint4 *>(psi), *l16 = reinterpret_cast<uint4 *>(sec);
-        for (uint32_t c = threadIdx.x; c < nchunk; c += blockDim.x) {
-            const uint64_t x = addr(c << S) >> S;
-            p16[x] = t16p[bswz(c)];
-            if (two) l16[x ^ (dsec >> S)] = t16l[bswz(c)];
+        const nu4 *t16p = reinterpret_cast<const nu4 *>(tp), *t16l = reinterpret_cast<const nu4 *>(tl);
+        nu4 *p16 = reinterpret_cast<nu4 *>(psi), *l16 = reinterpret_cast<nu4 *>(sec);
+        for (uint32_t u = 0; u * 256 + tid < nchunk; ++u) {
+            const uint64_t x = x0 | chunk_part(u);
+            const uint32_t z = zl ^ bswz(u * 256);
+            p16[x >> S] = t16p[z];
+            if (two) l16[(x ^ dsec) >> S] = t16l[z];
         }
     } else {
-        for (uint32_t e = threadIdx.x; e < T; e += blockDim.x) {
-            const uint64_t x = addr(e);
-            psi[x] = tp[bat<S>(e)];
-            if (two) sec[x ^ dsec] = tl[bat<S>(e)];
+        for (uint32_t u = 0; u * 256 + tid < nchunk; ++u) {
+            const uint64_t x = x0 | chunk_part(u);
+            const uint32_t e = bat<S>(u * 256 + tid);
+            psi[x] = tp[e];
+            if (two) sec[x ^ dsec] = tl[e];
         }
     }
-    __syncthreads();   // the LDS tables and tiles are reused by the next item
+    __syncthreads();   // the LDS sums and tiles are reused by the next item
 }
 
-// lambda[y] = (H psi)[y] for y in [y0, y1), and partial <psi|lambda>.
+// lambda[y] = (H psi)[y] for the 2^tb amplitudes from y0, and the partial sum
+// of Re <psi|lambda>.  A lane's amplitudes are y0 + tid + 256 j: a term's sign
+// is a per-lane parity, formed once, and a wave-uniform one per j.
 template <typename R>
-__device__ void hpsi_range(const BatchInst &in, const PauliSumGroup *tg, const PauliSumTerm *tt, uint64_t y0,
-                           uint64_t y1, double *pre, double *pim) {
+__device__ __forceinline__ double hpsi_range(const BatchDev &d, const BatchInst &in, uint64_t y0, uint32_t count) {
     using V = typename BAmp<R>::T;
+    constexpr int J = 4;
     const V *psi = reinterpret_cast<const V *>(in.psi);
     V *lam = reinterpret_cast<V *>(in.lam);
-    CPtr<PauliSumGroup> groups = cptr(tg) + in.tg_off;
-    CPtr<PauliSumTerm> terms = cptr(tt) + in.tt_off;
-    double sre = 0.0, sim = 0.0;
-    for (uint64_t y = y0 + threadIdx.x; y < y1; y += blockDim.x) {
-        double ar = 0.0, ai = 0.0;
+    CPtr<BatchHGroup> groups = cptr(d.tg) + in.tg_off;
+    CPtr<BatchHTerm> terms = cptr(d.tt) + in.tt_off;
+    double e = 0.0;
+    for (uint32_t c0 = 0; c0 < count; c0 += 256 * J) {
+        const uint64_t yb = y0 + c0;            // uniform
+        const uint64_t yt = yb + threadIdx.x;
+        const uint32_t left = count - c0;
+        double lr[J], li[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) lr[j] = li[j] = 0.0;
         for (uint32_t g = 0; g < in.ngroups; ++g) {
-            const uint64_t src = y ^ groups[g].x;
-            const V v = psi[src];
-            double cr = 0.0, ci = 0.0;
-            const int t1 = groups[g].first + groups[g].count;
-            for (int t = groups[g].first; t < t1; ++t) {
-                const bool neg = __popcll(terms[t].z & src) & 1;
-                cr += neg ? -terms[t].cre : terms[t].cre;
-                ci += neg ? -terms[t].cim : terms[t].cim;
+            const uint64_t x = groups[g].x;
+            const uint32_t first = groups[g].first, count_g = groups[g].count, odd = groups[g].odd;
+            V v[J];
+            double c[J];
+#pragma unroll
+            for (int j = 0; j < J; ++j) {
+                v[j].x = v[j].y = 0;
+                if (256u * j + threadIdx.x < left) v[j] = psi[(yt + 256 * j) ^ x];
+                c[j] = 0.0;
             }
-            ar += cr * (double)v.x - ci * (double)v.y;
-            ai += cr * (double)v.y + ci * (double)v.x;
+            for (uint32_t t = first; t < first + count_g; ++t) {
+                const uint64_t z = terms[t].z;
+                const double ct = terms[t].c;
+                const uint32_t neg = (uint32_t)__popcll(z & (yt ^ x)) & 1u;
+                const double cs = __hiloint2double(__double2hiint(ct) ^ (int)(neg << 31), __double2loint(ct));
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    const uint32_t nj = (uint32_t)__popc((uint32_t)z & (256u * j)) & 1u;   // uniform; bits 8-9 of yt are yb's
+                    c[j] += __hiloint2double(__double2hiint(cs) ^ (int)(nj << 31), __double2loint(cs));
+                }
+            }
+            if (odd) {
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    lr[j] = fma(-c[j], (double)v[j].y, lr[j]);
+                    li[j] = fma(c[j], (double)v[j].x, li[j]);
+                }
+            } else {
+#pragma unroll
+                for (int j = 0; j < J; ++j) {
+                    lr[j] = fma(c[j], (double)v[j].x, lr[j]);
+                    li[j] = fma(c[j], (double)v[j].y, li[j]);
+                }
+            }
         }
-        V o;
-        o.x = (R)ar;
-        o.y = (R)ai;
-        lam[y] = o;
-        const V p = psi[y];
-        // <psi|lambda> with lambda as stored (rounded to the state dtype)
-        sre += (double)p.x * (double)o.x + (double)p.y * (double)o.y;
-        sim += (double)p.x * (double)o.y - (double)p.y * (double)o.x;
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            if (256u * j + threadIdx.x >= left) continue;
+            V o;
+            o.x = (R)lr[j];
+            o.y = (R)li[j];
+            lam[yt + 256 * j] = o;
+            // <psi|lambda> with lambda as stored (rounded to the state dtype)
+            const V p = psi[yt + 256 * j];
+            e = fma((double)p.y, (double)o.y, fma((double)p.x, (double)o.x, e));
+        }
     }
-    *pre = sre;
-    *pim = sim;
+    return e;
 }
 
-// One work item: item w of record rec.
 // One work item: item w of record rec (pair: items w and w + 1 of a FWD record).
 template <typename R>
-__device__ void run_item(const BatchDev &d, CPtr<BatchRec> rec, uint32_t w, double *red, bool pair = false) {
+__device__ __forceinline__ void run_item(const BatchDev &d, CPtr<BatchRec> rec, uint32_t w, double *red, bool pair = false) {
     using V = typename BAmp<R>::T;
     const BatchInst in = load_inst(cptr(d.insts) + rec->inst);
     if (rec->kind != BK_HPSI) {
-        seg_item<R>(d, rec, in, w, red, reinterpret_cast<V *>(batch_lds), pair);
+        seg_item<R>(d, rec, in, w, reinterpret_cast<V *>(batch_lds), pair);
         return;
     }
-    double re = 0.0, im = 0.0;
-    {
-        const uint64_t N = 1ull << in.n, per = N / rec->wgs;
-        hpsi_range<R>(in, d.tg, d.tt, per * w, per * (w + 1), &re, &im);
-    }
-    if (rec->slot >= 0) {
-        const double sre = block_sum(re, red);
-        const double sim = block_sum(im, red);
-        if (threadIdx.x == 0) {
-            double *p = d.partials + in.part_off + 2 * ((uint64_t)rec->slot * in.wgs + w);
-            p[0] = sre;
-            p[1] = sim;
-        }
-    }
+    const uint32_t per = 1u << rec->tb;
+    const double sum = block_sum(hpsi_range<R>(d, in, (uint64_t)w << rec->tb, per), red);
+    if (threadIdx.x == 0) d.partials[in.part_off + w] = sum;   // slot 0
 }
 
 __device__ __forceinline__ uint64_t uniform64(uint64_t v) {
@@ -713,7 +742,7 @@ __device__ __forceinline__ uint64_t find_rec(CPtr<BatchRec> recs, uint64_t lo, u
 }
 
 template <typename R>
-__global__ void __launch_bounds__(256) k_batch_step(BatchDev d, int s) {
+__global__ void __launch_bounds__(256, 3) k_batch_step(BatchDev d, int s) {
     __shared__ double red[4];
     const uint64_t r = find_rec(cptr(d.recs), cptr(d.step_rec)[s], cptr(d.step_rec)[s + 1], blockIdx.x);
     CPtr<BatchRec> rec = cptr(d.recs) + r;   // by pointer: its qhi[] is indexed at run time
@@ -839,13 +868,16 @@ __global__ void __launch_bounds__(256) k_batch_init(BatchDev d) {
     }
 }
 
-__global__ void k_batch_finish(BatchDev d) {
+// One wave per result slot: its partial sums over the work items, in a fixed
+// order.
+__global__ void __launch_bounds__(256) k_batch_finish(BatchDev d) {
     const BatchInst in = d.insts[blockIdx.x];
-    for (int v = threadIdx.x; v < 2 * in.nslots; v += blockDim.x) {
-        const int slot = v >> 1, c = v & 1;
+    const int lane = threadIdx.x & 63;
+    for (int slot = (int)(blockIdx.y * 4 + (threadIdx.x >> 6)); slot < in.nslots; slot += (int)gridDim.y * 4) {
         double s = 0.0;
-        for (uint32_t w = 0; w < in.wgs; ++w) s += d.partials[in.part_off + 2 * ((uint64_t)slot * in.wgs + w) + c];
-        d.results[in.res_off + v] = s;
+        for (uint32_t w = lane; w < in.wgs; w += 64) s += d.partials[in.part_off + (uint64_t)slot * in.wgs + w];
+        for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (lane == 0) d.results[in.res_off + slot] = s;
     }
 }
 
@@ -906,7 +938,7 @@ cast_status batch_init_states(const BatchDev &d, cast_dtype dt, hipStream_t st) 
 }
 
 cast_status batch_finish(const BatchDev &d, hipStream_t st) {
-    hipLaunchKernelGGL(k_batch_finish, dim3(d.ninst), dim3(256), 0, st, d);
+    hipLaunchKernelGGL(k_batch_finish, dim3(d.ninst, 16), dim3(256), 0, st, d);
     return launched("batch finish");
 }
 
