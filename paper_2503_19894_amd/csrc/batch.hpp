@@ -123,6 +123,10 @@ struct BatchDev {           // device pointers of one program
     int ninst;
 };
 
+// 64-bit counters of the persistent launch, each on a cache line of its own:
+// next item, error flag, then per instance the items completed.
+constexpr size_t kCounterStride = 16;
+
 // Queues step s (one launch over all its records).
 cast_status batch_launch_step(const BatchDev &d, cast_dtype dt, int s, uint64_t nitems, size_t lds,
                               hipStream_t st);

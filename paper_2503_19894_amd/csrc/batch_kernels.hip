@@ -749,8 +749,8 @@ __global__ void __launch_bounds__(256, 3) k_batch_step(BatchDev d, int s) {
     run_item<R>(d, rec, blockIdx.x - rec->item0, red);
 }
 
-// counters[0]: next item; counters[1]: error flag; counters[2 + i]: items
-// of instance i completed.  A workgroup claims `chunk` consecutive items per
+// counters (stride kCounterStride): 0 next item; 1 error flag; 2 + i items of
+// instance i completed.  A workgroup claims `chunk` consecutive items per
 // counter atomic and publishes its completions per run of items of one
 // instance; before any wait it publishes what it holds, so it never waits on
 // its own unpublished work.  Items are claimed in global order and every
@@ -764,10 +764,11 @@ __global__ void __launch_bounds__(256) k_batch_persistent(BatchDev d, uint64_t t
     __shared__ int stop_sh;
     uint32_t pend_inst = 0;     // thread 0 only: completed, unpublished items
     unsigned long long pend = 0;
+    unsigned long long *const err = counters + kCounterStride;
     for (;;) {
         if (threadIdx.x == 0) {
             base_sh = atomicAdd(&counters[0], (unsigned long long)chunk);
-            stop_sh = __hip_atomic_load(&counters[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
+            stop_sh = __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0;
         }
         __syncthreads();
         // values read from LDS are not known to be uniform; read through
@@ -787,9 +788,9 @@ __global__ void __launch_bounds__(256) k_batch_persistent(BatchDev d, uint64_t t
             const uint64_t r = find_rec(cptr(d.recs), cptr(d.step_rec)[s], cptr(d.step_rec)[s + 1], x);
             CPtr<BatchRec> rec = cptr(d.recs) + r;   // by pointer: its qhi[] is indexed at run time
             if (threadIdx.x == 0) {
-                unsigned long long *done = &counters[2 + rec->inst];
+                unsigned long long *done = &counters[(2 + rec->inst) * kCounterStride];
                 if (pend && pend_inst != rec->inst) {
-                    __hip_atomic_fetch_add(&counters[2 + pend_inst], pend, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+                    __hip_atomic_fetch_add(&counters[(2 + pend_inst) * kCounterStride], pend, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
                     pend = 0;
                 }
                 // poll with relaxed loads (an acquire per poll would invalidate the
@@ -805,8 +806,8 @@ __global__ void __launch_bounds__(256) k_batch_persistent(BatchDev d, uint64_t t
                     uint32_t spins = 0;
                     while (force || __hip_atomic_load(done, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < rec->need) {
                         if (++spins > spin_limit ||
-                            __hip_atomic_load(&counters[1], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
-                            atomicExch(&counters[1], 1ull);
+                            __hip_atomic_load(err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) != 0) {
+                            atomicExch(err, 1ull);
                             stop_sh = 1;
                             break;
                         }
@@ -832,7 +833,7 @@ __global__ void __launch_bounds__(256) k_batch_persistent(BatchDev d, uint64_t t
             if (pair) ++item;
         }
         if (threadIdx.x == 0 && pend) {
-            __hip_atomic_fetch_add(&counters[2 + pend_inst], pend, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
+            __hip_atomic_fetch_add(&counters[(2 + pend_inst) * kCounterStride], pend, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_AGENT);
             pend = 0;
         }
         __syncthreads();
