@@ -44,14 +44,32 @@ struct InstPlan {
     uint32_t wgs = 1;
 };
 
-}  // namespace cast
-
-struct cast_batch {
+// A batch's program on the host: the device tables and their sizes.
+struct Program {
     int ninst = 0;
     cast_dtype dt = CAST_C128;
+    std::vector<InstPlan> inst;
+    std::vector<BatchRec> recs;         // step-major
+    std::vector<SegOp> ops;
+    std::vector<uint32_t> slots;
+    std::vector<SegSweep> sweeps;
+    std::vector<BatchInst> insts;       // psi, lam and init_src: set by the owner
+    std::vector<BatchHGroup> tg;
+    std::vector<BatchHTerm> tt;
+    std::vector<double> coefs;          // fixed gates' coefficients; rotations are bound per run
+    std::vector<uint64_t> step_rec, step_item;
+    std::vector<uint64_t> step_items;   // items per step
+    std::vector<size_t> step_lds;       // LDS bytes of each step's launch
+    uint64_t part_doubles = 0, result_doubles = 0, total_items = 0;
+    size_t state_elems = 0;             // psi and lambda of every instance, in order
+    int nsteps = 0;
+};
+
+}  // namespace cast
+
+struct cast_batch : cast::Program {
     int mode = 0;
     hipStream_t stream = nullptr;
-    std::vector<cast::InstPlan> inst;
     // device
     void *states = nullptr;
     cast::BatchRec *d_recs = nullptr;
@@ -69,12 +87,6 @@ struct cast_batch {
     // host
     void *h_mats = nullptr;      // pinned, matrices in the state dtype
     double *h_results = nullptr; // pinned
-    size_t mat_reals = 0, result_doubles = 0;
-    std::vector<uint64_t> step_rec, step_item;
-    std::vector<uint64_t> step_items;   // items per step
-    std::vector<size_t> step_lds;       // LDS bytes of each step's launch
-    int nsteps = 0;
-    uint64_t total_items = 0;
     cast::BatchDev dev;
     hipGraph_t graph = nullptr;
     hipGraphExec_t exec = nullptr;
@@ -217,18 +229,45 @@ static uint32_t fixed_op(const std::vector<cplx> &mat, int t0, int t1, bool dagg
     return D == 2 ? SO_GEN1 + bit : SO_GEN2 + pair;
 }
 
-// Writes coefficients into the pinned table in the state dtype.
-static void put_reals(cast_batch *b, uint64_t off, const double *v, size_t n) {
+// Writes coefficients into a table in the state dtype.
+static void put_reals(cast_dtype dt, void *table, uint64_t off, const double *v, size_t n) {
     for (size_t i = 0; i < n; ++i) {
-        if (b->dt == CAST_C128) ((double *)b->h_mats)[off + i] = v[i];
-        else ((float *)b->h_mats)[off + i] = (float)v[i];
+        if (dt == CAST_C128) ((double *)table)[off + i] = v[i];
+        else ((float *)table)[off + i] = (float)v[i];
+    }
+}
+
+// Binds parameters (host FP64, cast once).
+static void bind_rotations(const Program &p, const double *const *theta, void *table) {
+    for (int i = 0; i < p.ninst; ++i)
+        for (const BoundOp &o : p.inst[i].bound) {
+            const std::vector<cast_gate> &g = p.inst[i].gates;
+            double angle = 0.0;
+            for (int l : o.gates) angle += g[l].param_coeff * theta[i][g[l].param_id];
+            if (!o.diag || p.dt == CAST_C64) angle *= 0.5;
+            double cs[2] = {std::cos(angle), o.dagger ? -std::sin(angle) : std::sin(angle)};
+            if (!o.diag && p.dt == CAST_C128) shear_coefs(cs);
+            put_reals(p.dt, table, o.mat, cs, 2);
+        }
+}
+
+// Energy and gradient of one instance from its result slots.
+static void read_results(const InstPlan &ip, const double *r, double *energy, double *grad) {
+    *energy = r[0];
+    for (size_t p = 0; p < ip.nparams; ++p) grad[p] = 0.0;
+    for (size_t l = ip.gates.size(); l-- > 0;) {
+        const int s = ip.gslot[l];
+        if (s < 0) continue;
+        // Im i^{|x & z|} S from the part of S the kernel takes
+        const double v = __builtin_popcountll(ip.gx[l] & ip.gz[l]) & 2 ? -r[s] : r[s];
+        grad[ip.gates[l].param_id] += ip.gates[l].param_coeff * v;
     }
 }
 
 static cast_status queue_program(cast_batch *b) {
     hipStream_t s = b->stream;
     const size_t rsz = b->dt == CAST_C128 ? 8 : 4;
-    CAST_HIP_TRY(hipMemcpyAsync(b->d_mats, b->h_mats, b->mat_reals * rsz, hipMemcpyHostToDevice, s));
+    CAST_HIP_TRY(hipMemcpyAsync(b->d_mats, b->h_mats, b->coefs.size() * rsz, hipMemcpyHostToDevice, s));
     if (cast_status rc = batch_init_states(b->dev, b->dt, s)) return rc;
     if (b->mode == 2) {
         if (cast_status rc = batch_zero(b->d_counters, (2 + (size_t)b->ninst) * kCounterStride, s)) return rc;
@@ -455,50 +494,30 @@ static cast_status upload(T **dst, const std::vector<T> &src) {
 
 }  // namespace cast
 
-using namespace cast;
+namespace cast {
 
-extern "C" {
-
-cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const cast_gate *const *circuits,
-                         const size_t *n_gates, const size_t *n_params, const cast_pauli_term *const *hams,
-                         const size_t *n_terms, const int *init_kind, const cast_sv *const *init_states, int mode,
-                         cast_batch **out) {
-    if (!out) return fail(CAST_EINVAL, "out is NULL");
-    *out = nullptr;
-    if (n_inst < 1 || n_inst > 65535) return fail(CAST_EINVAL, "n_inst must be in [1, 65535]");
-    if (!n_qubits || !circuits || !n_gates || !n_params || !hams || !n_terms)
-        return fail(CAST_EINVAL, "NULL array argument");
-    if (dt != CAST_C64 && dt != CAST_C128) return fail(CAST_EINVAL, "bad dtype");
-    if (mode < 0 || mode > 2) return fail(CAST_EINVAL, "mode must be 0, 1 or 2");
-    cast_batch *b = new cast_batch;
+// Plans a batch (host only).  tile_bits: log2 amplitudes of a segment's tile;
+// group_bytes: states of the instances whose programs run side by side (0:
+// all of them).  The last two arguments of an instance with init_kind 2 are
+// checked here; its state's address is left to the owner.
+static cast_status plan_program(int n_inst, const int *n_qubits, cast_dtype dt, const cast_gate *const *circuits,
+                                const size_t *n_gates, const size_t *n_params, const cast_pauli_term *const *hams,
+                                const size_t *n_terms, const int *init_kind, const cast_sv *const *init_states,
+                                int tile_bits, double group_bytes, Program *out) {
+    Program *b = out;
     b->ninst = n_inst;
     b->dt = dt;
-    b->mode = mode;
     b->inst.resize(n_inst);
-    std::vector<BatchHGroup> tg;
-    std::vector<BatchHTerm> tt;
-    std::vector<BatchInst> hinst(n_inst);
-    size_t state_elems = 0;
-    // amplitudes per work item, and the cache budget of an instance group
-    // tile of a segment: 2^batch_tile_bits amplitudes of psi and of lambda
-    const int tile_bits = batch_tile_bits(dt);
-    // per-step launches: groups sized for the 256 MB last-level cache; the
-    // persistent launch keeps every instance in one step-major stream
-    double group_bytes = mode == 2 ? 0.0 : 192.0 * (1 << 20);
-    if (const char *e = std::getenv("CAST_BATCH_GROUP_MB"))
-        if (mode != 2) group_bytes = atof(e) * (1 << 20);
-    if (const char *e = std::getenv("CAST_PERSISTENT_GROUP_MB"))
-        if (mode == 2) group_bytes = atof(e) * (1 << 20);
+    std::vector<BatchHGroup> &tg = b->tg;
+    std::vector<BatchHTerm> &tt = b->tt;
+    std::vector<BatchInst> &hinst = b->insts;
+    hinst.resize(n_inst);
     uint64_t part = 0, res = 0;
-    auto bail = [&](cast_status rc) {
-        free_batch(b);
-        return rc;
-    };
     for (int i = 0; i < n_inst; ++i) {
         InstPlan &ip = b->inst[i];
         const int n = n_qubits[i];
-        if (n < 3 || n > kMaxQubits) return bail(fail(CAST_EINVAL, "instance qubit count must be in [3, 34]"));
-        if (n_gates[i] && !circuits[i]) return bail(fail(CAST_EINVAL, "circuit is NULL"));
+        if (n < 3 || n > kMaxQubits) return fail(CAST_EINVAL, "instance qubit count must be in [3, 34]");
+        if (n_gates[i] && !circuits[i]) return fail(CAST_EINVAL, "circuit is NULL");
         ip.n = n;
         ip.nparams = n_params[i];
         ip.gates.assign(circuits[i], circuits[i] + n_gates[i]);
@@ -513,17 +532,17 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         int slot = 1;  // slot 0: energy
         for (size_t l = 0; l < L; ++l) {
             const cast_gate &g = ip.gates[l];
-            if (g.k < 1 || g.k > 2) return bail(fail(CAST_EUNSUPPORTED, "batched programs take 1- and 2-qubit gates"));
+            if (g.k < 1 || g.k > 2) return fail(CAST_EUNSUPPORTED, "batched programs take 1- and 2-qubit gates");
             for (int a = 0; a < g.k; ++a) {
-                if (g.qubits[a] < 0 || g.qubits[a] >= n) return bail(fail(CAST_EINVAL, "gate qubit out of range"));
+                if (g.qubits[a] < 0 || g.qubits[a] >= n) return fail(CAST_EINVAL, "gate qubit out of range");
                 for (int c = 0; c < a; ++c)
-                    if (g.qubits[a] == g.qubits[c]) return bail(fail(CAST_EINVAL, "duplicate gate qubit"));
+                    if (g.qubits[a] == g.qubits[c]) return fail(CAST_EINVAL, "duplicate gate qubit");
             }
             const int D = 1 << g.k;
             if (g.param_id >= 0) {
-                if ((size_t)g.param_id >= ip.nparams) return bail(fail(CAST_EINVAL, "param_id out of range"));
+                if ((size_t)g.param_id >= ip.nparams) return fail(CAST_EINVAL, "param_id out of range");
                 if (g.generator <= 0 || g.generator >= (1 << (2 * g.k)))
-                    return bail(fail(CAST_EINVAL, "parametrised gate needs a Pauli generator"));
+                    return fail(CAST_EINVAL, "parametrised gate needs a Pauli generator");
                 ip.gslot[l] = slot++;
                 for (int a = 0; a < g.k; ++a) {
                     const int letter = (g.generator >> (2 * a)) & 3;
@@ -535,7 +554,7 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
                 ip.diag[l] = ip.gx[l] == 0;
                 continue;
             }
-            if (!g.matrix) return bail(fail(CAST_EINVAL, "fixed gate without a matrix"));
+            if (!g.matrix) return fail(CAST_EINVAL, "fixed gate without a matrix");
             std::vector<cplx> m((size_t)D * D);
             for (int e = 0; e < D * D; ++e) m[e] = cplx(g.matrix[2 * e], g.matrix[2 * e + 1]);
             sorted_matrix(g.k, g.qubits, m, &ip.sq0[l], &ip.sq1[l], &ip.fixed[l]);
@@ -558,7 +577,7 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         for (auto &sg : segment(true)) ip.ops.push_back(HostOp{BK_ADJ, sg});
         ip.wgs = 1u << (n - ip.tb);
         // Hamiltonian, grouped by x mask
-        if (n_terms[i] && !hams[i]) return bail(fail(CAST_EINVAL, "Hamiltonian is NULL"));
+        if (n_terms[i] && !hams[i]) return fail(CAST_EINVAL, "Hamiltonian is NULL");
         BatchInst &bi = hinst[i];
         bi.n = n;
         bi.nslots = ip.nslots;
@@ -570,7 +589,7 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         const uint64_t full = (1ull << n) - 1;
         for (size_t t = 0; t < n_terms[i]; ++t) {
             const cast_pauli_term &pt = hams[i][t];
-            if ((pt.xmask | pt.zmask) & ~full) return bail(fail(CAST_EINVAL, "Pauli term acts outside the state"));
+            if ((pt.xmask | pt.zmask) & ~full) return fail(CAST_EINVAL, "Pauli term acts outside the state");
             const std::pair<uint64_t, int> key(pt.xmask, __builtin_popcountll(pt.xmask & pt.zmask) & 1);
             if (!byx.count(key)) order.push_back(key);
             byx[key].push_back(t);
@@ -591,15 +610,16 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
         bi.res_off = res;
         res += (uint64_t)ip.nslots;
         bi.init_kind = init_kind ? init_kind[i] : 0;
-        if (bi.init_kind < 0 || bi.init_kind > 2) return bail(fail(CAST_EINVAL, "bad init kind"));
+        if (bi.init_kind < 0 || bi.init_kind > 2) return fail(CAST_EINVAL, "bad init kind");
         if (bi.init_kind == 2) {
             const cast_sv *src = init_states ? init_states[i] : nullptr;
             if (!src || !src->data || src->n != n || src->dt != dt)
-                return bail(fail(CAST_EINVAL, "init state missing or of the wrong size/dtype"));
+                return fail(CAST_EINVAL, "init state missing or of the wrong size/dtype");
             bi.init_src = src->data;
         }
-        state_elems += 2ull << n;  // psi and lambda
+        b->state_elems += 2ull << n;  // psi and lambda
     }
+    b->part_doubles = part;
     b->result_doubles = res;
     // ---- instance groups (consecutive instances whose psi and lambda fit the
     // cache budget run their whole programs before the next group), then
@@ -631,11 +651,11 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
             groups.swap(merged);
         }
     }
-    std::vector<BatchRec> recs;
-    std::vector<SegOp> segs;
-    std::vector<uint32_t> slots;
-    std::vector<SegSweep> sweeps;
-    std::vector<double> coefs;   // fixed gates' coefficients; rotations are bound per run
+    std::vector<BatchRec> &recs = b->recs;
+    std::vector<SegOp> &segs = b->ops;
+    std::vector<uint32_t> &slots = b->slots;
+    std::vector<SegSweep> &sweeps = b->sweeps;
+    std::vector<double> &coefs = b->coefs;
     uint64_t item_base = 0;
     for (auto &gr : groups) {
     size_t max_ops = 0;
@@ -763,7 +783,7 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
             recs.push_back(r);
             items += ip.wgs;
         }
-        if (items > 0x7fffffffull) return bail(fail(CAST_EUNSUPPORTED, "too many work items in one step"));
+        if (items > 0x7fffffffull) return fail(CAST_EUNSUPPORTED, "too many work items in one step");
         b->step_items.push_back(items);
         {
             // LDS of this step's launch: the tables, then one tile (forward) or
@@ -782,27 +802,127 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
     // the kernel reads two operations and two coefficients ahead
     segs.resize(segs.size() + 2, SegOp{0, 0});
     coefs.resize(coefs.size() + 2, 0.0);
-    if (coefs.size() > 0xffffffffull) return bail(fail(CAST_EUNSUPPORTED, "batch matrix table exceeds 2^32 entries"));
-    b->mat_reals = coefs.size();
+    if (coefs.size() > 0xffffffffull) return fail(CAST_EUNSUPPORTED, "batch matrix table exceeds 2^32 entries");
     b->nsteps = (int)b->step_items.size();
     b->step_rec.push_back(recs.size());
     b->step_item.push_back(item_base);
     b->total_items = item_base;
+    return CAST_OK;
+}
+
+cast_status adjoint_segments(const cast_sv *init, const cast_gate *gates, size_t n_gates, const double *theta,
+                             size_t n_params, const cast_pauli_term *terms, size_t n_terms, double *energy,
+                             double *grad) {
+    const int n = init->n, kind = CAST_INIT_STATE;
+    const cast_dtype dt = init->dt;
+    hipStream_t s = init->stream;
+    // one instance has 2^(n - tb) items per step: smaller tiles below 19 qubits
+    // keep some 256 workgroups busy
+    const int tb = std::min(batch_tile_bits(dt), std::max(9, n - 8));
+    Program p;
+    if (cast_status rc = plan_program(1, &n, dt, &gates, &n_gates, &n_params, &terms, &n_terms, &kind, &init, tb, 0.0,
+                                      &p))
+        return rc;
+    const size_t ab = amp_bytes(dt), rsz = ab / 2, N = (size_t)1 << n;
+    DevBuf states(s), tables(s), sums(s);
+    if (cast_status rc = states.alloc(2 * N * ab)) return rc;
+    if (cast_status rc = sums.alloc((p.part_doubles + p.result_doubles) * sizeof(double))) return rc;
+    p.insts[0].psi = states.p;
+    p.insts[0].lam = (char *)states.p + N * ab;
+    p.insts[0].init_src = init->data;
+    // all tables in one buffer and one copy
+    std::vector<char> h;
+    auto put = [&](const void *src, size_t bytes) {
+        const size_t off = (h.size() + 255) & ~(size_t)255;
+        h.resize(off + std::max<size_t>(bytes, 16));
+        if (bytes) std::memcpy(h.data() + off, src, bytes);
+        return off;
+    };
+    auto put_all = [&](const auto &v) { return put(v.data(), v.size() * sizeof(v[0])); };
+    const size_t o_recs = put_all(p.recs), o_ops = put_all(p.ops), o_slots = put_all(p.slots),
+                 o_sweeps = put_all(p.sweeps), o_srec = put_all(p.step_rec), o_sitem = put_all(p.step_item),
+                 o_insts = put_all(p.insts), o_tg = put_all(p.tg), o_tt = put_all(p.tt);
+    std::vector<char> mats(p.coefs.size() * rsz);
+    put_reals(dt, mats.data(), 0, p.coefs.data(), p.coefs.size());
+    bind_rotations(p, &theta, mats.data());
+    const size_t o_mats = put_all(mats);
+    if (cast_status rc = tables.alloc(h.size())) return rc;
+    CAST_HIP_TRY(hipMemcpyAsync(tables.p, h.data(), h.size(), hipMemcpyHostToDevice, s));
+    auto at = [&](size_t off) { return (void *)((char *)tables.p + off); };
+    BatchDev d;
+    d.recs = (const BatchRec *)at(o_recs);
+    d.ops = (const SegOp *)at(o_ops);
+    d.slots = (const uint32_t *)at(o_slots);
+    d.sweeps = (const SegSweep *)at(o_sweeps);
+    d.step_rec = (const uint64_t *)at(o_srec);
+    d.step_item = (const uint64_t *)at(o_sitem);
+    d.insts = (const BatchInst *)at(o_insts);
+    d.mats = at(o_mats);
+    d.tg = (const BatchHGroup *)at(o_tg);
+    d.tt = (const BatchHTerm *)at(o_tt);
+    d.partials = sums.as<double>();
+    d.results = sums.as<double>() + p.part_doubles;
+    d.nsteps = p.nsteps;
+    d.ninst = 1;
+    if (cast_status rc = batch_init_states(d, dt, s)) return rc;
+    for (int st = 0; st < p.nsteps; ++st)
+        if (cast_status rc = batch_launch_step(d, dt, st, p.step_items[st], p.step_lds[st], s)) return rc;
+    if (cast_status rc = batch_finish(d, s)) return rc;
+    std::vector<double> r(p.result_doubles);
+    CAST_HIP_TRY(hipMemcpyAsync(r.data(), d.results, r.size() * sizeof(double), hipMemcpyDeviceToHost, s));
+    CAST_HIP_TRY(hipStreamSynchronize(s));
+    read_results(p.inst[0], r.data(), energy, grad);
+    return CAST_OK;
+}
+
+}  // namespace cast
+
+using namespace cast;
+
+extern "C" {
+
+cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const cast_gate *const *circuits,
+                         const size_t *n_gates, const size_t *n_params, const cast_pauli_term *const *hams,
+                         const size_t *n_terms, const int *init_kind, const cast_sv *const *init_states, int mode,
+                         cast_batch **out) {
+    if (!out) return fail(CAST_EINVAL, "out is NULL");
+    *out = nullptr;
+    if (n_inst < 1 || n_inst > 65535) return fail(CAST_EINVAL, "n_inst must be in [1, 65535]");
+    if (!n_qubits || !circuits || !n_gates || !n_params || !hams || !n_terms)
+        return fail(CAST_EINVAL, "NULL array argument");
+    if (dt != CAST_C64 && dt != CAST_C128) return fail(CAST_EINVAL, "bad dtype");
+    if (mode < 0 || mode > 2) return fail(CAST_EINVAL, "mode must be 0, 1 or 2");
+    cast_batch *b = new cast_batch;
+    b->mode = mode;
+    auto bail = [&](cast_status rc) {
+        free_batch(b);
+        return rc;
+    };
+    // per-step launches: groups sized for the 256 MB last-level cache; the
+    // persistent launch keeps every instance in one step-major stream
+    double group_bytes = mode == 2 ? 0.0 : 192.0 * (1 << 20);
+    if (const char *e = std::getenv("CAST_BATCH_GROUP_MB"))
+        if (mode != 2) group_bytes = atof(e) * (1 << 20);
+    if (const char *e = std::getenv("CAST_PERSISTENT_GROUP_MB"))
+        if (mode == 2) group_bytes = atof(e) * (1 << 20);
+    if (cast_status rc = plan_program(n_inst, n_qubits, dt, circuits, n_gates, n_params, hams, n_terms, init_kind,
+                                      init_states, batch_tile_bits(dt), group_bytes, b))
+        return bail(rc);
     // ---- device and pinned buffers
     const size_t rsz = dt == CAST_C128 ? 8 : 4;
     const size_t ab = amp_bytes(dt);
-    if (cast_status rc = dev_alloc(&b->states, state_elems * ab)) return bail(rc);
+    if (cast_status rc = dev_alloc(&b->states, b->state_elems * ab)) return bail(rc);
     size_t off = 0;
     for (int i = 0; i < n_inst; ++i) {
-        const size_t N = (size_t)1 << hinst[i].n;
-        hinst[i].psi = (char *)b->states + off * ab;
-        hinst[i].lam = (char *)b->states + (off + N) * ab;
+        const size_t N = (size_t)1 << b->insts[i].n;
+        b->insts[i].psi = (char *)b->states + off * ab;
+        b->insts[i].lam = (char *)b->states + (off + N) * ab;
         off += 2 * N;
     }
-    if (cast_status rc = upload(&b->d_recs, recs)) return bail(rc);
-    if (cast_status rc = upload(&b->d_ops, segs)) return bail(rc);
-    if (cast_status rc = upload(&b->d_slots, slots)) return bail(rc);
-    if (cast_status rc = upload(&b->d_sweeps, sweeps)) return bail(rc);
+    if (cast_status rc = upload(&b->d_recs, b->recs)) return bail(rc);
+    if (cast_status rc = upload(&b->d_ops, b->ops)) return bail(rc);
+    if (cast_status rc = upload(&b->d_slots, b->slots)) return bail(rc);
+    if (cast_status rc = upload(&b->d_sweeps, b->sweeps)) return bail(rc);
     {
         int tbm = 0;
         for (auto &ip : b->inst) tbm = std::max(tbm, ip.tb);
@@ -810,21 +930,21 @@ cast_status batch_create(int n_inst, const int *n_qubits, cast_dtype dt, const c
     }
     if (cast_status rc = upload(&b->d_step_rec, b->step_rec)) return bail(rc);
     if (cast_status rc = upload(&b->d_step_item, b->step_item)) return bail(rc);
-    if (cast_status rc = upload(&b->d_insts, hinst)) return bail(rc);
-    if (cast_status rc = upload(&b->d_tg, tg)) return bail(rc);
-    if (cast_status rc = upload(&b->d_tt, tt)) return bail(rc);
-    if (cast_status rc = dev_alloc(&b->d_mats, b->mat_reals * rsz)) return bail(rc);
-    if (cast_status rc = dev_alloc((void **)&b->d_partials, std::max<uint64_t>(1, part) * sizeof(double)))
+    if (cast_status rc = upload(&b->d_insts, b->insts)) return bail(rc);
+    if (cast_status rc = upload(&b->d_tg, b->tg)) return bail(rc);
+    if (cast_status rc = upload(&b->d_tt, b->tt)) return bail(rc);
+    if (cast_status rc = dev_alloc(&b->d_mats, b->coefs.size() * rsz)) return bail(rc);
+    if (cast_status rc = dev_alloc((void **)&b->d_partials, std::max<uint64_t>(1, b->part_doubles) * sizeof(double)))
         return bail(rc);
-    if (cast_status rc = dev_alloc((void **)&b->d_results, std::max<uint64_t>(1, res) * sizeof(double)))
+    if (cast_status rc = dev_alloc((void **)&b->d_results, std::max<uint64_t>(1, b->result_doubles) * sizeof(double)))
         return bail(rc);
     if (cast_status rc = dev_alloc((void **)&b->d_counters, (2 + (size_t)n_inst) * kCounterStride * sizeof(unsigned long long)))
         return bail(rc);
-    if (hipHostMalloc(&b->h_mats, b->mat_reals * rsz) != hipSuccess)
+    if (hipHostMalloc(&b->h_mats, b->coefs.size() * rsz) != hipSuccess)
         return bail(fail(CAST_ENOMEM, "pinned matrix buffer"));
-    if (hipHostMalloc((void **)&b->h_results, (res + 1) * sizeof(double)) != hipSuccess)
+    if (hipHostMalloc((void **)&b->h_results, (b->result_doubles + 1) * sizeof(double)) != hipSuccess)
         return bail(fail(CAST_ENOMEM, "pinned result buffer"));
-    put_reals(b, 0, coefs.data(), coefs.size());
+    put_reals(dt, b->h_mats, 0, b->coefs.data(), b->coefs.size());
     if (hipStreamCreateWithFlags(&b->stream, hipStreamNonBlocking) != hipSuccess)
         return bail(fail(CAST_EHIP, "hipStreamCreate failed"));
     BatchDev &d = b->dev;
@@ -890,16 +1010,7 @@ cast_status batch_run(cast_batch *b, const double *const *theta, double *energie
         if (ip.nparams && (!theta || !theta[i] || !grads || !grads[i]))
             return fail(CAST_EINVAL, "theta/grads missing for an instance with parameters");
     }
-    // bind parameters (host FP64, cast once into the pinned buffer)
-    for (int i = 0; i < b->ninst; ++i)
-        for (const BoundOp &o : b->inst[i].bound) {
-            double angle = 0.0;
-            for (int l : o.gates) angle += b->inst[i].gates[l].param_coeff * theta[i][b->inst[i].gates[l].param_id];
-            if (!o.diag || b->dt == CAST_C64) angle *= 0.5;
-            double cs[2] = {std::cos(angle), o.dagger ? -std::sin(angle) : std::sin(angle)};
-            if (!o.diag && b->dt == CAST_C128) shear_coefs(cs);
-            put_reals(b, o.mat, cs, 2);
-        }
+    bind_rotations(*b, theta, b->h_mats);
     if (b->mode >= 1) {
         CAST_HIP_TRY(hipGraphLaunch(b->exec, b->stream));
     } else {
@@ -913,19 +1024,8 @@ cast_status batch_run(cast_batch *b, const double *const *theta, double *energie
     }
     size_t off = 0;
     for (int i = 0; i < b->ninst; ++i) {
-        const InstPlan &ip = b->inst[i];
-        const double *r = b->h_results + off;
-        off += (size_t)ip.nslots;
-        energies[i] = r[0];
-        if (!ip.nparams) continue;
-        for (size_t p = 0; p < ip.nparams; ++p) grads[i][p] = 0.0;
-        for (size_t l = ip.gates.size(); l-- > 0;) {
-            const int s = ip.gslot[l];
-            if (s < 0) continue;
-            // Im i^{|x & z|} S from the part of S the kernel takes
-            const double v = __builtin_popcountll(ip.gx[l] & ip.gz[l]) & 2 ? -r[s] : r[s];
-            grads[i][ip.gates[l].param_id] += ip.gates[l].param_coeff * v;
-        }
+        read_results(b->inst[i], b->h_results + off, &energies[i], b->inst[i].nparams ? grads[i] : nullptr);
+        off += (size_t)b->inst[i].nslots;
     }
     return CAST_OK;
 }

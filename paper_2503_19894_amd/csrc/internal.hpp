@@ -198,6 +198,31 @@ void dev_free(void *ptr);
 // needs back.  Return a block only once the work using it has completed.
 cast_status pool_alloc(void **ptr, size_t bytes, size_t *cls);
 void pool_free(void *ptr, size_t cls);
+
+// RAII device scratch from the reuse pool.  The block goes back only after
+// its stream has drained (a no-op when the call already synchronised), so
+// an early error return never hands out memory that queued work still uses.
+struct DevBuf {
+    void *p = nullptr;
+    size_t cls = 0;
+    hipStream_t s = nullptr;
+    explicit DevBuf(hipStream_t stream) : s(stream) {}
+    ~DevBuf() {
+        if (!p) return;
+        (void)hipStreamSynchronize(s);
+        pool_free(p, cls);
+    }
+    cast_status alloc(size_t bytes) { return pool_alloc(&p, bytes, &cls); }
+    template <typename T> T *as() const { return (T *)p; }
+};
+
+// adjoint_grad of a circuit of one- and two-qubit gates (n >= 3) as a
+// one-instance batch program on init's stream: segments of many gates per
+// pass.  CAST_ENOMEM leaves no trace; the caller has checked the terms.
+cast_status adjoint_segments(const cast_sv *init, const cast_gate *gates, size_t n_gates, const double *theta,
+                             size_t n_params, const cast_pauli_term *terms, size_t n_terms, double *energy,
+                             double *grad);
+
 // upload_plans into a pooled block (synchronous copy).
 cast_status upload_plans_pooled(const std::vector<PassPlan> &ps, cast_dtype dt, void **ptr, size_t *cls,
                                 std::vector<size_t> *offsets);
