@@ -184,54 +184,81 @@ def std_matrix(name, params=()):
     array of shape (2^k, 2^k, 2))."""
     p = np.zeros(3)
     p[:len(params)] = params
-    out = np.zeros(2 * 64 * 64)
+    out = np.zeros(2 * 4 * 4)   # standard gates have at most two qubits
     k = ctypes.c_int()
     gate_matrix(name.encode(), _dptr(p), ctypes.byref(k), _dptr(out))
     D = 1 << k.value
     return out[:2 * D * D].reshape(D, D, 2).copy()
 
 
+#: cast_gate as a numpy record (GateArray fills whole columns)
+_GATE_REC = np.dtype({"names": [f for f, _ in cast_gate._fields_],
+                      "formats": [np.int32, (np.int32, 6), np.uintp, np.int32, np.float64, np.int32],
+                      "offsets": [getattr(cast_gate, f).offset for f, _ in cast_gate._fields_],
+                      "itemsize": ctypes.sizeof(cast_gate)})
+
+
 class GateArray:
     """cast_gate[] for a list of gate records (keeps matrices alive)."""
 
     def __init__(self, gates):
-        self.arr = (cast_gate * max(1, len(gates)))()
-        self._keep = []
-        for i, g in enumerate(gates):
-            cg = self.arr[i]
-            cg.k = len(g.qubits)
-            for j, q in enumerate(g.qubits):
-                cg.qubits[j] = int(q)
-            cg.param_id = int(getattr(g, "param", -1))
-            cg.param_coeff = float(getattr(g, "coeff", 1.0))
-            if cg.param_id >= 0:
-                cg.generator = _GEN[g.name]
-                cg.matrix = None
-            else:
-                cg.generator = 0
-                if g.name == "unitary":
-                    m = np.ascontiguousarray(np.asarray(g.matrix, dtype=np.complex128)).view(np.float64).copy()
-                else:
-                    m = np.ascontiguousarray(std_matrix(g.name, g.params)).reshape(-1)
+        n = len(gates)
+        rec = np.zeros(max(1, n), dtype=_GATE_REC)
+        self._keep = [rec]
+        k, qubits, matrix, param, coeff, generator = [], [], [], [], [], []
+        std = {}   # addresses of this list's standard matrices, by name and angles
+        for g in gates:
+            q, p = g.qubits, int(getattr(g, "param", -1))
+            kq = len(q)
+            k.append(kq)
+            qubits.extend(q)
+            qubits.extend((0,) * (6 - kq))
+            param.append(p)
+            coeff.append(getattr(g, "coeff", 1.0))
+            if p >= 0:
+                generator.append(_GEN[g.name])
+                matrix.append(0)
+                continue
+            generator.append(0)
+            if g.name == "unitary":
+                m = np.ascontiguousarray(np.asarray(g.matrix, dtype=np.complex128)).view(np.float64).copy()
                 self._keep.append(m)
-                cg.matrix = _dptr(m)
-        self.n = len(gates)
+                matrix.append(m.ctypes.data)
+                continue
+            key = (g.name, tuple(g.params))
+            if key not in std:
+                m = std_matrix(g.name, g.params)
+                self._keep.append(m)
+                std[key] = m.ctypes.data
+            matrix.append(std[key])
+        if n:
+            rec["k"], rec["param_id"], rec["param_coeff"] = k, param, coeff
+            rec["qubits"] = np.array(qubits).astype(np.int32).reshape(n, 6)
+            rec["matrix"], rec["generator"] = matrix, generator
+        self.arr = (cast_gate * max(1, n)).from_buffer(rec)
+        self.n = n
+
+
+_TERM_REC = np.dtype([("coeff", np.float64), ("xmask", np.uint64), ("zmask", np.uint64)])
 
 
 def pauli_terms(terms):
     """cast_pauli_term[] from records with .coeff and .ops = ((qubit, 'X'|'Y'|'Z'), ...)."""
-    arr = (cast_pauli_term * max(1, len(terms)))()
-    for i, t in enumerate(terms):
+    coeff, xmask, zmask = [], [], []
+    for t in terms:
         x = z = 0
         for q, p in t.ops:
             if p in "XY":
                 x |= 1 << q
             if p in "YZ":
                 z |= 1 << q
-        arr[i].coeff = float(t.coeff)
-        arr[i].xmask = x
-        arr[i].zmask = z
-    return arr
+        coeff.append(float(t.coeff))
+        xmask.append(x & 0xffffffffffffffff)
+        zmask.append(z & 0xffffffffffffffff)
+    rec = np.zeros(max(1, len(terms)), dtype=_TERM_REC)
+    if len(terms):
+        rec["coeff"], rec["xmask"], rec["zmask"] = coeff, xmask, zmask
+    return (cast_pauli_term * len(rec)).from_buffer(rec)
 
 
 def fusion_options(k_max=5, opcount_cap=0.0, zero_tol=1e-14, one_tol=1e-14, agglomerative=True,
