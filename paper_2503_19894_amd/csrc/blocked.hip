@@ -5,6 +5,8 @@
 // free of bank conflicts.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
+
 #include "blocked.hpp"
 #include "internal.hpp"
 
@@ -258,7 +260,7 @@ __global__ void __launch_bounds__(NT, MAXD >= 3 ? 4 : 1) k_blocked(R *__restrict
                                                 const BlkGate *__restrict__ gates, BlkSeg s) {
     using V = typename Cx<R>::T;
     constexpr int S = sizeof(V) == 16 ? 0 : 1;
-    constexpr int B = 8;                       // chunks in flight per lane
+    constexpr int B = 4096 / NT;               // chunks per lane of a 64 KiB tile
     extern __shared__ u4 lds16[];
     V *tile = reinterpret_cast<V *>(lds16);
     const uint32_t tile_amps = 1u << s.tb;
@@ -267,22 +269,35 @@ __global__ void __launch_bounds__(NT, MAXD >= 3 ? 4 : 1) k_blocked(R *__restrict
     const uint32_t chunks = tile_amps >> S;
     const uint64_t glane = expand(threadIdx.x << S, s) >> S;
     const uint32_t slane = swz(threadIdx.x);
+    // One chunk per lane and slot when the tile is B * NT chunks (the default
+    // sizes): the next tile's loads are then issued before this tile's gates
+    // and wait in registers, so a workgroup always has a tile in flight.
+    const bool ahead = chunks == B * NT;
+    auto base_of = [&](uint64_t t) { return p16 + (deposit_bits(t << s.w, s.hlowmask, s.nh) >> S) + glane; };
+    uint64_t uoff[B];   // uniform
+#pragma unroll
+    for (int u = 0; u < B; ++u) uoff[u] = expand((uint32_t)(u * NT) << S, s) >> S;
+    u4 nxt[B];
+    if (ahead) {
+        const u4 *src = base_of(blockIdx.x);   // gridDim.x <= ntiles
+#pragma unroll
+        for (int u = 0; u < B; ++u) nxt[u] = __builtin_nontemporal_load(src + uoff[u]);
+    }
     for (uint64_t t = blockIdx.x; t < s.ntiles; t += gridDim.x) {
         const uint64_t tbase = deposit_bits(t << s.w, s.hlowmask, s.nh);
         u4 *base16 = p16 + (tbase >> S) + glane;
         // ---- load (chunk c = c0 + lane)
-        for (uint32_t c0 = 0; c0 < chunks; c0 += B * NT) {
-            u4 buf[B];
+        if (ahead) {
 #pragma unroll
-            for (int u = 0; u < B; ++u) {
-                const uint32_t c = c0 + u * NT;
-                if (c + threadIdx.x < chunks) buf[u] = __builtin_nontemporal_load(base16 + (expand(c << S, s) >> S));
-            }
+            for (int u = 0; u < B; ++u) lds16[slane ^ swz(u * NT)] = nxt[u];
+            if (t + gridDim.x < s.ntiles) {
+                const u4 *src = base_of(t + gridDim.x);
 #pragma unroll
-            for (int u = 0; u < B; ++u) {
-                const uint32_t c = c0 + u * NT;
-                if (c + threadIdx.x < chunks) lds16[slane ^ swz(c)] = buf[u];
+                for (int u = 0; u < B; ++u) nxt[u] = __builtin_nontemporal_load(src + uoff[u]);
             }
+        } else {
+            for (uint32_t c = threadIdx.x; c < chunks; c += NT)
+                lds16[swz(c)] = __builtin_nontemporal_load(base16 + (expand((c - threadIdx.x) << S, s) >> S));
         }
         Prefetch pf;
         prefetch<R, NT>(pf, mats, gates, s.g0);
@@ -314,13 +329,13 @@ __global__ void __launch_bounds__(NT, MAXD >= 3 ? 4 : 1) k_blocked(R *__restrict
             par ^= 1u;
         }
         // ---- store
-        for (uint32_t c0 = 0; c0 < chunks; c0 += B * NT) {
+        if (ahead) {
 #pragma unroll
-            for (int u = 0; u < B; ++u) {
-                const uint32_t c = c0 + u * NT;
-                if (c + threadIdx.x < chunks)
-                    __builtin_nontemporal_store(lds16[slane ^ swz(c)], base16 + (expand(c << S, s) >> S));
-            }
+            for (int u = 0; u < B; ++u)
+                __builtin_nontemporal_store(lds16[slane ^ swz(u * NT)], base16 + uoff[u]);
+        } else {
+            for (uint32_t c = threadIdx.x; c < chunks; c += NT)
+                __builtin_nontemporal_store(lds16[swz(c)], base16 + (expand((c - threadIdx.x) << S, s) >> S));
         }
         __syncthreads();   // the next tile overwrites LDS
     }
@@ -362,8 +377,10 @@ cast_status launch_blocked(void *psi, cast_dtype dt, const void *mats, const Blk
     if (lds > (128u << 10)) return fail(CAST_EUNSUPPORTED, "blocked tile and gate areas exceed 128 KiB of LDS");
     int nt = tuning().blocked_threads[dt];
     while (nt > 256 && ((size_t)1 << s.tb) < (size_t)nt) nt >>= 1;   // at least one amplitude per thread
+    // two workgroups per compute unit (their LDS allows no more), each looping
+    // over tiles with the next one's loads in flight
     uint64_t grid = s.ntiles;
-    const uint64_t cap = (uint64_t)tuning().max_grid[dt];
+    const uint64_t cap = std::min<uint64_t>(tuning().max_grid[dt], 512);
     if (grid > cap) grid = cap;
     const hipError_t e = dt == CAST_C128
         ? launch_r<double>(nt, (double *)psi, (const double *)mats, gates, s, (uint32_t)grid, lds, stream)
