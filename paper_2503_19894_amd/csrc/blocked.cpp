@@ -9,11 +9,8 @@
 
 namespace cast {
 
-cast_status launch_blocked(void *psi, cast_dtype dt, const void *mats, const BlkGate *gates, const BlkSeg &s,
-                           hipStream_t stream);
-
 struct BlockedPlan {
-    int tb = 0;
+    int tb = 0, nt = 0;                // tile bits, workgroup size
     struct Pass {
         size_t first = 0, count = 0;   // fused gates [first, first + count) covered by this pass
         bool segment = false;
@@ -22,7 +19,10 @@ struct BlockedPlan {
     };
     std::vector<Pass> passes;
     std::vector<BlkGate> gates;
-    void *dev = nullptr;               // device copy of `gates`
+    std::vector<BlkEnt> ent;
+    std::vector<double> tabs;          // phase tables of the runs (complex entries as pairs)
+    void *dev = nullptr;               // device copy of gates, entries and tables (in the state dtype)
+    size_t dev_ent = 0, dev_tabs = 0;  // byte offsets in it
 };
 
 void blocked_free(BlockedPlan *b) {
@@ -58,28 +58,31 @@ bool window_of(uint64_t need, int tb, int *w_out) {
     return true;
 }
 
-BlkGate make_gate(const PassPlan &p, int w, const int *qh, int nh, uint64_t mat) {
+// LDS element of tile position y (as the kernel's at<S>, linear over GF(2)).
+uint32_t lds_elem(uint32_t y, cast_dtype dt) {
+    const uint32_t sh = dt == CAST_C128 ? 0 : 1, c = y >> sh;
+    return ((c ^ (((c >> 4) ^ (c >> 8)) & 15u)) << sh) | (y & ((1u << sh) - 1));
+}
+
+void set_targets(BlkGate *g, int k, const int *q, int w, const int *qh, int nh) {
+    g->k = k;
+    for (int s = 0; s < k; ++s) {
+        g->q[s] = q[s];
+        g->tpos[s] = -1;
+        if (q[s] < w) g->tpos[s] = q[s];
+        for (int i = 0; i < nh; ++i)
+            if (qh[i] == q[s]) g->tpos[s] = w + i;
+    }
+}
+
+BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh, int nh, uint64_t mat,
+                  std::vector<BlkEnt> *ent) {
     BlkGate g;
     std::memset(&g, 0, sizeof g);
-    g.kind = p.d == 0 ? 0 : 1;
-    g.k = p.k;
+    g.kind = 1;
     g.d = p.d;
     g.mat = mat;
-    g.mat_reals = p.d == 0 ? 2u << p.k : (uint32_t)(2 * p.mat.size());
-    g.run = 1;
-    g.tshift = std::max(p.k, 1);
-    for (int s = 0; s < p.k; ++s) {
-        const int q = p.q[s];
-        g.q[s] = q;
-        g.tpos[s] = -1;
-        if (q < w) g.tpos[s] = q;
-        for (int i = 0; i < nh; ++i)
-            if (qh[i] == q) g.tpos[s] = w + i;
-    }
-    if (p.d == 0) {
-        for (uint32_t b : p.blk) g.amask |= 1ull << b;
-        return g;
-    }
+    set_targets(&g, p.k, p.q, w, qh, nh);
     // L^-1 by Gauss-Jordan: row r of [A | I] with A[r][c] = bit r of L[c]
     const int k = p.k;
     uint32_t rows[kMaxK];
@@ -119,10 +122,54 @@ BlkGate make_gate(const PassPlan &p, int w, const int *qh, int nh, uint64_t mat)
         for (int j = 0; j < i; ++j)
             if ((b[j] >> piv[i]) & 1u) b[j] ^= b[i];
     }
-    std::sort(piv, piv + p.d);
-    for (int i = 0; i < p.d; ++i) g.pivlow[i] = (1u << piv[i]) - 1;
-    std::memset(g.slot, -1, sizeof g.slot);
-    for (size_t i = 0; i < p.blk.size(); ++i) g.slot[p.blk[i]] = (int8_t)i;
+    for (uint32_t blk : p.blk) g.amask |= 1u << blk;
+    // coset bits: the lane takes tile bits that are no targets (u is then the
+    // same for the whole wave), spread over the LDS columns -- chunk bits i,
+    // i + 4 and i + 8 share one (lds_elem) -- the wave and iteration the rest
+    uint32_t targets = 0, pivots = 0, lane = 0;
+    for (int s = 0; s < k; ++s)
+        if (g.tpos[s] >= 0) targets |= 1u << g.tpos[s];
+    for (int i = 0; i < p.d; ++i) pivots |= 1u << piv[i];
+    int used[5] = {0, 0, 0, 0, 0};
+    auto column = [&](int bit) { return dt == CAST_C128 ? bit & 3 : bit == 0 ? 4 : (bit - 1) & 3; };
+    while (g.nlane < 6) {
+        int best = -1;
+        for (int t = 0; t < tb; ++t)
+            if (!(((targets | lane) >> t) & 1u) && (best < 0 || used[column(t)] < used[column(best)])) best = t;
+        if (best < 0) break;
+        lane |= 1u << best;
+        ++used[column(best)];
+        g.lanepos |= (uint64_t)best << (8 * g.nlane++);
+    }
+    std::vector<int> rest;
+    for (int t = 0; t < tb; ++t)
+        if (!(((pivots | lane) >> t) & 1u)) rest.push_back(t);
+    g.nuni = (uint32_t)rest.size();
+    g.ent = (uint32_t)ent->size();
+    for (uint32_t e = 0; e < (1u << g.nuni); ++e) {
+        uint32_t y = 0, u = 0;
+        for (uint32_t i = 0; i < g.nuni; ++i)
+            if ((e >> i) & 1u) y |= 1u << rest[i];
+        for (int s = 0; s < k; ++s)
+            if (g.tpos[s] >= 0 && ((y >> g.tpos[s]) & 1u)) u ^= g.colv[s];
+        ent->push_back(BlkEnt{u, lds_elem(y, dt)});
+    }
+    return g;
+}
+
+// One phase table inside a tile, and the uniform local index of each
+// iteration of nt threads over the tile.
+BlkGate make_table(const PhaseTable &t, int tb, int nt, int w, const int *qh, int nh, std::vector<BlkEnt> *ent) {
+    BlkGate g;
+    std::memset(&g, 0, sizeof g);
+    set_targets(&g, t.k, t.q, w, qh, nh);
+    g.ent = (uint32_t)ent->size();
+    for (uint32_t y = 0; y < (1u << tb); y += (uint32_t)nt) {
+        uint32_t j = 0;
+        for (int s = 0; s < t.k; ++s)
+            if (g.tpos[s] >= 0) j |= ((y >> g.tpos[s]) & 1u) << s;
+        ent->push_back(BlkEnt{j, 0});
+    }
     return g;
 }
 
@@ -132,14 +179,14 @@ cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
         return fail(CAST_EINVAL, "blocked_tile_bits: tile exceeds 64 KiB of LDS");
     auto *bp = new BlockedPlan;
     bp->tb = tb;
+    bp->nt = blocked_threads(dt, tb);
     const int n = f.n;
     const std::vector<PassPlan> &P = f.plans;
     const std::vector<size_t> off = plan_offsets(P, dt);
-    // matrices / phase tables of one gate area: tile + two areas within the LDS budget
-    const size_t tile_bytes = ((size_t)1 << tb) * amp_bytes(dt);
-    const size_t area_max = std::min<size_t>(tile_bytes + 2 * kBlkAreaHead < kBlkLdsBudget
-                                                 ? (kBlkLdsBudget - tile_bytes) / 2 - kBlkAreaHead : 0,
-                                             (size_t)kBlkMaxMatChunks * 16);
+    const size_t ab = amp_bytes(dt);
+    // largest merged table: half an area, so that a run may hold two
+    int tab_qubits = kRunMaxQ;
+    while (((size_t)2 << tab_qubits) * ab > kBlkAreaBytes / 2) --tab_qubits;
     std::vector<size_t> cur;   // non-identity gates of the open segment
     size_t first = 0;
     uint64_t need = 0;
@@ -163,39 +210,57 @@ cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
                     ++s.nh;
                 }
             s.g0 = (uint32_t)bp->gates.size();
-            for (size_t i : cur) bp->gates.push_back(make_gate(P[i], w, s.qh, s.nh, off[i]));
-            s.g1 = (uint32_t)bp->gates.size();
-            // consecutive diagonal gates form runs applied in one sweep of the
-            // tile; a run's phase tables sit at the stride of its largest table
-            for (uint32_t gi = s.g0; gi < s.g1;) {
-                uint32_t m = 0;
-                int ts = 1;
-                while (gi + m < s.g1 && m < kBlkRunMax && bp->gates[gi + m].kind == 0) {
-                    const int ts2 = std::max(ts, bp->gates[gi + m].tshift);
-                    if (((size_t)(m + 1) << ts2) * amp_bytes(dt) > area_max && m > 0) break;
-                    ts = ts2;
-                    ++m;
+            // consecutive diagonal gates: multiplied into tables while their
+            // union fits (each lookup and multiply then stands for several
+            // gates), then runs of tables applied in one sweep of the tile,
+            // at the stride of the run's largest table
+            std::vector<PhaseTable> tabs;
+            auto flush = [&] {
+                for (size_t t = 0; t < tabs.size();) {
+                    size_t m = 0;
+                    int ts = 1;
+                    while (t + m < tabs.size() && m < kBlkRunMax) {
+                        const int ts2 = std::max(ts, tabs[t + m].k);
+                        if (m > 0 && ((m + 1) << ts2) * ab > kBlkAreaBytes / 2) break;
+                        ts = ts2;
+                        ++m;
+                    }
+                    const size_t base = bp->tabs.size();   // a multiple of 16 bytes
+                    bp->tabs.resize(base + 2 * (m << ts), 0.0);
+                    for (size_t j = 0; j < m; ++j) {
+                        BlkGate g = make_table(tabs[t + j], tb, bp->nt, w, s.qh, s.nh, &bp->ent);
+                        if (j == 0) {
+                            g.run = (int)m;
+                            g.tshift = ts;
+                            g.area = (uint32_t)((m << ts) * ab);
+                            g.mat = base;
+                        }
+                        bp->gates.push_back(g);
+                        for (size_t e = 0; e < tabs[t + j].ph.size(); ++e) {
+                            const cplx z = tabs[t + j].ph[e];
+                            bp->tabs[base + 2 * ((j << ts) + e)] = z.real();
+                            bp->tabs[base + 2 * ((j << ts) + e) + 1] = z.imag();
+                        }
+                    }
+                    t += m;
                 }
-                if (m == 0) {
-                    ++gi;
+                tabs.clear();
+            };
+            for (size_t i : cur) {
+                if (P[i].d > 0) {
+                    flush();
+                    bp->gates.push_back(make_gate(P[i], dt, tb, w, s.qh, s.nh, off[i], &bp->ent));
                     continue;
                 }
-                bp->gates[gi].run = (int)m;
-                bp->gates[gi].tshift = ts;
-                for (uint32_t j = 1; j < m; ++j) bp->gates[gi + j].run = 0;
-                gi += m;
+                PhaseTable t = phase_table(P[i]);
+                if (tabs.empty() || !merge_tables(&tabs.back(), t, tab_qubits)) tabs.push_back(std::move(t));
             }
-            uint32_t mbytes = 0;
-            for (uint32_t gi = s.g0; gi < s.g1; ++gi) {
-                const BlkGate &g = bp->gates[gi];
-                if (g.kind == 0 && g.run == 0) continue;
-                const uint32_t b = g.kind == 0 ? ((uint32_t)g.run << g.tshift) * (uint32_t)amp_bytes(dt)
-                                               : g.mat_reals * (dt == CAST_C128 ? 8 : 4);
-                mbytes = std::max(mbytes, b);
-            }
-            s.area = kBlkAreaHead + ((mbytes + 15) & ~15u);
-            s.maxd = 0;
-            for (uint32_t gi = s.g0; gi < s.g1; ++gi) s.maxd = std::max(s.maxd, bp->gates[gi].d);
+            flush();
+            s.g1 = (uint32_t)bp->gates.size();
+            uint32_t total = 0, most = 0;
+            for (uint32_t gi = s.g0; gi < s.g1; ++gi) total += bp->gates[gi].area, most = std::max(most, bp->gates[gi].area);
+            s.resident = total <= kBlkAreaBytes;
+            s.lds_tabs = s.resident ? total : 2 * most;
             bp->passes.push_back(ps);
         }
         cur.clear();
@@ -207,9 +272,7 @@ cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
         if (p.identity()) continue;
         const uint64_t sp = span_qubits(p);
         int w;
-        const size_t mbytes = (p.d == 0 ? ((size_t)2 << std::max(p.k, 1)) : 2 * p.mat.size()) * amp_bytes(dt) / 2;
-        if (n < tb || p.d > kBlkMaxD || (mbytes + 15) / 16 > kBlkMaxMatChunks || mbytes > area_max ||
-            !window_of(sp, tb, &w)) {
+        if (n < tb || p.d > kBlkMaxD || !window_of(sp, tb, &w)) {
             // an ordinary pass of its own
             close(i);
             BlockedPlan::Pass ps;
@@ -240,7 +303,7 @@ cast_status prepare(const cast_fused *fc, int n, cast_dtype dt, bool device, Blo
     if (n != fc->n) return fail(CAST_EINVAL, "fused list was built for a different qubit count");
     cast_fused *f = const_cast<cast_fused *>(fc);
     BlockedPlan *&bp = f->blocked[dt];
-    if (bp && bp->tb != tuning().blocked_tile_bits[dt]) {
+    if (bp && (bp->tb != tuning().blocked_tile_bits[dt] || bp->nt != blocked_threads(dt, bp->tb))) {
         blocked_free(bp);
         bp = nullptr;
     }
@@ -252,9 +315,19 @@ cast_status prepare(const cast_fused *fc, int n, cast_dtype dt, bool device, Blo
             if (cast_status rc = upload_plans(f->plans, dt, &f->dev[dt], &f->dev_off[dt])) return rc;
         }
         if (!bp->dev && !bp->gates.empty()) {
-            const size_t bytes = bp->gates.size() * sizeof(BlkGate);
+            auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+            bp->dev_ent = up(bp->gates.size() * sizeof(BlkGate));
+            bp->dev_tabs = bp->dev_ent + up(bp->ent.size() * sizeof(BlkEnt));
+            const size_t rsz = amp_bytes(dt) / 2, bytes = bp->dev_tabs + std::max<size_t>(bp->tabs.size(), 4) * rsz;
+            std::vector<char> h(bytes, 0);
+            std::memcpy(h.data(), bp->gates.data(), bp->gates.size() * sizeof(BlkGate));
+            std::memcpy(h.data() + bp->dev_ent, bp->ent.data(), bp->ent.size() * sizeof(BlkEnt));
+            for (size_t i = 0; i < bp->tabs.size(); ++i) {
+                if (dt == CAST_C128) ((double *)(h.data() + bp->dev_tabs))[i] = bp->tabs[i];
+                else ((float *)(h.data() + bp->dev_tabs))[i] = (float)bp->tabs[i];
+            }
             if (cast_status rc = dev_alloc(&bp->dev, bytes)) return rc;
-            const hipError_t e = hipMemcpy(bp->dev, bp->gates.data(), bytes, hipMemcpyHostToDevice);
+            const hipError_t e = hipMemcpy(bp->dev, h.data(), bytes, hipMemcpyHostToDevice);
             if (e != hipSuccess) {
                 dev_free(bp->dev);
                 bp->dev = nullptr;
@@ -269,8 +342,11 @@ cast_status prepare(const cast_fused *fc, int n, cast_dtype dt, bool device, Blo
 cast_status launch(cast_sv *sv, const cast_fused *f, const BlockedPlan &bp, size_t i) {
     const BlockedPlan::Pass &ps = bp.passes[i];
     const void *mats = f->dev[sv->dt].ptr;
-    if (ps.segment)
-        return launch_blocked(sv->data, sv->dt, mats, static_cast<const BlkGate *>(bp.dev), ps.seg, sv->stream);
+    if (ps.segment) {
+        const char *dev = static_cast<const char *>(bp.dev);
+        const BlkPtrs ptrs{mats, dev + bp.dev_tabs, (const BlkGate *)dev, (const BlkEnt *)(dev + bp.dev_ent)};
+        return launch_blocked(sv->data, sv->dt, ptrs, ps.seg, bp.nt, sv->stream);
+    }
     const size_t rsz = sv->dt == CAST_C128 ? 8 : 4;
     const void *dm = (const char *)mats + f->dev_off[sv->dt][ps.gate] * rsz;
     return launch_pass(sv->data, sv->n, sv->dt, f->plans[ps.gate], dm, sv->stream);

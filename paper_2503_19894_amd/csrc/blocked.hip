@@ -44,126 +44,52 @@ __device__ __forceinline__ uint64_t expand(uint32_t y, const BlkSeg &s) {
     return x;
 }
 
-// Virtual coordinates contributed by the in-tile targets of position y.
-__device__ __forceinline__ uint32_t virt(uint32_t y, const BlkGate &g) {
-    uint32_t u = 0;
-#pragma unroll
-    for (int s = 0; s < 6; ++s)
-        if (s < g.k && g.tpos[s] >= 0 && ((y >> g.tpos[s]) & 1u)) u ^= g.colv[s];
-    return u;
-}
+// The plan's tables are read through the constant address space: nothing in
+// the kernel writes them, so uniform reads go to the scalar unit.
+template <typename T> using CPtr = const __attribute__((address_space(4))) T *;
+template <typename T> __device__ __forceinline__ CPtr<T> cptr(const T *p) { return (CPtr<T>)p; }
 
 // Local index bits contributed by the in-tile targets of position y.
-__device__ __forceinline__ uint32_t loc(uint32_t y, const BlkGate &g) {
+__device__ __forceinline__ uint32_t loc(uint32_t y, CPtr<BlkGate> g) {
     uint32_t j = 0;
-#pragma unroll
-    for (int s = 0; s < 6; ++s)
-        if (s < g.k && g.tpos[s] >= 0) j |= ((y >> g.tpos[s]) & 1u) << s;
+    for (int s = 0; s < g->k; ++s)
+        if (g->tpos[s] >= 0) j |= ((y >> g->tpos[s]) & 1u) << s;
     return j;
 }
 
-// Staging of a gate area in two halves: the matrices (or a diagonal run's
-// phase tables) are read from global memory into registers before the
-// current gate is applied, so their latency hides behind it, and written to
-// LDS afterwards, together with the slot table and this tile's iteration
-// tables.
-struct Prefetch {
-    u4 m[kBlkMaxMatChunks / 256];
-};
-
-template <typename R, int NT>
-__device__ __forceinline__ void prefetch(Prefetch &pf, const R *mats, const BlkGate *gates, uint32_t gi) {
-    const BlkGate &g = gates[gi];
-    // 16-byte chunks per phase-table stride: 2^tshift entries of 2 reals
-    const uint32_t cshift = g.tshift + (sizeof(R) == 8 ? 0 : -1);
-#pragma unroll
-    for (int r = 0; r < (int)((kBlkMaxMatChunks + NT - 1) / NT); ++r) {
-        const uint32_t i = threadIdx.x + r * NT;
-        if (g.kind == 0) {
-            const uint32_t t = i >> cshift, o = i & ((1u << cshift) - 1);
-            if (t < (uint32_t)g.run) {
-                const BlkGate &h = gates[gi + t];
-                if (o < (h.mat_reals * (uint32_t)sizeof(R) + 15) / 16)
-                    pf.m[r] = reinterpret_cast<const u4 *>(mats + h.mat)[o];
-            }
-        } else if (i < (g.mat_reals * (uint32_t)sizeof(R) + 15) / 16) {
-            pf.m[r] = reinterpret_cast<const u4 *>(mats + g.mat)[i];   // 256-byte aligned
-        }
-    }
+// Copies a run's tables to LDS (both 16-byte aligned and of whole chunks).
+template <int NT>
+__device__ __forceinline__ void stage_tables(u4 *dst, const u4 *src, uint32_t n16) {
+    for (uint32_t i = threadIdx.x; i < n16; i += NT) dst[i] = src[i];
 }
 
-template <typename R, int S, int NT>
-__device__ __forceinline__ void commit(char *area, const Prefetch &pf, const BlkGate *gates, uint32_t gi,
-                                       uint64_t tbase, uint32_t tile_amps) {
-    const BlkGate &g = gates[gi];
-    u4 *dst = reinterpret_cast<u4 *>(area + kBlkAreaHead);
-    uint2 *itab = reinterpret_cast<uint2 *>(area + kBlkIterOff);
-    if (g.kind == 0) {
-        const uint32_t cshift = g.tshift + (sizeof(R) == 8 ? 0 : -1);
-#pragma unroll
-        for (int r = 0; r < (int)((kBlkMaxMatChunks + NT - 1) / NT); ++r) {
-            const uint32_t i = threadIdx.x + r * NT;
-            const uint32_t t = i >> cshift, o = i & ((1u << cshift) - 1);
-            if (t < (uint32_t)g.run && o < (gates[gi + t].mat_reals * (uint32_t)sizeof(R) + 15) / 16)
-                dst[i] = pf.m[r];
-        }
-        // per (gate t of the run, iteration i): uniform part of its local index
-        const uint32_t iters = tile_amps / NT;
-        if (threadIdx.x < (uint32_t)g.run * iters) {
-            const uint32_t t = threadIdx.x / iters, i = threadIdx.x % iters;
-            const BlkGate &h = gates[gi + t];
-            uint32_t juni = 0;
-#pragma unroll
-            for (int q = 0; q < 6; ++q)
-                if (q < h.k && h.tpos[q] < 0 && ((tbase >> h.q[q]) & 1u)) juni |= 1u << q;
-            reinterpret_cast<uint32_t *>(area + kBlkJOff)[t * kBlkMaxIters + i] = juni ^ loc(i * NT, h);
-            if (t == 0) itab[i] = make_uint2(0u, at<S>(i * NT));
-        }
-        return;
-    }
-    if (threadIdx.x < 32) reinterpret_cast<int8_t *>(area)[threadIdx.x] = g.slot[threadIdx.x];
-    const uint32_t n16 = (g.mat_reals * (uint32_t)sizeof(R) + 15) / 16;
-#pragma unroll
-    for (int r = 0; r < (int)((kBlkMaxMatChunks + NT - 1) / NT); ++r) {
-        const uint32_t i = threadIdx.x + r * NT;
-        if (i < n16) dst[i] = pf.m[r];
-    }
-    // iteration i covers cosets i*NT + lane; its uniform part is coset i*NT
-    const uint32_t items = tile_amps >> g.d;
-    if (threadIdx.x < (items + NT - 1) / NT) {
-        uint32_t uuni = 0;   // targets outside the tile, fixed by the tile
-#pragma unroll
-        for (int q = 0; q < 6; ++q)
-            if (q < g.k && g.tpos[q] < 0 && ((tbase >> g.q[q]) & 1u)) uuni ^= g.colv[q];
-        uint32_t y = threadIdx.x * NT;
-        for (int i = 0; i < g.d; ++i) y = ((y & ~g.pivlow[i]) << 1) | (y & g.pivlow[i]);
-        itab[threadIdx.x] = make_uint2(uuni ^ virt(y, g), at<S>(y));
-    }
-}
-
-// A run of M diagonal gates: amplitude y is read once, multiplied by each
-// gate's phase D_t[j_t(y)] in order (identity phases are exactly 1), and
+// A run of M phase tables: amplitude y is read once, multiplied by each
+// table's phase D_t[j_t(y)] in order (identity phases are exactly 1), and
 // written once.  Instantiated per run length so the phase loop is straight
-// code.
+// code.  j_t(y) is a lane part and a wave-uniform part per iteration.
 template <typename R, int S, int NT, int M>
-__device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const char *area, const BlkGate *gates,
-                                           uint32_t gi, uint32_t tile_amps) {
+__device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const char *area, CPtr<BlkGate> g,
+                                           CPtr<BlkEnt> ent, uint64_t tbase, uint32_t tile_amps) {
     using V = typename Cx<R>::T;
-    const int ts = gates[gi].tshift;
-    const V *tabs = reinterpret_cast<const V *>(area + kBlkAreaHead);
-    const uint2 *itab = reinterpret_cast<const uint2 *>(area + kBlkIterOff);
-    const uint32_t *jt = reinterpret_cast<const uint32_t *>(area + kBlkJOff);
+    const int ts = g->tshift;
+    const V *tabs = reinterpret_cast<const V *>(area);
     uint32_t jl[M];
 #pragma unroll
-    for (int t = 0; t < M; ++t) jl[t] = loc(threadIdx.x, gates[gi + t]) | ((uint32_t)t << ts);
+    for (int t = 0; t < M; ++t) {
+        uint32_t juni = (uint32_t)t << ts;   // this tile's part
+        for (int q = 0; q < g[t].k; ++q)
+            if (g[t].tpos[q] < 0) juni |= (uint32_t)((tbase >> g[t].q[q]) & 1u) << q;
+        jl[t] = juni | loc(threadIdx.x, g + t);
+    }
     const uint32_t al = at<S>(threadIdx.x);
-    const uint32_t iters = tile_amps / NT;
+    const uint32_t iters = tile_amps > NT ? tile_amps / NT : 1;
+    if (threadIdx.x >= tile_amps) return;
     for (uint32_t i = 0; i < iters; ++i) {
-        const uint32_t a = al ^ itab[i].y;
+        const uint32_t a = al ^ at<S>(i * NT);
         V x = tile[a];
 #pragma unroll
         for (int t = 0; t < M; ++t) {
-            const V ph = tabs[jl[t] ^ jt[t * kBlkMaxIters + i]];
+            const V ph = tabs[jl[t] ^ ent[g[t].ent + i].u];
             const R re = x.x * ph.x - x.y * ph.y;
             const R im = x.x * ph.y + x.y * ph.x;
             x.x = re;
@@ -174,61 +100,66 @@ __device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const char *
 }
 
 template <typename R, int S, int NT>
-__device__ __forceinline__ void diag_run(typename Cx<R>::T *tile, const char *area, const BlkGate *gates,
-                                         uint32_t gi, uint32_t tile_amps) {
-    switch (gates[gi].run) {
-        case 1: diag_run_m<R, S, NT, 1>(tile, area, gates, gi, tile_amps); break;
-        case 2: diag_run_m<R, S, NT, 2>(tile, area, gates, gi, tile_amps); break;
-        case 3: diag_run_m<R, S, NT, 3>(tile, area, gates, gi, tile_amps); break;
-        case 4: diag_run_m<R, S, NT, 4>(tile, area, gates, gi, tile_amps); break;
-        case 5: diag_run_m<R, S, NT, 5>(tile, area, gates, gi, tile_amps); break;
-        case 6: diag_run_m<R, S, NT, 6>(tile, area, gates, gi, tile_amps); break;
-        case 7: diag_run_m<R, S, NT, 7>(tile, area, gates, gi, tile_amps); break;
-        default: diag_run_m<R, S, NT, 8>(tile, area, gates, gi, tile_amps); break;
+__device__ __forceinline__ void diag_run(typename Cx<R>::T *tile, const char *area, CPtr<BlkGate> g,
+                                         CPtr<BlkEnt> ent, uint64_t tbase, uint32_t tile_amps) {
+    switch (g->run) {
+        case 1: diag_run_m<R, S, NT, 1>(tile, area, g, ent, tbase, tile_amps); break;
+        case 2: diag_run_m<R, S, NT, 2>(tile, area, g, ent, tbase, tile_amps); break;
+        case 3: diag_run_m<R, S, NT, 3>(tile, area, g, ent, tbase, tile_amps); break;
+        case 4: diag_run_m<R, S, NT, 4>(tile, area, g, ent, tbase, tile_amps); break;
+        case 5: diag_run_m<R, S, NT, 5>(tile, area, g, ent, tbase, tile_amps); break;
+        case 6: diag_run_m<R, S, NT, 6>(tile, area, g, ent, tbase, tile_amps); break;
+        case 7: diag_run_m<R, S, NT, 7>(tile, area, g, ent, tbase, tile_amps); break;
+        default: diag_run_m<R, S, NT, 8>(tile, area, g, ent, tbase, tile_amps); break;
     }
 }
 
-// Block gate with 2^D x 2^D blocks: one work item per coset of the span.
-// The item's virtual coordinates u = L^-1 j give its block (u >> D; identity
-// blocks are skipped) and its place in the block (u mod 2^D), from which the
-// block's first element follows.
+// Block gate with 2^D x 2^D blocks: one work item per coset of the span.  The
+// virtual coordinates u = L^-1 j of a coset's first position give its block
+// (u >> D) and its place in it (u mod 2^D).  The lane's bits of a coset lie on
+// tile bits that are no targets, so u is wave-uniform: a wave skips identity
+// blocks, and the block's matrix is read with scalar loads.  (With the
+// matrices in LDS and a block per lane, a 4 x 4 block cost 16 LDS reads for
+// its matrix beside 8 for its amplitudes: 28 qubits, complex128, 0.24 ms more
+// per gate and pass.)
 template <int D, typename R, int S, int NT>
-__device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, const char *area, const BlkGate &g,
-                                              uint32_t tile_amps) {
+__device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, CPtr<BlkGate> g, CPtr<BlkEnt> ent,
+                                              CPtr<R> mats, uint64_t tbase) {
     using V = typename Cx<R>::T;
     constexpr int N = 1 << D;
-    const int8_t *slot = reinterpret_cast<const int8_t *>(area);
-    const uint2 *itab = reinterpret_cast<const uint2 *>(area + kBlkIterOff);
-    const V *mt = reinterpret_cast<const V *>(area + kBlkAreaHead);
-    uint32_t soff[N], sspan[D];
-#pragma unroll
-    for (int i = 0; i < D; ++i) sspan[i] = at<S>(g.span[i]);
+    uint32_t soff[N];
 #pragma unroll
     for (int c = 0; c < N; ++c) {
         uint32_t o = 0;
 #pragma unroll
         for (int i = 0; i < D; ++i)
-            if ((c >> i) & 1) o ^= sspan[i];
+            if ((c >> i) & 1) o ^= at<S>(g->span[i]);
         soff[c] = o;
     }
-    const uint32_t items = tile_amps >> D;
-    uint32_t ylane = threadIdx.x;
+    uint32_t uuni = 0;   // targets outside the tile
+    for (int q = 0; q < g->k; ++q)
+        if (g->tpos[q] < 0 && ((tbase >> g->q[q]) & 1u)) uuni ^= g->colv[q];
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t nl = g->nlane, nq = 1u << g->nuni, amask = g->amask;
+    const uint64_t lanepos = g->lanepos;
+    uint32_t al = 0;
 #pragma unroll
-    for (int i = 0; i < D; ++i) ylane = ((ylane & ~g.pivlow[i]) << 1) | (ylane & g.pivlow[i]);
-    const uint32_t ul = virt(ylane, g);
-    const uint32_t al = at<S>(ylane);
-    const uint32_t iters = (items + NT - 1) / NT;
-    for (uint32_t i = 0; i < iters; ++i) {
-        if (i * NT + threadIdx.x >= items) break;
-        const uint2 e = itab[i];
-        const uint32_t u = ul ^ e.x;
-        const int sl = slot[u >> D];
-        if (sl < 0) continue;
-        uint32_t a0 = al ^ e.y;
+    for (int i = 0; i < 6; ++i) {
+        const uint32_t bit = at<S>(1u << ((lanepos >> (8 * i)) & 255u));
+        if (i < (int)nl && ((lane >> i) & 1u)) al ^= bit;
+    }
+    CPtr<R> m0 = mats + g->mat;
+    CPtr<BlkEnt> e0 = ent + g->ent;
+    for (uint32_t q = wave; q < nq; q += NT / 64) {
+        const uint32_t u = uuni ^ e0[q].u, blk = u >> D;
+        if (!((amask >> blk) & 1u)) continue;
+        uint32_t a0 = e0[q].a;
 #pragma unroll
         for (int b = 0; b < D; ++b)
-            if ((u >> b) & 1u) a0 ^= sspan[b];
-        const V *m = mt + sl * N * N;
+            if ((u >> b) & 1u) a0 ^= soff[1 << b];
+        a0 ^= al;
+        CPtr<R> m = m0 + (uint32_t)__popc(amask & ((1u << blk) - 1)) * (2 * N * N);
+        if (lane >> nl) continue;   // tiles with fewer than 64 cosets of free bits
         V v[N];
 #pragma unroll
         for (int c = 0; c < N; ++c) v[c] = tile[a0 ^ soff[c]];
@@ -237,11 +168,11 @@ __device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, const cha
             R ar = 0, ai = 0;
 #pragma unroll
             for (int c = 0; c < N; ++c) {
-                const V x = m[r * N + c];
-                ar = fma(x.x, v[c].x, ar);
-                ar = fma(-x.y, v[c].y, ar);
-                ai = fma(x.x, v[c].y, ai);
-                ai = fma(x.y, v[c].x, ai);
+                const R mx = m[2 * (r * N + c)], my = m[2 * (r * N + c) + 1];
+                ar = fma(mx, v[c].x, ar);
+                ar = fma(-my, v[c].y, ar);
+                ai = fma(mx, v[c].y, ai);
+                ai = fma(my, v[c].x, ai);
             }
             V o;
             o.x = ar;
@@ -251,13 +182,10 @@ __device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, const cha
     }
 }
 
-// MAXD: the largest block dimension the instance handles (segments without
-// 8 x 8 blocks use the MAXD = 2 instance, which needs fewer registers; the
-// MAXD = 3 instance is held to 128 registers, four waves per SIMD, so that
-// two workgroups still share a compute unit).
-template <typename R, int NT, int MAXD>
-__global__ void __launch_bounds__(NT, MAXD >= 3 ? 4 : 1) k_blocked(R *__restrict__ psi_r, const R *__restrict__ mats,
-                                                const BlkGate *__restrict__ gates, BlkSeg s) {
+template <typename R, int NT>
+__global__ void __launch_bounds__(NT, 4) k_blocked(R *__restrict__ psi_r, const R *__restrict__ mats_g,
+                                                const R *__restrict__ tabs_g, const BlkGate *__restrict__ gates_g,
+                                                const BlkEnt *__restrict__ ent_g, BlkSeg s) {
     using V = typename Cx<R>::T;
     constexpr int S = sizeof(V) == 16 ? 0 : 1;
     constexpr int B = 4096 / NT;               // chunks per lane of a 64 KiB tile
@@ -265,6 +193,18 @@ __global__ void __launch_bounds__(NT, MAXD >= 3 ? 4 : 1) k_blocked(R *__restrict
     V *tile = reinterpret_cast<V *>(lds16);
     const uint32_t tile_amps = 1u << s.tb;
     char *area0 = reinterpret_cast<char *>(lds16) + (size_t)tile_amps * sizeof(V);
+    CPtr<BlkGate> gates = cptr(gates_g);
+    CPtr<BlkEnt> ent = cptr(ent_g);
+    CPtr<R> mats = cptr(mats_g);
+    if (s.resident) {
+        char *dst = area0;
+        for (uint32_t gi = s.g0; gi < s.g1; ++gi) {
+            if (gates[gi].kind != 0 || gates[gi].run == 0) continue;
+            stage_tables<NT>(reinterpret_cast<u4 *>(dst), reinterpret_cast<const u4 *>(tabs_g + gates[gi].mat),
+                             gates[gi].area / 16);
+            dst += gates[gi].area;
+        }
+    }
     u4 *p16 = reinterpret_cast<u4 *>(psi_r);
     const uint32_t chunks = tile_amps >> S;
     const uint64_t glane = expand(threadIdx.x << S, s) >> S;
@@ -299,34 +239,36 @@ __global__ void __launch_bounds__(NT, MAXD >= 3 ? 4 : 1) k_blocked(R *__restrict
             for (uint32_t c = threadIdx.x; c < chunks; c += NT)
                 lds16[swz(c)] = __builtin_nontemporal_load(base16 + (expand((c - threadIdx.x) << S, s) >> S));
         }
-        Prefetch pf;
-        prefetch<R, NT>(pf, mats, gates, s.g0);
-        commit<R, S, NT>(area0, pf, gates, s.g0, tbase, tile_amps);
-        __syncthreads();
-        // ---- the segment's gates (a diagonal run counts as one), in order;
-        // the next one is staged into the other area meanwhile
+        // ---- the segment's operations (a run of tables counts as one), in
+        // order; without resident tables the next run's are staged into the
+        // other area while the current operation runs
+        char *area = area0;
         uint32_t par = 0;
+        auto stage = [&](uint32_t gi) {
+            stage_tables<NT>(reinterpret_cast<u4 *>(area0 + par * (s.lds_tabs / 2)),
+                             reinterpret_cast<const u4 *>(tabs_g + gates[gi].mat), gates[gi].area / 16);
+        };
+        if (!s.resident && gates[s.g0].kind == 0) stage(s.g0);
+        __syncthreads();
         for (uint32_t gi = s.g0; gi < s.g1;) {
-            const BlkGate &g = gates[gi];
-            const uint32_t gn = gi + (g.kind == 0 ? (uint32_t)g.run : 1u);
-            char *area = area0 + par * s.area;
-            const bool more = gn < s.g1;
-            if (more) prefetch<R, NT>(pf, mats, gates, gn);
-            if (g.kind == 0) {
-                diag_run<R, S, NT>(tile, area, gates, gi, tile_amps);
+            CPtr<BlkGate> g = gates + gi;
+            const uint32_t gn = gi + (g->kind == 0 ? (uint32_t)g->run : 1u);
+            if (g->kind == 0) {
+                const char *tabs = s.resident ? area : area0 + par * (s.lds_tabs / 2);
+                if (s.resident) area += g->area;
+                else par ^= 1u;
+                if (!s.resident && gn < s.g1 && gates[gn].kind == 0) stage(gn);
+                diag_run<R, S, NT>(tile, tabs, g, ent, tbase, tile_amps);
             } else {
-                switch (g.d) {
-                    case 1: block_in_tile<1, R, S, NT>(tile, area, g, tile_amps); break;
-                    case 2: block_in_tile<2, R, S, NT>(tile, area, g, tile_amps); break;
-                    default:
-                        if (MAXD >= 3) block_in_tile<3, R, S, NT>(tile, area, g, tile_amps);
-                        break;
+                if (!s.resident && gn < s.g1 && gates[gn].kind == 0) stage(gn);
+                switch (g->d) {
+                    case 1: block_in_tile<1, R, S, NT>(tile, g, ent, mats, tbase); break;
+                    case 2: block_in_tile<2, R, S, NT>(tile, g, ent, mats, tbase); break;
+                    default: block_in_tile<3, R, S, NT>(tile, g, ent, mats, tbase); break;
                 }
             }
-            if (more) commit<R, S, NT>(area0 + (par ^ 1u) * s.area, pf, gates, gn, tbase, tile_amps);
             __syncthreads();
             gi = gn;
-            par ^= 1u;
         }
         // ---- store
         if (ahead) {
@@ -341,50 +283,44 @@ __global__ void __launch_bounds__(NT, MAXD >= 3 ? 4 : 1) k_blocked(R *__restrict
     }
 }
 
-template <typename R, int NT, int MAXD>
-hipError_t launch_nt(R *psi, const R *mats, const BlkGate *gates, const BlkSeg &s, uint32_t grid, size_t lds,
-                     hipStream_t stream) {
-    static const hipError_t attr = hipFuncSetAttribute((const void *)k_blocked<R, NT, MAXD>,
+template <typename R, int NT>
+hipError_t launch_nt(R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, size_t lds, hipStream_t stream) {
+    static const hipError_t attr = hipFuncSetAttribute((const void *)k_blocked<R, NT>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 128 << 10);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((k_blocked<R, NT, MAXD>), dim3(grid), dim3(NT), lds, stream, psi, mats, gates, s);
+    hipLaunchKernelGGL((k_blocked<R, NT>), dim3(grid), dim3(NT), lds, stream, psi, (const R *)p.mats, (const R *)p.tabs,
+                       p.gates, p.ent, s);
     return hipGetLastError();
 }
 
-template <typename R, int MAXD>
-hipError_t launch_d(int nt, R *psi, const R *mats, const BlkGate *gates, const BlkSeg &s, uint32_t grid,
-                    size_t lds, hipStream_t stream) {
-    switch (nt) {
-        case 256: return launch_nt<R, 256, MAXD>(psi, mats, gates, s, grid, lds, stream);
-        case 512: return launch_nt<R, 512, MAXD>(psi, mats, gates, s, grid, lds, stream);
-        default: return launch_nt<R, 1024, MAXD>(psi, mats, gates, s, grid, lds, stream);
-    }
-}
-
 template <typename R>
-hipError_t launch_r(int nt, R *psi, const R *mats, const BlkGate *gates, const BlkSeg &s, uint32_t grid,
-                    size_t lds, hipStream_t stream) {
-    if (s.maxd >= 3) return launch_d<R, 3>(nt, psi, mats, gates, s, grid, lds, stream);
-    return launch_d<R, 2>(nt, psi, mats, gates, s, grid, lds, stream);
+hipError_t launch_r(int nt, R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, size_t lds,
+                    hipStream_t stream) {
+    switch (nt) {
+        case 256: return launch_nt<R, 256>(psi, p, s, grid, lds, stream);
+        case 512: return launch_nt<R, 512>(psi, p, s, grid, lds, stream);
+        default: return launch_nt<R, 1024>(psi, p, s, grid, lds, stream);
+    }
 }
 
 }  // namespace
 
-cast_status launch_blocked(void *psi, cast_dtype dt, const void *mats, const BlkGate *gates, const BlkSeg &s,
-                           hipStream_t stream) {
-    const size_t tile = ((size_t)1 << s.tb) * amp_bytes(dt);
-    const size_t lds = tile + 2 * (size_t)s.area;
-    if (lds > (128u << 10)) return fail(CAST_EUNSUPPORTED, "blocked tile and gate areas exceed 128 KiB of LDS");
+int blocked_threads(cast_dtype dt, int tb) {
     int nt = tuning().blocked_threads[dt];
-    while (nt > 256 && ((size_t)1 << s.tb) < (size_t)nt) nt >>= 1;   // at least one amplitude per thread
+    while (nt > 256 && ((size_t)1 << tb) < (size_t)nt) nt >>= 1;   // at least one amplitude per thread
+    return nt;
+}
+
+cast_status launch_blocked(void *psi, cast_dtype dt, const BlkPtrs &p, const BlkSeg &s, int nt, hipStream_t stream) {
+    const size_t lds = ((size_t)1 << s.tb) * amp_bytes(dt) + s.lds_tabs;
+    if (lds > (128u << 10)) return fail(CAST_EUNSUPPORTED, "blocked tile and gate areas exceed 128 KiB of LDS");
     // two workgroups per compute unit (their LDS allows no more), each looping
     // over tiles with the next one's loads in flight
     uint64_t grid = s.ntiles;
     const uint64_t cap = std::min<uint64_t>(tuning().max_grid[dt], 512);
     if (grid > cap) grid = cap;
-    const hipError_t e = dt == CAST_C128
-        ? launch_r<double>(nt, (double *)psi, (const double *)mats, gates, s, (uint32_t)grid, lds, stream)
-        : launch_r<float>(nt, (float *)psi, (const float *)mats, gates, s, (uint32_t)grid, lds, stream);
+    const hipError_t e = dt == CAST_C128 ? launch_r<double>(nt, (double *)psi, p, s, (uint32_t)grid, lds, stream)
+                                         : launch_r<float>(nt, (float *)psi, p, s, (uint32_t)grid, lds, stream);
     if (e != hipSuccess) return fail(CAST_EHIP, std::string("blocked pass launch: ") + hipGetErrorString(e));
     return CAST_OK;
 }

@@ -17,54 +17,67 @@
 
 #include <cstdint>
 
+#include "../../include/cast.h"
+
 namespace cast {
 
 constexpr int kBlkMaxHigh = 10;    // tile qubits above the window
 constexpr int kBlkMaxD = 3;        // largest block dimension applied inside a tile
 constexpr int kBlkMinWindow = 4;   // smallest window: runs of >= 16 amplitudes
 
-struct BlkGate {             // one fused gate inside a tile
-    int kind;                // 0 diagonal (d = 0), 1 blocks of 2^d x 2^d
+// One operation inside a tile: a fused gate's blocks, or a run of consecutive
+// diagonal gates as phase tables (neighbouring gates multiplied together on
+// the host while their union has at most kRunMaxQ qubits).  Read at
+// wave-uniform indices: 32- and 64-bit fields only.
+struct BlkGate {
+    int kind;                // 0 phase table, 1 blocks of 2^d x 2^d
     int k, d;
-    int q[6];                // sorted targets
-    int tpos[6];             // tile bit of each target, -1 when the target is outside the tile
+    int q[8];                // sorted targets
+    int tpos[8];             // tile bit of each target, -1 when the target is outside the tile
+    // blocks
     uint32_t colv[6];        // virtual coordinates of local index bit s (the columns of L^-1)
     uint32_t span[kBlkMaxD]; // tile offset of virtual basis vector i < d
-    uint32_t pivlow[kBlkMaxD];   // coset enumeration: (1 << pivot) - 1 per pivot bit, ascending
-    int8_t slot[32];         // block id -> index among the active blocks, -1: identity block
-    uint64_t amask;          // diagonal: local indices whose phase is not 1
-    uint64_t mat;            // offset (reals) of the gate's matrices in the fused list's buffer
-    uint32_t mat_reals;      // their size: 2 * 2^k (diagonal) or 2 * blocks * 4^d
-    int run;                 // diagonal: gates applied together from here (a run), 0 inside a run
-    int tshift;              // first gate of a run: log2 of its phase-table stride (entries)
-    int pad;
+    uint32_t amask;          // bit b: block b is not the identity (its matrices lie in block order)
+    uint32_t nlane, nuni;    // coset bits given by the lane, and by the wave and iteration
+    uint64_t lanepos;        // tile bit of lane bit i (8 bits each)
+    uint32_t ent;            // entries of the 2^nuni uniform coset parts in the entry table;
+                             // phase tables: of the iterations' uniform local indices
+    int run;                 // phase tables: tables of the run from here (0 inside a run)
+    int tshift;              // first table of a run: log2 of the tables' stride (entries)
+    uint32_t area;           // first table of a run: its LDS bytes
+    uint64_t mat;            // offset (reals) of the matrices in the fused list's buffer, or of the
+                             // run's tables in the plan's table buffer
+};
+struct BlkEnt {              // uniform part of a coset: virtual coordinates, LDS element; of a phase
+    uint32_t u, a;           // table's iteration: local index (u)
 };
 
-// LDS of a segment pass: the tile, then two gate areas (the gate or run of
-// diagonal gates being applied and the next one, staged meanwhile).  An area
-// holds the slot table (32 bytes); the iteration table (per loop iteration
-// of the workgroup, the wave-uniform part of the virtual coordinates and of
-// the LDS address; at most 32 iterations); for a run of diagonal gates the
-// uniform part of each gate's local index per iteration; then the matrices,
-// or the run's phase tables at a stride of 2^tshift entries.  The planner
-// keeps tile + two areas within kBlkLdsBudget, so two workgroups share a
-// compute unit's 160 KiB of LDS.
-constexpr uint32_t kBlkIterOff = 64;
-constexpr uint32_t kBlkMaxIters = 32;
+// LDS of a segment pass: the tile, then the phase tables: all the segment's
+// when they fit kBlkAreaBytes (staged once per workgroup), else two areas,
+// the run being applied and the next one, staged meanwhile.  Tile and areas
+// stay within 80 KiB, so two workgroups share a compute unit's 160 KiB.
+constexpr uint32_t kBlkAreaBytes = 16u << 10;
 constexpr uint32_t kBlkRunMax = 8;
-constexpr uint32_t kBlkJOff = kBlkIterOff + kBlkMaxIters * 8;
-constexpr uint32_t kBlkAreaHead = kBlkJOff + kBlkRunMax * kBlkMaxIters * 4;
-constexpr uint32_t kBlkMaxMatChunks = 512;    // 16-byte chunks of one gate's matrices (<= 2 per thread)
-constexpr uint32_t kBlkLdsBudget = 80u << 10;
 
 struct BlkSeg {              // kernel arguments of one segment pass
     uint64_t ntiles;         // 2^(n - tb)
     uint64_t hlowmask[kBlkMaxHigh];  // per high tile qubit (ascending): global index bits below it
     int tb, w, nh;
     int qh[kBlkMaxHigh];     // high tile qubits, ascending
-    uint32_t g0, g1;         // gates [g0, g1) of the gate table
-    uint32_t area;           // bytes of one gate area (head + the largest matrices of the segment)
-    int maxd;                // largest block dimension among the segment's gates (selects the kernel)
+    uint32_t g0, g1;         // operations [g0, g1) of the gate table
+    int resident;            // every run's tables stay in LDS
+    uint32_t lds_tabs;       // bytes of phase tables in LDS
 };
+
+struct BlkPtrs {             // device tables of a plan
+    const void *mats, *tabs;
+    const BlkGate *gates;
+    const BlkEnt *ent;
+};
+
+// Workgroup size of a plan with tiles of 2^tb amplitudes (the knob, at most
+// one thread per amplitude).
+int blocked_threads(cast_dtype dt, int tb);
+cast_status launch_blocked(void *psi, cast_dtype dt, const BlkPtrs &p, const BlkSeg &s, int nt, hipStream_t stream);
 
 }  // namespace cast

@@ -561,6 +561,15 @@ void select_tiles(const SchedPass &p, int n, int tb, int pattern_major, cast_dty
 
 }  // namespace
 
+PhaseTable phase_table(const PassPlan &p) { return table_of(p); }
+
+bool merge_tables(PhaseTable *a, const PhaseTable &b, int max_qubits) {
+    int u[2 * kRunMaxQ];
+    if (qubit_union(a->q, a->k, b.q, b.k, u) > max_qubits) return false;
+    *a = combine(*a, b, 1e-14);
+    return true;
+}
+
 bool diag_pass(int n, cast_dtype dt, const PassPlan &p) { return !p.identity() && pass_kernel_kind(n, dt, p) == 3; }
 
 cast_status build_schedule(const std::vector<PassPlan> &plans, int n, cast_dtype dt, Schedule *out) {

@@ -185,6 +185,10 @@ struct Schedule {
     DeviceMatrix dev;                // run tables in the state dtype, 256 entries per table
 };
 bool diag_pass(int n, cast_dtype dt, const PassPlan &p);
+// The diagonal of a plan (d = 0) as a table; a *= b when their union has at
+// most max_qubits (<= kRunMaxQ) qubits.
+PhaseTable phase_table(const PassPlan &p);
+bool merge_tables(PhaseTable *a, const PhaseTable &b, int max_qubits);
 cast_status build_schedule(const std::vector<PassPlan> &plans, int n, cast_dtype dt, Schedule *out);
 cast_status upload_schedule(Schedule *s);
 cast_status launch_diag_run(void *psi, int n, cast_dtype dt, const SchedPass &p, const void *dtabs,
