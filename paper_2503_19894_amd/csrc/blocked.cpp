@@ -3,6 +3,7 @@
 // passes.
 #include <algorithm>
 #include <cstring>
+#include <iterator>
 
 #include "blocked.hpp"
 #include "internal.hpp"
@@ -20,9 +21,10 @@ struct BlockedPlan {
     std::vector<Pass> passes;
     std::vector<BlkGate> gates;
     std::vector<BlkEnt> ent;
-    std::vector<double> tabs;          // phase tables of the runs (complex entries as pairs)
-    void *dev = nullptr;               // device copy of gates, entries and tables (in the state dtype)
-    size_t dev_ent = 0, dev_tabs = 0;  // byte offsets in it
+    std::vector<BlkMember> members;
+    std::vector<double> tabs;          // phases of the diagonal gates (complex entries as pairs)
+    void *dev = nullptr;               // device copy of these tables (phases in the state dtype)
+    size_t dev_ent = 0, dev_mem = 0, dev_tabs = 0;   // byte offsets in it
 };
 
 void blocked_free(BlockedPlan *b) {
@@ -157,20 +159,39 @@ BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh
     return g;
 }
 
-// One phase table inside a tile, and the uniform local index of each
-// iteration of nt threads over the tile.
-BlkGate make_table(const PhaseTable &t, int tb, int nt, int w, const int *qh, int nh, std::vector<BlkEnt> *ent) {
-    BlkGate g;
-    std::memset(&g, 0, sizeof g);
-    set_targets(&g, t.k, t.q, w, qh, nh);
-    g.ent = (uint32_t)ent->size();
-    for (uint32_t y = 0; y < (1u << tb); y += (uint32_t)nt) {
-        uint32_t j = 0;
+// A stretch of diagonal gates as phase tables over tile bits: gates join a
+// table while its tile bits stay within kBlkTabBits (first fit; diagonal
+// gates commute).
+struct Cluster {
+    std::vector<int> bits;                    // tile bits, ascending
+    std::vector<const PhaseTable *> gates;
+};
+std::vector<Cluster> cluster_tables(const std::vector<PhaseTable> &tabs, const int *pos) {
+    std::vector<Cluster> out;
+    for (const PhaseTable &t : tabs) {
+        std::vector<int> in;
         for (int s = 0; s < t.k; ++s)
-            if (g.tpos[s] >= 0) j |= ((y >> g.tpos[s]) & 1u) << s;
-        ent->push_back(BlkEnt{j, 0});
+            if (pos[t.q[s]] >= 0) in.push_back(pos[t.q[s]]);
+        std::sort(in.begin(), in.end());
+        Cluster *to = nullptr;
+        std::vector<int> u;
+        for (Cluster &c : out) {
+            u.clear();
+            std::set_union(c.bits.begin(), c.bits.end(), in.begin(), in.end(), std::back_inserter(u));
+            if ((int)u.size() <= std::max(kBlkTabBits, (int)in.size())) {
+                to = &c;
+                break;
+            }
+        }
+        if (!to) {
+            out.emplace_back();
+            to = &out.back();
+            u = in;
+        }
+        to->bits = u;
+        to->gates.push_back(&t);
     }
-    return g;
+    return out;
 }
 
 cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
@@ -184,9 +205,6 @@ cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
     const std::vector<PassPlan> &P = f.plans;
     const std::vector<size_t> off = plan_offsets(P, dt);
     const size_t ab = amp_bytes(dt);
-    // largest merged table: half an area, so that a run may hold two
-    int tab_qubits = kRunMaxQ;
-    while (((size_t)2 << tab_qubits) * ab > kBlkAreaBytes / 2) --tab_qubits;
     std::vector<size_t> cur;   // non-identity gates of the open segment
     size_t first = 0;
     uint64_t need = 0;
@@ -210,39 +228,68 @@ cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
                     ++s.nh;
                 }
             s.g0 = (uint32_t)bp->gates.size();
-            // consecutive diagonal gates: multiplied into tables while their
-            // union fits (each lookup and multiply then stands for several
-            // gates), then runs of tables applied in one sweep of the tile,
-            // at the stride of the run's largest table
-            std::vector<PhaseTable> tabs;
+            int pos[64];
+            for (int q = 0; q < n; ++q) pos[q] = q < w ? q : -1;
+            for (int i = 0; i < s.nh; ++i) pos[s.qh[i]] = w + i;
+            uint32_t build = ~0u, used = 0;   // the open kind-2 operation, entries its tables take
+            std::vector<PhaseTable> tabs;     // the open stretch of diagonal gates
             auto flush = [&] {
-                for (size_t t = 0; t < tabs.size();) {
-                    size_t m = 0;
-                    int ts = 1;
-                    while (t + m < tabs.size() && m < kBlkRunMax) {
-                        const int ts2 = std::max(ts, tabs[t + m].k);
-                        if (m > 0 && ((m + 1) << ts2) * ab > kBlkAreaBytes / 2) break;
-                        ts = ts2;
-                        ++m;
-                    }
-                    const size_t base = bp->tabs.size();   // a multiple of 16 bytes
-                    bp->tabs.resize(base + 2 * (m << ts), 0.0);
-                    for (size_t j = 0; j < m; ++j) {
-                        BlkGate g = make_table(tabs[t + j], tb, bp->nt, w, s.qh, s.nh, &bp->ent);
-                        if (j == 0) {
-                            g.run = (int)m;
-                            g.tshift = ts;
-                            g.area = (uint32_t)((m << ts) * ab);
-                            g.mat = base;
+                const std::vector<Cluster> cl = cluster_tables(tabs, pos);
+                for (size_t c = 0; c < cl.size();) {
+                    // a run: tables that fit the area together
+                    const size_t first_gate = bp->gates.size();
+                    std::vector<BlkGate> run;
+                    uint32_t end = used;
+                    bool fresh = build == ~0u;
+                    for (; c < cl.size() && run.size() < kBlkRunMax; ++c) {
+                        const uint32_t sz = 1u << cl[c].bits.size(), at = (end + sz - 1) & ~(sz - 1);
+                        if ((at + sz) * ab > kBlkAreaBytes) {
+                            if (!run.empty()) break;
+                            fresh = true;   // the area starts anew
+                            end = 0;
+                            --c;
+                            continue;
                         }
+                        BlkGate g;
+                        std::memset(&g, 0, sizeof g);
+                        g.k = (int)cl[c].bits.size();
+                        for (int i = 0; i < g.k; ++i) g.tpos[i] = cl[c].bits[i];
+                        g.lds = at;
+                        end = at + sz;
+                        g.ent = (uint32_t)bp->ent.size();
+                        for (uint32_t y = 0; y < (1u << tb); y += (uint32_t)bp->nt) {
+                            uint32_t j = 0;
+                            for (int i = 0; i < g.k; ++i) j |= ((y >> g.tpos[i]) & 1u) << i;
+                            bp->ent.push_back(BlkEnt{j, 0});
+                        }
+                        g.m0 = (uint32_t)bp->members.size();
+                        for (const PhaseTable *t : cl[c].gates) {
+                            BlkMember m;
+                            std::memset(&m, 0, sizeof m);
+                            m.k = t->k;
+                            m.tab = bp->tabs.size();
+                            for (int i = 0; i < t->k; ++i) {
+                                m.q[i] = t->q[i];
+                                m.src[i] = pos[t->q[i]] < 0 ? -1
+                                    : (int)(std::lower_bound(cl[c].bits.begin(), cl[c].bits.end(), pos[t->q[i]]) - cl[c].bits.begin());
+                            }
+                            for (const cplx &z : t->ph) bp->tabs.push_back(z.real()), bp->tabs.push_back(z.imag());
+                            bp->members.push_back(m);
+                        }
+                        g.m1 = (uint32_t)bp->members.size();
+                        run.push_back(g);
+                    }
+                    if (fresh) {
+                        build = (uint32_t)first_gate;
+                        BlkGate g;
+                        std::memset(&g, 0, sizeof g);
+                        g.kind = 2;
                         bp->gates.push_back(g);
-                        for (size_t e = 0; e < tabs[t + j].ph.size(); ++e) {
-                            const cplx z = tabs[t + j].ph[e];
-                            bp->tabs[base + 2 * ((j << ts) + e)] = z.real();
-                            bp->tabs[base + 2 * ((j << ts) + e) + 1] = z.imag();
-                        }
                     }
-                    t += m;
+                    used = end;
+                    run[0].run = (int)run.size();
+                    bp->gates.insert(bp->gates.end(), run.begin(), run.end());
+                    s.lds_tabs = std::max(s.lds_tabs, (uint32_t)(used * ab));
                 }
                 tabs.clear();
             };
@@ -252,15 +299,30 @@ cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
                     bp->gates.push_back(make_gate(P[i], dt, tb, w, s.qh, s.nh, off[i], &bp->ent));
                     continue;
                 }
+                // neighbours are multiplied here while their union fits a
+                // table of the host's size, which leaves fewer to build with
                 PhaseTable t = phase_table(P[i]);
-                if (tabs.empty() || !merge_tables(&tabs.back(), t, tab_qubits)) tabs.push_back(std::move(t));
+                if (tabs.empty() || !merge_tables(&tabs.back(), t, kRunMaxQ)) tabs.push_back(std::move(t));
             }
             flush();
+            // the first tables are built at the start of the tile (nothing
+            // reads the area before), and every build lists its units
+            if (build != ~0u) {
+                for (uint32_t gi = s.g0; gi < bp->gates.size(); ++gi)
+                    if (bp->gates[gi].kind == 2) {
+                        std::rotate(bp->gates.begin() + s.g0, bp->gates.begin() + gi, bp->gates.begin() + gi + 1);
+                        break;
+                    }
+            }
             s.g1 = (uint32_t)bp->gates.size();
-            uint32_t total = 0, most = 0;
-            for (uint32_t gi = s.g0; gi < s.g1; ++gi) total += bp->gates[gi].area, most = std::max(most, bp->gates[gi].area);
-            s.resident = total <= kBlkAreaBytes;
-            s.lds_tabs = s.resident ? total : 2 * most;
+            for (uint32_t gi = s.g0; gi < s.g1; ++gi) {
+                if (bp->gates[gi].kind != 2) continue;
+                bp->gates[gi].ent = (uint32_t)bp->ent.size();
+                for (uint32_t gj = gi + 1; gj < s.g1 && bp->gates[gj].kind != 2; ++gj)
+                    if (bp->gates[gj].kind == 0)
+                        for (uint32_t sl = 0; sl * 64 < (1u << bp->gates[gj].k); ++sl) bp->ent.push_back(BlkEnt{gj, sl});
+                bp->gates[gi].nent = (uint32_t)bp->ent.size() - bp->gates[gi].ent;
+            }
             bp->passes.push_back(ps);
         }
         cur.clear();
@@ -317,11 +379,14 @@ cast_status prepare(const cast_fused *fc, int n, cast_dtype dt, bool device, Blo
         if (!bp->dev && !bp->gates.empty()) {
             auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
             bp->dev_ent = up(bp->gates.size() * sizeof(BlkGate));
-            bp->dev_tabs = bp->dev_ent + up(bp->ent.size() * sizeof(BlkEnt));
+            bp->dev_mem = bp->dev_ent + up(bp->ent.size() * sizeof(BlkEnt));
+            bp->dev_tabs = bp->dev_mem + up(bp->members.size() * sizeof(BlkMember));
             const size_t rsz = amp_bytes(dt) / 2, bytes = bp->dev_tabs + std::max<size_t>(bp->tabs.size(), 4) * rsz;
             std::vector<char> h(bytes, 0);
             std::memcpy(h.data(), bp->gates.data(), bp->gates.size() * sizeof(BlkGate));
-            std::memcpy(h.data() + bp->dev_ent, bp->ent.data(), bp->ent.size() * sizeof(BlkEnt));
+            if (!bp->ent.empty()) std::memcpy(h.data() + bp->dev_ent, bp->ent.data(), bp->ent.size() * sizeof(BlkEnt));
+            if (!bp->members.empty())
+                std::memcpy(h.data() + bp->dev_mem, bp->members.data(), bp->members.size() * sizeof(BlkMember));
             for (size_t i = 0; i < bp->tabs.size(); ++i) {
                 if (dt == CAST_C128) ((double *)(h.data() + bp->dev_tabs))[i] = bp->tabs[i];
                 else ((float *)(h.data() + bp->dev_tabs))[i] = (float)bp->tabs[i];
@@ -344,7 +409,8 @@ cast_status launch(cast_sv *sv, const cast_fused *f, const BlockedPlan &bp, size
     const void *mats = f->dev[sv->dt].ptr;
     if (ps.segment) {
         const char *dev = static_cast<const char *>(bp.dev);
-        const BlkPtrs ptrs{mats, dev + bp.dev_tabs, (const BlkGate *)dev, (const BlkEnt *)(dev + bp.dev_ent)};
+        const BlkPtrs ptrs{mats, dev + bp.dev_tabs, (const BlkGate *)dev, (const BlkEnt *)(dev + bp.dev_ent),
+                           (const BlkMember *)(dev + bp.dev_mem)};
         return launch_blocked(sv->data, sv->dt, ptrs, ps.seg, bp.nt, sv->stream);
     }
     const size_t rsz = sv->dt == CAST_C128 ? 8 : 4;

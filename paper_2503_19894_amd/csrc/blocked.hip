@@ -49,37 +49,56 @@ __device__ __forceinline__ uint64_t expand(uint32_t y, const BlkSeg &s) {
 template <typename T> using CPtr = const __attribute__((address_space(4))) T *;
 template <typename T> __device__ __forceinline__ CPtr<T> cptr(const T *p) { return (CPtr<T>)p; }
 
-// Local index bits contributed by the in-tile targets of position y.
-__device__ __forceinline__ uint32_t loc(uint32_t y, CPtr<BlkGate> g) {
-    uint32_t j = 0;
-    for (int s = 0; s < g->k; ++s)
-        if (g->tpos[s] >= 0) j |= ((y >> g->tpos[s]) & 1u) << s;
-    return j;
-}
-
-// Copies a run's tables to LDS (both 16-byte aligned and of whole chunks).
-template <int NT>
-__device__ __forceinline__ void stage_tables(u4 *dst, const u4 *src, uint32_t n16) {
-    for (uint32_t i = threadIdx.x; i < n16; i += NT) dst[i] = src[i];
+// Builds phase tables for the tile at tbase (kind 2): a wave takes 64 entries
+// of one table and multiplies its gates' phases, their indices being a part
+// fixed by the tile and the entry's bits.
+template <typename R, int NT>
+__device__ __forceinline__ void build_tables(typename Cx<R>::T *area, CPtr<BlkGate> gates, CPtr<BlkGate> g,
+                                             CPtr<BlkEnt> ent, CPtr<BlkMember> members, const R *tabs,
+                                             uint64_t tbase) {
+    using V = typename Cx<R>::T;
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    for (uint32_t i = wave; i < g->nent; i += NT / 64) {
+        CPtr<BlkGate> t = gates + ent[g->ent + i].u;
+        const uint32_t e = ent[g->ent + i].a * 64 + lane;
+        V p;
+        p.x = 1;
+        p.y = 0;
+        const uint32_t m1 = t->m1;
+#pragma unroll 4
+        for (uint32_t m = t->m0; m < m1; ++m) {
+            CPtr<BlkMember> b = members + m;
+            uint32_t j = 0;
+#pragma unroll
+            for (int s = 0; s < 8; ++s) {
+                if (s >= b->k) break;
+                const int src = b->src[s];
+                j |= (src < 0 ? (uint32_t)((tbase >> b->q[s]) & 1u) : (e >> src) & 1u) << s;
+            }
+            const V z = reinterpret_cast<const V *>(tabs + b->tab)[j];
+            const R re = p.x * z.x - p.y * z.y;
+            p.y = p.x * z.y + p.y * z.x;
+            p.x = re;
+        }
+        if (e < (1u << t->k)) area[t->lds + e] = p;
+    }
 }
 
 // A run of M phase tables: amplitude y is read once, multiplied by each
-// table's phase D_t[j_t(y)] in order (identity phases are exactly 1), and
-// written once.  Instantiated per run length so the phase loop is straight
-// code.  j_t(y) is a lane part and a wave-uniform part per iteration.
+// table's phase in order (identity phases are exactly 1), and written once.
+// Instantiated per run length so the phase loop is straight code.  A table's
+// index is a lane part and a wave-uniform part per iteration.
 template <typename R, int S, int NT, int M>
-__device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const char *area, CPtr<BlkGate> g,
-                                           CPtr<BlkEnt> ent, uint64_t tbase, uint32_t tile_amps) {
+__device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const typename Cx<R>::T *area, CPtr<BlkGate> g,
+                                           CPtr<BlkEnt> ent, uint32_t tile_amps) {
     using V = typename Cx<R>::T;
-    const int ts = g->tshift;
-    const V *tabs = reinterpret_cast<const V *>(area);
-    uint32_t jl[M];
+    uint32_t jl[M], e0[M];
 #pragma unroll
     for (int t = 0; t < M; ++t) {
-        uint32_t juni = (uint32_t)t << ts;   // this tile's part
-        for (int q = 0; q < g[t].k; ++q)
-            if (g[t].tpos[q] < 0) juni |= (uint32_t)((tbase >> g[t].q[q]) & 1u) << q;
-        jl[t] = juni | loc(threadIdx.x, g + t);
+        uint32_t j = g[t].lds;
+        for (int i = 0; i < g[t].k; ++i) j |= ((threadIdx.x >> g[t].tpos[i]) & 1u) << i;
+        jl[t] = j;
+        e0[t] = g[t].ent;
     }
     const uint32_t al = at<S>(threadIdx.x);
     const uint32_t iters = tile_amps > NT ? tile_amps / NT : 1;
@@ -89,7 +108,7 @@ __device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const char *
         V x = tile[a];
 #pragma unroll
         for (int t = 0; t < M; ++t) {
-            const V ph = tabs[jl[t] ^ ent[g[t].ent + i].u];
+            const V ph = area[jl[t] ^ ent[e0[t] + i].u];
             const R re = x.x * ph.x - x.y * ph.y;
             const R im = x.x * ph.y + x.y * ph.x;
             x.x = re;
@@ -100,17 +119,17 @@ __device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const char *
 }
 
 template <typename R, int S, int NT>
-__device__ __forceinline__ void diag_run(typename Cx<R>::T *tile, const char *area, CPtr<BlkGate> g,
-                                         CPtr<BlkEnt> ent, uint64_t tbase, uint32_t tile_amps) {
+__device__ __forceinline__ void diag_run(typename Cx<R>::T *tile, const typename Cx<R>::T *area, CPtr<BlkGate> g,
+                                         CPtr<BlkEnt> ent, uint32_t tile_amps) {
     switch (g->run) {
-        case 1: diag_run_m<R, S, NT, 1>(tile, area, g, ent, tbase, tile_amps); break;
-        case 2: diag_run_m<R, S, NT, 2>(tile, area, g, ent, tbase, tile_amps); break;
-        case 3: diag_run_m<R, S, NT, 3>(tile, area, g, ent, tbase, tile_amps); break;
-        case 4: diag_run_m<R, S, NT, 4>(tile, area, g, ent, tbase, tile_amps); break;
-        case 5: diag_run_m<R, S, NT, 5>(tile, area, g, ent, tbase, tile_amps); break;
-        case 6: diag_run_m<R, S, NT, 6>(tile, area, g, ent, tbase, tile_amps); break;
-        case 7: diag_run_m<R, S, NT, 7>(tile, area, g, ent, tbase, tile_amps); break;
-        default: diag_run_m<R, S, NT, 8>(tile, area, g, ent, tbase, tile_amps); break;
+        case 1: diag_run_m<R, S, NT, 1>(tile, area, g, ent, tile_amps); break;
+        case 2: diag_run_m<R, S, NT, 2>(tile, area, g, ent, tile_amps); break;
+        case 3: diag_run_m<R, S, NT, 3>(tile, area, g, ent, tile_amps); break;
+        case 4: diag_run_m<R, S, NT, 4>(tile, area, g, ent, tile_amps); break;
+        case 5: diag_run_m<R, S, NT, 5>(tile, area, g, ent, tile_amps); break;
+        case 6: diag_run_m<R, S, NT, 6>(tile, area, g, ent, tile_amps); break;
+        case 7: diag_run_m<R, S, NT, 7>(tile, area, g, ent, tile_amps); break;
+        default: diag_run_m<R, S, NT, 8>(tile, area, g, ent, tile_amps); break;
     }
 }
 
@@ -184,27 +203,20 @@ __device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, CPtr<BlkG
 
 template <typename R, int NT>
 __global__ void __launch_bounds__(NT, 4) k_blocked(R *__restrict__ psi_r, const R *__restrict__ mats_g,
-                                                const R *__restrict__ tabs_g, const BlkGate *__restrict__ gates_g,
-                                                const BlkEnt *__restrict__ ent_g, BlkSeg s) {
+                                                const R *__restrict__ tabs, const BlkGate *__restrict__ gates_g,
+                                                const BlkEnt *__restrict__ ent_g,
+                                                const BlkMember *__restrict__ members_g, BlkSeg s) {
     using V = typename Cx<R>::T;
     constexpr int S = sizeof(V) == 16 ? 0 : 1;
     constexpr int B = 4096 / NT;               // chunks per lane of a 64 KiB tile
     extern __shared__ u4 lds16[];
     V *tile = reinterpret_cast<V *>(lds16);
     const uint32_t tile_amps = 1u << s.tb;
-    char *area0 = reinterpret_cast<char *>(lds16) + (size_t)tile_amps * sizeof(V);
+    V *area = tile + tile_amps;
     CPtr<BlkGate> gates = cptr(gates_g);
     CPtr<BlkEnt> ent = cptr(ent_g);
+    CPtr<BlkMember> members = cptr(members_g);
     CPtr<R> mats = cptr(mats_g);
-    if (s.resident) {
-        char *dst = area0;
-        for (uint32_t gi = s.g0; gi < s.g1; ++gi) {
-            if (gates[gi].kind != 0 || gates[gi].run == 0) continue;
-            stage_tables<NT>(reinterpret_cast<u4 *>(dst), reinterpret_cast<const u4 *>(tabs_g + gates[gi].mat),
-                             gates[gi].area / 16);
-            dst += gates[gi].area;
-        }
-    }
     u4 *p16 = reinterpret_cast<u4 *>(psi_r);
     const uint32_t chunks = tile_amps >> S;
     const uint64_t glane = expand(threadIdx.x << S, s) >> S;
@@ -230,45 +242,43 @@ __global__ void __launch_bounds__(NT, 4) k_blocked(R *__restrict__ psi_r, const 
         if (ahead) {
 #pragma unroll
             for (int u = 0; u < B; ++u) lds16[slane ^ swz(u * NT)] = nxt[u];
-            if (t + gridDim.x < s.ntiles) {
-                const u4 *src = base_of(t + gridDim.x);
-#pragma unroll
-                for (int u = 0; u < B; ++u) nxt[u] = __builtin_nontemporal_load(src + uoff[u]);
-            }
         } else {
             for (uint32_t c = threadIdx.x; c < chunks; c += NT)
                 lds16[swz(c)] = __builtin_nontemporal_load(base16 + (expand((c - threadIdx.x) << S, s) >> S));
         }
         // ---- the segment's operations (a run of tables counts as one), in
-        // order; without resident tables the next run's are staged into the
-        // other area while the current operation runs
-        char *area = area0;
-        uint32_t par = 0;
-        auto stage = [&](uint32_t gi) {
-            stage_tables<NT>(reinterpret_cast<u4 *>(area0 + par * (s.lds_tabs / 2)),
-                             reinterpret_cast<const u4 *>(tabs_g + gates[gi].mat), gates[gi].area / 16);
-        };
-        if (!s.resident && gates[s.g0].kind == 0) stage(s.g0);
+        // order.  The first tables are built before the next tile's loads are
+        // issued: loads return in order, so a phase read after them would wait
+        // for them.
+        uint32_t gi = s.g0;
+        if (gates[gi].kind == 2) {
+            build_tables<R, NT>(area, gates, gates + gi, ent, members, tabs, tbase);
+            ++gi;
+        }
+        if (ahead && t + gridDim.x < s.ntiles) {
+            const u4 *src = base_of(t + gridDim.x);
+#pragma unroll
+            for (int u = 0; u < B; ++u) nxt[u] = __builtin_nontemporal_load(src + uoff[u]);
+        }
         __syncthreads();
-        for (uint32_t gi = s.g0; gi < s.g1;) {
+        while (gi < s.g1) {
             CPtr<BlkGate> g = gates + gi;
-            const uint32_t gn = gi + (g->kind == 0 ? (uint32_t)g->run : 1u);
             if (g->kind == 0) {
-                const char *tabs = s.resident ? area : area0 + par * (s.lds_tabs / 2);
-                if (s.resident) area += g->area;
-                else par ^= 1u;
-                if (!s.resident && gn < s.g1 && gates[gn].kind == 0) stage(gn);
-                diag_run<R, S, NT>(tile, tabs, g, ent, tbase, tile_amps);
+                diag_run<R, S, NT>(tile, area, g, ent, tile_amps);
+                gi += (uint32_t)g->run;
             } else {
-                if (!s.resident && gn < s.g1 && gates[gn].kind == 0) stage(gn);
-                switch (g->d) {
-                    case 1: block_in_tile<1, R, S, NT>(tile, g, ent, mats, tbase); break;
-                    case 2: block_in_tile<2, R, S, NT>(tile, g, ent, mats, tbase); break;
-                    default: block_in_tile<3, R, S, NT>(tile, g, ent, mats, tbase); break;
+                if (g->kind == 2) {
+                    build_tables<R, NT>(area, gates, g, ent, members, tabs, tbase);
+                } else {
+                    switch (g->d) {
+                        case 1: block_in_tile<1, R, S, NT>(tile, g, ent, mats, tbase); break;
+                        case 2: block_in_tile<2, R, S, NT>(tile, g, ent, mats, tbase); break;
+                        default: block_in_tile<3, R, S, NT>(tile, g, ent, mats, tbase); break;
+                    }
                 }
+                ++gi;
             }
             __syncthreads();
-            gi = gn;
         }
         // ---- store
         if (ahead) {
@@ -289,7 +299,7 @@ hipError_t launch_nt(R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, s
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, 128 << 10);
     if (attr != hipSuccess) return attr;
     hipLaunchKernelGGL((k_blocked<R, NT>), dim3(grid), dim3(NT), lds, stream, psi, (const R *)p.mats, (const R *)p.tabs,
-                       p.gates, p.ent, s);
+                       p.gates, p.ent, p.members, s);
     return hipGetLastError();
 }
 

@@ -25,13 +25,21 @@ constexpr int kBlkMaxHigh = 10;    // tile qubits above the window
 constexpr int kBlkMaxD = 3;        // largest block dimension applied inside a tile
 constexpr int kBlkMinWindow = 4;   // smallest window: runs of >= 16 amplitudes
 
-// One operation inside a tile: a fused gate's blocks, or a run of consecutive
-// diagonal gates as phase tables (neighbouring gates multiplied together on
-// the host while their union has at most kRunMaxQ qubits).  Read at
-// wave-uniform indices: 32- and 64-bit fields only.
+// One operation inside a tile.  Read at wave-uniform indices: 32- and 64-bit
+// fields only.
+//   kind 0  a phase table over at most kBlkTabBits tile bits.  A stretch of
+//           consecutive diagonal gates becomes a run of such tables: the gates'
+//           targets outside the tile are fixed per tile, and gates are put
+//           together while their targets inside it fit one table, whatever
+//           their number; kind 2 multiplies the gates' phases into the tables,
+//           per tile, so that an amplitude meets one lookup and one multiply
+//           per table instead of per gate.
+//   kind 1  a fused gate's blocks of 2^d x 2^d.
+//   kind 2  builds the phase tables up to the next kind 2 (one or more runs,
+//           as many as the table area holds).
 struct BlkGate {
-    int kind;                // 0 phase table, 1 blocks of 2^d x 2^d
-    int k, d;
+    int kind;
+    int k, d;                // targets (phase table: its tile bits)
     int q[8];                // sorted targets
     int tpos[8];             // tile bit of each target, -1 when the target is outside the tile
     // blocks
@@ -40,23 +48,32 @@ struct BlkGate {
     uint32_t amask;          // bit b: block b is not the identity (its matrices lie in block order)
     uint32_t nlane, nuni;    // coset bits given by the lane, and by the wave and iteration
     uint64_t lanepos;        // tile bit of lane bit i (8 bits each)
-    uint32_t ent;            // entries of the 2^nuni uniform coset parts in the entry table;
-                             // phase tables: of the iterations' uniform local indices
-    int run;                 // phase tables: tables of the run from here (0 inside a run)
-    int tshift;              // first table of a run: log2 of the tables' stride (entries)
-    uint32_t area;           // first table of a run: its LDS bytes
-    uint64_t mat;            // offset (reals) of the matrices in the fused list's buffer, or of the
-                             // run's tables in the plan's table buffer
+    uint64_t mat;            // offset (reals) of the matrices in the fused list's buffer
+    // entry table: blocks, the 2^nuni uniform coset parts; phase table, the
+    // uniform local index of each iteration over the tile; kind 2, its work
+    // units
+    uint32_t ent, nent;
+    // phase table
+    int run;                 // tables applied together from here (0 inside a run)
+    uint32_t lds;            // its first entry in the table area, a multiple of its 2^k entries
+    uint32_t m0, m1;         // its gates [m0, m1) of the member table
 };
-struct BlkEnt {              // uniform part of a coset: virtual coordinates, LDS element; of a phase
-    uint32_t u, a;           // table's iteration: local index (u)
+struct BlkEnt {
+    uint32_t u, a;           // blocks: virtual coordinates, LDS element; phase table: local index;
+                             // kind 2: phase table (gate index), 64-entry slice
+};
+struct BlkMember {           // a diagonal gate of a phase table
+    int k;
+    int q[8];                // targets
+    int src[8];              // bit of the table's index each comes from, -1: outside the tile
+    uint64_t tab;            // offset (reals) of its 2^k phases
 };
 
-// LDS of a segment pass: the tile, then the phase tables: all the segment's
-// when they fit kBlkAreaBytes (staged once per workgroup), else two areas,
-// the run being applied and the next one, staged meanwhile.  Tile and areas
-// stay within 80 KiB, so two workgroups share a compute unit's 160 KiB.
+// LDS of a segment pass: the tile, then the table area; 80 KiB together, so
+// two workgroups share a compute unit's 160 KiB.  Tables of 2^7 entries: three
+// of them take a QFT run's targets with all other bits of a tile.
 constexpr uint32_t kBlkAreaBytes = 16u << 10;
+constexpr int kBlkTabBits = 7;
 constexpr uint32_t kBlkRunMax = 8;
 
 struct BlkSeg {              // kernel arguments of one segment pass
@@ -65,14 +82,14 @@ struct BlkSeg {              // kernel arguments of one segment pass
     int tb, w, nh;
     int qh[kBlkMaxHigh];     // high tile qubits, ascending
     uint32_t g0, g1;         // operations [g0, g1) of the gate table
-    int resident;            // every run's tables stay in LDS
-    uint32_t lds_tabs;       // bytes of phase tables in LDS
+    uint32_t lds_tabs;       // bytes of the table area
 };
 
 struct BlkPtrs {             // device tables of a plan
     const void *mats, *tabs;
     const BlkGate *gates;
     const BlkEnt *ent;
+    const BlkMember *members;
 };
 
 // Workgroup size of a plan with tiles of 2^tb amplitudes (the knob, at most
