@@ -171,19 +171,24 @@ cast_status fused_gate(const cast_fused *f, size_t i, int *k, int *qubits, doubl
  * Sec. III-C, does not grow), so the host multiplies the run, in FP64, into
  * at most "diag_run_tables" phase tables of at most "diag_run_qubits" qubits
  * each, and the pass multiplies each amplitude by the product of its entries
- * (knob diag_run_tables = 0: one pass per fused gate).  The schedule is built
+ * (knob diag_run_tables = 0: one pass per fused gate).  Consecutive passes of
+ * that schedule whose gates mix only amplitudes of one LDS tile share a launch
+ * and one read and write of the state where that is predicted to be faster
+ * (knob tile_groups = 0: one launch per pass; the results agree up to
+ * rounding).  The schedule is built
  * for the state's dtype with the knobs current at first use and cached in the
  * list (rebuilt when those knobs change).  The state's n must equal the n
  * given to fuse_circuit.  Queued on the state's stream. */
 cast_status apply_circuit(cast_sv *sv, const cast_fused *f);
 
-/* Same as apply_circuit, but records a HIP event pair around every pass on
+/* Same as apply_circuit with one launch per pass (knob tile_groups = 0), but
+ * records a HIP event pair around every pass on
  * the state's stream and returns each pass's device time in pass_ms (one
  * float per pass of circuit_passes, milliseconds).  Synchronous.  For
  * measurement. */
 cast_status apply_circuit_timed(cast_sv *sv, const cast_fused *f, float *pass_ms);
 
-/* Number of device passes apply_circuit makes for a 2^n state of dtype dt
+/* Number of passes in apply_circuit's schedule for a 2^n state of dtype dt
  * with the current knobs (host only; builds and caches the schedule). */
 cast_status circuit_passes(const cast_fused *f, int n, cast_dtype dt, size_t *n_passes);
 
@@ -333,7 +338,9 @@ void fused_destroy(cast_fused *f);
  * pattern-major 1), "blocked_tile_bits" (log2 amplitudes per tile of the
  * cache-blocked passes, 8..12 for complex128, 8..13 for complex64: tiles of
  * at most 64 KiB, so two workgroups share a compute unit's LDS),
- * "blocked_threads" (their workgroup size: 256, 512 or 1024),
+ * "blocked_threads" (their workgroup size: 256, 512 or 1024), "tile_groups"
+ * (apply_circuit: passes that fit one LDS tile share a launch 1 / one launch
+ * per pass 0),
  * "mfma_3m_min_d" (matrix-core passes with blocks of d >= this value form
  * complex products with three real products instead of four; 4..7, 7 = never),
  * "mfma_low_tile" (1: a matrix-core pass with d <= 4 and a target below bit 4

@@ -51,6 +51,7 @@ Tuning &tuning() {
         env("CAST_MFMA_3M_MIN_D", x.mfma_3m_min_d);
         env("CAST_BLOCKED_TILE_BITS", x.blocked_tile_bits);
         env("CAST_BLOCKED_THREADS", x.blocked_threads);
+        env("CAST_TILE_GROUPS", x.tile_groups);
         return x;
     }();
     return t;
@@ -517,6 +518,7 @@ static int *tuning_field(const std::string &key, cast_dtype dt, int *lo, int *hi
     if (key == "mfma_low_tile") { *hi = 1; return &t.mfma_low_tile[i]; }
     if (key == "mfma_3m_min_d") { *lo = 4; *hi = 7; return &t.mfma_3m_min_d[i]; }
     if (key == "blocked_tile_bits") { *lo = 8; *hi = i == CAST_C64 ? 13 : 12; return &t.blocked_tile_bits[i]; }
+    if (key == "tile_groups") { *hi = 1; return &t.tile_groups[i]; }
     if (key == "blocked_threads") { *lo = 256; *hi = 1024; return &t.blocked_threads[i]; }
     if (key == "persistent_spin_limit") return &t.persistent_spin_limit[i];
     if (key == "diag_run_tables") { *hi = kRunMaxTables; return &t.diag_run_tables[i]; }
@@ -676,7 +678,9 @@ static cast_status get_schedule(cast_fused *f, int n, cast_dtype dt, bool upload
     if (s && (s->n != n || s->run_tables != tu.diag_run_tables[dt] || s->run_qubits != tu.diag_run_qubits[dt] ||
               s->use_diag != tu.use_diag[dt])) {
         schedule_free(s);
+        blocked_free(f->groups[dt]);
         s = f->sched[dt] = nullptr;
+        f->groups[dt] = nullptr;
     }
     if (!s) {
         s = new Schedule;
@@ -718,8 +722,19 @@ cast_status apply_circuit(cast_sv *sv, const cast_fused *fc) {
     cast_fused *f;
     Schedule *sc;
     if (cast_status rc = prepare_circuit(sv, fc, &f, &sc)) return rc;
-    for (const SchedPass &sp : sc->passes)
-        if (cast_status rc = launch_sched_pass(sv, f, *sc, sp)) return rc;
+    if (!tuning().tile_groups[sv->dt]) {
+        for (const SchedPass &sp : sc->passes)
+            if (cast_status rc = launch_sched_pass(sv, f, *sc, sp)) return rc;
+        return CAST_OK;
+    }
+    BlockedPlan *groups;
+    if (cast_status rc = tile_groups(f, *sc, sv->dt, &groups)) return rc;
+    for (size_t i = 0; i < group_count(*groups); ++i) {
+        size_t pass;
+        if (cast_status rc = launch_group(sv, f, *groups, i, &pass)) return rc;
+        if (pass != (size_t)-1)
+            if (cast_status rc = launch_sched_pass(sv, f, *sc, sc->passes[pass])) return rc;
+    }
     return CAST_OK;
 }
 
@@ -901,7 +916,7 @@ cast_status fused_pass_info(const cast_fused *f, size_t i, int n, cast_dtype dt,
 void fused_destroy(cast_fused *f) {
     if (!f) return;
     for (int d = 0; d < 3; ++d)
-        dev_free(f->dev[d].ptr), blocked_free(f->blocked[d]), jit_free(f->jit[d]), schedule_free(f->sched[d]);
+        dev_free(f->dev[d].ptr), blocked_free(f->blocked[d]), blocked_free(f->groups[d]), jit_free(f->jit[d]), schedule_free(f->sched[d]);
     delete f;
 }
 

@@ -24,6 +24,7 @@
 #include <cstring>
 
 #include "internal.hpp"
+#include "mfma.hpp"
 #include "pass_args.hpp"
 
 namespace cast {
@@ -466,25 +467,6 @@ __global__ void __launch_bounds__(256) k_tile(R *__restrict__ psi_r, const R *__
 // The active blocks' matrices are staged transposed in LDS (lanes with
 // consecutive rows read consecutive entries).  A wave reads all inputs of its
 // 16 groups before writing any output, so updates are in place.
-typedef double mf_v4d __attribute__((ext_vector_type(4)));
-typedef float mf_v4f __attribute__((ext_vector_type(4)));
-
-template <typename R> struct Mfma;
-template <> struct Mfma<double> {
-    using acc = mf_v4d;
-    static __device__ __forceinline__ acc mma(double a, double b, acc c) {
-        return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ int row(int lane, int v) { return (lane >> 4) + 4 * v; }
-};
-template <> struct Mfma<float> {
-    using acc = mf_v4f;
-    static __device__ __forceinline__ acc mma(float a, float b, acc c) {
-        return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
-    }
-    static __device__ __forceinline__ int row(int lane, int v) { return 4 * (lane >> 4) + v; }
-};
-
 // Stages the active blocks' matrices transposed: mt[(b * N + c) * N + i] = M_b[i][c].
 template <int D, typename V, typename R>
 __device__ __forceinline__ void stage_blocks(V *mt, const R *mat, uint32_t nblk) {

@@ -12,10 +12,12 @@ namespace cast {
 
 struct BlockedPlan {
     int tb = 0, nt = 0;                // tile bits, workgroup size
+    int knob_tb = 0;                   // tile groups: the tile-size knob they were planned with
     struct Pass {
         size_t first = 0, count = 0;   // fused gates [first, first + count) covered by this pass
         bool segment = false;
-        size_t gate = 0;               // ordinary pass: the fused gate it applies
+        size_t gate = 0;               // ordinary pass: the fused gate it applies (a tile group's plan: the
+                                       // schedule pass)
         BlkSeg seg{};
     };
     std::vector<Pass> passes;
@@ -114,8 +116,8 @@ BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh
     }
     // pivot bits of a reduced echelon basis of the span: the tile positions
     // with zeros there hold one element of every coset
-    uint32_t b[kBlkMaxD];
-    int piv[kBlkMaxD];
+    uint32_t b[kGroupMaxD];
+    int piv[kGroupMaxD];
     for (int i = 0; i < p.d; ++i) {
         b[i] = g.span[i];
         for (int j = 0; j < i; ++j)
@@ -134,7 +136,7 @@ BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh
     for (int i = 0; i < p.d; ++i) pivots |= 1u << piv[i];
     int used[5] = {0, 0, 0, 0, 0};
     auto column = [&](int bit) { return dt == CAST_C128 ? bit & 3 : bit == 0 ? 4 : (bit - 1) & 3; };
-    while (g.nlane < 6) {
+    while (g.nlane < (p.d >= 4 ? 4u : 6u)) {
         int best = -1;
         for (int t = 0; t < tb; ++t)
             if (!(((targets | lane) >> t) & 1u) && (best < 0 || used[column(t)] < used[column(best)])) best = t;
@@ -194,6 +196,134 @@ std::vector<Cluster> cluster_tables(const std::vector<PhaseTable> &tabs, const i
     return out;
 }
 
+// Appends the segment that applies the (non-identity) gates `cur`, fused gates
+// [first, first + count), whose mixed qubits `need` fit a tile.
+void emit_segment(BlockedPlan *bp, const std::vector<PassPlan> &P, const std::vector<size_t> &off, int n,
+                  cast_dtype dt, const std::vector<size_t> &cur, size_t first, size_t count, uint64_t need) {
+    const int tb = bp->tb;
+    const size_t ab = amp_bytes(dt);
+    const bool dense = std::any_of(cur.begin(), cur.end(), [&](size_t i) { return P[i].d >= 4; });
+    const int nt = dense ? kGroupThreads : bp->nt;
+    int w = tb;
+    window_of(need, tb, &w);
+    BlockedPlan::Pass ps;
+    ps.first = first, ps.count = count, ps.segment = true;
+    BlkSeg &s = ps.seg;
+    s.tb = tb, s.w = w, s.nh = 0;
+    s.ntiles = 1ull << (n - tb);
+    for (int q = w; q < n; ++q)
+        if ((need >> q) & 1u) {
+            s.qh[s.nh] = q;
+            s.hlowmask[s.nh] = (1ull << q) - 1;
+            ++s.nh;
+        }
+    s.g0 = (uint32_t)bp->gates.size();
+    int pos[64];
+    for (int q = 0; q < n; ++q) pos[q] = q < w ? q : -1;
+    for (int i = 0; i < s.nh; ++i) pos[s.qh[i]] = w + i;
+    uint32_t build = ~0u, used = 0;   // the open kind-2 operation, entries its tables take
+    std::vector<PhaseTable> tabs;     // the open stretch of diagonal gates
+    auto flush = [&] {
+        const std::vector<Cluster> cl = cluster_tables(tabs, pos);
+        for (size_t c = 0; c < cl.size();) {
+            // a run: tables that fit the area together
+            const size_t first_gate = bp->gates.size();
+            std::vector<BlkGate> run;
+            uint32_t end = used;
+            bool fresh = build == ~0u;
+            for (; c < cl.size() && run.size() < kBlkRunMax; ++c) {
+                const uint32_t sz = 1u << cl[c].bits.size(), at = (end + sz - 1) & ~(sz - 1);
+                if ((at + sz) * ab > kBlkAreaBytes) {
+                    if (!run.empty()) break;
+                    fresh = true;   // the area starts anew
+                    end = 0;
+                    --c;
+                    continue;
+                }
+                BlkGate g;
+                std::memset(&g, 0, sizeof g);
+                g.k = (int)cl[c].bits.size();
+                for (int i = 0; i < g.k; ++i) g.tpos[i] = cl[c].bits[i];
+                g.lds = at;
+                end = at + sz;
+                g.ent = (uint32_t)bp->ent.size();
+                for (uint32_t y = 0; y < (1u << tb); y += (uint32_t)nt) {
+                    uint32_t j = 0;
+                    for (int i = 0; i < g.k; ++i) j |= ((y >> g.tpos[i]) & 1u) << i;
+                    bp->ent.push_back(BlkEnt{j, 0});
+                }
+                g.m0 = (uint32_t)bp->members.size();
+                for (const PhaseTable *t : cl[c].gates) {
+                    BlkMember m;
+                    std::memset(&m, 0, sizeof m);
+                    m.k = t->k;
+                    m.tab = bp->tabs.size();
+                    for (int i = 0; i < t->k; ++i) {
+                        m.q[i] = t->q[i];
+                        m.src[i] = pos[t->q[i]] < 0 ? -1
+                            : (int)(std::lower_bound(cl[c].bits.begin(), cl[c].bits.end(), pos[t->q[i]]) - cl[c].bits.begin());
+                    }
+                    for (const cplx &z : t->ph) bp->tabs.push_back(z.real()), bp->tabs.push_back(z.imag());
+                    bp->members.push_back(m);
+                }
+                g.m1 = (uint32_t)bp->members.size();
+                run.push_back(g);
+            }
+            if (fresh) {
+                build = (uint32_t)first_gate;
+                BlkGate g;
+                std::memset(&g, 0, sizeof g);
+                g.kind = 2;
+                bp->gates.push_back(g);
+            }
+            used = end;
+            run[0].run = (int)run.size();
+            bp->gates.insert(bp->gates.end(), run.begin(), run.end());
+            s.lds_tabs = std::max(s.lds_tabs, (uint32_t)(used * ab));
+        }
+        tabs.clear();
+    };
+    for (size_t i : cur) {
+        if (P[i].d > 0) {
+            flush();
+            bp->gates.push_back(make_gate(P[i], dt, tb, w, s.qh, s.nh, off[i], &bp->ent));
+            continue;
+        }
+        // neighbours are multiplied here while their union fits a
+        // table of the host's size, which leaves fewer to build with
+        PhaseTable t = phase_table(P[i]);
+        if (tabs.empty() || !merge_tables(&tabs.back(), t, kRunMaxQ)) tabs.push_back(std::move(t));
+    }
+    flush();
+    // the first tables are built at the start of the tile (nothing
+    // reads the area before), and every build lists its units
+    if (build != ~0u) {
+        for (uint32_t gi = s.g0; gi < bp->gates.size(); ++gi)
+            if (bp->gates[gi].kind == 2) {
+                std::rotate(bp->gates.begin() + s.g0, bp->gates.begin() + gi, bp->gates.begin() + gi + 1);
+                break;
+            }
+    }
+    s.g1 = (uint32_t)bp->gates.size();
+    for (uint32_t gi = s.g0; gi < s.g1; ++gi) {
+        if (bp->gates[gi].kind != 2) continue;
+        bp->gates[gi].ent = (uint32_t)bp->ent.size();
+        for (uint32_t gj = gi + 1; gj < s.g1 && bp->gates[gj].kind != 2; ++gj)
+            if (bp->gates[gj].kind == 0)
+                for (uint32_t sl = 0; sl * 64 < (1u << bp->gates[gj].k); ++sl) bp->ent.push_back(BlkEnt{gj, sl});
+        bp->gates[gi].nent = (uint32_t)bp->ent.size() - bp->gates[gi].ent;
+    }
+    s.nt = nt;
+    s.lds_tabs = (s.lds_tabs + 15) & ~15u;
+    for (uint32_t gi = s.g0; gi < s.g1; ++gi) {
+        BlkGate &g = bp->gates[gi];
+        if (g.kind != 1 || g.d < 4) continue;
+        g.lds = s.lds_mats / (uint32_t)ab;
+        s.lds_mats += (uint32_t)((size_t)__builtin_popcount(g.amask) * ab << (2 * g.d));
+    }
+    bp->passes.push_back(ps);
+}
+
 cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
     const int tb = tuning().blocked_tile_bits[dt];
     if (((size_t)1 << tb) * amp_bytes(dt) > (64u << 10))
@@ -204,7 +334,6 @@ cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
     const int n = f.n;
     const std::vector<PassPlan> &P = f.plans;
     const std::vector<size_t> off = plan_offsets(P, dt);
-    const size_t ab = amp_bytes(dt);
     std::vector<size_t> cur;   // non-identity gates of the open segment
     size_t first = 0;
     uint64_t need = 0;
@@ -214,116 +343,7 @@ cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
             ps.first = first, ps.count = end - first, ps.gate = cur[0];
             bp->passes.push_back(ps);
         } else if (cur.size() > 1) {
-            int w = tb;
-            window_of(need, tb, &w);
-            BlockedPlan::Pass ps;
-            ps.first = first, ps.count = end - first, ps.segment = true;
-            BlkSeg &s = ps.seg;
-            s.tb = tb, s.w = w, s.nh = 0;
-            s.ntiles = 1ull << (n - tb);
-            for (int q = w; q < n; ++q)
-                if ((need >> q) & 1u) {
-                    s.qh[s.nh] = q;
-                    s.hlowmask[s.nh] = (1ull << q) - 1;
-                    ++s.nh;
-                }
-            s.g0 = (uint32_t)bp->gates.size();
-            int pos[64];
-            for (int q = 0; q < n; ++q) pos[q] = q < w ? q : -1;
-            for (int i = 0; i < s.nh; ++i) pos[s.qh[i]] = w + i;
-            uint32_t build = ~0u, used = 0;   // the open kind-2 operation, entries its tables take
-            std::vector<PhaseTable> tabs;     // the open stretch of diagonal gates
-            auto flush = [&] {
-                const std::vector<Cluster> cl = cluster_tables(tabs, pos);
-                for (size_t c = 0; c < cl.size();) {
-                    // a run: tables that fit the area together
-                    const size_t first_gate = bp->gates.size();
-                    std::vector<BlkGate> run;
-                    uint32_t end = used;
-                    bool fresh = build == ~0u;
-                    for (; c < cl.size() && run.size() < kBlkRunMax; ++c) {
-                        const uint32_t sz = 1u << cl[c].bits.size(), at = (end + sz - 1) & ~(sz - 1);
-                        if ((at + sz) * ab > kBlkAreaBytes) {
-                            if (!run.empty()) break;
-                            fresh = true;   // the area starts anew
-                            end = 0;
-                            --c;
-                            continue;
-                        }
-                        BlkGate g;
-                        std::memset(&g, 0, sizeof g);
-                        g.k = (int)cl[c].bits.size();
-                        for (int i = 0; i < g.k; ++i) g.tpos[i] = cl[c].bits[i];
-                        g.lds = at;
-                        end = at + sz;
-                        g.ent = (uint32_t)bp->ent.size();
-                        for (uint32_t y = 0; y < (1u << tb); y += (uint32_t)bp->nt) {
-                            uint32_t j = 0;
-                            for (int i = 0; i < g.k; ++i) j |= ((y >> g.tpos[i]) & 1u) << i;
-                            bp->ent.push_back(BlkEnt{j, 0});
-                        }
-                        g.m0 = (uint32_t)bp->members.size();
-                        for (const PhaseTable *t : cl[c].gates) {
-                            BlkMember m;
-                            std::memset(&m, 0, sizeof m);
-                            m.k = t->k;
-                            m.tab = bp->tabs.size();
-                            for (int i = 0; i < t->k; ++i) {
-                                m.q[i] = t->q[i];
-                                m.src[i] = pos[t->q[i]] < 0 ? -1
-                                    : (int)(std::lower_bound(cl[c].bits.begin(), cl[c].bits.end(), pos[t->q[i]]) - cl[c].bits.begin());
-                            }
-                            for (const cplx &z : t->ph) bp->tabs.push_back(z.real()), bp->tabs.push_back(z.imag());
-                            bp->members.push_back(m);
-                        }
-                        g.m1 = (uint32_t)bp->members.size();
-                        run.push_back(g);
-                    }
-                    if (fresh) {
-                        build = (uint32_t)first_gate;
-                        BlkGate g;
-                        std::memset(&g, 0, sizeof g);
-                        g.kind = 2;
-                        bp->gates.push_back(g);
-                    }
-                    used = end;
-                    run[0].run = (int)run.size();
-                    bp->gates.insert(bp->gates.end(), run.begin(), run.end());
-                    s.lds_tabs = std::max(s.lds_tabs, (uint32_t)(used * ab));
-                }
-                tabs.clear();
-            };
-            for (size_t i : cur) {
-                if (P[i].d > 0) {
-                    flush();
-                    bp->gates.push_back(make_gate(P[i], dt, tb, w, s.qh, s.nh, off[i], &bp->ent));
-                    continue;
-                }
-                // neighbours are multiplied here while their union fits a
-                // table of the host's size, which leaves fewer to build with
-                PhaseTable t = phase_table(P[i]);
-                if (tabs.empty() || !merge_tables(&tabs.back(), t, kRunMaxQ)) tabs.push_back(std::move(t));
-            }
-            flush();
-            // the first tables are built at the start of the tile (nothing
-            // reads the area before), and every build lists its units
-            if (build != ~0u) {
-                for (uint32_t gi = s.g0; gi < bp->gates.size(); ++gi)
-                    if (bp->gates[gi].kind == 2) {
-                        std::rotate(bp->gates.begin() + s.g0, bp->gates.begin() + gi, bp->gates.begin() + gi + 1);
-                        break;
-                    }
-            }
-            s.g1 = (uint32_t)bp->gates.size();
-            for (uint32_t gi = s.g0; gi < s.g1; ++gi) {
-                if (bp->gates[gi].kind != 2) continue;
-                bp->gates[gi].ent = (uint32_t)bp->ent.size();
-                for (uint32_t gj = gi + 1; gj < s.g1 && bp->gates[gj].kind != 2; ++gj)
-                    if (bp->gates[gj].kind == 0)
-                        for (uint32_t sl = 0; sl * 64 < (1u << bp->gates[gj].k); ++sl) bp->ent.push_back(BlkEnt{gj, sl});
-                bp->gates[gi].nent = (uint32_t)bp->ent.size() - bp->gates[gi].ent;
-            }
-            bp->passes.push_back(ps);
+            emit_segment(bp, P, off, n, dt, cur, first, end - first, need);
         }
         cur.clear();
         need = 0;
@@ -356,6 +376,32 @@ cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
     return CAST_OK;
 }
 
+cast_status upload_plan_tables(BlockedPlan *bp, cast_dtype dt) {
+    if (bp->dev || bp->gates.empty()) return CAST_OK;
+    auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
+    bp->dev_ent = up(bp->gates.size() * sizeof(BlkGate));
+    bp->dev_mem = bp->dev_ent + up(bp->ent.size() * sizeof(BlkEnt));
+    bp->dev_tabs = bp->dev_mem + up(bp->members.size() * sizeof(BlkMember));
+    const size_t rsz = amp_bytes(dt) / 2, bytes = bp->dev_tabs + std::max<size_t>(bp->tabs.size(), 4) * rsz;
+    std::vector<char> h(bytes, 0);
+    std::memcpy(h.data(), bp->gates.data(), bp->gates.size() * sizeof(BlkGate));
+    if (!bp->ent.empty()) std::memcpy(h.data() + bp->dev_ent, bp->ent.data(), bp->ent.size() * sizeof(BlkEnt));
+    if (!bp->members.empty())
+        std::memcpy(h.data() + bp->dev_mem, bp->members.data(), bp->members.size() * sizeof(BlkMember));
+    for (size_t i = 0; i < bp->tabs.size(); ++i) {
+        if (dt == CAST_C128) ((double *)(h.data() + bp->dev_tabs))[i] = bp->tabs[i];
+        else ((float *)(h.data() + bp->dev_tabs))[i] = (float)bp->tabs[i];
+    }
+    if (cast_status rc = dev_alloc(&bp->dev, bytes)) return rc;
+    const hipError_t e = hipMemcpy(bp->dev, h.data(), bytes, hipMemcpyHostToDevice);
+    if (e != hipSuccess) {
+        dev_free(bp->dev);
+        bp->dev = nullptr;
+        return fail(CAST_EHIP, std::string("blocked gate table upload: ") + hipGetErrorString(e));
+    }
+    return CAST_OK;
+}
+
 // The blocked grouping of a fused list for dtype dt (built on first use,
 // rebuilt when the tile size knob has changed).  `device`: also upload the
 // list's matrices and the grouping's gate table.
@@ -376,45 +422,24 @@ cast_status prepare(const cast_fused *fc, int n, cast_dtype dt, bool device, Blo
         if (!f->dev[dt].ptr && !f->plans.empty()) {
             if (cast_status rc = upload_plans(f->plans, dt, &f->dev[dt], &f->dev_off[dt])) return rc;
         }
-        if (!bp->dev && !bp->gates.empty()) {
-            auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
-            bp->dev_ent = up(bp->gates.size() * sizeof(BlkGate));
-            bp->dev_mem = bp->dev_ent + up(bp->ent.size() * sizeof(BlkEnt));
-            bp->dev_tabs = bp->dev_mem + up(bp->members.size() * sizeof(BlkMember));
-            const size_t rsz = amp_bytes(dt) / 2, bytes = bp->dev_tabs + std::max<size_t>(bp->tabs.size(), 4) * rsz;
-            std::vector<char> h(bytes, 0);
-            std::memcpy(h.data(), bp->gates.data(), bp->gates.size() * sizeof(BlkGate));
-            if (!bp->ent.empty()) std::memcpy(h.data() + bp->dev_ent, bp->ent.data(), bp->ent.size() * sizeof(BlkEnt));
-            if (!bp->members.empty())
-                std::memcpy(h.data() + bp->dev_mem, bp->members.data(), bp->members.size() * sizeof(BlkMember));
-            for (size_t i = 0; i < bp->tabs.size(); ++i) {
-                if (dt == CAST_C128) ((double *)(h.data() + bp->dev_tabs))[i] = bp->tabs[i];
-                else ((float *)(h.data() + bp->dev_tabs))[i] = (float)bp->tabs[i];
-            }
-            if (cast_status rc = dev_alloc(&bp->dev, bytes)) return rc;
-            const hipError_t e = hipMemcpy(bp->dev, h.data(), bytes, hipMemcpyHostToDevice);
-            if (e != hipSuccess) {
-                dev_free(bp->dev);
-                bp->dev = nullptr;
-                return fail(CAST_EHIP, std::string("blocked gate table upload: ") + hipGetErrorString(e));
-            }
-        }
+        if (cast_status rc = upload_plan_tables(bp, dt)) return rc;
     }
     *out = bp;
     return CAST_OK;
 }
 
+cast_status launch_segment(cast_sv *sv, const cast_fused *f, const BlockedPlan &bp, const BlkSeg &seg) {
+    const char *dev = static_cast<const char *>(bp.dev);
+    const BlkPtrs ptrs{f->dev[sv->dt].ptr, dev + bp.dev_tabs, (const BlkGate *)dev, (const BlkEnt *)(dev + bp.dev_ent),
+                       (const BlkMember *)(dev + bp.dev_mem)};
+    return launch_blocked(sv->data, sv->dt, ptrs, seg, sv->stream);
+}
+
 cast_status launch(cast_sv *sv, const cast_fused *f, const BlockedPlan &bp, size_t i) {
     const BlockedPlan::Pass &ps = bp.passes[i];
-    const void *mats = f->dev[sv->dt].ptr;
-    if (ps.segment) {
-        const char *dev = static_cast<const char *>(bp.dev);
-        const BlkPtrs ptrs{mats, dev + bp.dev_tabs, (const BlkGate *)dev, (const BlkEnt *)(dev + bp.dev_ent),
-                           (const BlkMember *)(dev + bp.dev_mem)};
-        return launch_blocked(sv->data, sv->dt, ptrs, ps.seg, bp.nt, sv->stream);
-    }
+    if (ps.segment) return launch_segment(sv, f, bp, ps.seg);
     const size_t rsz = sv->dt == CAST_C128 ? 8 : 4;
-    const void *dm = (const char *)mats + f->dev_off[sv->dt][ps.gate] * rsz;
+    const void *dm = (const char *)f->dev[sv->dt].ptr + f->dev_off[sv->dt][ps.gate] * rsz;
     return launch_pass(sv->data, sv->n, sv->dt, f->plans[ps.gate], dm, sv->stream);
 }
 
@@ -423,7 +448,160 @@ cast_status check(const cast_sv *sv) {
     return CAST_OK;
 }
 
+// ------------------------------------------------------------ tile groups
+// apply_circuit's launches: consecutive passes of the schedule whose mixed
+// qubits fit one LDS tile share a launch (and one read and write of the
+// state) where that is predicted to be faster.  Times in microseconds:
+//   a pass    3.5 + bytes at 5.4 TB/s, or its products at 60 / 120 TFLOP/s
+//             (launch-bound passes of small states take 3.6 to 5.5);
+//   a group   4 + the longer of the state's read and write at 4.9 TB/s and
+//             its operations, + 0.3 of the shorter.  An operation's time on a
+//             tile of 2^12 amplitudes with two workgroups per compute unit:
+//             table 0.5, d <= 2 1.8, d = 3 2.1, d = 4 / 5 3.7 / 7.4
+//             (complex64: half, matrix cores), from segments at 26 and 27
+//             qubits; at least 0.8 for its barrier and loads.
+struct Span {
+    size_t a, b;          // schedule passes [a, b)
+    uint64_t need;
+    bool group;
+};
+
+double pass_us(const Schedule &sc, const SchedPass &sp, const std::vector<PassPlan> &P) {
+    const double ab = (double)amp_bytes(sc.dt);
+    if (sp.kind < 0) return 0.0;
+    if (sp.kind == 6) return 3.5 + 2 * ab * sp.active_amps / 5.4e6;
+    const PassPlan &p = P[sp.first];
+    const double amps = std::ldexp((double)p.blk.size(), sc.n - p.k + p.d);
+    const double mem = 2 * ab * amps / 5.4e6, fl = p.d >= 4 ? 8 * amps * (1 << p.d) / (sc.dt == CAST_C128 ? 60e6 : 120e6) : 0;
+    return 3.5 + std::max(mem, fl);
+}
+
+double group_us(const Schedule &sc, const std::vector<PassPlan> &P, size_t a, size_t b, int tb) {
+    const double scale = std::ldexp(1.0, tb - 12), tiles = std::ldexp(1.0, sc.n - tb);
+    // one workgroup per compute unit runs an operation twice as fast as two
+    const double share = tiles <= 256 ? 0.5 : 1.0;
+    double ops = 0;
+    for (size_t i = a; i < b; ++i) {
+        const SchedPass &sp = sc.passes[i];
+        if (sp.kind < 0) continue;
+        const int d = sp.kind == 6 ? 0 : P[sp.first].d;
+        double t = d == 0 ? 0.5 * std::max<size_t>(1, sp.tabs.size()) : d <= 2 ? 1.8 : d == 3 ? 2.1 : d == 4 ? 3.7 : 7.4;
+        if (d >= 4 && sc.dt == CAST_C64) t *= 0.5;
+        ops += std::max(0.8, t * scale * share);
+    }
+    ops *= std::max(1.0, tiles / 512);
+    const double mem = 2 * std::ldexp((double)amp_bytes(sc.dt), sc.n) / 4.9e6;
+    return 4.0 + std::max(mem, ops) + 0.3 * std::min(mem, ops);
+}
+
+// Groups the schedule with tiles of 2^tb amplitudes; *us: predicted time.
+std::vector<Span> plan_groups(const Schedule &sc, const std::vector<PassPlan> &P, int tb, double *us) {
+    std::vector<Span> out;
+    *us = 0;
+    size_t a = 0, mats = 0;   // mats: LDS bytes of the open group's dense blocks
+    uint64_t need = 0;
+    auto close = [&](size_t b) {
+        mats = 0;
+        if (a >= b) return;
+        double sep = 0;
+        size_t live = 0;
+        for (size_t i = a; i < b; ++i) sep += pass_us(sc, sc.passes[i], P), live += sc.passes[i].kind >= 0;
+        const double grp = group_us(sc, P, a, b, tb);
+        if (live > 1 && grp < sep) {
+            out.push_back(Span{a, b, need, true});
+            *us += grp;
+        } else {
+            for (size_t i = a; i < b; ++i) out.push_back(Span{i, i + 1, 0, false});
+            *us += sep;
+        }
+    };
+    for (size_t i = 0; i < sc.passes.size(); ++i) {
+        const SchedPass &sp = sc.passes[i];
+        if (sp.kind < 0 || sp.kind == 6 || P[sp.first].d == 0) continue;
+        const PassPlan &p = P[sp.first];
+        const uint64_t span = span_qubits(p);
+        int w = 0;
+        bool fits = p.d <= kGroupMaxD && window_of(span, tb, &w);
+        const size_t mb = p.d >= 4 ? (p.blk.size() * amp_bytes(sc.dt)) << (2 * p.d) : 0;
+        // sixteen columns on tile bits that are no targets
+        if (fits && p.d >= 4) fits = tb - p.k >= 4 && mb <= kBlkMatBytes;
+        if (!fits) {
+            close(i);
+            a = i;
+            need = 0;
+            close(i + 1);
+            a = i + 1;
+            continue;
+        }
+        if (!window_of(need | span, tb, &w) || mats + mb > kBlkMatBytes) {
+            close(i);
+            a = i;
+            need = 0;
+        }
+        need |= span;
+        mats += mb;
+    }
+    close(sc.passes.size());
+    return out;
+}
+
 }  // namespace
+
+cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, BlockedPlan **out) {
+    BlockedPlan *&bp = f->groups[dt];
+    const int knob = tuning().blocked_tile_bits[dt];
+    if (bp && (bp->knob_tb != knob || bp->nt != blocked_threads(dt, bp->tb))) {
+        blocked_free(bp);
+        bp = nullptr;
+    }
+    if (!bp) {
+        const std::vector<PassPlan> &P = f->plans;
+        std::vector<Span> best;
+        int best_tb = 0;
+        double best_us = 0;
+        for (int tb = std::min(8, std::min(knob, sc.n)); tb <= std::min(knob, sc.n); ++tb) {
+            if (tb < 8) continue;   // 256 threads, one amplitude each
+            double us;
+            std::vector<Span> g = plan_groups(sc, P, tb, &us);
+            if (!best_tb || us <= best_us) best = std::move(g), best_tb = tb, best_us = us;
+        }
+        auto *p = new BlockedPlan;
+        p->tb = best_tb;
+        p->knob_tb = knob;
+        p->nt = blocked_threads(dt, best_tb);
+        if (!best_tb)
+            for (size_t i = 0; i < sc.passes.size(); ++i) best.push_back(Span{i, i + 1, 0, false});
+        const std::vector<size_t> off = plan_offsets(P, dt);
+        for (const Span &g : best) {
+            if (!g.group) {
+                BlockedPlan::Pass ps;
+                ps.gate = g.a;
+                p->passes.push_back(ps);
+                continue;
+            }
+            const size_t first = sc.passes[g.a].first, end = sc.passes[g.b - 1].first + sc.passes[g.b - 1].count;
+            std::vector<size_t> cur;
+            for (size_t i = first; i < end; ++i)
+                if (!P[i].identity()) cur.push_back(i);
+            emit_segment(p, P, off, sc.n, dt, cur, first, end - first, g.need);
+        }
+        bp = p;
+    }
+    if (cast_status rc = upload_plan_tables(bp, dt)) return rc;
+    *out = bp;
+    return CAST_OK;
+}
+
+size_t group_count(const BlockedPlan &bp) { return bp.passes.size(); }
+
+cast_status launch_group(cast_sv *sv, const cast_fused *f, const BlockedPlan &bp, size_t i, size_t *pass) {
+    const BlockedPlan::Pass &ps = bp.passes[i];
+    *pass = ps.gate;
+    if (!ps.segment) return CAST_OK;
+    *pass = (size_t)-1;
+    return launch_segment(sv, f, bp, ps.seg);
+}
+
 }  // namespace cast
 
 using namespace cast;

@@ -9,6 +9,7 @@
 
 #include "blocked.hpp"
 #include "internal.hpp"
+#include "mfma.hpp"
 
 namespace cast {
 namespace {
@@ -201,7 +202,103 @@ __device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, CPtr<BlkG
     }
 }
 
-template <typename R, int NT>
+// Dense blocks (d = 4, 5) on the matrix cores: a unit is sixteen cosets of one
+// block, one per column, and the wave forms all 2^D output rows as 16 x 16
+// tiles (four real products per complex one, as in the single-gate kernels).
+// Inputs and matrix (transposed, in LDS for the whole launch) are read one
+// k-step ahead.  The outputs are written after the last input is read, so the
+// update is in place.
+template <int D, typename R, int S, int NT>
+__device__ __forceinline__ void mfma_in_tile(typename Cx<R>::T *tile, CPtr<BlkGate> g, CPtr<BlkEnt> ent,
+                                             const typename Cx<R>::T *mt, uint64_t tbase) {
+    using V = typename Cx<R>::T;
+    using M = Mfma<R>;
+    constexpr int N = 1 << D, T = N / 16, K = N / 4;
+    uint32_t sp[D];
+#pragma unroll
+    for (int i = 0; i < D; ++i) sp[i] = at<S>(g->span[i]);
+    auto off = [&](int c) {   // bits 2.. of a row or column: wave-uniform
+        uint32_t o = 0;
+#pragma unroll
+        for (int i = 0; i < D; ++i)
+            if ((c >> i) & 1) o ^= sp[i];
+        return o;
+    };
+    uint32_t uuni = 0;
+    for (int q = 0; q < g->k; ++q)
+        if (g->tpos[q] < 0 && ((tbase >> g->q[q]) & 1u)) uuni ^= g->colv[q];
+    const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t j = lane & 15, kk = lane >> 4;
+    const uint32_t nq = 1u << g->nuni, amask = g->amask;
+    const uint64_t lanepos = g->lanepos;
+    uint32_t al = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+        if ((j >> i) & 1u) al ^= at<S>(1u << ((lanepos >> (8 * i)) & 255u));
+    // k-row 4 s + kk of the inputs; result rows M::row(lane, v) + 16 t
+    uint32_t ain = al, aout = al;
+#pragma unroll
+    for (int i = 0; i < 2; ++i)
+        if ((kk >> i) & 1u) {
+            ain ^= sp[i];
+            aout ^= sizeof(R) == 8 ? sp[i] : sp[2 + i];
+        }
+    const V *m0 = mt + g->lds + kk * N + j;   // column kk, row j
+    CPtr<BlkEnt> e0 = ent + g->ent;
+    for (uint32_t q = wave; q < nq; q += NT / 64) {
+        const uint32_t u = uuni ^ e0[q].u, blk = u >> D;
+        if (!((amask >> blk) & 1u)) continue;
+        const uint32_t a0 = e0[q].a ^ off((int)(u & (N - 1)));
+        const V *m = m0 + (uint32_t)__popc(amask & ((1u << blk) - 1)) * (N * N);
+        typename M::acc cr[T], ci[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) cr[t][v] = ci[t][v] = 0;
+        V x = tile[a0 ^ ain], a[T];
+#pragma unroll
+        for (int t = 0; t < T; ++t) a[t] = m[16 * t];
+#pragma unroll
+        for (int s = 0; s < K; ++s) {
+            V xn = x, an[T];
+            if (s + 1 < K) {
+                xn = tile[a0 ^ ain ^ off(4 * (s + 1))];
+#pragma unroll
+                for (int t = 0; t < T; ++t) an[t] = m[4 * (s + 1) * N + 16 * t];
+            }
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                cr[t] = M::mma(a[t].x, x.x, cr[t]);
+                ci[t] = M::mma(a[t].x, x.y, ci[t]);
+            }
+#pragma unroll
+            for (int t = 0; t < T; ++t) {
+                cr[t] = M::mma(-a[t].y, x.y, cr[t]);
+                ci[t] = M::mma(a[t].y, x.x, ci[t]);
+            }
+            x = xn;
+#pragma unroll
+            for (int t = 0; t < T; ++t)
+                if (s + 1 < K) a[t] = an[t];
+        }
+#pragma unroll
+        for (int t = 0; t < T; ++t)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) {
+                V y;
+                y.x = cr[t][v];
+                y.y = ci[t][v];
+                tile[a0 ^ aout ^ off(16 * t + (sizeof(R) == 8 ? 4 * v : v))] = y;
+            }
+    }
+}
+
+// MF: the segment has dense blocks for the matrix cores.  One workgroup of
+// 1024 threads per compute unit then holds the tile and every such block's
+// matrix in LDS.  (Two workgroups that read the matrices from global memory
+// ran in step, both loading, then both multiplying: 24 passes of 4- and
+// 5-qubit gates on 26 qubits, complex64, 5.2 ms.)
+template <typename R, int NT, bool MF>
 __global__ void __launch_bounds__(NT, 4) k_blocked(R *__restrict__ psi_r, const R *__restrict__ mats_g,
                                                 const R *__restrict__ tabs, const BlkGate *__restrict__ gates_g,
                                                 const BlkEnt *__restrict__ ent_g,
@@ -217,6 +314,19 @@ __global__ void __launch_bounds__(NT, 4) k_blocked(R *__restrict__ psi_r, const 
     CPtr<BlkEnt> ent = cptr(ent_g);
     CPtr<BlkMember> members = cptr(members_g);
     CPtr<R> mats = cptr(mats_g);
+    V *mt = area + s.lds_tabs / sizeof(V);
+    if (MF) {
+        // dense blocks transposed: entry (i, c) at c * 2^d + i
+        for (uint32_t gi = s.g0; gi < s.g1; ++gi) {
+            CPtr<BlkGate> g = gates + gi;
+            if (g->kind != 1 || g->d < 4) continue;
+            const V *src = reinterpret_cast<const V *>(mats_g + g->mat);
+            const int d = g->d;
+            const uint32_t n2 = (1u << d) - 1, count = (uint32_t)__popc(g->amask) << (2 * d);
+            for (uint32_t e = threadIdx.x; e < count; e += NT)
+                mt[g->lds + ((e >> (2 * d)) << (2 * d)) + ((e & n2) << d) + ((e >> d) & n2)] = src[e];
+        }
+    }
     u4 *p16 = reinterpret_cast<u4 *>(psi_r);
     const uint32_t chunks = tile_amps >> S;
     const uint64_t glane = expand(threadIdx.x << S, s) >> S;
@@ -273,6 +383,8 @@ __global__ void __launch_bounds__(NT, 4) k_blocked(R *__restrict__ psi_r, const 
                     switch (g->d) {
                         case 1: block_in_tile<1, R, S, NT>(tile, g, ent, mats, tbase); break;
                         case 2: block_in_tile<2, R, S, NT>(tile, g, ent, mats, tbase); break;
+                        case 4: if (MF) mfma_in_tile<4, R, S, NT>(tile, g, ent, mt, tbase); break;
+                        case 5: if (MF) mfma_in_tile<5, R, S, NT>(tile, g, ent, mt, tbase); break;
                         default: block_in_tile<3, R, S, NT>(tile, g, ent, mats, tbase); break;
                     }
                 }
@@ -293,23 +405,24 @@ __global__ void __launch_bounds__(NT, 4) k_blocked(R *__restrict__ psi_r, const 
     }
 }
 
-template <typename R, int NT>
+template <typename R, int NT, bool MF>
 hipError_t launch_nt(R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, size_t lds, hipStream_t stream) {
-    static const hipError_t attr = hipFuncSetAttribute((const void *)k_blocked<R, NT>,
-                                                       hipFuncAttributeMaxDynamicSharedMemorySize, 128 << 10);
+    static const hipError_t attr = hipFuncSetAttribute((const void *)k_blocked<R, NT, MF>,
+                                                       hipFuncAttributeMaxDynamicSharedMemorySize, kBlkMaxLds);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((k_blocked<R, NT>), dim3(grid), dim3(NT), lds, stream, psi, (const R *)p.mats, (const R *)p.tabs,
-                       p.gates, p.ent, p.members, s);
+    hipLaunchKernelGGL((k_blocked<R, NT, MF>), dim3(grid), dim3(NT), lds, stream, psi, (const R *)p.mats,
+                       (const R *)p.tabs, p.gates, p.ent, p.members, s);
     return hipGetLastError();
 }
 
 template <typename R>
-hipError_t launch_r(int nt, R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, size_t lds,
+hipError_t launch_r(R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, size_t lds,
                     hipStream_t stream) {
-    switch (nt) {
-        case 256: return launch_nt<R, 256>(psi, p, s, grid, lds, stream);
-        case 512: return launch_nt<R, 512>(psi, p, s, grid, lds, stream);
-        default: return launch_nt<R, 1024>(psi, p, s, grid, lds, stream);
+    if (s.lds_mats) return launch_nt<R, kGroupThreads, true>(psi, p, s, grid, lds, stream);
+    switch (s.nt) {
+        case 256: return launch_nt<R, 256, false>(psi, p, s, grid, lds, stream);
+        case 512: return launch_nt<R, 512, false>(psi, p, s, grid, lds, stream);
+        default: return launch_nt<R, 1024, false>(psi, p, s, grid, lds, stream);
     }
 }
 
@@ -321,16 +434,17 @@ int blocked_threads(cast_dtype dt, int tb) {
     return nt;
 }
 
-cast_status launch_blocked(void *psi, cast_dtype dt, const BlkPtrs &p, const BlkSeg &s, int nt, hipStream_t stream) {
-    const size_t lds = ((size_t)1 << s.tb) * amp_bytes(dt) + s.lds_tabs;
-    if (lds > (128u << 10)) return fail(CAST_EUNSUPPORTED, "blocked tile and gate areas exceed 128 KiB of LDS");
-    // two workgroups per compute unit (their LDS allows no more), each looping
-    // over tiles with the next one's loads in flight
+cast_status launch_blocked(void *psi, cast_dtype dt, const BlkPtrs &p, const BlkSeg &s, hipStream_t stream) {
+    const size_t lds = ((size_t)1 << s.tb) * amp_bytes(dt) + s.lds_tabs + s.lds_mats;
+    if (lds > kBlkMaxLds) return fail(CAST_EUNSUPPORTED, "tile and gate tables exceed a compute unit's LDS");
+    // two workgroups per compute unit (one with matrices in LDS; their LDS
+    // allows no more), each looping over tiles with the next one's loads in
+    // flight
     uint64_t grid = s.ntiles;
-    const uint64_t cap = std::min<uint64_t>(tuning().max_grid[dt], 512);
+    const uint64_t cap = std::min<uint64_t>(tuning().max_grid[dt], s.lds_mats ? 256 : 512);
     if (grid > cap) grid = cap;
-    const hipError_t e = dt == CAST_C128 ? launch_r<double>(nt, (double *)psi, p, s, (uint32_t)grid, lds, stream)
-                                         : launch_r<float>(nt, (float *)psi, p, s, (uint32_t)grid, lds, stream);
+    const hipError_t e = dt == CAST_C128 ? launch_r<double>((double *)psi, p, s, (uint32_t)grid, lds, stream)
+                                         : launch_r<float>((float *)psi, p, s, (uint32_t)grid, lds, stream);
     if (e != hipSuccess) return fail(CAST_EHIP, std::string("blocked pass launch: ") + hipGetErrorString(e));
     return CAST_OK;
 }

@@ -22,7 +22,8 @@
 namespace cast {
 
 constexpr int kBlkMaxHigh = 10;    // tile qubits above the window
-constexpr int kBlkMaxD = 3;        // largest block dimension applied inside a tile
+constexpr int kBlkMaxD = 3;        // largest block dimension of apply_circuit_blocked's segments
+constexpr int kGroupMaxD = 5;      // and of apply_circuit's tile groups (matrix cores from 4)
 constexpr int kBlkMinWindow = 4;   // smallest window: runs of >= 16 amplitudes
 
 // One operation inside a tile.  Read at wave-uniform indices: 32- and 64-bit
@@ -44,7 +45,7 @@ struct BlkGate {
     int tpos[8];             // tile bit of each target, -1 when the target is outside the tile
     // blocks
     uint32_t colv[6];        // virtual coordinates of local index bit s (the columns of L^-1)
-    uint32_t span[kBlkMaxD]; // tile offset of virtual basis vector i < d
+    uint32_t span[kGroupMaxD]; // tile offset of virtual basis vector i < d
     uint32_t amask;          // bit b: block b is not the identity (its matrices lie in block order)
     uint32_t nlane, nuni;    // coset bits given by the lane, and by the wave and iteration
     uint64_t lanepos;        // tile bit of lane bit i (8 bits each)
@@ -53,9 +54,11 @@ struct BlkGate {
     // uniform local index of each iteration over the tile; kind 2, its work
     // units
     uint32_t ent, nent;
+    // first entry in LDS: phase table, in the table area, a multiple of its
+    // 2^k entries; blocks of d >= 4, in the matrices
+    uint32_t lds;
     // phase table
     int run;                 // tables applied together from here (0 inside a run)
-    uint32_t lds;            // its first entry in the table area, a multiple of its 2^k entries
     uint32_t m0, m1;         // its gates [m0, m1) of the member table
 };
 struct BlkEnt {
@@ -74,6 +77,10 @@ struct BlkMember {           // a diagonal gate of a phase table
 // of them take a QFT run's targets with all other bits of a tile.
 constexpr uint32_t kBlkAreaBytes = 16u << 10;
 constexpr int kBlkTabBits = 7;
+// With dense blocks: one workgroup of kGroupThreads and the matrices besides.
+constexpr uint32_t kBlkMaxLds = 160u << 10;
+constexpr uint32_t kBlkMatBytes = kBlkMaxLds - (64u << 10) - kBlkAreaBytes;
+constexpr int kGroupThreads = 1024;
 constexpr uint32_t kBlkRunMax = 8;
 
 struct BlkSeg {              // kernel arguments of one segment pass
@@ -83,6 +90,8 @@ struct BlkSeg {              // kernel arguments of one segment pass
     int qh[kBlkMaxHigh];     // high tile qubits, ascending
     uint32_t g0, g1;         // operations [g0, g1) of the gate table
     uint32_t lds_tabs;       // bytes of the table area
+    uint32_t lds_mats;       // bytes of matrices (blocks of d >= 4; 0: none)
+    int nt;                  // workgroup size
 };
 
 struct BlkPtrs {             // device tables of a plan
@@ -95,6 +104,6 @@ struct BlkPtrs {             // device tables of a plan
 // Workgroup size of a plan with tiles of 2^tb amplitudes (the knob, at most
 // one thread per amplitude).
 int blocked_threads(cast_dtype dt, int tb);
-cast_status launch_blocked(void *psi, cast_dtype dt, const BlkPtrs &p, const BlkSeg &s, int nt, hipStream_t stream);
+cast_status launch_blocked(void *psi, cast_dtype dt, const BlkPtrs &p, const BlkSeg &s, hipStream_t stream);
 
 }  // namespace cast

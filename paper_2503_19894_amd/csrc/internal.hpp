@@ -82,6 +82,7 @@ struct Tuning {                      // launch parameters, by dtype index (CAST_
     int mfma_low_tile[3] = {0, 1, 1};  // low-target d <= 4 MFMA passes on the LDS tile when its runs are long
     int mfma_3m_min_d[3] = {0, 6, 6};  // matrix cores: three-multiplication complex product from this d (7: never)
     int blocked_tile_bits[3] = {0, 13, 12};  // cache-blocked passes: log2(amplitudes per LDS tile)
+    int tile_groups[3] = {0, 1, 1};    // apply_circuit: passes that fit one LDS tile share a launch (0: one launch per pass)
     int blocked_threads[3] = {0, 512, 512};  // cache-blocked passes: threads per workgroup (256, 512, 1024)
     // persistent batch launch: polls before a dependency wait gives up; 0
     // makes every dependency fail at once (exercises the error path)
@@ -258,6 +259,12 @@ struct cast_sv {
 namespace cast {
 struct BlockedPlan;                  // cache-blocked grouping of a fused list (blocked.cpp)
 void blocked_free(BlockedPlan *b);
+// apply_circuit's launches for a schedule of f (built on first use, cached in
+// f): launch i of group_count is either a schedule pass, which the caller
+// makes (*pass its index), or a tile group, queued here (*pass = -1).
+cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, BlockedPlan **out);
+size_t group_count(const BlockedPlan &bp);
+cast_status launch_group(cast_sv *sv, const cast_fused *f, const BlockedPlan &bp, size_t i, size_t *pass);
 struct JitModule;                    // generated kernels of a fused list (jit.cpp)
 void jit_free(JitModule *j);
 }  // namespace cast
@@ -271,6 +278,8 @@ struct cast_fused {
     std::vector<size_t> dev_off[3];
     // cache-blocked grouping, per dtype (built on first use)
     cast::BlockedPlan *blocked[3] = {nullptr, nullptr, nullptr};
+    // apply_circuit's launches for the schedule below, per dtype
+    cast::BlockedPlan *groups[3] = {nullptr, nullptr, nullptr};
     // generated kernels, per dtype (compiled on first use)
     cast::JitModule *jit[3] = {nullptr, nullptr, nullptr};
     // pass schedule of apply_circuit, per dtype (built on first use)
