@@ -8,7 +8,8 @@
 // are ever multiplied (all structural zeros are skipped) and identity blocks
 // are never loaded or stored.  Block matrices are read with wave-uniform
 // scalar loads whenever every lane of a wave works on the same block (the
-// paper's GPU kernels take the matrix by pointer, Sec. IV-A).
+// paper's GPU kernels take the matrix by pointer, Sec. IV-A).  Gates applied
+// one at a time bring matrices of up to 1 KiB in the kernel arguments.
 //
 // Two kernels:
 //  * k_direct: every target is at or above a coalescing threshold, so lanes
@@ -60,6 +61,17 @@ __device__ __forceinline__ void cmac(V &acc, R mre, R mim, const V &v) {
     acc.y = fma(mim, v.x, acc.y);
 }
 
+// The pass's matrices: device memory, or (null) the MatArg behind the
+// (pointer, pointer, argument block) of the launch.  Read-only address space,
+// so uniform reads stay scalar loads on either.
+template <typename R, typename Args>
+__device__ __forceinline__ const __attribute__((address_space(4))) R *pass_matrix(const R *mat) {
+    static_assert(sizeof(Args) % 8 == 0 && alignof(Args) == 8, "MatArg follows the argument block");
+    typedef const __attribute__((address_space(4))) R *P;
+    typedef const __attribute__((address_space(4))) char *B;
+    return mat ? (P)(uintptr_t)mat : (P)((B)__builtin_amdgcn_kernarg_segment_ptr() + 16 + sizeof(Args));
+}
+
 // ------------------------------------------------------------------ direct
 // IPT work items per thread per iteration, all loads issued before any
 // store.  NT: non-temporal hint on the state's loads and stores (the state is
@@ -109,11 +121,12 @@ __device__ __forceinline__ void direct_item(uint64_t i, uint32_t nblk, int cl, u
 }
 
 template <int D, typename R, int IPT, bool NT>
-__global__ void __launch_bounds__(256) k_direct(R *__restrict__ psi_r, const R *__restrict__ mat,
-                                                PassArgs a) {
+__global__ void __launch_bounds__(256) k_direct(R *__restrict__ psi_r, const R *__restrict__ dmat,
+                                                PassArgs a, MatArg) {
     using V = typename Amp<R>::T;
     constexpr int N = 1 << D;
     V *psi = reinterpret_cast<V *>(psi_r);
+    const auto mat = pass_matrix<R, PassArgs>(dmat);
     const uint64_t items = a.ngroups * a.nblk;
     constexpr uint64_t per_iter = 256ull * IPT;
     const uint64_t nfull = items / per_iter;
@@ -124,7 +137,7 @@ __global__ void __launch_bounds__(256) k_direct(R *__restrict__ psi_r, const R *
         const uint64_t it =
             a.rot ? (((it0 << a.rot) | (it0 >> (a.it_bits - a.rot))) & ((1ull << a.it_bits) - 1)) : it0;
         uint64_t base[IPT];
-        const R *m[IPT];
+        decltype(pass_matrix<R, PassArgs>(nullptr)) m[IPT];
         V v[IPT][N];
 #pragma unroll
         for (int u = 0; u < IPT; ++u) {
@@ -165,7 +178,7 @@ __global__ void __launch_bounds__(256) k_direct(R *__restrict__ psi_r, const R *
         uint64_t b = deposit(g, a.lowmask, a.k);
         for (int j = 0; j < a.k - D; ++j)
             if ((bid >> j) & 1u) b ^= a.off[D + j];
-        const R *mm = mat + (size_t)(D == 0 ? bid : bs) * (2 * N * N);
+        const auto mm = mat + (size_t)(D == 0 ? bid : bs) * (2 * N * N);
         V w[N];
 #pragma unroll
         for (int c = 0; c < N; ++c) w[c] = psi[b ^ off_lo<D>(a.off, c)];
@@ -205,13 +218,20 @@ __device__ __forceinline__ uint64_t xcd_spread(uint64_t it) {
 }
 
 template <typename R, int U, bool LDS_TABLE>
-__global__ void __launch_bounds__(256) k_diag(R *__restrict__ psi_r, const R *__restrict__ table, DiagArgs a) {
+__global__ void __launch_bounds__(256) k_diag(R *__restrict__ psi_r, const R *__restrict__ dmat, DiagArgs a, MatArg) {
     using V = typename Amp<R>::T;
     constexpr int S = sizeof(V) == 16 ? 0 : 1;   // log2(amplitudes per 16-byte chunk)
     constexpr int A = 1 << S;
     // phases: staged in LDS, or read straight from the (L1-resident) table
     __shared__ V tab_lds[LDS_TABLE ? 64 : 1];
-    const V *tab = LDS_TABLE ? tab_lds : reinterpret_cast<const V *>(table);
+    const auto table = pass_matrix<R, DiagArgs>(dmat);
+    auto phase = [&](uint32_t j) {
+        if (LDS_TABLE) return tab_lds[j];
+        V t;
+        t.x = table[2 * j];
+        t.y = table[2 * j + 1];
+        return t;
+    };
     if (LDS_TABLE) {
         const int D = 1 << a.k;
         for (int j = threadIdx.x; j < D; j += 256) {
@@ -271,7 +291,7 @@ __global__ void __launch_bounds__(256) k_diag(R *__restrict__ psi_r, const R *__
             for (int h = 0; h < A; ++h) {
                 const uint32_t j = ju[u] | jl[h];
                 if ((a.amask >> j) & 1u) {
-                    const V t = tab[j];
+                    const V t = phase(j);
                     const R re = v[h].x * t.x - v[h].y * t.y;
                     const R im = v[h].x * t.y + v[h].y * t.x;
                     v[h].x = re;
@@ -298,7 +318,7 @@ __global__ void __launch_bounds__(256) k_diag(R *__restrict__ psi_r, const R *__
 #pragma unroll
         for (int h = 0; h < A; ++h) {
             if ((a.amask >> js[h]) & 1u) {
-                const V t = tab[js[h]];
+                const V t = phase(js[h]);
                 const R re = v[h].x * t.x - v[h].y * t.y;
                 const R im = v[h].x * t.y + v[h].y * t.x;
                 v[h].x = re;
@@ -337,11 +357,12 @@ __device__ __forceinline__ uint64_t tile_chunk_addr(uint32_t c, uint64_t tbase, 
 // from LDS for each output row and the results go to a second LDS tile (used
 // when 2^d inputs do not fit in registers).
 template <int D, typename R, bool UNI, bool TWOBUF>
-__global__ void __launch_bounds__(256) k_tile(R *__restrict__ psi_r, const R *__restrict__ mat,
-                                              PassArgs a) {
+__global__ void __launch_bounds__(256) k_tile(R *__restrict__ psi_r, const R *__restrict__ dmat,
+                                              PassArgs a, MatArg) {
     using V = typename Amp<R>::T;
     constexpr int N = 1 << D;
     constexpr int S = sizeof(V) == 16 ? 0 : 1;   // log2(amplitudes per 16-byte chunk)
+    const auto mat = pass_matrix<R, PassArgs>(dmat);
     extern __shared__ uint4 lds_raw[];
     V *tile = reinterpret_cast<V *>(lds_raw);
     const uint32_t tile_amps = 1u << a.tb;
@@ -398,7 +419,7 @@ __global__ void __launch_bounds__(256) k_tile(R *__restrict__ psi_r, const R *__
                     if ((c >> j) & 1) o ^= a.toff[j];
                 olo[c] = o;
             }
-            const R *m = mat + (size_t)(D == 0 ? bid : bs) * (2 * N * N);
+            const auto m = mat + (size_t)(D == 0 ? bid : bs) * (2 * N * N);
             if (!TWOBUF) {
                 V v[N];
 #pragma unroll
@@ -791,16 +812,16 @@ __global__ void __launch_bounds__(256) k_mfma_tile(R *__restrict__ psi_r, const 
 
 // ------------------------------------------------------------------ dispatch
 template <int DD, typename R, int IPT, bool NT>
-static void launch_one(R *psi, const R *m, const PassArgs &a, int grid, hipStream_t s) {
+static void launch_one(R *psi, const R *m, const PassArgs &a, const MatArg &mi, int grid, hipStream_t s) {
     // several items per thread only pay (and only fit) for small blocks
     if constexpr (IPT == 1 || DD <= 3)
-        hipLaunchKernelGGL((k_direct<DD, R, IPT, NT>), dim3(grid), dim3(256), 0, s, psi, m, a);
+        hipLaunchKernelGGL((k_direct<DD, R, IPT, NT>), dim3(grid), dim3(256), 0, s, psi, m, a, mi);
 }
 
 template <typename R, int IPT, bool NT>
-static void launch_direct_t(int D, R *psi, const R *m, const PassArgs &a, int grid, hipStream_t s) {
+static void launch_direct_t(int D, R *psi, const R *m, const PassArgs &a, const MatArg &mi, int grid, hipStream_t s) {
 #define CAST_DIRECT(DD) \
-    case DD: launch_one<DD, R, IPT, NT>(psi, m, a, grid, s); break;
+    case DD: launch_one<DD, R, IPT, NT>(psi, m, a, mi, grid, s); break;
     switch (D) {
         CAST_DIRECT(0) CAST_DIRECT(1) CAST_DIRECT(2) CAST_DIRECT(3) CAST_DIRECT(4) CAST_DIRECT(5) CAST_DIRECT(6)
         default: break;
@@ -818,8 +839,8 @@ static int direct_ipt(int D, cast_dtype dt) {
 }
 
 template <typename R>
-static hipError_t launch_direct(int D, cast_dtype dt, R *psi, const R *m, const PassArgs &a, hipStream_t s,
-                                int rot_override) {
+static hipError_t launch_direct(int D, cast_dtype dt, R *psi, const R *m, const PassArgs &a, const MatArg &mi,
+                                hipStream_t s, int rot_override) {
     const int ipt = direct_ipt(D, dt);
     const bool nt = tuning().direct_nt[dt] != 0;
     const uint64_t items = a.ngroups * a.nblk;
@@ -845,12 +866,12 @@ static hipError_t launch_direct(int D, cast_dtype dt, R *psi, const R *m, const 
         }
     }
     switch (ipt * 2 + (nt ? 1 : 0)) {
-        case 2: launch_direct_t<R, 1, false>(D, psi, m, b, g, s); break;
-        case 3: launch_direct_t<R, 1, true>(D, psi, m, b, g, s); break;
-        case 4: launch_direct_t<R, 2, false>(D, psi, m, b, g, s); break;
-        case 5: launch_direct_t<R, 2, true>(D, psi, m, b, g, s); break;
-        case 8: launch_direct_t<R, 4, false>(D, psi, m, b, g, s); break;
-        case 9: launch_direct_t<R, 4, true>(D, psi, m, b, g, s); break;
+        case 2: launch_direct_t<R, 1, false>(D, psi, m, b, mi, g, s); break;
+        case 3: launch_direct_t<R, 1, true>(D, psi, m, b, mi, g, s); break;
+        case 4: launch_direct_t<R, 2, false>(D, psi, m, b, mi, g, s); break;
+        case 5: launch_direct_t<R, 2, true>(D, psi, m, b, mi, g, s); break;
+        case 8: launch_direct_t<R, 4, false>(D, psi, m, b, mi, g, s); break;
+        case 9: launch_direct_t<R, 4, true>(D, psi, m, b, mi, g, s); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();
@@ -858,7 +879,7 @@ static hipError_t launch_direct(int D, cast_dtype dt, R *psi, const R *m, const 
 
 template <typename R>
 static hipError_t launch_tile(int D, bool uni, bool twobuf, R *psi, const R *m, const PassArgs &a,
-                              int grid, int wg, size_t lds, hipStream_t s) {
+                              const MatArg &mi, int grid, int wg, size_t lds, hipStream_t s) {
     if (lds > 65536) {
         // only the k = d = 6 two-buffer variants need more than 64 KiB
         static bool done[2][2] = {{false, false}, {false, false}};
@@ -875,11 +896,11 @@ static hipError_t launch_tile(int D, bool uni, bool twobuf, R *psi, const R *m, 
 #define CAST_TILE(DD)                                                                                      \
     case DD:                                                                                               \
         if (twobuf) {                                                                                      \
-            if (uni) hipLaunchKernelGGL((k_tile<DD, R, true, true>), dim3(grid), dim3(wg), lds, s, psi, m, a); \
-            else hipLaunchKernelGGL((k_tile<DD, R, false, true>), dim3(grid), dim3(wg), lds, s, psi, m, a);    \
+            if (uni) hipLaunchKernelGGL((k_tile<DD, R, true, true>), dim3(grid), dim3(wg), lds, s, psi, m, a, mi); \
+            else hipLaunchKernelGGL((k_tile<DD, R, false, true>), dim3(grid), dim3(wg), lds, s, psi, m, a, mi);    \
         } else {                                                                                           \
-            if (uni) hipLaunchKernelGGL((k_tile<DD, R, true, false>), dim3(grid), dim3(wg), lds, s, psi, m, a); \
-            else hipLaunchKernelGGL((k_tile<DD, R, false, false>), dim3(grid), dim3(wg), lds, s, psi, m, a);    \
+            if (uni) hipLaunchKernelGGL((k_tile<DD, R, true, false>), dim3(grid), dim3(wg), lds, s, psi, m, a, mi); \
+            else hipLaunchKernelGGL((k_tile<DD, R, false, false>), dim3(grid), dim3(wg), lds, s, psi, m, a, mi);    \
         }                                                                                                  \
         break;
     switch (D) {
@@ -891,11 +912,12 @@ static hipError_t launch_tile(int D, bool uni, bool twobuf, R *psi, const R *m, 
 }
 
 template <typename R>
-static hipError_t launch_diag(int U, bool lds_table, R *psi, const R *m, const DiagArgs &g, int grid, hipStream_t s) {
+static hipError_t launch_diag(int U, bool lds_table, R *psi, const R *m, const DiagArgs &g, const MatArg &mi, int grid,
+                              hipStream_t s) {
 #define CAST_DIAG(UU)                                                                                     \
     case UU:                                                                                              \
-        if (lds_table) hipLaunchKernelGGL((k_diag<R, UU, true>), dim3(grid), dim3(256), 0, s, psi, m, g);  \
-        else hipLaunchKernelGGL((k_diag<R, UU, false>), dim3(grid), dim3(256), 0, s, psi, m, g);          \
+        if (lds_table) hipLaunchKernelGGL((k_diag<R, UU, true>), dim3(grid), dim3(256), 0, s, psi, m, g, mi);  \
+        else hipLaunchKernelGGL((k_diag<R, UU, false>), dim3(grid), dim3(256), 0, s, psi, m, g, mi);          \
         break;
     switch (U) {
         CAST_DIAG(1) CAST_DIAG(2) CAST_DIAG(4) CAST_DIAG(8)
@@ -1008,8 +1030,11 @@ static hipError_t launch_mfma(int D, bool tile, bool m3, int prefetch, R *psi, c
 }
 
 cast_status launch_pass(void *psi, int n, cast_dtype dt, const PassPlan &p, const void *dmat,
-                        hipStream_t stream, const PassShape *shape) {
+                        hipStream_t stream, const PassShape *shape, const MatArg *inl) {
     if (p.identity()) return CAST_OK;
+    static const MatArg unread{};
+    const MatArg &mi = inl ? *inl : unread;
+    if (inl) dmat = nullptr;
     const Tuning &tu = tuning();
     const int k = p.k, D = p.d;
     PassArgs a;
@@ -1029,6 +1054,7 @@ cast_status launch_pass(void *psi, int n, cast_dtype dt, const PassPlan &p, cons
     const bool direct = kind == 0;
     hipError_t e;
     if (kind == 4 || kind == 5) {
+        if (inl) return fail(CAST_EINVAL, "matrix-core passes read device matrices");
         for (int i = 0; i < k; ++i) a.lowmask[i] = (1ull << p.q[i]) - 1;
         a.ngroups = 1ull << (n - k);
         size_t lds = mfma_mat_bytes(dt, p);
@@ -1133,8 +1159,8 @@ cast_status launch_pass(void *psi, int n, cast_dtype dt, const PassPlan &p, cons
             if (grid == 0) return CAST_OK;   // every phase is 1
         }
         if (grid > (uint64_t)tu.diag_max_grid[dt]) grid = tu.diag_max_grid[dt];
-        if (dt == CAST_C128) e = launch_diag<double>(U, tu.diag_lds_table[dt] != 0, (double *)psi, (const double *)dmat, g, (int)grid, stream);
-        else e = launch_diag<float>(U, tu.diag_lds_table[dt] != 0, (float *)psi, (const float *)dmat, g, (int)grid, stream);
+        if (dt == CAST_C128) e = launch_diag<double>(U, tu.diag_lds_table[dt] != 0, (double *)psi, (const double *)dmat, g, mi, (int)grid, stream);
+        else e = launch_diag<float>(U, tu.diag_lds_table[dt] != 0, (float *)psi, (const float *)dmat, g, mi, (int)grid, stream);
     } else if (direct) {
         for (int i = 0; i < k; ++i) a.lowmask[i] = (1ull << p.q[i]) - 1;
         a.ngroups = 1ull << (n - k);
@@ -1144,9 +1170,9 @@ cast_status launch_pass(void *psi, int n, cast_dtype dt, const PassPlan &p, cons
         if (a.chunk_log > n - k) a.chunk_log = n - k;
         const int rot = shape ? shape->rot : -1;
         if (dt == CAST_C128)
-            e = launch_direct<double>(D, dt, (double *)psi, (const double *)dmat, a, stream, rot);
+            e = launch_direct<double>(D, dt, (double *)psi, (const double *)dmat, a, mi, stream, rot);
         else
-            e = launch_direct<float>(D, dt, (float *)psi, (const float *)dmat, a, stream, rot);
+            e = launch_direct<float>(D, dt, (float *)psi, (const float *)dmat, a, mi, stream, rot);
     } else {
         int tb = tu.tile_bits[dt];
         if (twobuf) tb = 12;
@@ -1185,10 +1211,10 @@ cast_status launch_pass(void *psi, int n, cast_dtype dt, const PassPlan &p, cons
         const bool uni = (tb - k) >= 6;
         const size_t lds = ((size_t)1 << tb) * amp_bytes(dt) * (twobuf ? 2 : 1);
         if (dt == CAST_C128)
-            e = launch_tile<double>(D, uni, twobuf, (double *)psi, (const double *)dmat, a, (int)grid, wg,
+            e = launch_tile<double>(D, uni, twobuf, (double *)psi, (const double *)dmat, a, mi, (int)grid, wg,
                                     lds, stream);
         else
-            e = launch_tile<float>(D, uni, twobuf, (float *)psi, (const float *)dmat, a, (int)grid, wg, lds,
+            e = launch_tile<float>(D, uni, twobuf, (float *)psi, (const float *)dmat, a, mi, (int)grid, wg, lds,
                                    stream);
     }
     if (e != hipSuccess) return fail(CAST_EHIP, std::string("pass launch: ") + hipGetErrorString(e));

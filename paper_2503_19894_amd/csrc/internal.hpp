@@ -10,6 +10,7 @@
 #include <vector>
 
 #include "../../include/cast.h"
+#include "pass_args.hpp"
 
 namespace cast {
 
@@ -148,7 +149,8 @@ struct PassShape {
 
 // Queues one pass on `stream`.  `dmat` holds the plan's blocks in dtype `dt`.
 cast_status launch_pass(void *psi, int n, cast_dtype dt, const PassPlan &p, const void *dmat,
-                        hipStream_t stream, const PassShape *shape = nullptr);
+                        hipStream_t stream, const PassShape *shape = nullptr,
+                        const MatArg *inl = nullptr);
 
 // Uploads a plan's matrices (cast to dt) into a new device buffer; the host
 // staging is synchronous (the buffer is ready when this returns).

@@ -1,5 +1,6 @@
 // Kernel argument block of one gate pass (passed by value).
 #pragma once
+#include <cstddef>
 #include <cstdint>
 
 namespace cast {
@@ -21,6 +22,15 @@ struct PassArgs {
     int khi, klo;           // tile: targets at/above and below W
     int qhi[6];             // tile: high targets, ascending
     int rot, it_bits;       // direct (iterations) and matrix-core direct (four-unit runs): order rotated left by rot bits of it_bits (rot 0: in order)
+};
+
+// A pass's matrices (or phase table) carried by the launch itself, for a pass
+// whose matrix is on the host and used once.  It follows the argument block in
+// the kernel's arguments; a launch that passes a device pointer leaves it
+// unread.
+struct MatArg {
+    static constexpr std::size_t kBytes = 1024;   // a dense 3-qubit gate, or a 6-qubit phase table, in complex128
+    alignas(8) unsigned char b[kBytes];
 };
 
 // Kernel argument block of a diagonal pass (every block 1 x 1).
