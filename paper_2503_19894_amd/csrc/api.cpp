@@ -213,10 +213,14 @@ static size_t pack_all(const std::vector<PassPlan> &ps, cast_dtype dt, std::vect
 }
 
 std::vector<size_t> plan_offsets(const std::vector<PassPlan> &ps, cast_dtype dt) {
-    std::vector<double> hd;
-    std::vector<float> hf;
+    const size_t align = 256 / (dt == CAST_C128 ? 8 : 4);
     std::vector<size_t> off;
-    pack_all(ps, dt, hd, hf, &off);
+    size_t elems = 0;
+    for (const PassPlan &p : ps) {
+        off.push_back(elems);
+        elems += p.d == 0 ? (size_t)2 << p.k : 2 * p.mat.size();   // as pack_plan
+        elems = (elems + align - 1) & ~(align - 1);
+    }
     return off;
 }
 
@@ -240,17 +244,26 @@ cast_status upload_plans_pooled(const std::vector<PassPlan> &ps, cast_dtype dt, 
 }
 
 cast_status upload_plans(const std::vector<PassPlan> &ps, cast_dtype dt, DeviceMatrix *out,
-                         std::vector<size_t> *offsets) {
+                         std::vector<size_t> *offsets, const std::vector<char> *tail, size_t *tail_at) {
     std::vector<double> hd;
     std::vector<float> hf;
     const size_t elems = pack_all(ps, dt, hd, hf, offsets);
-    const size_t bytes = elems * (dt == CAST_C128 ? 8 : 4);
+    const void *src = dt == CAST_C128 ? (void *)hd.data() : (void *)hf.data();
+    size_t bytes = elems * (dt == CAST_C128 ? 8 : 4);
+    std::vector<char> both;
+    if (tail) {
+        *tail_at = (bytes + 255) & ~(size_t)255;
+        both.resize(*tail_at + tail->size());
+        if (bytes) std::memcpy(both.data(), src, bytes);
+        std::memcpy(both.data() + *tail_at, tail->data(), tail->size());
+        src = both.data();
+        bytes = both.size();
+    }
     cast_status st = dev_alloc(&out->ptr, bytes);
     if (st) return st;
     out->bytes = bytes;
     if (bytes) {
-        hipError_t e = hipMemcpy(out->ptr, dt == CAST_C128 ? (void *)hd.data() : (void *)hf.data(), bytes,
-                                 hipMemcpyHostToDevice);
+        hipError_t e = hipMemcpy(out->ptr, src, bytes, hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             dev_free(out->ptr);
             out->ptr = nullptr;
@@ -710,17 +723,24 @@ static cast_status get_schedule(cast_fused *f, int n, cast_dtype dt, bool upload
     return CAST_OK;
 }
 
-static cast_status launch_sched_pass(cast_sv *sv, cast_fused *f, const Schedule &sc, const SchedPass &sp) {
+static cast_status launch_sched_pass(cast_sv *sv, cast_fused *f, Schedule &sc, const SchedPass &sp) {
+    if (sp.kind == 6 && !sc.dev.ptr)   // a list whose runs have all shared launches so far
+        if (cast_status rc = upload_schedule(&sc)) return rc;
     if (sp.kind == 6) return launch_diag_run(sv->data, sv->n, sv->dt, sp, sc.dev.ptr, sv->stream);
     const size_t rsz = sv->dt == CAST_C128 ? 8 : 4;
     const void *dm = (const char *)f->dev[sv->dt].ptr + f->dev_off[sv->dt][sp.first] * rsz;
     return launch_pass(sv->data, sv->n, sv->dt, f->plans[sp.first], dm, sv->stream, &sp.shape);
 }
 
-static cast_status prepare_circuit(cast_sv *sv, const cast_fused *fc, cast_fused **f, Schedule **sc) {
+static cast_status check_circuit(cast_sv *sv, const cast_fused *fc) {
     if (cast_status rc = check_sv(sv)) return rc;
     if (!fc) return fail(CAST_EINVAL, "fused list is NULL");
     if (fc->n != sv->n) return fail(CAST_EINVAL, "fused list was built for a different qubit count");
+    return CAST_OK;
+}
+
+static cast_status prepare_circuit(cast_sv *sv, const cast_fused *fc, cast_fused **f, Schedule **sc) {
+    if (cast_status rc = check_circuit(sv, fc)) return rc;
     *f = const_cast<cast_fused *>(fc);
     const int dt = sv->dt;
     if (!(*f)->dev[dt].ptr && !(*f)->plans.empty())
@@ -733,16 +753,21 @@ static cast_status prepare_circuit(cast_sv *sv, const cast_fused *fc, cast_fused
 extern "C" {
 
 cast_status apply_circuit(cast_sv *sv, const cast_fused *fc) {
-    cast_fused *f;
+    if (cast_status rc = check_circuit(sv, fc)) return rc;
+    cast_fused *f = const_cast<cast_fused *>(fc);
     Schedule *sc;
-    if (cast_status rc = prepare_circuit(sv, fc, &f, &sc)) return rc;
-    if (!tuning().tile_groups[sv->dt]) {
+    BlockedPlan *groups = nullptr;
+    if (tuning().tile_groups[sv->dt] && !f->plans.empty()) {
+        if (cast_status rc = get_schedule(f, sv->n, sv->dt, false, &sc)) return rc;
+        // without memory for the groups' tables the passes run one by one
+        if (cast_status rc = tile_groups(f, *sc, sv->dt, &groups); rc && rc != CAST_ENOMEM) return rc;
+    }
+    if (!groups) {
+        if (cast_status rc = prepare_circuit(sv, fc, &f, &sc)) return rc;
         for (const SchedPass &sp : sc->passes)
             if (cast_status rc = launch_sched_pass(sv, f, *sc, sp)) return rc;
         return CAST_OK;
     }
-    BlockedPlan *groups;
-    if (cast_status rc = tile_groups(f, *sc, sv->dt, &groups)) return rc;
     for (size_t i = 0; i < group_count(*groups); ++i) {
         size_t pass;
         if (cast_status rc = launch_group(sv, f, *groups, i, &pass)) return rc;

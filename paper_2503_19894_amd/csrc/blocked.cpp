@@ -22,16 +22,18 @@ struct BlockedPlan {
     };
     std::vector<Pass> passes;
     std::vector<BlkGate> gates;
-    std::vector<BlkEnt> ent;
+    std::vector<BlkEnt> ent;           // kBlkEnts per operation
+    std::vector<BlkEnt> units;         // work units of the table builds, behind them on the device
     std::vector<BlkMember> members;
     std::vector<double> tabs;          // phases of the diagonal gates (complex entries as pairs)
     void *dev = nullptr;               // device copy of these tables (phases in the state dtype)
+    bool shares = false;               // it lies in the fused list's matrix block
     size_t dev_ent = 0, dev_mem = 0, dev_tabs = 0;   // byte offsets in it
 };
 
 void blocked_free(BlockedPlan *b) {
     if (!b) return;
-    dev_free(b->dev);
+    if (!b->shares) dev_free(b->dev);
     delete b;
 }
 
@@ -68,15 +70,12 @@ uint32_t lds_elem(uint32_t y, cast_dtype dt) {
     return ((c ^ (((c >> 4) ^ (c >> 8)) & 15u)) << sh) | (y & ((1u << sh) - 1));
 }
 
-void set_targets(BlkGate *g, int k, const int *q, int w, const int *qh, int nh) {
-    g->k = k;
-    for (int s = 0; s < k; ++s) {
-        g->q[s] = q[s];
-        g->tpos[s] = -1;
-        if (q[s] < w) g->tpos[s] = q[s];
-        for (int i = 0; i < nh; ++i)
-            if (qh[i] == q[s]) g->tpos[s] = w + i;
-    }
+// Index of qubit q in the tile number: the bits of the global index that are
+// no tile bits, in order.
+int tile_number_bit(int q, int w, const int *qh, int nh) {
+    int b = q - w;
+    for (int i = 0; i < nh; ++i) b -= qh[i] < q;
+    return b;
 }
 
 BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh, int nh, uint64_t mat,
@@ -86,7 +85,12 @@ BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh
     g.kind = 1;
     g.d = p.d;
     g.mat = mat;
-    set_targets(&g, p.k, p.q, w, qh, nh);
+    int tpos[kMaxK];   // tile bit of each target, -1: outside the tile
+    for (int s = 0; s < p.k; ++s) {
+        tpos[s] = p.q[s] < w ? p.q[s] : -1;
+        for (int i = 0; i < nh; ++i)
+            if (qh[i] == p.q[s]) tpos[s] = w + i;
+    }
     // L^-1 by Gauss-Jordan: row r of [A | I] with A[r][c] = bit r of L[c]
     const int k = p.k;
     uint32_t rows[kMaxK];
@@ -102,24 +106,29 @@ BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh
         for (int r = 0; r < k; ++r)
             if (r != c && ((rows[r] >> c) & 1u)) rows[r] ^= rows[c];
     }
+    // columns of L^-1: virtual coordinates of local index bit s
+    uint32_t colv[kMaxK];
     for (int s = 0; s < k; ++s) {
-        uint32_t col = 0;
-        for (int i = 0; i < k; ++i) col |= ((rows[i] >> (k + s)) & 1u) << i;
-        g.colv[s] = col;
+        colv[s] = 0;
+        for (int i = 0; i < k; ++i) colv[s] |= ((rows[i] >> (k + s)) & 1u) << i;
+        if (tpos[s] >= 0) continue;
+        for (int i = 0; i < k; ++i)
+            if ((colv[s] >> i) & 1u) g.par[i] |= 1u << tile_number_bit(p.q[s], w, qh, nh);
     }
     // span offsets in tile coordinates (every span target is in the tile)
+    uint32_t span[kGroupMaxD];
     for (int i = 0; i < p.d; ++i) {
-        uint32_t o = 0;
+        span[i] = 0;
         for (int s = 0; s < k; ++s)
-            if ((p.L[i] >> s) & 1u) o |= 1u << g.tpos[s];
-        g.span[i] = o;
+            if ((p.L[i] >> s) & 1u) span[i] |= 1u << tpos[s];
+        g.span[i] = lds_elem(span[i], dt);
     }
     // pivot bits of a reduced echelon basis of the span: the tile positions
     // with zeros there hold one element of every coset
     uint32_t b[kGroupMaxD];
     int piv[kGroupMaxD];
     for (int i = 0; i < p.d; ++i) {
-        b[i] = g.span[i];
+        b[i] = span[i];
         for (int j = 0; j < i; ++j)
             if ((b[i] >> piv[j]) & 1u) b[i] ^= b[j];
         piv[i] = 31 - __builtin_clz(b[i]);
@@ -132,7 +141,7 @@ BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh
     // i + 4 and i + 8 share one (lds_elem) -- the wave and iteration the rest
     uint32_t targets = 0, pivots = 0, lane = 0;
     for (int s = 0; s < k; ++s)
-        if (g.tpos[s] >= 0) targets |= 1u << g.tpos[s];
+        if (tpos[s] >= 0) targets |= 1u << tpos[s];
     for (int i = 0; i < p.d; ++i) pivots |= 1u << piv[i];
     int used[5] = {0, 0, 0, 0, 0};
     auto column = [&](int bit) { return dt == CAST_C128 ? bit & 3 : bit == 0 ? 4 : (bit - 1) & 3; };
@@ -143,19 +152,18 @@ BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh
         if (best < 0) break;
         lane |= 1u << best;
         ++used[column(best)];
-        g.lanepos |= (uint64_t)best << (8 * g.nlane++);
+        g.lane[g.nlane++] = lds_elem(1u << best, dt);
     }
     std::vector<int> rest;
     for (int t = 0; t < tb; ++t)
         if (!(((pivots | lane) >> t) & 1u)) rest.push_back(t);
     g.nuni = (uint32_t)rest.size();
-    g.ent = (uint32_t)ent->size();
-    for (uint32_t e = 0; e < (1u << g.nuni); ++e) {
+    for (uint32_t e = 0; e < kBlkEnts; ++e) {   // (the kernel reads past the last, but does not use it)
         uint32_t y = 0, u = 0;
         for (uint32_t i = 0; i < g.nuni; ++i)
             if ((e >> i) & 1u) y |= 1u << rest[i];
         for (int s = 0; s < k; ++s)
-            if (g.tpos[s] >= 0 && ((y >> g.tpos[s]) & 1u)) u ^= g.colv[s];
+            if (tpos[s] >= 0 && ((y >> tpos[s]) & 1u)) u ^= colv[s];
         ent->push_back(BlkEnt{u, lds_elem(y, dt)});
     }
     return g;
@@ -202,8 +210,15 @@ void emit_segment(BlockedPlan *bp, const std::vector<PassPlan> &P, const std::ve
                   cast_dtype dt, const std::vector<size_t> &cur, size_t first, size_t count, uint64_t need) {
     const int tb = bp->tb;
     const size_t ab = amp_bytes(dt);
-    const bool dense = std::any_of(cur.begin(), cur.end(), [&](size_t i) { return P[i].d >= 4; });
-    const int nt = dense ? kGroupThreads : bp->nt;
+    size_t mats = 0, area = 0;
+    for (size_t i : cur) {
+        if (P[i].d >= 4) mats += (P[i].blk.size() * ab) << (2 * P[i].d);
+        if (P[i].d == 0) area = kBlkAreaBytes;
+    }
+    // with matrices in LDS: two workgroups where a compute unit holds both
+    const size_t tile = ab << tb;
+    const bool two = tile >= kBlkTileBytes / 2 && tile + mats + area <= kBlkMaxLds / 2;
+    const int nt = !mats ? bp->nt : two ? 512 : kGroupThreads;
     int w = tb;
     window_of(need, tb, &w);
     BlockedPlan::Pass ps;
@@ -229,6 +244,7 @@ void emit_segment(BlockedPlan *bp, const std::vector<PassPlan> &P, const std::ve
             // a run: tables that fit the area together
             const size_t first_gate = bp->gates.size();
             std::vector<BlkGate> run;
+            std::vector<BlkEnt> ent;
             uint32_t end = used;
             bool fresh = build == ~0u;
             for (; c < cl.size() && run.size() < kBlkRunMax; ++c) {
@@ -243,14 +259,13 @@ void emit_segment(BlockedPlan *bp, const std::vector<PassPlan> &P, const std::ve
                 BlkGate g;
                 std::memset(&g, 0, sizeof g);
                 g.k = (int)cl[c].bits.size();
-                for (int i = 0; i < g.k; ++i) g.tpos[i] = cl[c].bits[i];
+                for (int i = 0; i < g.k; ++i) g.pos[i] = cl[c].bits[i];
                 g.lds = at;
                 end = at + sz;
-                g.ent = (uint32_t)bp->ent.size();
-                for (uint32_t y = 0; y < (1u << tb); y += (uint32_t)nt) {
+                for (uint32_t it = 0; it < kBlkEnts; ++it) {
                     uint32_t j = 0;
-                    for (int i = 0; i < g.k; ++i) j |= ((y >> g.tpos[i]) & 1u) << i;
-                    bp->ent.push_back(BlkEnt{j, 0});
+                    for (int i = 0; i < g.k; ++i) j |= (((it * (uint32_t)nt) >> g.pos[i]) & 1u) << i;
+                    ent.push_back(BlkEnt{j, 0});
                 }
                 g.m0 = (uint32_t)bp->members.size();
                 for (const PhaseTable *t : cl[c].gates) {
@@ -275,7 +290,9 @@ void emit_segment(BlockedPlan *bp, const std::vector<PassPlan> &P, const std::ve
                 std::memset(&g, 0, sizeof g);
                 g.kind = 2;
                 bp->gates.push_back(g);
+                bp->ent.resize(bp->ent.size() + kBlkEnts);
             }
+            bp->ent.insert(bp->ent.end(), ent.begin(), ent.end());
             used = end;
             run[0].run = (int)run.size();
             bp->gates.insert(bp->gates.end(), run.begin(), run.end());
@@ -301,17 +318,19 @@ void emit_segment(BlockedPlan *bp, const std::vector<PassPlan> &P, const std::ve
         for (uint32_t gi = s.g0; gi < bp->gates.size(); ++gi)
             if (bp->gates[gi].kind == 2) {
                 std::rotate(bp->gates.begin() + s.g0, bp->gates.begin() + gi, bp->gates.begin() + gi + 1);
+                std::rotate(bp->ent.begin() + (size_t)s.g0 * kBlkEnts, bp->ent.begin() + (size_t)gi * kBlkEnts,
+                            bp->ent.begin() + (size_t)(gi + 1) * kBlkEnts);
                 break;
             }
     }
     s.g1 = (uint32_t)bp->gates.size();
     for (uint32_t gi = s.g0; gi < s.g1; ++gi) {
         if (bp->gates[gi].kind != 2) continue;
-        bp->gates[gi].ent = (uint32_t)bp->ent.size();
+        bp->gates[gi].ent = (uint32_t)bp->units.size();   // behind the operations' entries (upload_tables)
         for (uint32_t gj = gi + 1; gj < s.g1 && bp->gates[gj].kind != 2; ++gj)
             if (bp->gates[gj].kind == 0)
-                for (uint32_t sl = 0; sl * 64 < (1u << bp->gates[gj].k); ++sl) bp->ent.push_back(BlkEnt{gj, sl});
-        bp->gates[gi].nent = (uint32_t)bp->ent.size() - bp->gates[gi].ent;
+                for (uint32_t sl = 0; sl * 64 < (1u << bp->gates[gj].k); ++sl) bp->units.push_back(BlkEnt{gj, sl});
+        bp->gates[gi].nent = (uint32_t)bp->units.size() - bp->gates[gi].ent;
     }
     s.nt = nt;
     s.lds_tabs = (s.lds_tabs + 15) & ~15u;
@@ -376,21 +395,37 @@ cast_status build(const cast_fused &f, cast_dtype dt, BlockedPlan **out) {
     return CAST_OK;
 }
 
-cast_status upload_plan_tables(BlockedPlan *bp, cast_dtype dt) {
-    if (bp->dev || bp->gates.empty()) return CAST_OK;
+// Uploads the list's matrices and the plan's tables, whichever are missing: a
+// first call's in one allocation and one copy.
+cast_status upload_tables(cast_fused *f, BlockedPlan *bp, cast_dtype dt) {
+    const bool mats = !f->dev[dt].ptr && !f->plans.empty();
+    if (bp->dev || bp->gates.empty())
+        return mats ? upload_plans(f->plans, dt, &f->dev[dt], &f->dev_off[dt]) : CAST_OK;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     bp->dev_ent = up(bp->gates.size() * sizeof(BlkGate));
-    bp->dev_mem = bp->dev_ent + up(bp->ent.size() * sizeof(BlkEnt));
+    bp->dev_mem = bp->dev_ent + up((bp->ent.size() + bp->units.size()) * sizeof(BlkEnt));
     bp->dev_tabs = bp->dev_mem + up(bp->members.size() * sizeof(BlkMember));
     const size_t rsz = amp_bytes(dt) / 2, bytes = bp->dev_tabs + std::max<size_t>(bp->tabs.size(), 4) * rsz;
     std::vector<char> h(bytes, 0);
     std::memcpy(h.data(), bp->gates.data(), bp->gates.size() * sizeof(BlkGate));
-    if (!bp->ent.empty()) std::memcpy(h.data() + bp->dev_ent, bp->ent.data(), bp->ent.size() * sizeof(BlkEnt));
+    BlkGate *hg = (BlkGate *)h.data();
+    for (size_t i = 0; i < bp->gates.size(); ++i)
+        if (hg[i].kind == 2) hg[i].ent += (uint32_t)bp->ent.size();
+    BlkEnt *he = (BlkEnt *)(h.data() + bp->dev_ent);
+    std::copy(bp->ent.begin(), bp->ent.end(), he);
+    std::copy(bp->units.begin(), bp->units.end(), he + bp->ent.size());
     if (!bp->members.empty())
         std::memcpy(h.data() + bp->dev_mem, bp->members.data(), bp->members.size() * sizeof(BlkMember));
     for (size_t i = 0; i < bp->tabs.size(); ++i) {
         if (dt == CAST_C128) ((double *)(h.data() + bp->dev_tabs))[i] = bp->tabs[i];
         else ((float *)(h.data() + bp->dev_tabs))[i] = (float)bp->tabs[i];
+    }
+    if (mats) {
+        size_t at;
+        if (cast_status rc = upload_plans(f->plans, dt, &f->dev[dt], &f->dev_off[dt], &h, &at)) return rc;
+        bp->dev = (char *)f->dev[dt].ptr + at;
+        bp->shares = true;
+        return CAST_OK;
     }
     if (cast_status rc = dev_alloc(&bp->dev, bytes)) return rc;
     const hipError_t e = hipMemcpy(bp->dev, h.data(), bytes, hipMemcpyHostToDevice);
@@ -418,12 +453,8 @@ cast_status prepare(const cast_fused *fc, int n, cast_dtype dt, bool device, Blo
     if (!bp) {
         if (cast_status rc = build(*f, dt, &bp)) return rc;
     }
-    if (device) {
-        if (!f->dev[dt].ptr && !f->plans.empty()) {
-            if (cast_status rc = upload_plans(f->plans, dt, &f->dev[dt], &f->dev_off[dt])) return rc;
-        }
-        if (cast_status rc = upload_plan_tables(bp, dt)) return rc;
-    }
+    if (device)
+        if (cast_status rc = upload_tables(f, bp, dt)) return rc;
     *out = bp;
     return CAST_OK;
 }
@@ -451,15 +482,16 @@ cast_status check(const cast_sv *sv) {
 // ------------------------------------------------------------ tile groups
 // apply_circuit's launches: consecutive passes of the schedule whose mixed
 // qubits fit one LDS tile share a launch (and one read and write of the
-// state) where that is predicted to be faster.  Times in microseconds:
-//   a pass    3.5 + bytes at 5.4 TB/s, or its products at 60 / 120 TFLOP/s
-//             (launch-bound passes of small states take 3.6 to 5.5);
-//   a group   4 + the longer of the state's read and write at 4.9 TB/s and
-//             its operations, + 0.3 of the shorter.  An operation's time on a
-//             tile of 2^12 amplitudes with two workgroups per compute unit:
-//             table 0.5, d <= 2 1.8, d = 3 2.1, d = 4 / 5 3.7 / 7.4
-//             (complex64: half, matrix cores), from segments at 26 and 27
-//             qubits; at least 0.8 for its barrier and loads.
+// state) where that is predicted to be faster.  Times in microseconds, from
+// kernel times at 12 to 26 qubits:
+//   a pass    3.8 (direct, diagonal) to 6.5 (through LDS) on any small state,
+//             then its bytes at 5.4 TB/s or its products at 60 / 120 TFLOP/s;
+//   a group   5 + the longer of the state's read and write at 5.2 TB/s and
+//             its operations, + 0.3 of the shorter.  An operation occupies a
+//             compute unit for, per tile of 2^12 amplitudes: a table 0.3,
+//             d = 1 0.7, d = 2 0.8, d = 3 1.1, d = 4 / 5 3.0 / 5.3
+//             (complex64: 1.5 / 2.8, matrix cores); never less than 0.8, 1.6
+//             or 2.6 (its barriers and first reads).
 struct Span {
     size_t a, b;          // schedule passes [a, b)
     uint64_t need;
@@ -469,29 +501,29 @@ struct Span {
 double pass_us(const Schedule &sc, const SchedPass &sp, const std::vector<PassPlan> &P) {
     const double ab = (double)amp_bytes(sc.dt);
     if (sp.kind < 0) return 0.0;
-    if (sp.kind == 6) return 3.5 + 2 * ab * sp.active_amps / 5.4e6;
+    if (sp.kind == 6) return 3.8 + 2 * ab * sp.active_amps / 5.4e6;
     const PassPlan &p = P[sp.first];
     const double amps = std::ldexp((double)p.blk.size(), sc.n - p.k + p.d);
     const double mem = 2 * ab * amps / 5.4e6, fl = p.d >= 4 ? 8 * amps * (1 << p.d) / (sc.dt == CAST_C128 ? 60e6 : 120e6) : 0;
-    return 3.5 + std::max(mem, fl);
+    const double base = sp.kind == 1 || sp.kind == 2 ? 5.3 : sp.kind == 5 ? 6.5 : p.d >= 5 ? 4.8 : 3.8;
+    return base + std::max(mem, fl);
 }
 
 double group_us(const Schedule &sc, const std::vector<PassPlan> &P, size_t a, size_t b, int tb) {
     const double scale = std::ldexp(1.0, tb - 12), tiles = std::ldexp(1.0, sc.n - tb);
-    // one workgroup per compute unit runs an operation twice as fast as two
-    const double share = tiles <= 256 ? 0.5 : 1.0;
+    static const double op_us[] = {0.3, 0.7, 0.8, 1.1, 3.0, 5.3}, least_us[] = {0.8, 0.8, 0.8, 0.8, 1.6, 2.6};
     double ops = 0;
     for (size_t i = a; i < b; ++i) {
         const SchedPass &sp = sc.passes[i];
         if (sp.kind < 0) continue;
         const int d = sp.kind == 6 ? 0 : P[sp.first].d;
-        double t = d == 0 ? 0.5 * std::max<size_t>(1, sp.tabs.size()) : d <= 2 ? 1.8 : d == 3 ? 2.1 : d == 4 ? 3.7 : 7.4;
-        if (d >= 4 && sc.dt == CAST_C64) t *= 0.5;
-        ops += std::max(0.8, t * scale * share);
+        double t = op_us[d] * scale;
+        if (sp.kind == 6) t *= (double)sp.tabs.size();
+        if (d >= 4 && sc.dt == CAST_C64) t *= 0.52;
+        ops += std::max(least_us[d], t * std::max(1.0, tiles / 256));
     }
-    ops *= std::max(1.0, tiles / 512);
-    const double mem = 2 * std::ldexp((double)amp_bytes(sc.dt), sc.n) / 4.9e6;
-    return 4.0 + std::max(mem, ops) + 0.3 * std::min(mem, ops);
+    const double mem = 2 * std::ldexp((double)amp_bytes(sc.dt), sc.n) / 5.2e6;
+    return 5.0 + std::max(mem, ops) + 0.3 * std::min(mem, ops);
 }
 
 // Groups the schedule with tiles of 2^tb amplitudes; *us: predicted time.
@@ -587,7 +619,7 @@ cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, Blocke
         }
         bp = p;
     }
-    if (cast_status rc = upload_plan_tables(bp, dt)) return rc;
+    if (cast_status rc = upload_tables(f, bp, dt)) return rc;
     *out = bp;
     return CAST_OK;
 }

@@ -50,18 +50,30 @@ __device__ __forceinline__ uint64_t expand(uint32_t y, const BlkSeg &s) {
 template <typename T> using CPtr = const __attribute__((address_space(4))) T *;
 template <typename T> __device__ __forceinline__ CPtr<T> cptr(const T *p) { return (CPtr<T>)p; }
 
+// Reads a whole record by the widest scalar loads, with one wait.
+template <typename T> __device__ __forceinline__ T load_const(CPtr<T> p) {
+    typedef uint32_t W __attribute__((ext_vector_type(sizeof(T) >= 64 ? 16 : sizeof(T) / 4)));
+    constexpr int C = sizeof(T) / sizeof(W);
+    static_assert(C * sizeof(W) == sizeof(T), "whole loads");
+    union { W w[C]; T t; } x;
+#pragma unroll
+    for (int i = 0; i < C; ++i) x.w[i] = reinterpret_cast<CPtr<W>>(p)[i];
+    return x.t;
+}
+
 // Builds phase tables for the tile at tbase (kind 2): a wave takes 64 entries
 // of one table and multiplies its gates' phases, their indices being a part
 // fixed by the tile and the entry's bits.
 template <typename R, int NT>
-__device__ __forceinline__ void build_tables(typename Cx<R>::T *area, CPtr<BlkGate> gates, CPtr<BlkGate> g,
+__device__ __forceinline__ void build_tables(typename Cx<R>::T *area, CPtr<BlkGate> gates, const BlkGate &g,
                                              CPtr<BlkEnt> ent, CPtr<BlkMember> members, const R *tabs,
                                              uint64_t tbase) {
     using V = typename Cx<R>::T;
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    for (uint32_t i = wave; i < g->nent; i += NT / 64) {
-        CPtr<BlkGate> t = gates + ent[g->ent + i].u;
-        const uint32_t e = ent[g->ent + i].a * 64 + lane;
+    for (uint32_t i = wave; i < g.nent; i += NT / 64) {
+        const BlkEnt unit = load_const(ent + g.ent + i);
+        CPtr<BlkGate> t = gates + unit.u;
+        const uint32_t e = unit.a * 64 + lane;
         V p;
         p.x = 1;
         p.y = 0;
@@ -93,13 +105,15 @@ template <typename R, int S, int NT, int M>
 __device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const typename Cx<R>::T *area, CPtr<BlkGate> g,
                                            CPtr<BlkEnt> ent, uint32_t tile_amps) {
     using V = typename Cx<R>::T;
-    uint32_t jl[M], e0[M];
+    uint32_t jl[M];
 #pragma unroll
     for (int t = 0; t < M; ++t) {
-        uint32_t j = g[t].lds;
-        for (int i = 0; i < g[t].k; ++i) j |= ((threadIdx.x >> g[t].tpos[i]) & 1u) << i;
+        const BlkGate r = load_const(g + t);
+        uint32_t j = r.lds;
+#pragma unroll
+        for (int i = 0; i < 8; ++i)
+            if (i < r.k) j |= ((threadIdx.x >> r.pos[i]) & 1u) << i;
         jl[t] = j;
-        e0[t] = g[t].ent;
     }
     const uint32_t al = at<S>(threadIdx.x);
     const uint32_t iters = tile_amps > NT ? tile_amps / NT : 1;
@@ -109,7 +123,7 @@ __device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const typena
         V x = tile[a];
 #pragma unroll
         for (int t = 0; t < M; ++t) {
-            const V ph = area[jl[t] ^ ent[e0[t] + i].u];
+            const V ph = area[jl[t] ^ ent[t * kBlkEnts + i].u];
             const R re = x.x * ph.x - x.y * ph.y;
             const R im = x.x * ph.y + x.y * ph.x;
             x.x = re;
@@ -121,8 +135,8 @@ __device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const typena
 
 template <typename R, int S, int NT>
 __device__ __forceinline__ void diag_run(typename Cx<R>::T *tile, const typename Cx<R>::T *area, CPtr<BlkGate> g,
-                                         CPtr<BlkEnt> ent, uint32_t tile_amps) {
-    switch (g->run) {
+                                         CPtr<BlkEnt> ent, int run, uint32_t tile_amps) {
+    switch (run) {
         case 1: diag_run_m<R, S, NT, 1>(tile, area, g, ent, tile_amps); break;
         case 2: diag_run_m<R, S, NT, 2>(tile, area, g, ent, tile_amps); break;
         case 3: diag_run_m<R, S, NT, 3>(tile, area, g, ent, tile_amps); break;
@@ -134,6 +148,14 @@ __device__ __forceinline__ void diag_run(typename Cx<R>::T *tile, const typename
     }
 }
 
+// The virtual coordinates that the tile's number fixes.
+__device__ __forceinline__ uint32_t tile_coords(const BlkGate &g, uint32_t tnum) {
+    uint32_t u = 0;
+#pragma unroll
+    for (int b = 0; b < 6; ++b) u |= ((uint32_t)__popc(tnum & g.par[b]) & 1u) << b;
+    return u;
+}
+
 // Block gate with 2^D x 2^D blocks: one work item per coset of the span.  The
 // virtual coordinates u = L^-1 j of a coset's first position give its block
 // (u >> D) and its place in it (u mod 2^D).  The lane's bits of a coset lie on
@@ -143,8 +165,8 @@ __device__ __forceinline__ void diag_run(typename Cx<R>::T *tile, const typename
 // its matrix beside 8 for its amplitudes: 28 qubits, complex128, 0.24 ms more
 // per gate and pass.)
 template <int D, typename R, int S, int NT>
-__device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, CPtr<BlkGate> g, CPtr<BlkEnt> ent,
-                                              CPtr<R> mats, uint64_t tbase) {
+__device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, const BlkGate &g, CPtr<BlkEnt> ent,
+                                              CPtr<R> mats, uint32_t tnum) {
     using V = typename Cx<R>::T;
     constexpr int N = 1 << D;
     uint32_t soff[N];
@@ -153,27 +175,24 @@ __device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, CPtr<BlkG
         uint32_t o = 0;
 #pragma unroll
         for (int i = 0; i < D; ++i)
-            if ((c >> i) & 1) o ^= at<S>(g->span[i]);
+            if ((c >> i) & 1) o ^= g.span[i];
         soff[c] = o;
     }
-    uint32_t uuni = 0;   // targets outside the tile
-    for (int q = 0; q < g->k; ++q)
-        if (g->tpos[q] < 0 && ((tbase >> g->q[q]) & 1u)) uuni ^= g->colv[q];
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t nl = g->nlane, nq = 1u << g->nuni, amask = g->amask;
-    const uint64_t lanepos = g->lanepos;
+    BlkEnt nxt = load_const(ent + wave);   // wave < kBlkEnts
+    const uint32_t uuni = tile_coords(g, tnum);
+    const uint32_t nl = g.nlane, nq = 1u << g.nuni, amask = g.amask;
     uint32_t al = 0;
 #pragma unroll
-    for (int i = 0; i < 6; ++i) {
-        const uint32_t bit = at<S>(1u << ((lanepos >> (8 * i)) & 255u));
-        if (i < (int)nl && ((lane >> i) & 1u)) al ^= bit;
-    }
-    CPtr<R> m0 = mats + g->mat;
-    CPtr<BlkEnt> e0 = ent + g->ent;
+    for (int i = 0; i < 6; ++i)
+        if ((lane >> i) & 1u) al ^= g.lane[i];   // 0 from nlane
+    CPtr<R> m0 = mats + g.mat;
     for (uint32_t q = wave; q < nq; q += NT / 64) {
-        const uint32_t u = uuni ^ e0[q].u, blk = u >> D;
+        const BlkEnt e = nxt;
+        nxt = load_const(ent + (q + NT / 64 < nq ? q + NT / 64 : q));
+        const uint32_t u = uuni ^ e.u, blk = u >> D;
         if (!((amask >> blk) & 1u)) continue;
-        uint32_t a0 = e0[q].a;
+        uint32_t a0 = e.a;
 #pragma unroll
         for (int b = 0; b < D; ++b)
             if ((u >> b) & 1u) a0 ^= soff[1 << b];
@@ -208,15 +227,20 @@ __device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, CPtr<BlkG
 // Inputs and matrix (transposed, in LDS for the whole launch) are read one
 // k-step ahead.  The outputs are written after the last input is read, so the
 // update is in place.
+// Rows of a staged matrix's column c are permuted by i ^ matrix_swz(c), so
+// that neither the transposing writes (a lane per column) nor the reads (four
+// columns, sixteen rows each) meet in a bank.
+__device__ __forceinline__ uint32_t matrix_swz(uint32_t c) { return (c & 15u) ^ ((c & 1u) << 4); }
+
 template <int D, typename R, int S, int NT>
-__device__ __forceinline__ void mfma_in_tile(typename Cx<R>::T *tile, CPtr<BlkGate> g, CPtr<BlkEnt> ent,
-                                             const typename Cx<R>::T *mt, uint64_t tbase) {
+__device__ __forceinline__ void mfma_in_tile(typename Cx<R>::T *tile, const BlkGate &g, CPtr<BlkEnt> ent,
+                                             const typename Cx<R>::T *mt, uint32_t tnum) {
     using V = typename Cx<R>::T;
     using M = Mfma<R>;
     constexpr int N = 1 << D, T = N / 16, K = N / 4;
     uint32_t sp[D];
 #pragma unroll
-    for (int i = 0; i < D; ++i) sp[i] = at<S>(g->span[i]);
+    for (int i = 0; i < D; ++i) sp[i] = g.span[i];
     auto off = [&](int c) {   // bits 2.. of a row or column: wave-uniform
         uint32_t o = 0;
 #pragma unroll
@@ -224,17 +248,15 @@ __device__ __forceinline__ void mfma_in_tile(typename Cx<R>::T *tile, CPtr<BlkGa
             if ((c >> i) & 1) o ^= sp[i];
         return o;
     };
-    uint32_t uuni = 0;
-    for (int q = 0; q < g->k; ++q)
-        if (g->tpos[q] < 0 && ((tbase >> g->q[q]) & 1u)) uuni ^= g->colv[q];
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t j = lane & 15, kk = lane >> 4;
-    const uint32_t nq = 1u << g->nuni, amask = g->amask;
-    const uint64_t lanepos = g->lanepos;
+    BlkEnt nxt = load_const(ent + wave);   // wave < kBlkEnts
+    const uint32_t uuni = tile_coords(g, tnum);
+    const uint32_t nq = 1u << g.nuni, amask = g.amask;
     uint32_t al = 0;
 #pragma unroll
     for (int i = 0; i < 4; ++i)
-        if ((j >> i) & 1u) al ^= at<S>(1u << ((lanepos >> (8 * i)) & 255u));
+        if ((j >> i) & 1u) al ^= g.lane[i];
     // k-row 4 s + kk of the inputs; result rows M::row(lane, v) + 16 t
     uint32_t ain = al, aout = al;
 #pragma unroll
@@ -243,13 +265,16 @@ __device__ __forceinline__ void mfma_in_tile(typename Cx<R>::T *tile, CPtr<BlkGa
             ain ^= sp[i];
             aout ^= sizeof(R) == 8 ? sp[i] : sp[2 + i];
         }
-    const V *m0 = mt + g->lds + kk * N + j;   // column kk, row j
-    CPtr<BlkEnt> e0 = ent + g->ent;
+    const uint32_t jk = kk * N + ((j ^ matrix_swz(kk)) & (N - 1));   // column kk, row j
     for (uint32_t q = wave; q < nq; q += NT / 64) {
-        const uint32_t u = uuni ^ e0[q].u, blk = u >> D;
+        const BlkEnt e = nxt;
+        nxt = load_const(ent + (q + NT / 64 < nq ? q + NT / 64 : q));
+        const uint32_t u = uuni ^ e.u, blk = u >> D;
         if (!((amask >> blk) & 1u)) continue;
-        const uint32_t a0 = e0[q].a ^ off((int)(u & (N - 1)));
-        const V *m = m0 + (uint32_t)__popc(amask & ((1u << blk) - 1)) * (N * N);
+        const uint32_t a0 = e.a ^ off((int)(u & (N - 1)));
+        const V *m0 = mt + g.lds + (uint32_t)__popc(amask & ((1u << blk) - 1)) * (N * N);
+        // column 4 s + kk, row 16 t + j
+        auto entry = [&](int s, int t) { return m0[(jk ^ (uint32_t)(((4 * s) & 15) ^ (16 * t))) + 4 * s * N]; };
         typename M::acc cr[T], ci[T];
 #pragma unroll
         for (int t = 0; t < T; ++t)
@@ -257,14 +282,14 @@ __device__ __forceinline__ void mfma_in_tile(typename Cx<R>::T *tile, CPtr<BlkGa
             for (int v = 0; v < 4; ++v) cr[t][v] = ci[t][v] = 0;
         V x = tile[a0 ^ ain], a[T];
 #pragma unroll
-        for (int t = 0; t < T; ++t) a[t] = m[16 * t];
+        for (int t = 0; t < T; ++t) a[t] = entry(0, t);
 #pragma unroll
         for (int s = 0; s < K; ++s) {
             V xn = x, an[T];
             if (s + 1 < K) {
                 xn = tile[a0 ^ ain ^ off(4 * (s + 1))];
 #pragma unroll
-                for (int t = 0; t < T; ++t) an[t] = m[4 * (s + 1) * N + 16 * t];
+                for (int t = 0; t < T; ++t) an[t] = entry(s + 1, t);
             }
 #pragma unroll
             for (int t = 0; t < T; ++t) {
@@ -293,19 +318,24 @@ __device__ __forceinline__ void mfma_in_tile(typename Cx<R>::T *tile, CPtr<BlkGa
     }
 }
 
-// MF: the segment has dense blocks for the matrix cores.  One workgroup of
-// 1024 threads per compute unit then holds the tile and every such block's
-// matrix in LDS.  (Two workgroups that read the matrices from global memory
-// ran in step, both loading, then both multiplying: 24 passes of 4- and
-// 5-qubit gates on 26 qubits, complex64, 5.2 ms.)
-template <typename R, int NT, bool MF>
+// MF: the segment has dense blocks for the matrix cores.  The workgroup then
+// holds the tile and every such block's matrix in LDS: two of 512 threads on a
+// compute unit where both fit (23 qubits, complex64, two 4-qubit gates: 44 us
+// against 53 with one of 1024), else one of 1024.  (Two workgroups that read
+// the matrices from global memory ran in step, both loading, then both
+// multiplying.)  Seven 4- and 5-qubit gates on 26 qubits keep the matrix cores
+// busy for 0.6 of the launch's 2.03 ms (complex128) and 1.04 ms (complex64).
+// NB: 16-byte chunks per lane of the tile, 0: any number (tiles of small
+// states).  Fixed, so that the wait for a tile's loads need not also wait for
+// the stores of the tile before, issued after them.
+template <typename R, int NT, bool MF, int NB>
 __global__ void __launch_bounds__(NT, 4) k_blocked(R *__restrict__ psi_r, const R *__restrict__ mats_g,
                                                 const R *__restrict__ tabs, const BlkGate *__restrict__ gates_g,
                                                 const BlkEnt *__restrict__ ent_g,
                                                 const BlkMember *__restrict__ members_g, BlkSeg s) {
     using V = typename Cx<R>::T;
     constexpr int S = sizeof(V) == 16 ? 0 : 1;
-    constexpr int B = 4096 / NT;               // chunks per lane of a 64 KiB tile
+    constexpr int B = NB ? NB : (int)(kBlkTileBytes / 16) / NT;
     extern __shared__ u4 lds16[];
     V *tile = reinterpret_cast<V *>(lds16);
     const uint32_t tile_amps = 1u << s.tb;
@@ -316,109 +346,131 @@ __global__ void __launch_bounds__(NT, 4) k_blocked(R *__restrict__ psi_r, const 
     CPtr<R> mats = cptr(mats_g);
     V *mt = area + s.lds_tabs / sizeof(V);
     if (MF) {
-        // dense blocks transposed: entry (i, c) at c * 2^d + i
+        // dense blocks transposed: entry (i, c) at c * 2^d + (i ^ matrix_swz(c))
         for (uint32_t gi = s.g0; gi < s.g1; ++gi) {
-            CPtr<BlkGate> g = gates + gi;
-            if (g->kind != 1 || g->d < 4) continue;
-            const V *src = reinterpret_cast<const V *>(mats_g + g->mat);
-            const int d = g->d;
-            const uint32_t n2 = (1u << d) - 1, count = (uint32_t)__popc(g->amask) << (2 * d);
-            for (uint32_t e = threadIdx.x; e < count; e += NT)
-                mt[g->lds + ((e >> (2 * d)) << (2 * d)) + ((e & n2) << d) + ((e >> d) & n2)] = src[e];
+            const BlkGate g = load_const(gates + gi);
+            if (g.kind != 1 || g.d < 4) continue;
+            const V *src = reinterpret_cast<const V *>(mats_g + g.mat);
+            const int d = g.d;
+            const uint32_t n2 = (1u << d) - 1, count = (uint32_t)__popc(g.amask) << (2 * d);
+            for (uint32_t e = threadIdx.x; e < count; e += NT) {
+                const uint32_t c = e & n2, i = (e >> d) & n2;
+                mt[g.lds + ((e >> (2 * d)) << (2 * d)) + (c << d) + (i ^ (matrix_swz(c) & n2))] = src[e];
+            }
         }
     }
     u4 *p16 = reinterpret_cast<u4 *>(psi_r);
     const uint32_t chunks = tile_amps >> S;
     const uint64_t glane = expand(threadIdx.x << S, s) >> S;
     const uint32_t slane = swz(threadIdx.x);
-    // One chunk per lane and slot when the tile is B * NT chunks (the default
-    // sizes): the next tile's loads are then issued before this tile's gates
-    // and wait in registers, so a workgroup always has a tile in flight.
-    const bool ahead = chunks == B * NT;
+    // One chunk per lane and slot (nb slots; a tile of fewer than NT chunks
+    // leaves lanes idle).  The next tile's loads are issued before this tile's
+    // gates and wait in registers, so a workgroup always has a tile in flight.
+    const int nb = NB ? NB : chunks > NT ? (int)(chunks / NT) : 1;
+    const bool mine = NB || threadIdx.x < chunks;
     auto base_of = [&](uint64_t t) { return p16 + (deposit_bits(t << s.w, s.hlowmask, s.nh) >> S) + glane; };
     uint64_t uoff[B];   // uniform
 #pragma unroll
     for (int u = 0; u < B; ++u) uoff[u] = expand((uint32_t)(u * NT) << S, s) >> S;
     u4 nxt[B];
-    if (ahead) {
-        const u4 *src = base_of(blockIdx.x);   // gridDim.x <= ntiles
+    auto load_ahead = [&](uint64_t t) {
+        const u4 *src = base_of(t);
+        if (!mine) return;
 #pragma unroll
-        for (int u = 0; u < B; ++u) nxt[u] = __builtin_nontemporal_load(src + uoff[u]);
-    }
+        for (int u = 0; u < B; ++u)
+            if (u < nb) nxt[u] = __builtin_nontemporal_load(src + uoff[u]);
+    };
+    load_ahead(blockIdx.x);   // gridDim.x <= ntiles
     for (uint64_t t = blockIdx.x; t < s.ntiles; t += gridDim.x) {
         const uint64_t tbase = deposit_bits(t << s.w, s.hlowmask, s.nh);
         u4 *base16 = p16 + (tbase >> S) + glane;
         // ---- load (chunk c = c0 + lane)
-        if (ahead) {
+        if (mine) {
 #pragma unroll
-            for (int u = 0; u < B; ++u) lds16[slane ^ swz(u * NT)] = nxt[u];
-        } else {
-            for (uint32_t c = threadIdx.x; c < chunks; c += NT)
-                lds16[swz(c)] = __builtin_nontemporal_load(base16 + (expand((c - threadIdx.x) << S, s) >> S));
+            for (int u = 0; u < B; ++u)
+                if (u < nb) lds16[slane ^ swz(u * NT)] = nxt[u];
         }
         // ---- the segment's operations (a run of tables counts as one), in
         // order.  The first tables are built before the next tile's loads are
         // issued: loads return in order, so a phase read after them would wait
         // for them.
         uint32_t gi = s.g0;
-        if (gates[gi].kind == 2) {
-            build_tables<R, NT>(area, gates, gates + gi, ent, members, tabs, tbase);
-            ++gi;
+        BlkGate g = load_const(gates + gi);
+        if (g.kind == 2) {
+            build_tables<R, NT>(area, gates, g, ent, members, tabs, tbase);
+            g = load_const(gates + ++gi);   // a table of it
         }
-        if (ahead && t + gridDim.x < s.ntiles) {
-            const u4 *src = base_of(t + gridDim.x);
-#pragma unroll
-            for (int u = 0; u < B; ++u) nxt[u] = __builtin_nontemporal_load(src + uoff[u]);
-        }
+        if (t + gridDim.x < s.ntiles) load_ahead(t + gridDim.x);
         __syncthreads();
         while (gi < s.g1) {
-            CPtr<BlkGate> g = gates + gi;
-            if (g->kind == 0) {
-                diag_run<R, S, NT>(tile, area, g, ent, tile_amps);
-                gi += (uint32_t)g->run;
+            CPtr<BlkEnt> e = ent + gi * kBlkEnts;
+            if (g.kind == 0) {
+                diag_run<R, S, NT>(tile, area, gates + gi, e, g.run, tile_amps);
+                gi += (uint32_t)g.run;
             } else {
-                if (g->kind == 2) {
+                if (g.kind == 2) {
                     build_tables<R, NT>(area, gates, g, ent, members, tabs, tbase);
                 } else {
-                    switch (g->d) {
-                        case 1: block_in_tile<1, R, S, NT>(tile, g, ent, mats, tbase); break;
-                        case 2: block_in_tile<2, R, S, NT>(tile, g, ent, mats, tbase); break;
-                        case 4: if (MF) mfma_in_tile<4, R, S, NT>(tile, g, ent, mt, tbase); break;
-                        case 5: if (MF) mfma_in_tile<5, R, S, NT>(tile, g, ent, mt, tbase); break;
-                        default: block_in_tile<3, R, S, NT>(tile, g, ent, mats, tbase); break;
+                    const uint32_t tnum = (uint32_t)t;
+                    switch (g.d) {
+                        case 1: block_in_tile<1, R, S, NT>(tile, g, e, mats, tnum); break;
+                        case 2: block_in_tile<2, R, S, NT>(tile, g, e, mats, tnum); break;
+                        case 4: if (MF) mfma_in_tile<4, R, S, NT>(tile, g, e, mt, tnum); break;
+                        case 5: if (MF) mfma_in_tile<5, R, S, NT>(tile, g, e, mt, tnum); break;
+                        default: block_in_tile<3, R, S, NT>(tile, g, e, mats, tnum); break;
                     }
                 }
                 ++gi;
             }
+            if (gi < s.g1) g = load_const(gates + gi);
             __syncthreads();
         }
         // ---- store
-        if (ahead) {
+        if (NB) {
+            u4 out[B];
+#pragma unroll
+            for (int u = 0; u < B; ++u) out[u] = lds16[slane ^ swz(u * NT)];
+#pragma unroll
+            for (int u = 0; u < B; ++u) __builtin_nontemporal_store(out[u], base16 + uoff[u]);
+        } else if (mine) {
 #pragma unroll
             for (int u = 0; u < B; ++u)
-                __builtin_nontemporal_store(lds16[slane ^ swz(u * NT)], base16 + uoff[u]);
-        } else {
-            for (uint32_t c = threadIdx.x; c < chunks; c += NT)
-                __builtin_nontemporal_store(lds16[swz(c)], base16 + (expand((c - threadIdx.x) << S, s) >> S));
+                if (u < nb) __builtin_nontemporal_store(lds16[slane ^ swz(u * NT)], base16 + uoff[u]);
         }
         __syncthreads();   // the next tile overwrites LDS
     }
 }
 
-template <typename R, int NT, bool MF>
-hipError_t launch_nt(R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, size_t lds, hipStream_t stream) {
-    static const hipError_t attr = hipFuncSetAttribute((const void *)k_blocked<R, NT, MF>,
+template <typename R, int NT, bool MF, int NB>
+hipError_t launch_nb(R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, size_t lds, hipStream_t stream) {
+    static const hipError_t attr = hipFuncSetAttribute((const void *)k_blocked<R, NT, MF, NB>,
                                                        hipFuncAttributeMaxDynamicSharedMemorySize, kBlkMaxLds);
     if (attr != hipSuccess) return attr;
-    hipLaunchKernelGGL((k_blocked<R, NT, MF>), dim3(grid), dim3(NT), lds, stream, psi, (const R *)p.mats,
+    hipLaunchKernelGGL((k_blocked<R, NT, MF, NB>), dim3(grid), dim3(NT), lds, stream, psi, (const R *)p.mats,
                        (const R *)p.tabs, p.gates, p.ent, p.members, s);
     return hipGetLastError();
+}
+
+// Whole and half tiles have kernels of their own at the workgroup sizes in use
+// (half: complex64 below the largest tile, and two workgroups with matrices).
+template <typename R, int NT, bool MF>
+hipError_t launch_nt(R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, size_t lds, hipStream_t stream) {
+    constexpr int B = (int)(kBlkTileBytes / 16) / NT;
+    const size_t tile = (2 * sizeof(R)) << s.tb;
+    if constexpr (MF || NT == 512) {
+        if (tile == kBlkTileBytes) return launch_nb<R, NT, MF, B>(psi, p, s, grid, lds, stream);
+        if (tile == kBlkTileBytes / 2) return launch_nb<R, NT, MF, B / 2>(psi, p, s, grid, lds, stream);
+    }
+    if constexpr (MF && NT == 512) return hipErrorInvalidValue;   // at least half a tile
+    else return launch_nb<R, NT, MF, 0>(psi, p, s, grid, lds, stream);
 }
 
 template <typename R>
 hipError_t launch_r(R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, size_t lds,
                     hipStream_t stream) {
-    if (s.lds_mats) return launch_nt<R, kGroupThreads, true>(psi, p, s, grid, lds, stream);
+    if (s.lds_mats)
+        return s.nt == 512 ? launch_nt<R, 512, true>(psi, p, s, grid, lds, stream)
+                           : launch_nt<R, kGroupThreads, true>(psi, p, s, grid, lds, stream);
     switch (s.nt) {
         case 256: return launch_nt<R, 256, false>(psi, p, s, grid, lds, stream);
         case 512: return launch_nt<R, 512, false>(psi, p, s, grid, lds, stream);
@@ -441,7 +493,7 @@ cast_status launch_blocked(void *psi, cast_dtype dt, const BlkPtrs &p, const Blk
     // allows no more), each looping over tiles with the next one's loads in
     // flight
     uint64_t grid = s.ntiles;
-    const uint64_t cap = std::min<uint64_t>(tuning().max_grid[dt], s.lds_mats ? 256 : 512);
+    const uint64_t cap = std::min<uint64_t>(tuning().max_grid[dt], s.nt == kGroupThreads && s.lds_mats ? 256 : 512);
     if (grid > cap) grid = cap;
     const hipError_t e = dt == CAST_C128 ? launch_r<double>((double *)psi, p, s, (uint32_t)grid, lds, stream)
                                          : launch_r<float>((float *)psi, p, s, (uint32_t)grid, lds, stream);

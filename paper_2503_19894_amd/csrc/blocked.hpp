@@ -38,29 +38,40 @@ constexpr int kBlkMinWindow = 4;   // smallest window: runs of >= 16 amplitudes
 //   kind 1  a fused gate's blocks of 2^d x 2^d.
 //   kind 2  builds the phase tables up to the next kind 2 (one or more runs,
 //           as many as the table area holds).
-struct BlkGate {
+// A record is read whole, in one go, by scalar loads: what the kernel needs of
+// a gate is worked out here rather than derived, load by load, for every tile
+// (a 27-qubit QFT, complex64, six passes: 5.35 -> 4.66 ms; a 12-qubit random
+// circuit in one launch: 41 -> 34 us).
+struct alignas(128) BlkGate {
     int kind;
-    int k, d;                // targets (phase table: its tile bits)
-    int q[8];                // sorted targets
-    int tpos[8];             // tile bit of each target, -1 when the target is outside the tile
-    // blocks
-    uint32_t colv[6];        // virtual coordinates of local index bit s (the columns of L^-1)
-    uint32_t span[kGroupMaxD]; // tile offset of virtual basis vector i < d
-    uint32_t amask;          // bit b: block b is not the identity (its matrices lie in block order)
-    uint32_t nlane, nuni;    // coset bits given by the lane, and by the wave and iteration
-    uint64_t lanepos;        // tile bit of lane bit i (8 bits each)
-    uint64_t mat;            // offset (reals) of the matrices in the fused list's buffer
-    // entry table: blocks, the 2^nuni uniform coset parts; phase table, the
-    // uniform local index of each iteration over the tile; kind 2, its work
-    // units
-    uint32_t ent, nent;
+    int d;
+    int run;                 // phase table: tables applied together from here (0 inside a run)
+    uint32_t nuni, nlane;    // blocks: coset bits given by the wave and iteration, and by the lane
+    uint32_t amask;          // blocks: bit b: block b is not the identity (its matrices lie in block order)
     // first entry in LDS: phase table, in the table area, a multiple of its
     // 2^k entries; blocks of d >= 4, in the matrices
     uint32_t lds;
-    // phase table
-    int run;                 // tables applied together from here (0 inside a run)
-    uint32_t m0, m1;         // its gates [m0, m1) of the member table
+    uint32_t ent, nent;      // kind 2: its work units in the entry table
+    uint32_t span[kGroupMaxD];  // blocks: LDS element of virtual basis vector i < d
+    uint64_t mat;            // blocks: offset (reals) of the matrices in the fused list's buffer
+    union {
+        struct {
+            uint32_t lane[6];    // blocks: LDS element of lane bit i < nlane
+            uint32_t par[6];     // blocks: bit b of the virtual coordinates that the tile fixes is the
+                                 // parity of the tile number's bits par[b]
+        };
+        struct {
+            int k;               // phase table: its tile bits
+            int pos[8];          // and their places
+            uint32_t m0, m1;     // its gates [m0, m1) of the member table
+        };
+    };
 };
+static_assert(sizeof(BlkGate) == 128, "two scalar loads of 16 words");
+// Entries of operation g start at g * kBlkEnts: blocks, the 2^nuni uniform
+// coset parts; phase table, the uniform local index of each iteration over the
+// tile.  The work units of kind 2 follow those of every operation.
+constexpr uint32_t kBlkEnts = 64;
 struct BlkEnt {
     uint32_t u, a;           // blocks: virtual coordinates, LDS element; phase table: local index;
                              // kind 2: phase table (gate index), 64-entry slice
@@ -75,11 +86,12 @@ struct BlkMember {           // a diagonal gate of a phase table
 // LDS of a segment pass: the tile, then the table area; 80 KiB together, so
 // two workgroups share a compute unit's 160 KiB.  Tables of 2^7 entries: three
 // of them take a QFT run's targets with all other bits of a tile.
+constexpr uint32_t kBlkTileBytes = 64u << 10;   // the largest
 constexpr uint32_t kBlkAreaBytes = 16u << 10;
 constexpr int kBlkTabBits = 7;
 // With dense blocks: one workgroup of kGroupThreads and the matrices besides.
 constexpr uint32_t kBlkMaxLds = 160u << 10;
-constexpr uint32_t kBlkMatBytes = kBlkMaxLds - (64u << 10) - kBlkAreaBytes;
+constexpr uint32_t kBlkMatBytes = kBlkMaxLds - kBlkTileBytes - kBlkAreaBytes;
 constexpr int kGroupThreads = 1024;
 constexpr uint32_t kBlkRunMax = 8;
 

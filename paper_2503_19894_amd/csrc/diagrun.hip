@@ -437,16 +437,23 @@ PhaseTable combine(const PhaseTable &a, const PhaseTable &b, double tol) {
     for (int i = 0; i < t.k; ++i) t.q[i] = u[i];
     const uint32_t D = 1u << t.k;
     t.ph.resize(D);
-    for (uint32_t j = 0; j < D; ++j) {
-        // bits of j at a's and b's qubits
-        uint32_t ja = 0, jb = 0;
+    // each bit's place in a's and b's indices, then the indices by the lowest
+    // set bit of j (a list's first call merges hundreds of tables)
+    uint32_t pa[kRunMaxQ * 2] = {0}, pb[kRunMaxQ * 2] = {0};
+    for (int s = 0; s < t.k; ++s) {
         for (int i = 0; i < a.k; ++i)
-            for (int s = 0; s < t.k; ++s)
-                if (t.q[s] == a.q[i] && ((j >> s) & 1u)) ja |= 1u << i;
+            if (a.q[i] == t.q[s]) pa[s] = 1u << i;
         for (int i = 0; i < b.k; ++i)
-            for (int s = 0; s < t.k; ++s)
-                if (t.q[s] == b.q[i] && ((j >> s) & 1u)) jb |= 1u << i;
-        t.ph[j] = snap_one(a.ph[ja] * b.ph[jb], tol);
+            if (b.q[i] == t.q[s]) pb[s] = 1u << i;
+    }
+    std::vector<uint32_t> ja(D, 0), jb(D, 0);
+    for (uint32_t j = 0; j < D; ++j) {
+        if (j) {
+            const int s = __builtin_ctz(j);
+            ja[j] = ja[j & (j - 1)] | pa[s];
+            jb[j] = jb[j & (j - 1)] | pb[s];
+        }
+        t.ph[j] = snap_one(a.ph[ja[j]] * b.ph[jb[j]], tol);
     }
     return t;
 }

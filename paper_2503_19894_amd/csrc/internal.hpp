@@ -155,8 +155,11 @@ cast_status launch_pass(void *psi, int n, cast_dtype dt, const PassPlan &p, cons
 // Uploads a plan's matrices (cast to dt) into a new device buffer; the host
 // staging is synchronous (the buffer is ready when this returns).
 cast_status upload_plan(const PassPlan &p, cast_dtype dt, DeviceMatrix *out);
+// `tail`: further bytes for the same allocation and copy, at a multiple of 256
+// (*tail_at); the block is then larger than the matrices alone.
 cast_status upload_plans(const std::vector<PassPlan> &ps, cast_dtype dt, DeviceMatrix *out,
-                         std::vector<size_t> *offsets);
+                         std::vector<size_t> *offsets, const std::vector<char> *tail = nullptr,
+                         size_t *tail_at = nullptr);
 // The offsets (in reals) upload_plans gives each plan, computed on the host.
 std::vector<size_t> plan_offsets(const std::vector<PassPlan> &ps, cast_dtype dt);
 
