@@ -4,8 +4,9 @@
 Workload: 30-qubit QFT (30 H + 435 controlled-phase + 15 SWAP gates) applied
 to a random normalised state with i.i.d. complex Gaussian amplitudes, after
 host fusion with k_max = 5.  One step = one application of the whole fused
-circuit (every fused gate = one in-place pass over the 2^30 amplitudes), with
-the state already resident in HBM.  Before the warmup the passes' launch
+circuit (every fused gate = one in-place pass over the 2^30 amplitudes; the
+library's default of passes sharing a launch, knob tile_groups, is off here and
+timed beside it as "grouped"), with the state already resident in HBM.  Before the warmup the passes' launch
 shapes are measured on the state (circuit_tune, extras.<dtype>.tune),
 which is then drawn again from its seed; marker dispatches bracket the timed
 steps so that kernel traces can be cut to them (--summarize-kernel-trace on a
@@ -29,6 +30,9 @@ extras.c128.dense_equivalent_gbs.  The line also carries:
   blocked      -- the same fused QFT cache-blocked (several fused gates per
                   HBM pass, apply_circuit_blocked): ms per step and HBM passes
                   for both dtypes (details under extras.<dtype>.blocked);
+  grouped      -- the same fused QFT by apply_circuit as it runs by default
+                  (passes that fit one LDS tile share a launch): ms per step
+                  for both dtypes;
   extras       -- the complex64 run and per-kernel breakdowns.
 """
 import argparse
@@ -168,6 +172,7 @@ def run_gpu(n, k_max, dtype_name, steps, warmup, seed=0, tune_reps=3):
         "event_ms_per_step": float(per_pass.sum()),
         "kernels": kern, "dominant": dominant, "tune": tune,
     }
+    out["grouped"] = run_grouped(sv, fc, dtype, steps, warmup, out["ms_per_step"])
     out["blocked"] = run_blocked(sv, psi, fc, n, dtype, state_bytes, steps, warmup, out["ms_per_step"])
     del sv, psi
     torch.cuda.empty_cache()
@@ -417,6 +422,25 @@ def run_sweep(ns=(28, 30), reps=5):
             del sv, psi
             torch.cuda.empty_cache()
     return rows
+
+
+def run_grouped(sv, fc, dtype, steps, warmup, per_pass_ms):
+    """apply_circuit with passes sharing launches (tile_groups, its default)."""
+    import torch
+
+    import paper_2503_19894_amd as cast
+
+    cast.set_tuning("tile_groups", 1, dtype)
+    for _ in range(max(warmup, 1)):
+        sv.apply_circuit(fc)
+    torch.cuda.synchronize()
+    t0 = time.perf_counter()
+    for _ in range(steps):
+        sv.apply_circuit(fc)
+    torch.cuda.synchronize()
+    ms = (time.perf_counter() - t0) / steps * 1e3
+    cast.set_tuning("tile_groups", 0, dtype)
+    return {"ms_per_step": ms, "speedup_vs_per_pass": per_pass_ms / ms}
 
 
 def run_blocked(sv, psi, fc, n, dtype, state_bytes, steps, warmup, per_pass_ms):
@@ -961,6 +985,10 @@ def main():
         dst.copy_(src)
         torch.cuda.synchronize()
         del src, dst
+    import paper_2503_19894_amd as cast
+
+    for dt in (torch.complex64, torch.complex128):
+        cast.set_tuning("tile_groups", 0, dt)   # one launch per pass: what the per-pass figures measure
     if args.tfim_only:
         print(json.dumps(run_tfim(oracle_check=False)), flush=True)
         return
@@ -1036,6 +1064,8 @@ def main():
         "vqa_grads_per_s": None if vqa is None else vqa_summary(vqa),
         "blocked": {d: {"ms_per_step": round(r["blocked"]["ms_per_step"], 3), "hbm_passes": r["blocked"]["hbm_passes"],
                         "speedup_vs_per_pass": round(r["blocked"]["speedup_vs_per_pass"], 3)}
+                    for d, r in (("c128", main_run), ("c64", extras.get("c64"))) if r},
+        "grouped": {d: {k: round(v, 3) for k, v in r["grouped"].items()}
                     for d, r in (("c128", main_run), ("c64", extras.get("c64"))) if r},
         "extras": {"c128": main_run, **extras, "vqa": vqa, "dense32": dense, "tfim_mixed": tfim},
     }

@@ -215,7 +215,8 @@ cast_status circuit_pass_info(const cast_fused *f, int n, cast_dtype dt, size_t 
  * rotation at or above the order's bit count is ignored.  Which rate a shape reaches depends on how the gate's planes
  * fall onto the DRAM channels and banks, so no one knob value suits every
  * pass (the paper's cost model is likewise measured, Sec. III-C).  The shape is kept
- * per pass in the list's schedule for (n, dt); -1 means the knob's value
+ * per pass in the list's schedule for (n, dt), and is used where the pass has
+ * a launch of its own (tile_groups); -1 means the knob's value
  * (direct_rot / direct_chunk_log).  Every shape computes each amplitude with
  * the same operations, so results are bitwise the same whatever the shape.
  * A schedule rebuilt after a change of diag_run_tables, diag_run_qubits or

@@ -487,11 +487,16 @@ cast_status check(const cast_sv *sv) {
 //   a pass    3.8 (direct, diagonal) to 6.5 (through LDS) on any small state,
 //             then its bytes at 5.4 TB/s or its products at 60 / 120 TFLOP/s;
 //   a group   5 + the longer of the state's read and write at 5.2 TB/s and
-//             its operations, + 0.3 of the shorter.  An operation occupies a
+//             its operations, + 0.3 of the shorter (up to 256 tiles, a
+//             compute unit has one: their sum, tile by tile at 0.1 TB/s, and
+//             operations but for the matrix cores' take 1.2 as long).  An
+//             operation occupies a
 //             compute unit for, per tile of 2^12 amplitudes: a table 0.3,
-//             d = 1 0.7, d = 2 0.8, d = 3 1.1, d = 4 / 5 3.0 / 5.3
-//             (complex64: 1.5 / 2.8, matrix cores); never less than 0.8, 1.6
-//             or 2.6 (its barriers and first reads).
+//             d = 1 0.7, d = 2 0.8, d = 3 1.1, and per tile of any size 0.1;
+//             d = 4 / 5 3.0 / 5.3 (complex64: 1.5 / 2.8, matrix cores); never
+//             less than 0.8, 1.6 or 2.6 (its barriers and first reads), nor
+//             per tile than 0.55 of these for d = 4 and 5 (sixteen cosets are
+//             a wave's: small tiles leave matrix cores idle).
 struct Span {
     size_t a, b;          // schedule passes [a, b)
     uint64_t need;
@@ -519,10 +524,12 @@ double group_us(const Schedule &sc, const std::vector<PassPlan> &P, size_t a, si
         const int d = sp.kind == 6 ? 0 : P[sp.first].d;
         double t = op_us[d] * scale;
         if (sp.kind == 6) t *= (double)sp.tabs.size();
-        if (d >= 4 && sc.dt == CAST_C64) t *= 0.52;
+        if (d < 4) t = 0.1 + (tiles <= 256 ? 1.2 * t : t);
+        if (d >= 4) t = std::max(t, 0.55 * op_us[d]) * (sc.dt == CAST_C64 ? 0.52 : 1.0);
         ops += std::max(least_us[d], t * std::max(1.0, tiles / 256));
     }
     const double mem = 2 * std::ldexp((double)amp_bytes(sc.dt), sc.n) / 5.2e6;
+    if (tiles <= 256) return 5.0 + std::max(mem, 2 * std::ldexp((double)amp_bytes(sc.dt), tb) / 1e5) + ops;
     return 5.0 + std::max(mem, ops) + 0.3 * std::min(mem, ops);
 }
 
