@@ -65,10 +65,13 @@ __global__ void __launch_bounds__(kRedThreads) k_pauli_inner(const R *__restrict
     }
 }
 
-// One block: out[v] = sum over rows of partial[row][v], v < nvals, fixed order.
+// Block i: out[v] = sum over rows of partial[row][v], v < nvals, fixed order, of
+// the i-th set of partials; its results lie i sets before the first's.
 __global__ void __launch_bounds__(kRedThreads) k_finish(const double *__restrict__ partial, int rows, int nvals,
                                                        double *__restrict__ out) {
     __shared__ double red[kRedThreads];
+    partial += (size_t)blockIdx.x * rows * nvals;
+    out -= (size_t)blockIdx.x * nvals;
     for (int v = 0; v < nvals; ++v) {
         double s = 0.0;
         for (int b = threadIdx.x; b < rows; b += blockDim.x) s += partial[(size_t)b * nvals + v];
@@ -91,20 +94,30 @@ static int red_blocks(int n) {
     return (int)b;
 }
 
-cast_status pauli_inner(const void *a, const void *b, int n, cast_dtype dt, uint64_t x, uint64_t z, double *scratch,
-                        double *dev_out, hipStream_t s) {
+size_t inner_partials(int n) { return 2 * (size_t)red_blocks(n); }
+
+static cast_status reduce_error() {
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return fail(CAST_EHIP, std::string("reduction launch: ") + hipGetErrorString(e));
+    return CAST_OK;
+}
+
+cast_status pauli_inner(const void *a, const void *b, int n, cast_dtype dt, uint64_t x, uint64_t z, double *partials,
+                        hipStream_t s) {
     const int blocks = red_blocks(n);
     const uint64_t N = 1ull << n;
     if (dt == CAST_C128)
         hipLaunchKernelGGL(k_pauli_inner<double>, dim3(blocks), dim3(kRedThreads), 0, s, (const double *)a,
-                           (const double *)b, N, x, z, scratch);
+                           (const double *)b, N, x, z, partials);
     else
         hipLaunchKernelGGL(k_pauli_inner<float>, dim3(blocks), dim3(kRedThreads), 0, s, (const float *)a,
-                           (const float *)b, N, x, z, scratch);
-    hipLaunchKernelGGL(k_finish, dim3(1), dim3(kRedThreads), 0, s, scratch, blocks, 2, dev_out);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return fail(CAST_EHIP, std::string("reduction launch: ") + hipGetErrorString(e));
-    return CAST_OK;
+                           (const float *)b, N, x, z, partials);
+    return reduce_error();
+}
+
+cast_status finish_inner(const double *partials, int n, int count, double *dev_out, hipStream_t s) {
+    hipLaunchKernelGGL(k_finish, dim3(count), dim3(kRedThreads), 0, s, partials, red_blocks(n), 2, dev_out);
+    return reduce_error();
 }
 
 // ------------------------------------------------------------------ expval
