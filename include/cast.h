@@ -101,9 +101,11 @@ cast_status sv_info(const cast_sv *sv, void **dev_ptr, int *n, cast_dtype *dt);
 /* Applies one k-qubit gate (1 <= k <= 6; Eq. 3) in place: each group of 2^k
  * amplitudes that agree off `qubits` is multiplied by `matrix`.  The matrix is
  * analysed on the host (zero/one snapping, XOR-subspace block structure) and
- * copied to the device in the state's dtype; zero blocks are skipped and
- * identity blocks are neither read nor written.  Queued on the state's stream
- * (the staging buffer is kept alive by the library until the work is done). */
+ * passed to the device in the state's dtype; zero blocks are skipped and
+ * identity blocks are neither read nor written.  Queued on the state's stream;
+ * the matrix is consumed when it returns (up to 1 KiB of blocks travel with the
+ * launch, without a wait; larger ones through a buffer that the library keeps
+ * alive until the work is done).  Not for a stream that is being captured. */
 cast_status apply_gate(cast_sv *sv, const int *qubits, int k, const double *matrix);
 
 /* Fills `out` (2 * 4^k doubles) with the matrix of a standard gate, in the

@@ -356,8 +356,8 @@ class FusedCircuit:
         return self
 
     def predict_ms(self, dtype, path):
-        """Predicted device time of apply_circuit (path 0) or
-        apply_circuit_blocked (path 1) under the measured path costs."""
+        """Predicted device time of apply_circuit (path 0, one launch per
+        pass) or apply_circuit_blocked (path 1) under the measured path costs."""
         v = ctypes.c_double()
         predict_ms(self.handle, self.n, C128 if dtype == torch.complex128 else C64, int(path), ctypes.byref(v))
         return v.value
@@ -399,7 +399,8 @@ class FusedCircuit:
         return {"kernel": kern.value, "d": d.value, "alg_bytes": b.value, "flops": f.value}
 
     def num_passes(self, dtype):
-        """Device passes apply_circuit makes for this dtype (current knobs)."""
+        """Device passes of apply_circuit for this dtype (current knobs; with
+        tile_groups several may share a launch)."""
         dt = C128 if dtype == torch.complex128 else C64
         npass = ctypes.c_size_t()
         circuit_passes(self.handle, self.n, dt, ctypes.byref(npass))
