@@ -198,6 +198,18 @@ _GATE_REC = np.dtype({"names": [f for f, _ in cast_gate._fields_],
                       "itemsize": ctypes.sizeof(cast_gate)})
 
 
+def _int32(values):
+    """int(v) of each value as a C int array; like a ctypes field, it keeps the
+    low 32 bits."""
+    try:
+        a = np.array(values)
+    except ValueError:
+        a = None
+    if a is None or a.dtype != np.int64 or a.ndim != 1:   # floats, texts, integers past 64 bits, nested values
+        a = np.array([int(v) & 0xffffffff for v in values], dtype=np.int64)
+    return a.astype(np.int32)
+
+
 class GateArray:
     """cast_gate[] for a list of gate records (keeps matrices alive)."""
 
@@ -210,11 +222,15 @@ class GateArray:
         for g in gates:
             q, p = g.qubits, int(getattr(g, "param", -1))
             kq = len(q)
+            if kq > 6:
+                raise IndexError("a gate record holds at most six qubits")
+            if not -0x80000000 <= p < 0x80000000:
+                p = int(_int32([p])[0])
             k.append(kq)
             qubits.extend(q)
             qubits.extend((0,) * (6 - kq))
             param.append(p)
-            coeff.append(getattr(g, "coeff", 1.0))
+            coeff.append(float(getattr(g, "coeff", 1.0)))
             if p >= 0:
                 generator.append(_GEN[g.name])
                 matrix.append(0)
@@ -225,15 +241,21 @@ class GateArray:
                 self._keep.append(m)
                 matrix.append(m.ctypes.data)
                 continue
-            key = (g.name, tuple(g.params))
-            if key not in std:
+            try:
+                key = (g.name, tuple(g.params))
+                hit = std.get(key)
+            except TypeError:   # angles that cannot be hashed (0-d arrays)
+                key = hit = None
+            if hit is None:
                 m = std_matrix(g.name, g.params)
                 self._keep.append(m)
-                std[key] = m.ctypes.data
-            matrix.append(std[key])
+                hit = m.ctypes.data
+                if key is not None:
+                    std[key] = hit
+            matrix.append(hit)
         if n:
             rec["k"], rec["param_id"], rec["param_coeff"] = k, param, coeff
-            rec["qubits"] = np.array(qubits).astype(np.int32).reshape(n, 6)
+            rec["qubits"] = _int32(qubits).reshape(n, 6)
             rec["matrix"], rec["generator"] = matrix, generator
         self.arr = (cast_gate * max(1, n)).from_buffer(rec)
         self.n = n
@@ -253,8 +275,8 @@ def pauli_terms(terms):
             if p in "YZ":
                 z |= 1 << q
         coeff.append(float(t.coeff))
-        xmask.append(x & 0xffffffffffffffff)
-        zmask.append(z & 0xffffffffffffffff)
+        xmask.append(int(x) & 0xffffffffffffffff)   # (qubits may be numpy integers)
+        zmask.append(int(z) & 0xffffffffffffffff)
     rec = np.zeros(max(1, len(terms)), dtype=_TERM_REC)
     if len(terms):
         rec["coeff"], rec["xmask"], rec["zmask"] = coeff, xmask, zmask
