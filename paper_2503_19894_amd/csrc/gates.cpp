@@ -96,4 +96,19 @@ bool standard_gate(const std::string &name, const double *p, int *k, std::vector
     return false;
 }
 
+bool unitary_gate(const cast_gate &g) {
+    if (!g.matrix) return false;
+    const int D = 1 << g.k;
+    for (int r = 0; r < D; ++r)
+        for (int c = r; c < D; ++c) {
+            cplx dot(r == c ? -1.0 : 0.0, 0.0);
+            for (int e = 0; e < D; ++e) {
+                const double *a = g.matrix + 2 * (r * D + e), *b = g.matrix + 2 * (c * D + e);
+                dot += cplx(a[0], a[1]) * cplx(b[0], -b[1]);
+            }
+            if (!(std::abs(dot) <= 1e-13)) return false;
+        }
+    return true;
+}
+
 }  // namespace cast

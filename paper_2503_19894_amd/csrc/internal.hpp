@@ -249,6 +249,9 @@ cast_status fuse(int n, std::vector<FusionGate> gates, const cast_fusion_opts &o
 bool standard_gate(const std::string &name, const double *params, int *k, std::vector<cplx> *m);
 // exp(-i a G / 2) for a Pauli string G (letters in 2-bit fields, see cast.h).
 std::vector<cplx> rotation_matrix(int k, int generator, double angle);
+// Whether a fixed gate's matrix is unitary up to the rounding of its entries
+// (no: NaN, and a missing matrix, which the caller reports).
+bool unitary_gate(const cast_gate &g);
 std::vector<cplx> pauli_string_matrix(int k, int generator);
 
 }  // namespace cast

@@ -98,14 +98,17 @@ cast_status adjoint_grad(const cast_sv *init, const cast_gate *gates, size_t n_g
     const int n = init->n;
     const cast_dtype dt = init->dt;
     hipStream_t s = init->stream;
-    // One- and two-qubit gates in complex128 run as segments, many gates per
-    // pass over psi and lambda; the launches below (four per gate as they were) bound
-    // small states (17 qubits, 204 gates: 4.6 ms).  complex64 keeps to one gate
-    // at a time: segments apply commuting gates in another order, and there
-    // each gate rounds the state to 24 bits, so the results would differ in the
-    // sixth digit.
-    if (dt == CAST_C128 && n >= 3 &&
-        std::all_of(gates, gates + n_gates, [](const cast_gate &g) { return g.k == 1 || g.k == 2; })) {
+    // One- and two-qubit unitaries in complex128 run as segments, many gates per
+    // pass over psi and lambda; the launches below, three per gate, bound
+    // small states (17 qubits, 204 gates: 4.6 ms with four of them, 0.56 as
+    // segments).  Segments apply commuting gates in another order.  complex64
+    // keeps the circuit's: there each gate rounds the state to 24 bits, so the
+    // results would differ in the sixth digit.  So does a list with a fixed
+    // gate that is not unitary: the sweep's U^dag does not undo it, so an inner
+    // product depends on whether that gate has been passed.
+    if (dt == CAST_C128 && n >= 3 && std::all_of(gates, gates + n_gates, [](const cast_gate &g) {
+            return (g.k == 1 || g.k == 2) && (g.param_id >= 0 || unitary_gate(g));
+        })) {
         const cast_status rc = adjoint_segments(init, gates, n_gates, theta, n_params, terms, n_terms, energy, grad);
         // (its partial sums, one per parameter and tile, may not fit)
         if (rc != CAST_ENOMEM) return rc;

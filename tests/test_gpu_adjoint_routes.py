@@ -1,0 +1,51 @@
+"""adjoint_grad's choice between segments and one gate at a time: fixed gates
+that are not unitary keep their place in the circuit's order, against the
+oracle's adjoint."""
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import oracle  # noqa: E402
+import paper_2503_19894_amd as cast  # noqa: E402
+from circuits import Gate, PauliTerm, haar_unitary, random_state  # noqa: E402
+
+
+def _matrix(kind, rng):
+    if kind == "projector":
+        return np.diag([1.0, 0.0])
+    if kind == "damped":        # singular values 1 and 0.6
+        return haar_unitary(2, rng) @ np.diag([1.0, 0.6]) @ haar_unitary(2, rng)
+    if kind == "diagonal":
+        return np.diag([1.0, 0.5, 0.7j, 1.0])
+    return rng.normal(size=(4, 4)) / 3 + 1j * rng.normal(size=(4, 4)) / 3
+
+
+@pytest.mark.parametrize("kind", ["projector", "damped", "diagonal", "general"])
+@pytest.mark.parametrize("n", [3, 7, 12])
+def test_gates_that_are_not_unitary(n, kind):
+    rng = np.random.default_rng([n, len(kind)])
+    m = _matrix(kind, rng)
+    gates, p = [Gate("u3", (q,), tuple(rng.uniform(-3, 3, 3))) for q in range(n)], 0
+    for _ in range(3):
+        qs = tuple(int(q) for q in rng.permutation(n)[:1 if m.shape[0] == 2 else 2])
+        gates.append(Gate("unitary", qs, matrix=m))
+        for q in rng.permutation(n):    # rotations on other qubits and on its own
+            gates.append(Gate(("rx", "ry", "rz")[rng.integers(3)], (int(q),), param=p, coeff=1.2))
+            p += 1
+        gates.append(Gate("rxx", (0, n - 1), param=p))
+        p += 1
+    theta = rng.uniform(-3, 3, p)
+    psi0 = random_state(n, seed=n, workload=17)
+    H = [PauliTerm(1.0, ((0, "Z"), (1, "X"))), PauliTerm(0.5, ((2, "Y"),)), PauliTerm(-0.7, ((0, "X"), (n - 1, "Z")))]
+    print(f"adjoint n={n} {kind} gates={len(gates)}", flush=True)
+    init = cast.StateVector(n, tensor=torch.tensor(psi0, dtype=torch.complex128, device="cuda"))
+    e, g = cast.adjoint(init, gates, theta, H)
+    ew, gw = oracle.adjoint_grad(n, gates, theta, H, psi0)
+    # each gate rounds psi and lambda by a few 2^-53; the matrices' norms are at most 3
+    tol = 1e-14 * len(gates) * 3.0 ** 6
+    assert abs(e - ew) <= tol and np.max(np.abs(g - gw)) <= tol
