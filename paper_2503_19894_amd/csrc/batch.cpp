@@ -817,8 +817,10 @@ cast_status adjoint_segments(const cast_sv *init, const cast_gate *gates, size_t
     const cast_dtype dt = init->dt;
     hipStream_t s = init->stream;
     // one instance has 2^(n - tb) items per step: smaller tiles below 19 qubits
-    // keep some 256 workgroups busy
-    const int tb = std::min(batch_tile_bits(dt), std::max(9, n - 8));
+    // keep some 256 workgroups busy; and whatever the knob asks for, psi's and
+    // lambda's tiles fit a launch's LDS
+    int tb = std::min(batch_tile_bits(dt), std::max(9, n - 8));
+    while (kSegLdsExtra + ((2 * amp_bytes(dt)) << tb) > kSegMaxLds) --tb;
     Program p;
     if (cast_status rc = plan_program(1, &n, dt, &gates, &n_gates, &n_params, &terms, &n_terms, &kind, &init, tb, 0.0,
                                       &p))

@@ -28,6 +28,7 @@ enum BatchKind : uint32_t { BK_FWD = 0, BK_HPSI = 1, BK_ADJ = 2 };
 constexpr int kSegMaxGates = 64;   // gates per segment (bounds the LDS reduction area)
 // LDS of a segment item beyond its two tiles: the inner products' per-wave sums
 constexpr size_t kSegLdsExtra = (size_t)kSegMaxGates * 4 * sizeof(double);
+constexpr size_t kSegMaxLds = 128u << 10;   // of a launch
 
 // Operations of a register sweep, in sweep coordinates (a thread holds eight
 // amplitudes x[j], bit i of j <-> the sweep's tile bit i).  Codes below 64

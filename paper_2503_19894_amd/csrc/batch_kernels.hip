@@ -893,10 +893,10 @@ template <typename R>
 static hipError_t allow_lds() {
     static hipError_t done = [] {
         hipError_t e = hipFuncSetAttribute((const void *)k_batch_step<R>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                           128 << 10);
+                                           (int)kSegMaxLds);
         if (e == hipSuccess)
             e = hipFuncSetAttribute((const void *)k_batch_persistent<R>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                    128 << 10);
+                                    (int)kSegMaxLds);
         return e;
     }();
     return done;
@@ -904,7 +904,7 @@ static hipError_t allow_lds() {
 
 cast_status batch_launch_step(const BatchDev &d, cast_dtype dt, int s, uint64_t nitems, size_t lds,
                               hipStream_t st) {
-    if (lds > (128u << 10)) return fail(CAST_EUNSUPPORTED, "segment tiles exceed 128 KiB of LDS");
+    if (lds > kSegMaxLds) return fail(CAST_EUNSUPPORTED, "segment tiles exceed 128 KiB of LDS");
     const hipError_t ae = dt == CAST_C128 ? allow_lds<double>() : allow_lds<float>();
     if (ae != hipSuccess) return fail(CAST_EHIP, std::string("LDS attribute: ") + hipGetErrorString(ae));
     if (dt == CAST_C128) hipLaunchKernelGGL(k_batch_step<double>, dim3((uint32_t)nitems), dim3(256), lds, st, d, s);
@@ -915,7 +915,7 @@ cast_status batch_launch_step(const BatchDev &d, cast_dtype dt, int s, uint64_t 
 cast_status batch_launch_persistent(const BatchDev &d, cast_dtype dt, uint64_t total_items, int grid,
                                     unsigned long long *counters, uint32_t spin_limit, uint32_t chunk, size_t lds,
                                     hipStream_t st) {
-    if (lds > (128u << 10)) return fail(CAST_EUNSUPPORTED, "segment tiles exceed 128 KiB of LDS");
+    if (lds > kSegMaxLds) return fail(CAST_EUNSUPPORTED, "segment tiles exceed 128 KiB of LDS");
     const hipError_t ae = dt == CAST_C128 ? allow_lds<double>() : allow_lds<float>();
     if (ae != hipSuccess) return fail(CAST_EHIP, std::string("LDS attribute: ") + hipGetErrorString(ae));
     if (dt == CAST_C128)

@@ -1,6 +1,6 @@
 """adjoint_grad's choice between segments and one gate at a time: fixed gates
-that are not unitary keep their place in the circuit's order, against the
-oracle's adjoint."""
+that are not unitary keep their place in the circuit's order, and every tile
+size that the knob allows is taken, against the oracle's adjoint."""
 import numpy as np
 import pytest
 
@@ -12,7 +12,7 @@ if not torch.cuda.is_available():
 
 import oracle  # noqa: E402
 import paper_2503_19894_amd as cast  # noqa: E402
-from circuits import Gate, PauliTerm, haar_unitary, random_state  # noqa: E402
+from circuits import Gate, PauliTerm, haar_unitary, hea_vqa, random_state, vqa_hamiltonian  # noqa: E402
 
 
 def _matrix(kind, rng):
@@ -48,4 +48,24 @@ def test_gates_that_are_not_unitary(n, kind):
     ew, gw = oracle.adjoint_grad(n, gates, theta, H, psi0)
     # each gate rounds psi and lambda by a few 2^-53; the matrices' norms are at most 3
     tol = 1e-14 * len(gates) * 3.0 ** 6
+    assert abs(e - ew) <= tol and np.max(np.abs(g - gw)) <= tol
+
+
+@pytest.mark.parametrize("bits", [4, 9, 11, 12])
+def test_tile_knob(bits):
+    """batch_tile_bits 12 holds for batches of complex64 instances; psi and
+    lambda in complex128 would take more LDS than a launch has."""
+    n = 20
+    gates, P = hea_vqa(n, 1)
+    theta = np.random.default_rng(bits).uniform(-3, 3, P)
+    H = vqa_hamiltonian(n)
+    old = cast.get_tuning("batch_tile_bits", torch.complex128)
+    try:
+        cast.set_tuning("batch_tile_bits", bits, torch.complex128)
+        print(f"adjoint n={n} tile bits {bits}", flush=True)
+        e, g = cast.adjoint(cast.StateVector(n), gates, theta, H)
+    finally:
+        cast.set_tuning("batch_tile_bits", old, torch.complex128)
+    ew, gw = oracle.adjoint_grad(n, gates, theta, H)
+    tol = 1e-14 * len(gates) * sum(abs(t.coeff) for t in H)
     assert abs(e - ew) <= tol and np.max(np.abs(g - gw)) <= tol
