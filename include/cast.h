@@ -253,6 +253,17 @@ cast_status circuit_tune(cast_sv *sv, cast_fused *f, int reps, double *before_ms
 cast_status fused_pass_info(const cast_fused *f, size_t i, int n, cast_dtype dt, int *kernel, int *d,
                             double *alg_bytes, double *flops);
 
+/* Number of launches apply_circuit makes of that schedule with the current
+ * knobs (tile_groups; host only, builds and caches the grouping). */
+cast_status circuit_launches(const cast_fused *f, int n, cast_dtype dt, size_t *n_launches);
+
+/* Launch i of those: the fused gates [first, first + count) it applies, and
+ * for a tile group log2 of the amplitudes of a tile and the workgroup size
+ * (0, 0: a pass of the schedule).  Any output may be NULL.  CAST_EINVAL for i out of
+ * range. */
+cast_status circuit_launch_info(const cast_fused *f, int n, cast_dtype dt, size_t i, size_t *first, size_t *count,
+                                int *tile_bits, int *threads);
+
 /* Streaming reference for the rooflines: multiplies `bytes` of device memory
  * (16-byte aligned, a multiple of 16, read as doubles) in place by `factor`,
  * each of 256 lanes per workgroup moving chunks_per_lane (1, 2, 4 or 8)

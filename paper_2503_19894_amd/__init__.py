@@ -71,6 +71,10 @@ SIGNATURES = {
     "fused_destroy": (None, [ctypes.c_void_p]),
     "apply_circuit_timed": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_void_p, ctypes.POINTER(ctypes.c_float)]),
     "circuit_passes": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)]),
+    "circuit_launches": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.POINTER(ctypes.c_size_t)]),
+    "circuit_launch_info": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_size_t,
+                                           ctypes.POINTER(ctypes.c_size_t), ctypes.POINTER(ctypes.c_size_t),
+                                           _c_int_p, _c_int_p]),
     "circuit_pass_info": (ctypes.c_int, [ctypes.c_void_p, ctypes.c_int, ctypes.c_int, ctypes.c_size_t,
                                          ctypes.POINTER(ctypes.c_size_t), ctypes.POINTER(ctypes.c_size_t), _c_int_p,
                                          _c_int_p, _c_double_p, _c_double_p]),
@@ -441,6 +445,21 @@ class FusedCircuit:
                               ctypes.byref(kern), ctypes.byref(tabs), ctypes.byref(b), ctypes.byref(f))
             out.append({"first": first.value, "count": count.value, "kernel": kern.value, "tables": tabs.value,
                         "alg_bytes": b.value, "flops": f.value})
+        return out
+
+    def launches(self, dtype):
+        """The launches of apply_circuit (current knobs): fused gates covered,
+        and the tile and workgroup size of a tile group (0: a pass of its own)."""
+        dt = C128 if dtype == torch.complex128 else C64
+        nl = ctypes.c_size_t()
+        circuit_launches(self.handle, self.n, dt, ctypes.byref(nl))
+        out = []
+        for i in range(nl.value):
+            first, count = ctypes.c_size_t(), ctypes.c_size_t()
+            tb, nt = ctypes.c_int(), ctypes.c_int()
+            circuit_launch_info(self.handle, self.n, dt, i, ctypes.byref(first), ctypes.byref(count), ctypes.byref(tb),
+                                ctypes.byref(nt))
+            out.append({"first": first.value, "count": count.value, "tile_bits": tb.value, "threads": nt.value})
         return out
 
     def pass_shape(self, dtype, i):

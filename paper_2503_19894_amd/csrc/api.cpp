@@ -760,7 +760,7 @@ cast_status apply_circuit(cast_sv *sv, const cast_fused *fc) {
     if (tuning().tile_groups[sv->dt] && !f->plans.empty()) {
         if (cast_status rc = get_schedule(f, sv->n, sv->dt, false, &sc)) return rc;
         // without memory for the groups' tables the passes run one by one
-        if (cast_status rc = tile_groups(f, *sc, sv->dt, &groups); rc && rc != CAST_ENOMEM) return rc;
+        if (cast_status rc = tile_groups(f, *sc, sv->dt, true, &groups); rc && rc != CAST_ENOMEM) return rc;
     }
     if (!groups) {
         if (cast_status rc = prepare_circuit(sv, fc, &f, &sc)) return rc;
@@ -935,6 +935,41 @@ cast_status circuit_pass_info(const cast_fused *fc, int n, cast_dtype dt, size_t
         return CAST_OK;
     }
     return fused_pass_info(fc, sp.first, n, dt, nullptr, nullptr, alg_bytes, flops);
+}
+
+// The launches of apply_circuit under the current knobs (*groups NULL: the schedule's passes).
+static cast_status plan_launches(const cast_fused *fc, int n, cast_dtype dt, Schedule **sc, BlockedPlan **groups) {
+    if (!fc) return fail(CAST_EINVAL, "fused list is NULL");
+    if (dt != CAST_C64 && dt != CAST_C128) return fail(CAST_EINVAL, "bad dtype");
+    if (n != fc->n) return fail(CAST_EINVAL, "n differs from the fused list's");
+    cast_fused *f = const_cast<cast_fused *>(fc);
+    if (cast_status rc = get_schedule(f, n, dt, false, sc)) return rc;
+    *groups = nullptr;
+    if (tuning().tile_groups[dt] && !f->plans.empty()) return tile_groups(f, **sc, dt, false, groups);
+    return CAST_OK;
+}
+
+cast_status circuit_launches(const cast_fused *fc, int n, cast_dtype dt, size_t *n_launches) {
+    if (!n_launches) return fail(CAST_EINVAL, "NULL argument");
+    Schedule *sc;
+    BlockedPlan *groups;
+    if (cast_status rc = plan_launches(fc, n, dt, &sc, &groups)) return rc;
+    *n_launches = groups ? group_count(*groups) : sc->passes.size();
+    return CAST_OK;
+}
+
+cast_status circuit_launch_info(const cast_fused *fc, int n, cast_dtype dt, size_t i, size_t *first, size_t *count,
+                                int *tile_bits, int *threads) {
+    Schedule *sc;
+    BlockedPlan *groups;
+    if (cast_status rc = plan_launches(fc, n, dt, &sc, &groups)) return rc;
+    if (i >= (groups ? group_count(*groups) : sc->passes.size())) return fail(CAST_EINVAL, "launch index out of range");
+    const GroupInfo gi = groups ? group_info(*groups, i) : GroupInfo{sc->passes[i].first, sc->passes[i].count, 0, 0};
+    if (first) *first = gi.first;
+    if (count) *count = gi.count;
+    if (tile_bits) *tile_bits = gi.tile_bits;
+    if (threads) *threads = gi.threads;
+    return CAST_OK;
 }
 
 cast_status fused_pass_info(const cast_fused *f, size_t i, int n, cast_dtype dt, int *kernel, int *d,

@@ -586,9 +586,11 @@ std::vector<Span> plan_groups(const Schedule &sc, const std::vector<PassPlan> &P
 
 }  // namespace
 
-cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, BlockedPlan **out) {
+cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, bool upload, BlockedPlan **out) {
     BlockedPlan *&bp = f->groups[dt];
-    const int knob = tuning().blocked_tile_bits[dt];
+    // (an environment variable for both dtypes may ask for more than this one's tile)
+    const int most = 31 - __builtin_clz(kBlkTileBytes / (uint32_t)amp_bytes(dt));
+    const int knob = std::min(tuning().blocked_tile_bits[dt], most);
     if (bp && (bp->knob_tb != knob || bp->nt != blocked_threads(dt, bp->tb))) {
         blocked_free(bp);
         bp = nullptr;
@@ -614,7 +616,7 @@ cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, Blocke
         for (const Span &g : best) {
             if (!g.group) {
                 BlockedPlan::Pass ps;
-                ps.gate = g.a;
+                ps.first = sc.passes[g.a].first, ps.count = sc.passes[g.a].count, ps.gate = g.a;
                 p->passes.push_back(ps);
                 continue;
             }
@@ -626,12 +628,18 @@ cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, Blocke
         }
         bp = p;
     }
-    if (cast_status rc = upload_tables(f, bp, dt)) return rc;
+    if (upload)
+        if (cast_status rc = upload_tables(f, bp, dt)) return rc;
     *out = bp;
     return CAST_OK;
 }
 
 size_t group_count(const BlockedPlan &bp) { return bp.passes.size(); }
+
+GroupInfo group_info(const BlockedPlan &bp, size_t i) {
+    const BlockedPlan::Pass &ps = bp.passes[i];
+    return GroupInfo{ps.first, ps.count, ps.segment ? ps.seg.tb : 0, ps.segment ? ps.seg.nt : 0};
+}
 
 cast_status launch_group(cast_sv *sv, const cast_fused *f, const BlockedPlan &bp, size_t i, size_t *pass) {
     const BlockedPlan::Pass &ps = bp.passes[i];

@@ -481,14 +481,15 @@ hipError_t launch_r(R *psi, const BlkPtrs &p, const BlkSeg &s, uint32_t grid, si
 }  // namespace
 
 int blocked_threads(cast_dtype dt, int tb) {
-    int nt = tuning().blocked_threads[dt];
+    int nt = tuning().blocked_threads[dt];   // (an environment variable's may be any number)
+    if (nt != 256 && nt != 512) nt = 1024;
     while (nt > 256 && ((size_t)1 << tb) < (size_t)nt) nt >>= 1;   // at least one amplitude per thread
     return nt;
 }
 
 cast_status launch_blocked(void *psi, cast_dtype dt, const BlkPtrs &p, const BlkSeg &s, hipStream_t stream) {
-    const size_t lds = ((size_t)1 << s.tb) * amp_bytes(dt) + s.lds_tabs + s.lds_mats;
-    if (lds > kBlkMaxLds) return fail(CAST_EUNSUPPORTED, "tile and gate tables exceed a compute unit's LDS");
+    const size_t tile = ((size_t)1 << s.tb) * amp_bytes(dt), lds = tile + s.lds_tabs + s.lds_mats;
+    if (tile > kBlkTileBytes || lds > kBlkMaxLds) return fail(CAST_EUNSUPPORTED, "tile and gate tables exceed a compute unit's LDS");
     // two workgroups per compute unit (one with matrices in LDS; their LDS
     // allows no more), each looping over tiles with the next one's loads in
     // flight

@@ -268,9 +268,15 @@ namespace cast {
 struct BlockedPlan;                  // cache-blocked grouping of a fused list (blocked.cpp)
 void blocked_free(BlockedPlan *b);
 // apply_circuit's launches for a schedule of f (built on first use, cached in
-// f): launch i of group_count is either a schedule pass, which the caller
+// f; `upload`: with the list's matrices and the groups' tables on the device):
+// launch i of group_count is either a schedule pass, which the caller
 // makes (*pass its index), or a tile group, queued here (*pass = -1).
-cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, BlockedPlan **out);
+cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, bool upload, BlockedPlan **out);
+struct GroupInfo {
+    size_t first, count;             // fused gates [first, first + count)
+    int tile_bits, threads;          // 0: a schedule pass
+};
+GroupInfo group_info(const BlockedPlan &bp, size_t i);
 size_t group_count(const BlockedPlan &bp);
 cast_status launch_group(cast_sv *sv, const cast_fused *f, const BlockedPlan &bp, size_t i, size_t *pass);
 struct JitModule;                    // generated kernels of a fused list (jit.cpp)
