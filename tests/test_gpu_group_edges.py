@@ -1,9 +1,11 @@
 """Tile groups at the edges of what reaches them: knobs from the environment,
-which no range check has seen, against the oracle."""
+which no range check has seen, against the oracle, and amplitudes that are not
+finite."""
 import os
 import subprocess
 import sys
 
+import numpy as np
 import pytest
 
 pytestmark = pytest.mark.gpu
@@ -11,6 +13,9 @@ pytestmark = pytest.mark.gpu
 torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_2503_19894_amd as cast  # noqa: E402
+from circuits import Gate, random_state  # noqa: E402
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -36,3 +41,27 @@ def test_environment_knobs(bits, threads):
     print(f"tile bits {bits} threads {threads}", flush=True)
     r = subprocess.run([sys.executable, "-c", PROBE], cwd=ROOT, env=env, capture_output=True, text=True, timeout=100)
     assert r.returncode == 0 and "agree" in r.stdout, r.stderr[-2000:]
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64], ids=["c128", "c64"])
+@pytest.mark.parametrize("n", [10, 14, 18])
+@pytest.mark.parametrize("bad", [(np.inf, 0.0), (-np.inf, np.inf), (np.nan, 1.0)])
+def test_untouched_amplitudes(dtype, n, bad):
+    """No gate acts on amplitude 0 (every phase is 1, every control 0, and the
+    fused gates' blocks with it are the identity): it keeps its value, infinite
+    or not, and no other amplitude meets it."""
+    rng = np.random.default_rng(n)
+    gates = []
+    for q in range(4, n):
+        gates += [Gate("cp", (q, int(p)), (float(rng.uniform(0.1, 3)),)) for p in rng.permutation(np.setdiff1d(range(4, n), q))[:3]]
+        gates.append(Gate("cx", (q, q - 1)))
+    psi = random_state(n, seed=n, workload=19)
+    psi[0] = complex(*bad)
+    fc = cast.FusedCircuit(n, gates, k_max=2)
+    assert len(fc.launches(dtype)) < fc.num_passes(dtype)
+    print(f"amplitude {bad} n={n} {dtype}: {len(fc.launches(dtype))} launches", flush=True)
+    sv = cast.StateVector(n, tensor=torch.tensor(psi, dtype=dtype, device="cuda"))
+    sv.apply_circuit(fc)
+    out = sv.numpy()
+    assert np.array_equal([out[0].real, out[0].imag], bad, equal_nan=True)
+    assert np.isfinite(out[1:]).all()
