@@ -38,6 +38,7 @@ struct InstPlan {
     std::vector<int> gslot;                // result slot per gate (-1: none)
     std::vector<HostOp> ops;
     std::vector<BoundOp> bound;
+    bool unitary = true;                   // every fixed gate is
     int tb = 0;                            // tile bits of this instance's segments
     size_t nparams = 0;
     int nslots = 0;
@@ -555,6 +556,7 @@ static cast_status plan_program(int n_inst, const int *n_qubits, cast_dtype dt, 
                 continue;
             }
             if (!g.matrix) return fail(CAST_EINVAL, "fixed gate without a matrix");
+            ip.unitary &= unitary_gate(g);
             std::vector<cplx> m((size_t)D * D);
             for (int e = 0; e < D * D; ++e) m[e] = cplx(g.matrix[2 * e], g.matrix[2 * e + 1]);
             sorted_matrix(g.k, g.qubits, m, &ip.sq0[l], &ip.sq1[l], &ip.fixed[l]);
@@ -702,7 +704,9 @@ static cast_status plan_program(int n_inst, const int *n_qubits, cast_dtype dt, 
                 // gate in between on its qubits, joins it: one inner product
                 // (they commute) and one application with the summed angle.
                 // complex64 keeps every rotation: each rounds the state, and
-                // its results stay those of the gates one by one.
+                // its results stay those of the gates one by one.  So does an
+                // instance with a fixed gate that is not unitary: U^dag does
+                // not undo it, so the inner products on its two sides differ.
                 std::vector<int> head(gl.size(), -1);     // gate position it joins
                 std::vector<std::vector<int>> joined(gl.size());
                 {
@@ -711,7 +715,7 @@ static cast_status plan_program(int n_inst, const int *n_qubits, cast_dtype dt, 
                         const int l = gl[q];
                         const int p0 = last[ip.sq0[l]], p1 = ip.sq1[l] < 0 ? p0 : last[ip.sq1[l]];
                         const int lp = p0 >= 0 ? gl[p0] : -1;
-                        if (dt == CAST_C128 && lp >= 0 && p0 == p1 && ip.gates[l].param_id >= 0 && ip.gates[lp].param_id >= 0 &&
+                        if (dt == CAST_C128 && ip.unitary && lp >= 0 && p0 == p1 && ip.gates[l].param_id >= 0 && ip.gates[lp].param_id >= 0 &&
                             ip.gx[l] == ip.gx[lp] && ip.gz[l] == ip.gz[lp] && ip.sq0[l] == ip.sq0[lp] &&
                             ip.sq1[l] == ip.sq1[lp]) {
                             head[q] = p0;

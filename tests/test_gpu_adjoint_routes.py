@@ -1,6 +1,7 @@
 """adjoint_grad's choice between segments and one gate at a time: fixed gates
 that are not unitary keep their place in the circuit's order, and every tile
-size that the knob allows is taken, against the oracle's adjoint."""
+size that the knob allows is taken; equal rotations of a batched program on two
+sides of such a gate stay apart; against the oracle's adjoint."""
 import numpy as np
 import pytest
 
@@ -69,3 +70,23 @@ def test_tile_knob(bits):
     ew, gw = oracle.adjoint_grad(n, gates, theta, H)
     tol = 1e-14 * len(gates) * sum(abs(t.coeff) for t in H)
     assert abs(e - ew) <= tol and np.max(np.abs(g - gw)) <= tol
+
+
+@pytest.mark.parametrize("mode", [cast.BATCH_STEPS, cast.BATCH_STEPS_GRAPH, cast.BATCH_PERSISTENT_GRAPH])
+@pytest.mark.parametrize("dtype,tol", [(torch.complex128, 1e-13), (torch.complex64, 1e-5)], ids=["c128", "c64"])
+def test_equal_rotations_around_a_gate_that_is_not_unitary(dtype, tol, mode):
+    """Two RY on qubit 0 with a damped qubit 1 between them: in reverse order
+    the second is taken before the damping is passed, the first after it."""
+    n = 3
+    gates = [Gate("u3", (q,), (0.4 + q, 0.3, -0.2)) for q in range(n)]
+    gates += [Gate("ry", (0,), param=0), Gate("unitary", (1,), matrix=np.array([[1.0, 0.3], [0.1, 0.5]])),
+              Gate("ry", (0,), param=1), Gate("cx", (0, 1))]
+    H = [PauliTerm(1.0, ((1, "Z"),)), PauliTerm(0.5, ((0, "X"), (2, "Z")))]
+    theta = np.array([0.7, -1.1])
+    b = cast.Batch([gates, gates], [n, n], [2, 2], [H, H], dtype=dtype, mode=mode)
+    print(f"batched rotations {dtype} mode {mode}", flush=True)
+    e, g = b.run([theta, -theta])
+    for i, th in enumerate((theta, -theta)):
+        ew, gw = oracle.adjoint_grad(n, gates, th, H)
+        assert abs(gw[0] - gw[1]) > 100 * tol   # taken together they would differ from the oracle
+        assert abs(e[i] - ew) <= tol and np.max(np.abs(g[i] - gw)) <= tol
