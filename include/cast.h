@@ -354,7 +354,10 @@ void fused_destroy(cast_fused *f);
  * at most 64 KiB, so two workgroups share a compute unit's LDS),
  * "blocked_threads" (their workgroup size: 256, 512 or 1024), "tile_groups"
  * (apply_circuit: passes that fit one LDS tile share a launch 1 / one launch
- * per pass 0),
+ * per pass 0; a shared launch takes its tiles and workgroups from the two
+ * blocked_ knobs and leaves out blocks that mfma_min_d keeps off the matrix
+ * cores or mfma_3m_min_d gives three products; the other knobs choose among
+ * the kernels of passes with a launch of their own),
  * "mfma_3m_min_d" (matrix-core passes with blocks of d >= this value form
  * complex products with three real products instead of four; 4..7, 7 = never),
  * "mfma_low_tile" (1: a matrix-core pass with d <= 4 and a target below bit 4

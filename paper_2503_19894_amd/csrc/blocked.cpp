@@ -12,7 +12,7 @@ namespace cast {
 
 struct BlockedPlan {
     int tb = 0, nt = 0;                // tile bits, workgroup size
-    int knob_tb = 0;                   // tile groups: the tile-size knob they were planned with
+    int knob_tb = 0, knob_mfma = 0, knob_3m = 0;   // tile groups: the knobs they were planned with
     struct Pass {
         size_t first = 0, count = 0;   // fused gates [first, first + count) covered by this pass
         bool segment = false;
@@ -535,6 +535,7 @@ double group_us(const Schedule &sc, const std::vector<PassPlan> &P, size_t a, si
 
 // Groups the schedule with tiles of 2^tb amplitudes; *us: predicted time.
 std::vector<Span> plan_groups(const Schedule &sc, const std::vector<PassPlan> &P, int tb, double *us) {
+    const Tuning &tu = tuning();
     std::vector<Span> out;
     *us = 0;
     size_t a = 0, mats = 0;   // mats: LDS bytes of the open group's dense blocks
@@ -562,8 +563,10 @@ std::vector<Span> plan_groups(const Schedule &sc, const std::vector<PassPlan> &P
         int w = 0;
         bool fits = p.d <= kGroupMaxD && window_of(span, tb, &w);
         const size_t mb = p.d >= 4 ? (p.blk.size() * amp_bytes(sc.dt)) << (2 * p.d) : 0;
-        // sixteen columns on tile bits that are no targets
-        if (fits && p.d >= 4) fits = tb - p.k >= 4 && mb <= kBlkMatBytes;
+        // sixteen columns on tile bits that are no targets; and the knobs keep
+        // a block off the matrix cores, or to three products, in single passes
+        if (fits && p.d >= 4)
+            fits = tb - p.k >= 4 && mb <= kBlkMatBytes && p.d >= tu.mfma_min_d[sc.dt] && p.d < tu.mfma_3m_min_d[sc.dt];
         if (!fits) {
             close(i);
             a = i;
@@ -591,7 +594,9 @@ cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, bool u
     // (an environment variable for both dtypes may ask for more than this one's tile)
     const int most = 31 - __builtin_clz(kBlkTileBytes / (uint32_t)amp_bytes(dt));
     const int knob = std::min(tuning().blocked_tile_bits[dt], most);
-    if (bp && (bp->knob_tb != knob || bp->nt != blocked_threads(dt, bp->tb))) {
+    const int mfma = tuning().mfma_min_d[dt], m3 = tuning().mfma_3m_min_d[dt];
+    if (bp && (bp->knob_tb != knob || bp->knob_mfma != mfma || bp->knob_3m != m3 ||
+               bp->nt != blocked_threads(dt, bp->tb))) {
         blocked_free(bp);
         bp = nullptr;
     }
@@ -608,7 +613,7 @@ cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, bool u
         }
         auto *p = new BlockedPlan;
         p->tb = best_tb;
-        p->knob_tb = knob;
+        p->knob_tb = knob, p->knob_mfma = mfma, p->knob_3m = m3;
         p->nt = blocked_threads(dt, best_tb);
         if (!best_tb)
             for (size_t i = 0; i < sc.passes.size(); ++i) best.push_back(Span{i, i + 1, 0, false});

@@ -1,6 +1,7 @@
 """The launches apply_circuit plans (no GPU: grouping is planned on the host):
 tiles and workgroups stay within what the kernel takes whatever an environment
-variable, which no range check has seen, asks for."""
+variable, which no range check has seen, asks for, and blocks that the knobs
+keep off the matrix cores keep a launch of their own."""
 import os
 import subprocess
 import sys
@@ -9,7 +10,7 @@ import pytest
 import torch
 
 import paper_2503_19894_amd as cast
-from circuits import qft
+from circuits import qft, rqc_u3_cx
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 TILE_BYTES = 64 << 10
@@ -56,3 +57,25 @@ def test_launches_cover_the_list(dtype):
         assert [(x["first"], x["count"], 0, 0) for x in fc.schedule(dtype)] == [tuple(x.values()) for x in fc.launches(dtype)]
     finally:
         cast.set_tuning("tile_groups", 1, dtype)
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64], ids=["c128", "c64"])
+@pytest.mark.parametrize("knob,value,kept_out", [("mfma_min_d", 7, (4, 5)), ("mfma_min_d", 5, (4,)),
+                                                 ("mfma_3m_min_d", 4, (4, 5)), ("mfma_3m_min_d", 5, (5,))])
+def test_matrix_core_knobs(dtype, knob, value, kept_out):
+    n = 16
+    fc = cast.FusedCircuit(n, rqc_u3_cx(n, 5, seed=2), k_max=5)
+
+    def grouped():
+        return {fc.gate(g)["d"] for x in fc.launches(dtype) if x["tile_bits"]
+                for g in range(x["first"], x["first"] + x["count"])}
+
+    before = grouped()
+    assert {4, 5} <= before
+    old = cast.get_tuning(knob, dtype)
+    cast.set_tuning(knob, value, dtype)
+    try:
+        assert not grouped() & set(kept_out)
+    finally:
+        cast.set_tuning(knob, old, dtype)
+    assert grouped() == before
