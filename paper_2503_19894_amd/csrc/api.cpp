@@ -759,8 +759,18 @@ cast_status apply_circuit(cast_sv *sv, const cast_fused *fc) {
     BlockedPlan *groups = nullptr;
     if (tuning().tile_groups[sv->dt] && !f->plans.empty()) {
         if (cast_status rc = get_schedule(f, sv->n, sv->dt, false, &sc)) return rc;
-        // without memory for the groups' tables the passes run one by one
-        if (cast_status rc = tile_groups(f, *sc, sv->dt, true, &groups); rc && rc != CAST_ENOMEM) return rc;
+        if (cast_status rc = tile_groups(f, *sc, sv->dt, false, &groups)) return rc;
+        if (!groups_ready(f, *groups, sv->dt)) {
+            // without memory for the groups' tables, or while the stream is
+            // being captured (nothing can be uploaded; circuit_tune and
+            // apply_circuit_timed leave what single passes need), the passes
+            // run one by one
+            hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+            CAST_HIP_TRY(hipStreamIsCapturing(sv->stream, &cap));
+            cast_status rc = cap == hipStreamCaptureStatusNone ? tile_groups(f, *sc, sv->dt, true, &groups) : CAST_ENOMEM;
+            if (rc == CAST_ENOMEM) groups = nullptr;
+            else if (rc) return rc;
+        }
     }
     if (!groups) {
         if (cast_status rc = prepare_circuit(sv, fc, &f, &sc)) return rc;

@@ -639,6 +639,10 @@ cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, bool u
     return CAST_OK;
 }
 
+bool groups_ready(const cast_fused *f, const BlockedPlan &bp, cast_dtype dt) {
+    return f->dev[dt].ptr && (bp.dev || bp.gates.empty());
+}
+
 size_t group_count(const BlockedPlan &bp) { return bp.passes.size(); }
 
 GroupInfo group_info(const BlockedPlan &bp, size_t i) {

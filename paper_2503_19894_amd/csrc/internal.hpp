@@ -272,6 +272,7 @@ void blocked_free(BlockedPlan *b);
 // launch i of group_count is either a schedule pass, which the caller
 // makes (*pass its index), or a tile group, queued here (*pass = -1).
 cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, bool upload, BlockedPlan **out);
+bool groups_ready(const cast_fused *f, const BlockedPlan &bp, cast_dtype dt);   // all of it on the device
 struct GroupInfo {
     size_t first, count;             // fused gates [first, first + count)
     int tile_bits, threads;          // 0: a schedule pass

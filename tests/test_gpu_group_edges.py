@@ -1,6 +1,6 @@
 """Tile groups at the edges of what reaches them: knobs from the environment,
-which no range check has seen, against the oracle, and amplitudes that are not
-finite."""
+which no range check has seen, a stream that is being captured, and amplitudes
+that are not finite, against the oracle."""
 import os
 import subprocess
 import sys
@@ -14,8 +14,11 @@ torch = pytest.importorskip("torch")
 if not torch.cuda.is_available():
     pytest.skip("needs a GPU", allow_module_level=True)
 
+import oracle  # noqa: E402
 import paper_2503_19894_amd as cast  # noqa: E402
-from circuits import Gate, random_state  # noqa: E402
+from circuits import Gate, qft, random_state, rqc_u3_cx  # noqa: E402
+
+TOL = {torch.complex128: 1e-12, torch.complex64: 1e-5}
 
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
@@ -65,3 +68,31 @@ def test_untouched_amplitudes(dtype, n, bad):
     out = sv.numpy()
     assert np.array_equal([out[0].real, out[0].imag], bad, equal_nan=True)
     assert np.isfinite(out[1:]).all()
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64], ids=["c128", "c64"])
+@pytest.mark.parametrize("before", ["tune", "timed", "apply"])
+def test_captured_after(before, dtype):
+    """A list that any earlier call has put on the device can be captured."""
+    n = 13
+    gates = qft(n) + rqc_u3_cx(n, 3, seed=4)
+    psi0 = random_state(n, seed=3, workload=20)
+    fc = cast.FusedCircuit(n, gates, k_max=4)
+    psi = torch.tensor(psi0, dtype=dtype, device="cuda")
+    sv = cast.StateVector(n, tensor=psi)
+    {"tune": sv.tune_circuit, "timed": sv.apply_circuit_timed, "apply": sv.apply_circuit}[before](fc)
+    torch.cuda.synchronize()
+    print(f"capture after {before} {dtype}", flush=True)
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        cast.StateVector(n, tensor=psi).apply_circuit(fc)
+    want = oracle.run_circuit(n, gates, psi0)
+    for i in range(3):
+        psi.copy_(torch.tensor(psi0, dtype=dtype))
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.max(np.abs(psi.cpu().numpy() - want)) <= TOL[dtype]
+        other = cast.StateVector(n, tensor=torch.tensor(psi0, dtype=dtype, device="cuda"))   # eager work between
+        other.apply_circuit(fc)
+        assert np.max(np.abs(other.numpy() - want)) <= TOL[dtype]
