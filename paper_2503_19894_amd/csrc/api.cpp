@@ -188,28 +188,35 @@ void dev_free(void *ptr) {
 }
 
 // ----------------------------------------------------------------- uploads
-template <typename R>
-static void pack(const PassPlan &p, std::vector<R> &dst) {
-    pack_plan<R>(p, dst);
+// A list's tables are copied in pieces of at most 16 KiB, which the runtime
+// moves with a kernel (12 us each), while those are few: a larger copy goes to
+// a copy engine, which takes some 60 us when it has been idle.
+hipError_t copy_to_device(void *dst, const void *src, size_t bytes) {
+    constexpr size_t kPiece = 16u << 10;
+    if (bytes > 2 * kPiece) return hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
+    hipError_t e = hipSuccess;
+    for (size_t o = 0; o < bytes && e == hipSuccess; o += kPiece)
+        e = hipMemcpy((char *)dst + o, (const char *)src + o, std::min(kPiece, bytes - o), hipMemcpyHostToDevice);
+    return e;
 }
 
 // Every plan's matrices, cast to the state dtype, one after another with each
-// plan's start 256-byte aligned (for scalar loads); offsets in reals.
-static size_t pack_all(const std::vector<PassPlan> &ps, cast_dtype dt, std::vector<double> &hd,
-                       std::vector<float> &hf, std::vector<size_t> *offsets) {
-    offsets->clear();
-    size_t elems = 0;
-    for (const PassPlan &p : ps) {
-        offsets->push_back(elems);
-        if (dt == CAST_C128) pack<double>(p, hd), elems = hd.size();
-        else pack<float>(p, hf), elems = hf.size();
-        const size_t align = 256 / (dt == CAST_C128 ? 8 : 4);
-        while (elems % align) {
-            if (dt == CAST_C128) hd.push_back(0); else hf.push_back(0);
-            ++elems;
-        }
+// plan's start 256-byte aligned (for scalar loads), and room for `tail` bytes
+// at *tail_at; offsets in reals.
+static std::vector<char> pack_all(const std::vector<PassPlan> &ps, cast_dtype dt, std::vector<size_t> *offsets,
+                                  size_t tail = 0, size_t *tail_at = nullptr) {
+    *offsets = plan_offsets(ps, dt);
+    const size_t rsz = amp_bytes(dt) / 2;
+    size_t bytes = ps.empty() ? 0 : (offsets->back() + plan_reals(ps.back())) * rsz;
+    bytes = (bytes + 255) & ~(size_t)255;
+    if (tail_at) *tail_at = bytes;
+    std::vector<char> h(bytes + tail);
+    for (size_t i = 0; i < ps.size(); ++i) {
+        char *at = h.data() + (*offsets)[i] * rsz;
+        if (dt == CAST_C128) write_plan(ps[i], (double *)at);
+        else write_plan(ps[i], (float *)at);
     }
-    return elems;
+    return h;
 }
 
 std::vector<size_t> plan_offsets(const std::vector<PassPlan> &ps, cast_dtype dt) {
@@ -218,7 +225,7 @@ std::vector<size_t> plan_offsets(const std::vector<PassPlan> &ps, cast_dtype dt)
     size_t elems = 0;
     for (const PassPlan &p : ps) {
         off.push_back(elems);
-        elems += p.d == 0 ? (size_t)2 << p.k : 2 * p.mat.size();   // as pack_plan
+        elems += plan_reals(p);
         elems = (elems + align - 1) & ~(align - 1);
     }
     return off;
@@ -226,14 +233,10 @@ std::vector<size_t> plan_offsets(const std::vector<PassPlan> &ps, cast_dtype dt)
 
 cast_status upload_plans_pooled(const std::vector<PassPlan> &ps, cast_dtype dt, void **ptr, size_t *cls,
                                 std::vector<size_t> *offsets) {
-    std::vector<double> hd;
-    std::vector<float> hf;
-    const size_t elems = pack_all(ps, dt, hd, hf, offsets);
-    const size_t bytes = elems * (dt == CAST_C128 ? 8 : 4);
-    if (cast_status st = pool_alloc(ptr, bytes, cls)) return st;
-    if (bytes) {
-        const hipError_t e = hipMemcpy(*ptr, dt == CAST_C128 ? (void *)hd.data() : (void *)hf.data(), bytes,
-                                       hipMemcpyHostToDevice);
+    const std::vector<char> h = pack_all(ps, dt, offsets);
+    if (cast_status st = pool_alloc(ptr, h.size(), cls)) return st;
+    if (!h.empty()) {
+        const hipError_t e = hipMemcpy(*ptr, h.data(), h.size(), hipMemcpyHostToDevice);
         if (e != hipSuccess) {
             pool_free(*ptr, *cls);
             *ptr = nullptr;
@@ -244,26 +247,15 @@ cast_status upload_plans_pooled(const std::vector<PassPlan> &ps, cast_dtype dt, 
 }
 
 cast_status upload_plans(const std::vector<PassPlan> &ps, cast_dtype dt, DeviceMatrix *out,
-                         std::vector<size_t> *offsets, const std::vector<char> *tail, size_t *tail_at) {
-    std::vector<double> hd;
-    std::vector<float> hf;
-    const size_t elems = pack_all(ps, dt, hd, hf, offsets);
-    const void *src = dt == CAST_C128 ? (void *)hd.data() : (void *)hf.data();
-    size_t bytes = elems * (dt == CAST_C128 ? 8 : 4);
-    std::vector<char> both;
-    if (tail) {
-        *tail_at = (bytes + 255) & ~(size_t)255;
-        both.resize(*tail_at + tail->size());
-        if (bytes) std::memcpy(both.data(), src, bytes);
-        std::memcpy(both.data() + *tail_at, tail->data(), tail->size());
-        src = both.data();
-        bytes = both.size();
-    }
-    cast_status st = dev_alloc(&out->ptr, bytes);
+                         std::vector<size_t> *offsets, size_t tail, const std::function<void(char *)> &write,
+                         size_t *tail_at) {
+    std::vector<char> h = pack_all(ps, dt, offsets, tail, tail_at);
+    if (tail) write(h.data() + *tail_at);
+    cast_status st = dev_alloc(&out->ptr, h.size());
     if (st) return st;
-    out->bytes = bytes;
-    if (bytes) {
-        hipError_t e = hipMemcpy(out->ptr, src, bytes, hipMemcpyHostToDevice);
+    out->bytes = h.size();
+    if (!h.empty()) {
+        const hipError_t e = copy_to_device(out->ptr, h.data(), h.size());
         if (e != hipSuccess) {
             dev_free(out->ptr);
             out->ptr = nullptr;
@@ -482,12 +474,11 @@ cast_status apply_gate(cast_sv *sv, const int *qubits, int k, const double *matr
     PassPlan p;
     if (cast_status rc = make_plan(k, qubits, m.data(), 1e-14, 1e-14, &p)) return rc;
     if (p.identity()) return CAST_OK;
-    std::vector<double> hd;
-    std::vector<float> hf;
-    size_t bytes;
-    const void *src;
-    if (sv->dt == CAST_C128) { pack<double>(p, hd); bytes = hd.size() * 8; src = hd.data(); }
-    else { pack<float>(p, hf); bytes = hf.size() * 4; src = hf.data(); }
+    const size_t bytes = plan_reals(p) * (amp_bytes(sv->dt) / 2);
+    std::vector<double> host((bytes + 7) / 8);
+    const void *src = host.data();
+    if (sv->dt == CAST_C128) write_plan(p, host.data());
+    else write_plan(p, (float *)host.data());
     if (bytes <= MatArg::kBytes && p.d < 4) {
         // No copy and no wait: the launch carries the matrix.  A gate whose
         // matrix went through a staging buffer (pageable copy, stream

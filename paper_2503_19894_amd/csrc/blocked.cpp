@@ -22,7 +22,7 @@ struct BlockedPlan {
     };
     std::vector<Pass> passes;
     std::vector<BlkGate> gates;
-    std::vector<BlkEnt> ent;           // kBlkEnts per operation
+    std::vector<BlkEnt> ent;           // of the operations
     std::vector<BlkEnt> units;         // work units of the table builds, behind them on the device
     std::vector<BlkMember> members;
     std::vector<double> tabs;          // phases of the diagonal gates (complex entries as pairs)
@@ -76,6 +76,12 @@ int tile_number_bit(int q, int w, const int *qh, int nh) {
     int b = q - w;
     for (int i = 0; i < nh; ++i) b -= qh[i] < q;
     return b;
+}
+
+// Appends n zeroed entries.
+BlkEnt *append(std::vector<BlkEnt> *ent, uint32_t n) {
+    ent->resize(ent->size() + n);
+    return ent->data() + ent->size() - n;
 }
 
 BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh, int nh, uint64_t mat,
@@ -158,13 +164,14 @@ BlkGate make_gate(const PassPlan &p, cast_dtype dt, int tb, int w, const int *qh
     for (int t = 0; t < tb; ++t)
         if (!(((pivots | lane) >> t) & 1u)) rest.push_back(t);
     g.nuni = (uint32_t)rest.size();
-    for (uint32_t e = 0; e < kBlkEnts; ++e) {   // (the kernel reads past the last, but does not use it)
-        uint32_t y = 0, u = 0;
-        for (uint32_t i = 0; i < g.nuni; ++i)
-            if ((e >> i) & 1u) y |= 1u << rest[i];
+    g.ent = (uint32_t)ent->size();
+    // both parts are linear over GF(2): entry e from the one without its lowest bit
+    BlkEnt *es = append(ent, 1u << g.nuni);
+    for (uint32_t i = 0; i < g.nuni; ++i) {
+        BlkEnt b{0, lds_elem(1u << rest[i], dt)};
         for (int s = 0; s < k; ++s)
-            if (tpos[s] >= 0 && ((y >> tpos[s]) & 1u)) u ^= colv[s];
-        ent->push_back(BlkEnt{u, lds_elem(y, dt)});
+            if (tpos[s] == rest[i]) b.u ^= colv[s];
+        for (uint32_t e = 0; e < (1u << i); ++e) es[e | 1u << i] = BlkEnt{es[e].u ^ b.u, es[e].a ^ b.a};
     }
     return g;
 }
@@ -244,7 +251,6 @@ void emit_segment(BlockedPlan *bp, const std::vector<PassPlan> &P, const std::ve
             // a run: tables that fit the area together
             const size_t first_gate = bp->gates.size();
             std::vector<BlkGate> run;
-            std::vector<BlkEnt> ent;
             uint32_t end = used;
             bool fresh = build == ~0u;
             for (; c < cl.size() && run.size() < kBlkRunMax; ++c) {
@@ -262,11 +268,6 @@ void emit_segment(BlockedPlan *bp, const std::vector<PassPlan> &P, const std::ve
                 for (int i = 0; i < g.k; ++i) g.pos[i] = cl[c].bits[i];
                 g.lds = at;
                 end = at + sz;
-                for (uint32_t it = 0; it < kBlkEnts; ++it) {
-                    uint32_t j = 0;
-                    for (int i = 0; i < g.k; ++i) j |= (((it * (uint32_t)nt) >> g.pos[i]) & 1u) << i;
-                    ent.push_back(BlkEnt{j, 0});
-                }
                 g.m0 = (uint32_t)bp->members.size();
                 for (const PhaseTable *t : cl[c].gates) {
                     BlkMember m;
@@ -290,11 +291,16 @@ void emit_segment(BlockedPlan *bp, const std::vector<PassPlan> &P, const std::ve
                 std::memset(&g, 0, sizeof g);
                 g.kind = 2;
                 bp->gates.push_back(g);
-                bp->ent.resize(bp->ent.size() + kBlkEnts);
             }
-            bp->ent.insert(bp->ent.end(), ent.begin(), ent.end());
             used = end;
-            run[0].run = (int)run.size();
+            const uint32_t M = (uint32_t)run.size(), iters = std::max(1u, (1u << tb) / (uint32_t)nt);
+            run[0].run = (int)M;
+            run[0].ent = (uint32_t)bp->ent.size();
+            BlkEnt *es = append(&bp->ent, iters * M);
+            for (uint32_t it = 0; it < iters; ++it)
+                for (uint32_t t = 0; t < M; ++t)
+                    for (int i = 0; i < run[t].k; ++i)
+                        es[it * M + t].u |= (((it * (uint32_t)nt) >> run[t].pos[i]) & 1u) << i;
             bp->gates.insert(bp->gates.end(), run.begin(), run.end());
             s.lds_tabs = std::max(s.lds_tabs, (uint32_t)(used * ab));
         }
@@ -318,8 +324,6 @@ void emit_segment(BlockedPlan *bp, const std::vector<PassPlan> &P, const std::ve
         for (uint32_t gi = s.g0; gi < bp->gates.size(); ++gi)
             if (bp->gates[gi].kind == 2) {
                 std::rotate(bp->gates.begin() + s.g0, bp->gates.begin() + gi, bp->gates.begin() + gi + 1);
-                std::rotate(bp->ent.begin() + (size_t)s.g0 * kBlkEnts, bp->ent.begin() + (size_t)gi * kBlkEnts,
-                            bp->ent.begin() + (size_t)(gi + 1) * kBlkEnts);
                 break;
             }
     }
@@ -403,32 +407,36 @@ cast_status upload_tables(cast_fused *f, BlockedPlan *bp, cast_dtype dt) {
         return mats ? upload_plans(f->plans, dt, &f->dev[dt], &f->dev_off[dt]) : CAST_OK;
     auto up = [](size_t x) { return (x + 255) & ~(size_t)255; };
     bp->dev_ent = up(bp->gates.size() * sizeof(BlkGate));
-    bp->dev_mem = bp->dev_ent + up((bp->ent.size() + bp->units.size()) * sizeof(BlkEnt));
+    bp->dev_mem = bp->dev_ent + up((bp->ent.size() + bp->units.size() + kBlkEntsPad) * sizeof(BlkEnt));
     bp->dev_tabs = bp->dev_mem + up(bp->members.size() * sizeof(BlkMember));
     const size_t rsz = amp_bytes(dt) / 2, bytes = bp->dev_tabs + std::max<size_t>(bp->tabs.size(), 4) * rsz;
-    std::vector<char> h(bytes, 0);
-    std::memcpy(h.data(), bp->gates.data(), bp->gates.size() * sizeof(BlkGate));
-    BlkGate *hg = (BlkGate *)h.data();
-    for (size_t i = 0; i < bp->gates.size(); ++i)
-        if (hg[i].kind == 2) hg[i].ent += (uint32_t)bp->ent.size();
-    BlkEnt *he = (BlkEnt *)(h.data() + bp->dev_ent);
-    std::copy(bp->ent.begin(), bp->ent.end(), he);
-    std::copy(bp->units.begin(), bp->units.end(), he + bp->ent.size());
-    if (!bp->members.empty())
-        std::memcpy(h.data() + bp->dev_mem, bp->members.data(), bp->members.size() * sizeof(BlkMember));
-    for (size_t i = 0; i < bp->tabs.size(); ++i) {
-        if (dt == CAST_C128) ((double *)(h.data() + bp->dev_tabs))[i] = bp->tabs[i];
-        else ((float *)(h.data() + bp->dev_tabs))[i] = (float)bp->tabs[i];
-    }
+    auto write = [&](char *h) {
+        for (size_t i = 0; i < bp->gates.size(); ++i) {
+            BlkGate g = bp->gates[i];
+            if (g.kind == 2) g.ent += (uint32_t)bp->ent.size();
+            std::memcpy(h + i * sizeof g, &g, sizeof g);
+        }
+        BlkEnt *he = (BlkEnt *)(h + bp->dev_ent);
+        std::copy(bp->ent.begin(), bp->ent.end(), he);
+        std::copy(bp->units.begin(), bp->units.end(), he + bp->ent.size());
+        if (!bp->members.empty())
+            std::memcpy(h + bp->dev_mem, bp->members.data(), bp->members.size() * sizeof(BlkMember));
+        for (size_t i = 0; i < bp->tabs.size(); ++i) {
+            if (dt == CAST_C128) ((double *)(h + bp->dev_tabs))[i] = bp->tabs[i];
+            else ((float *)(h + bp->dev_tabs))[i] = (float)bp->tabs[i];
+        }
+    };
     if (mats) {
         size_t at;
-        if (cast_status rc = upload_plans(f->plans, dt, &f->dev[dt], &f->dev_off[dt], &h, &at)) return rc;
+        if (cast_status rc = upload_plans(f->plans, dt, &f->dev[dt], &f->dev_off[dt], bytes, write, &at)) return rc;
         bp->dev = (char *)f->dev[dt].ptr + at;
         bp->shares = true;
         return CAST_OK;
     }
+    std::vector<char> h(bytes);
+    write(h.data());
     if (cast_status rc = dev_alloc(&bp->dev, bytes)) return rc;
-    const hipError_t e = hipMemcpy(bp->dev, h.data(), bytes, hipMemcpyHostToDevice);
+    const hipError_t e = copy_to_device(bp->dev, h.data(), bytes);
     if (e != hipSuccess) {
         dev_free(bp->dev);
         bp->dev = nullptr;
@@ -503,85 +511,104 @@ struct Span {
     bool group;
 };
 
-double pass_us(const Schedule &sc, const SchedPass &sp, const std::vector<PassPlan> &P) {
-    const double ab = (double)amp_bytes(sc.dt);
-    if (sp.kind < 0) return 0.0;
-    if (sp.kind == 6) return 3.8 + 2 * ab * sp.active_amps / 5.4e6;
-    const PassPlan &p = P[sp.first];
-    const double amps = std::ldexp((double)p.blk.size(), sc.n - p.k + p.d);
-    const double mem = 2 * ab * amps / 5.4e6, fl = p.d >= 4 ? 8 * amps * (1 << p.d) / (sc.dt == CAST_C128 ? 60e6 : 120e6) : 0;
-    const double base = sp.kind == 1 || sp.kind == 2 ? 5.3 : sp.kind == 5 ? 6.5 : p.d >= 5 ? 4.8 : 3.8;
-    return base + std::max(mem, fl);
-}
+// What the planning of every tile size asks of a schedule pass.
+struct PassCost {
+    bool live;            // not an identity
+    bool mixes;           // has blocks of d >= 1
+    int d;
+    uint64_t span;        // qubits it mixes
+    size_t mats;          // LDS bytes of its dense blocks
+    double us;            // of its own launch
+    double tabs;          // phase tables (diagonal run), else 1
+};
 
-double group_us(const Schedule &sc, const std::vector<PassPlan> &P, size_t a, size_t b, int tb) {
-    const double scale = std::ldexp(1.0, tb - 12), tiles = std::ldexp(1.0, sc.n - tb);
-    static const double op_us[] = {0.3, 0.7, 0.8, 1.1, 3.0, 5.3}, least_us[] = {0.8, 0.8, 0.8, 0.8, 1.6, 2.6};
-    double ops = 0;
-    for (size_t i = a; i < b; ++i) {
-        const SchedPass &sp = sc.passes[i];
-        if (sp.kind < 0) continue;
-        const int d = sp.kind == 6 ? 0 : P[sp.first].d;
-        double t = op_us[d] * scale;
-        if (sp.kind == 6) t *= (double)sp.tabs.size();
-        if (d < 4) t = 0.1 + (tiles <= 256 ? 1.2 * t : t);
-        if (d >= 4) t = std::max(t, 0.55 * op_us[d]) * (sc.dt == CAST_C64 ? 0.52 : 1.0);
-        ops += std::max(least_us[d], t * std::max(1.0, tiles / 256));
+std::vector<PassCost> pass_costs(const Schedule &sc, const std::vector<PassPlan> &P) {
+    const double ab = (double)amp_bytes(sc.dt);
+    std::vector<PassCost> out;
+    out.reserve(sc.passes.size());
+    for (const SchedPass &sp : sc.passes) {
+        PassCost c{sp.kind >= 0, false, 0, 0, 0, 0.0, 1.0};
+        if (sp.kind == 6) {
+            c.us = 3.8 + 2 * ab * sp.active_amps / 5.4e6;
+            c.tabs = (double)sp.tabs.size();
+        } else if (c.live) {
+            const PassPlan &p = P[sp.first];
+            c.d = p.d;
+            c.mixes = p.d > 0;
+            c.span = span_qubits(p);
+            if (p.d >= 4) c.mats = (p.blk.size() * amp_bytes(sc.dt)) << (2 * p.d);
+            const double amps = std::ldexp((double)p.blk.size(), sc.n - p.k + p.d);
+            const double mem = 2 * ab * amps / 5.4e6, fl = p.d >= 4 ? 8 * amps * (1 << p.d) / (sc.dt == CAST_C128 ? 60e6 : 120e6) : 0;
+            const double base = sp.kind == 1 || sp.kind == 2 ? 5.3 : sp.kind == 5 ? 6.5 : p.d >= 5 ? 4.8 : 3.8;
+            c.us = base + std::max(mem, fl);
+        }
+        out.push_back(c);
     }
-    const double mem = 2 * std::ldexp((double)amp_bytes(sc.dt), sc.n) / 5.2e6;
-    if (tiles <= 256) return 5.0 + std::max(mem, 2 * std::ldexp((double)amp_bytes(sc.dt), tb) / 1e5) + ops;
-    return 5.0 + std::max(mem, ops) + 0.3 * std::min(mem, ops);
+    return out;
 }
 
 // Groups the schedule with tiles of 2^tb amplitudes; *us: predicted time.
-std::vector<Span> plan_groups(const Schedule &sc, const std::vector<PassPlan> &P, int tb, double *us) {
+std::vector<Span> plan_groups(const Schedule &sc, const std::vector<PassPlan> &P, const std::vector<PassCost> &costs,
+                              int tb, double *us) {
     const Tuning &tu = tuning();
+    static const double op_us[] = {0.3, 0.7, 0.8, 1.1, 3.0, 5.3}, least_us[] = {0.8, 0.8, 0.8, 0.8, 1.6, 2.6};
+    const double tiles = std::ldexp(1.0, sc.n - tb), rounds = std::max(1.0, tiles / 256);
+    double op[6];   // of an operation of dimension d, but for a run's tables
+    for (int d = 0; d < 6; ++d) op[d] = op_us[d] * std::ldexp(1.0, tb - 12);
+    const double mem = 2 * std::ldexp((double)amp_bytes(sc.dt), sc.n) / 5.2e6;
+    const double lone = std::max(mem, 2 * std::ldexp((double)amp_bytes(sc.dt), tb) / 1e5);
     std::vector<Span> out;
+    out.reserve(sc.passes.size());
     *us = 0;
-    size_t a = 0, mats = 0;   // mats: LDS bytes of the open group's dense blocks
+    size_t a = 0, mats = 0, live = 0;   // the open group [a, ..): LDS bytes of its dense blocks, passes
     uint64_t need = 0;
+    double sep = 0, ops = 0;            // their own launches, and as operations of a tile
     auto close = [&](size_t b) {
-        mats = 0;
-        if (a >= b) return;
-        double sep = 0;
-        size_t live = 0;
-        for (size_t i = a; i < b; ++i) sep += pass_us(sc, sc.passes[i], P), live += sc.passes[i].kind >= 0;
-        const double grp = group_us(sc, P, a, b, tb);
-        if (live > 1 && grp < sep) {
-            out.push_back(Span{a, b, need, true});
-            *us += grp;
-        } else {
-            for (size_t i = a; i < b; ++i) out.push_back(Span{i, i + 1, 0, false});
-            *us += sep;
+        if (a < b) {
+            const double grp = tiles <= 256 ? 5.0 + lone + ops : 5.0 + std::max(mem, ops) + 0.3 * std::min(mem, ops);
+            if (live > 1 && grp < sep) {
+                out.push_back(Span{a, b, need, true});
+                *us += grp;
+            } else {
+                for (size_t i = a; i < b; ++i) out.push_back(Span{i, i + 1, 0, false});
+                *us += sep;
+            }
         }
+        a = b, mats = live = 0, need = 0, sep = ops = 0;
+    };
+    auto take = [&](const PassCost &c) {
+        sep += c.us;
+        if (!c.live) return;
+        ++live;
+        double t = op[std::min(c.d, 5)] * c.tabs;
+        if (c.d < 4) t = 0.1 + (tiles <= 256 ? 1.2 * t : t);
+        else t = std::max(t, 0.55 * op_us[std::min(c.d, 5)]) * (sc.dt == CAST_C64 ? 0.52 : 1.0);
+        ops += std::max(least_us[std::min(c.d, 5)], t * rounds);
     };
     for (size_t i = 0; i < sc.passes.size(); ++i) {
-        const SchedPass &sp = sc.passes[i];
-        if (sp.kind < 0 || sp.kind == 6 || P[sp.first].d == 0) continue;
-        const PassPlan &p = P[sp.first];
-        const uint64_t span = span_qubits(p);
+        const PassCost &c = costs[i];
+        if (!c.mixes) {
+            take(c);
+            continue;
+        }
+        const PassPlan &p = P[sc.passes[i].first];
         int w = 0;
-        bool fits = p.d <= kGroupMaxD && window_of(span, tb, &w);
-        const size_t mb = p.d >= 4 ? (p.blk.size() * amp_bytes(sc.dt)) << (2 * p.d) : 0;
+        bool fits = p.d <= kGroupMaxD && window_of(c.span, tb, &w);
         // sixteen columns on tile bits that are no targets; and the knobs keep
         // a block off the matrix cores, or to three products, in single passes
         if (fits && p.d >= 4)
-            fits = tb - p.k >= 4 && mb <= kBlkMatBytes && p.d >= tu.mfma_min_d[sc.dt] && p.d < tu.mfma_3m_min_d[sc.dt];
+            fits = tb - p.k >= 4 && c.mats <= kBlkMatBytes && p.d >= tu.mfma_min_d[sc.dt] && p.d < tu.mfma_3m_min_d[sc.dt];
         if (!fits) {
             close(i);
-            a = i;
-            need = 0;
-            close(i + 1);
+            out.push_back(Span{i, i + 1, 0, false});
+            *us += c.us;
             a = i + 1;
             continue;
         }
-        if (!window_of(need | span, tb, &w) || mats + mb > kBlkMatBytes) {
-            close(i);
-            a = i;
-            need = 0;
-        }
-        need |= span;
-        mats += mb;
+        if (!window_of(need | c.span, tb, &w) || mats + c.mats > kBlkMatBytes) close(i);
+        need |= c.span;
+        mats += c.mats;
+        take(c);
     }
     close(sc.passes.size());
     return out;
@@ -602,13 +629,14 @@ cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, bool u
     }
     if (!bp) {
         const std::vector<PassPlan> &P = f->plans;
+        const std::vector<PassCost> costs = pass_costs(sc, P);
         std::vector<Span> best;
         int best_tb = 0;
         double best_us = 0;
         for (int tb = std::min(8, std::min(knob, sc.n)); tb <= std::min(knob, sc.n); ++tb) {
             if (tb < 8) continue;   // 256 threads, one amplitude each
             double us;
-            std::vector<Span> g = plan_groups(sc, P, tb, &us);
+            std::vector<Span> g = plan_groups(sc, P, costs, tb, &us);
             if (!best_tb || us <= best_us) best = std::move(g), best_tb = tb, best_us = us;
         }
         auto *p = new BlockedPlan;
@@ -618,6 +646,9 @@ cast_status tile_groups(cast_fused *f, const Schedule &sc, cast_dtype dt, bool u
         if (!best_tb)
             for (size_t i = 0; i < sc.passes.size(); ++i) best.push_back(Span{i, i + 1, 0, false});
         const std::vector<size_t> off = plan_offsets(P, dt);
+        p->passes.reserve(best.size());
+        p->gates.reserve(P.size() + 16);
+        p->ent.reserve(16 * P.size());
         for (const Span &g : best) {
             if (!g.group) {
                 BlockedPlan::Pass ps;

@@ -132,13 +132,13 @@ __device__ __forceinline__ void diag_run_m(typename Cx<R>::T *tile, const typena
         const uint32_t a = al ^ at<S>(i * NT);
         V x = tile[a];
 #pragma unroll
-        for (int t = 0; t < M; ++t) x = cmul(x, area[jl[t] ^ ent[t * kBlkEnts + i].u]);
+        for (int t = 0; t < M; ++t) x = cmul(x, area[jl[t] ^ ent[i * M + t].u]);
         const bool nan = __builtin_isunordered(x.x, x.y);
         if (__builtin_expect(__ballot(nan) != 0, 0)) {
             const V x0 = tile[a];
-            V p = area[jl[0] ^ ent[i].u];
+            V p = area[jl[0] ^ ent[i * M].u];
 #pragma unroll
-            for (int t = 1; t < M; ++t) p = cmul(p, area[jl[t] ^ ent[t * kBlkEnts + i].u]);
+            for (int t = 1; t < M; ++t) p = cmul(p, area[jl[t] ^ ent[i * M + t].u]);
             if (nan) x = p.x == 1 && p.y == 0 ? x0 : cmul(x0, p);
         }
         tile[a] = x;
@@ -191,7 +191,7 @@ __device__ __forceinline__ void block_in_tile(typename Cx<R>::T *tile, const Blk
         soff[c] = o;
     }
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    BlkEnt nxt = load_const(ent + wave);   // wave < kBlkEnts
+    BlkEnt nxt = load_const(ent + wave);   // wave < kBlkEntsPad
     const uint32_t uuni = tile_coords(g, tnum);
     const uint32_t nl = g.nlane, nq = 1u << g.nuni, amask = g.amask;
     uint32_t al = 0;
@@ -262,7 +262,7 @@ __device__ __forceinline__ void mfma_in_tile(typename Cx<R>::T *tile, const BlkG
     };
     const uint32_t lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t j = lane & 15, kk = lane >> 4;
-    BlkEnt nxt = load_const(ent + wave);   // wave < kBlkEnts
+    BlkEnt nxt = load_const(ent + wave);   // wave < kBlkEntsPad
     const uint32_t uuni = tile_coords(g, tnum);
     const uint32_t nq = 1u << g.nuni, amask = g.amask;
     uint32_t al = 0;
@@ -415,7 +415,7 @@ __global__ void __launch_bounds__(NT, 4) k_blocked(R *__restrict__ psi_r, const 
         if (t + gridDim.x < s.ntiles) load_ahead(t + gridDim.x);
         __syncthreads();
         while (gi < s.g1) {
-            CPtr<BlkEnt> e = ent + gi * kBlkEnts;
+            CPtr<BlkEnt> e = ent + g.ent;
             if (g.kind == 0) {
                 diag_run<R, S, NT>(tile, area, gates + gi, e, g.run, tile_amps);
                 gi += (uint32_t)g.run;

@@ -51,7 +51,7 @@ struct alignas(128) BlkGate {
     // first entry in LDS: phase table, in the table area, a multiple of its
     // 2^k entries; blocks of d >= 4, in the matrices
     uint32_t lds;
-    uint32_t ent, nent;      // kind 2: its work units in the entry table
+    uint32_t ent, nent;      // its first entry in the entry table; kind 2: its work units there
     uint32_t span[kGroupMaxD];  // blocks: LDS element of virtual basis vector i < d
     uint64_t mat;            // blocks: offset (reals) of the matrices in the fused list's buffer
     union {
@@ -68,10 +68,14 @@ struct alignas(128) BlkGate {
     };
 };
 static_assert(sizeof(BlkGate) == 128, "two scalar loads of 16 words");
-// Entries of operation g start at g * kBlkEnts: blocks, the 2^nuni uniform
-// coset parts; phase table, the uniform local index of each iteration over the
-// tile.  The work units of kind 2 follow those of every operation.
-constexpr uint32_t kBlkEnts = 64;
+// Entries of an operation: blocks, the 2^nuni <= 64 uniform coset parts; phase
+// table, the uniform local index of each iteration over the tile, a run's
+// tables side by side.  The work units of kind 2 follow those of every
+// operation.  Every wave reads one entry before it knows whether it has work,
+// so the table ends in kBlkEntsPad unused ones.  (64 entries for each operation
+// whatever it uses made the upload of a fresh list's tables the largest part of
+// its first application.)
+constexpr uint32_t kBlkEntsPad = 16;
 struct BlkEnt {
     uint32_t u, a;           // blocks: virtual coordinates, LDS element; phase table: local index;
                              // kind 2: phase table (gate index), 64-entry slice

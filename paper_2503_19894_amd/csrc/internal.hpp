@@ -6,6 +6,7 @@
 #include <complex>
 #include <cstdint>
 #include <memory>
+#include <functional>
 #include <string>
 #include <vector>
 
@@ -124,20 +125,21 @@ bool mfma_fits(int n, cast_dtype dt, const PassPlan &p);
 // Device layout of a plan's matrices (reals of the state dtype): the active
 // blocks, or for diagonal plans (d = 0) the full diagonal of 2^k entries.
 template <typename R>
-void pack_plan(const PassPlan &p, std::vector<R> &dst) {
+void write_plan(const PassPlan &p, R *dst) {
     if (p.d == 0) {
         const size_t D = (size_t)1 << p.k;
         for (size_t j = 0; j < D; ++j) {
-            dst.push_back((R)p.full[j * D + j].real());
-            dst.push_back((R)p.full[j * D + j].imag());
+            *dst++ = (R)p.full[j * D + j].real();
+            *dst++ = (R)p.full[j * D + j].imag();
         }
         return;
     }
     for (const cplx &z : p.mat) {
-        dst.push_back((R)z.real());
-        dst.push_back((R)z.imag());
+        *dst++ = (R)z.real();
+        *dst++ = (R)z.imag();
     }
 }
+inline size_t plan_reals(const PassPlan &p) { return p.d == 0 ? (size_t)2 << p.k : 2 * p.mat.size(); }
 int pass_kernel_kind(int n, cast_dtype dt, const PassPlan &p);
 
 // Launch shape of one direct pass, overriding the knobs (-1: the knob's
@@ -152,14 +154,18 @@ cast_status launch_pass(void *psi, int n, cast_dtype dt, const PassPlan &p, cons
                         hipStream_t stream, const PassShape *shape = nullptr,
                         const MatArg *inl = nullptr);
 
+// Synchronous copy of a list's tables.
+hipError_t copy_to_device(void *dst, const void *src, size_t bytes);
+
 // Uploads a plan's matrices (cast to dt) into a new device buffer; the host
 // staging is synchronous (the buffer is ready when this returns).
 cast_status upload_plan(const PassPlan &p, cast_dtype dt, DeviceMatrix *out);
 // `tail`: further bytes for the same allocation and copy, at a multiple of 256
-// (*tail_at); the block is then larger than the matrices alone.
+// (*tail_at), which `write` fills (they are 0 before); the block is then larger
+// than the matrices alone.
 cast_status upload_plans(const std::vector<PassPlan> &ps, cast_dtype dt, DeviceMatrix *out,
-                         std::vector<size_t> *offsets, const std::vector<char> *tail = nullptr,
-                         size_t *tail_at = nullptr);
+                         std::vector<size_t> *offsets, size_t tail = 0,
+                         const std::function<void(char *)> &write = nullptr, size_t *tail_at = nullptr);
 // The offsets (in reals) upload_plans gives each plan, computed on the host.
 std::vector<size_t> plan_offsets(const std::vector<PassPlan> &ps, cast_dtype dt);
 
