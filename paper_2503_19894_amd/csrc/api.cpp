@@ -479,7 +479,7 @@ cast_status apply_gate(cast_sv *sv, const int *qubits, int k, const double *matr
     const void *src = host.data();
     if (sv->dt == CAST_C128) write_plan(p, host.data());
     else write_plan(p, (float *)host.data());
-    if (bytes <= MatArg::kBytes && p.d < 4) {
+    if (bytes <= MatArg::kBytes && p.d <= kMatArgMaxD) {
         // No copy and no wait: the launch carries the matrix.  A gate whose
         // matrix went through a staging buffer (pageable copy, stream
         // synchronisation, event) took 21 us on a 12-qubit state, now 6.9 us.

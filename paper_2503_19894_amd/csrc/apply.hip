@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 
 #include <cstring>
+#include <type_traits>
 
 #include "internal.hpp"
 #include "mfma.hpp"
@@ -61,15 +62,25 @@ __device__ __forceinline__ void cmac(V &acc, R mre, R mim, const V &v) {
     acc.y = fma(mim, v.x, acc.y);
 }
 
-// The pass's matrices: device memory, or (null) the MatArg behind the
-// (pointer, pointer, argument block) of the launch.  Read-only address space,
-// so uniform reads stay scalar loads on either.
-template <typename R, typename Args>
-__device__ __forceinline__ const __attribute__((address_space(4))) R *pass_matrix(const R *mat) {
-    static_assert(sizeof(Args) % 8 == 0 && alignof(Args) == 8, "MatArg follows the argument block");
+// The pass's matrices: device memory, or the MatArg behind the (pointer,
+// pointer, argument block) of a launch that has one (Arg...: MatArg or nothing;
+// in every launch, read or not, it costs the runtime the copy of 1 KiB more of
+// arguments: 35 two-qubit gates on 8 qubits, a launch each, 155 us instead of
+// 147).  In the read-only address space uniform reads stay scalar loads on
+// either; blocks of 16 and more dimensions never come as a MatArg and keep an
+// ordinary pointer, with which the compiler holds less of the matrix in registers.
+template <int D, typename Args, typename... Arg, typename R>
+__device__ __forceinline__ auto pass_mats(const R *__restrict__ mat) {
     typedef const __attribute__((address_space(4))) R *P;
-    typedef const __attribute__((address_space(4))) char *B;
-    return mat ? (P)(uintptr_t)mat : (P)((B)__builtin_amdgcn_kernarg_segment_ptr() + 16 + sizeof(Args));
+    if constexpr (sizeof...(Arg) != 0) {
+        static_assert(sizeof(Args) % 8 == 0 && alignof(Args) == 8, "MatArg follows the argument block");
+        typedef const __attribute__((address_space(4))) char *B;
+        return (P)((B)__builtin_amdgcn_kernarg_segment_ptr() + 16 + sizeof(Args));
+    } else if constexpr (D <= kMatArgMaxD) {
+        return (P)(uintptr_t)mat;
+    } else {
+        return mat;
+    }
 }
 
 // ------------------------------------------------------------------ direct
@@ -120,13 +131,13 @@ __device__ __forceinline__ void direct_item(uint64_t i, uint32_t nblk, int cl, u
     g = ((uint64_t)gs << cl) | (i & ((1ull << cl) - 1));
 }
 
-template <int D, typename R, int IPT, bool NT>
+template <int D, typename R, int IPT, bool NT, typename... Arg>
 __global__ void __launch_bounds__(256) k_direct(R *__restrict__ psi_r, const R *__restrict__ dmat,
-                                                PassArgs a, MatArg) {
+                                                PassArgs a, Arg...) {
+    const auto mat = pass_mats<D, PassArgs, Arg...>(dmat);
     using V = typename Amp<R>::T;
     constexpr int N = 1 << D;
     V *psi = reinterpret_cast<V *>(psi_r);
-    const auto mat = pass_matrix<R, PassArgs>(dmat);
     const uint64_t items = a.ngroups * a.nblk;
     constexpr uint64_t per_iter = 256ull * IPT;
     const uint64_t nfull = items / per_iter;
@@ -137,7 +148,7 @@ __global__ void __launch_bounds__(256) k_direct(R *__restrict__ psi_r, const R *
         const uint64_t it =
             a.rot ? (((it0 << a.rot) | (it0 >> (a.it_bits - a.rot))) & ((1ull << a.it_bits) - 1)) : it0;
         uint64_t base[IPT];
-        decltype(pass_matrix<R, PassArgs>(nullptr)) m[IPT];
+        std::remove_const_t<decltype(mat)> m[IPT];
         V v[IPT][N];
 #pragma unroll
         for (int u = 0; u < IPT; ++u) {
@@ -217,14 +228,14 @@ __device__ __forceinline__ uint64_t xcd_spread(uint64_t it) {
     return (r << 3) | ((it ^ f) & 7);
 }
 
-template <typename R, int U, bool LDS_TABLE>
-__global__ void __launch_bounds__(256) k_diag(R *__restrict__ psi_r, const R *__restrict__ dmat, DiagArgs a, MatArg) {
+template <typename R, int U, bool LDS_TABLE, typename... Arg>
+__global__ void __launch_bounds__(256) k_diag(R *__restrict__ psi_r, const R *__restrict__ dmat, DiagArgs a, Arg...) {
+    const auto table = pass_mats<0, DiagArgs, Arg...>(dmat);
     using V = typename Amp<R>::T;
     constexpr int S = sizeof(V) == 16 ? 0 : 1;   // log2(amplitudes per 16-byte chunk)
     constexpr int A = 1 << S;
     // phases: staged in LDS, or read straight from the (L1-resident) table
     __shared__ V tab_lds[LDS_TABLE ? 64 : 1];
-    const auto table = pass_matrix<R, DiagArgs>(dmat);
     auto phase = [&](uint32_t j) {
         if (LDS_TABLE) return tab_lds[j];
         V t;
@@ -356,13 +367,13 @@ __device__ __forceinline__ uint64_t tile_chunk_addr(uint32_t c, uint64_t tbase, 
 // high target j lands on bit W + j.  TWOBUF: the group's inputs are re-read
 // from LDS for each output row and the results go to a second LDS tile (used
 // when 2^d inputs do not fit in registers).
-template <int D, typename R, bool UNI, bool TWOBUF>
+template <int D, typename R, bool UNI, bool TWOBUF, typename... Arg>
 __global__ void __launch_bounds__(256) k_tile(R *__restrict__ psi_r, const R *__restrict__ dmat,
-                                              PassArgs a, MatArg) {
+                                              PassArgs a, Arg...) {
+    const auto mat = pass_mats<D, PassArgs, Arg...>(dmat);
     using V = typename Amp<R>::T;
     constexpr int N = 1 << D;
     constexpr int S = sizeof(V) == 16 ? 0 : 1;   // log2(amplitudes per 16-byte chunk)
-    const auto mat = pass_matrix<R, PassArgs>(dmat);
     extern __shared__ uint4 lds_raw[];
     V *tile = reinterpret_cast<V *>(lds_raw);
     const uint32_t tile_amps = 1u << a.tb;
@@ -812,14 +823,19 @@ __global__ void __launch_bounds__(256) k_mfma_tile(R *__restrict__ psi_r, const 
 
 // ------------------------------------------------------------------ dispatch
 template <int DD, typename R, int IPT, bool NT>
-static void launch_one(R *psi, const R *m, const PassArgs &a, const MatArg &mi, int grid, hipStream_t s) {
+static void launch_one(R *psi, const R *m, const PassArgs &a, const MatArg *mi, int grid, hipStream_t s) {
+    if constexpr (DD <= kMatArgMaxD)
+        if (mi) {
+            hipLaunchKernelGGL((k_direct<DD, R, IPT, NT, MatArg>), dim3(grid), dim3(256), 0, s, psi, m, a, *mi);
+            return;
+        }
     // several items per thread only pay (and only fit) for small blocks
     if constexpr (IPT == 1 || DD <= 3)
-        hipLaunchKernelGGL((k_direct<DD, R, IPT, NT>), dim3(grid), dim3(256), 0, s, psi, m, a, mi);
+        hipLaunchKernelGGL((k_direct<DD, R, IPT, NT>), dim3(grid), dim3(256), 0, s, psi, m, a);
 }
 
 template <typename R, int IPT, bool NT>
-static void launch_direct_t(int D, R *psi, const R *m, const PassArgs &a, const MatArg &mi, int grid, hipStream_t s) {
+static void launch_direct_t(int D, R *psi, const R *m, const PassArgs &a, const MatArg *mi, int grid, hipStream_t s) {
 #define CAST_DIRECT(DD) \
     case DD: launch_one<DD, R, IPT, NT>(psi, m, a, mi, grid, s); break;
     switch (D) {
@@ -839,7 +855,7 @@ static int direct_ipt(int D, cast_dtype dt) {
 }
 
 template <typename R>
-static hipError_t launch_direct(int D, cast_dtype dt, R *psi, const R *m, const PassArgs &a, const MatArg &mi,
+static hipError_t launch_direct(int D, cast_dtype dt, R *psi, const R *m, const PassArgs &a, const MatArg *mi,
                                 hipStream_t s, int rot_override) {
     const int ipt = direct_ipt(D, dt);
     const bool nt = tuning().direct_nt[dt] != 0;
@@ -879,7 +895,7 @@ static hipError_t launch_direct(int D, cast_dtype dt, R *psi, const R *m, const 
 
 template <typename R>
 static hipError_t launch_tile(int D, bool uni, bool twobuf, R *psi, const R *m, const PassArgs &a,
-                              const MatArg &mi, int grid, int wg, size_t lds, hipStream_t s) {
+                              const MatArg *mi, int grid, int wg, size_t lds, hipStream_t s) {
     if (lds > 65536) {
         // only the k = d = 6 two-buffer variants need more than 64 KiB
         static bool done[2][2] = {{false, false}, {false, false}};
@@ -893,14 +909,29 @@ static hipError_t launch_tile(int D, bool uni, bool twobuf, R *psi, const R *m, 
             done[ri][uni] = true;
         }
     }
+    if (mi) {
+        if (twobuf) return hipErrorInvalidValue;
+#define CAST_TILE(DD)                                                                                      \
+    case DD:                                                                                               \
+        if (uni) hipLaunchKernelGGL((k_tile<DD, R, true, false, MatArg>), dim3(grid), dim3(wg), lds, s, psi, m, a, *mi); \
+        else hipLaunchKernelGGL((k_tile<DD, R, false, false, MatArg>), dim3(grid), dim3(wg), lds, s, psi, m, a, *mi);    \
+        break;
+        static_assert(kMatArgMaxD == 3, "every dimension a MatArg comes with");
+        switch (D) {
+            CAST_TILE(0) CAST_TILE(1) CAST_TILE(2) CAST_TILE(3)
+            default: return hipErrorInvalidValue;
+        }
+#undef CAST_TILE
+        return hipGetLastError();
+    }
 #define CAST_TILE(DD)                                                                                      \
     case DD:                                                                                               \
         if (twobuf) {                                                                                      \
-            if (uni) hipLaunchKernelGGL((k_tile<DD, R, true, true>), dim3(grid), dim3(wg), lds, s, psi, m, a, mi); \
-            else hipLaunchKernelGGL((k_tile<DD, R, false, true>), dim3(grid), dim3(wg), lds, s, psi, m, a, mi);    \
+            if (uni) hipLaunchKernelGGL((k_tile<DD, R, true, true>), dim3(grid), dim3(wg), lds, s, psi, m, a); \
+            else hipLaunchKernelGGL((k_tile<DD, R, false, true>), dim3(grid), dim3(wg), lds, s, psi, m, a);    \
         } else {                                                                                           \
-            if (uni) hipLaunchKernelGGL((k_tile<DD, R, true, false>), dim3(grid), dim3(wg), lds, s, psi, m, a, mi); \
-            else hipLaunchKernelGGL((k_tile<DD, R, false, false>), dim3(grid), dim3(wg), lds, s, psi, m, a, mi);    \
+            if (uni) hipLaunchKernelGGL((k_tile<DD, R, true, false>), dim3(grid), dim3(wg), lds, s, psi, m, a); \
+            else hipLaunchKernelGGL((k_tile<DD, R, false, false>), dim3(grid), dim3(wg), lds, s, psi, m, a);    \
         }                                                                                                  \
         break;
     switch (D) {
@@ -912,12 +943,14 @@ static hipError_t launch_tile(int D, bool uni, bool twobuf, R *psi, const R *m, 
 }
 
 template <typename R>
-static hipError_t launch_diag(int U, bool lds_table, R *psi, const R *m, const DiagArgs &g, const MatArg &mi, int grid,
+static hipError_t launch_diag(int U, bool lds_table, R *psi, const R *m, const DiagArgs &g, const MatArg *mi, int grid,
                               hipStream_t s) {
 #define CAST_DIAG(UU)                                                                                     \
     case UU:                                                                                              \
-        if (lds_table) hipLaunchKernelGGL((k_diag<R, UU, true>), dim3(grid), dim3(256), 0, s, psi, m, g, mi);  \
-        else hipLaunchKernelGGL((k_diag<R, UU, false>), dim3(grid), dim3(256), 0, s, psi, m, g, mi);          \
+        if (mi && lds_table) hipLaunchKernelGGL((k_diag<R, UU, true, MatArg>), dim3(grid), dim3(256), 0, s, psi, m, g, *mi); \
+        else if (mi) hipLaunchKernelGGL((k_diag<R, UU, false, MatArg>), dim3(grid), dim3(256), 0, s, psi, m, g, *mi); \
+        else if (lds_table) hipLaunchKernelGGL((k_diag<R, UU, true>), dim3(grid), dim3(256), 0, s, psi, m, g);  \
+        else hipLaunchKernelGGL((k_diag<R, UU, false>), dim3(grid), dim3(256), 0, s, psi, m, g);          \
         break;
     switch (U) {
         CAST_DIAG(1) CAST_DIAG(2) CAST_DIAG(4) CAST_DIAG(8)
@@ -1032,9 +1065,8 @@ static hipError_t launch_mfma(int D, bool tile, bool m3, int prefetch, R *psi, c
 cast_status launch_pass(void *psi, int n, cast_dtype dt, const PassPlan &p, const void *dmat,
                         hipStream_t stream, const PassShape *shape, const MatArg *inl) {
     if (p.identity()) return CAST_OK;
-    static const MatArg unread{};
-    const MatArg &mi = inl ? *inl : unread;
-    if (inl) dmat = nullptr;
+    if (inl && p.d > kMatArgMaxD) return fail(CAST_EINVAL, "matrices of this dimension are read from the device");
+    const MatArg *mi = inl;
     const Tuning &tu = tuning();
     const int k = p.k, D = p.d;
     PassArgs a;
@@ -1054,7 +1086,6 @@ cast_status launch_pass(void *psi, int n, cast_dtype dt, const PassPlan &p, cons
     const bool direct = kind == 0;
     hipError_t e;
     if (kind == 4 || kind == 5) {
-        if (inl) return fail(CAST_EINVAL, "matrix-core passes read device matrices");
         for (int i = 0; i < k; ++i) a.lowmask[i] = (1ull << p.q[i]) - 1;
         a.ngroups = 1ull << (n - k);
         size_t lds = mfma_mat_bytes(dt, p);

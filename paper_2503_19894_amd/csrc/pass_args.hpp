@@ -24,10 +24,9 @@ struct PassArgs {
     int rot, it_bits;       // direct (iterations) and matrix-core direct (four-unit runs): order rotated left by rot bits of it_bits (rot 0: in order)
 };
 
-// A pass's matrices (or phase table) carried by the launch itself, for a pass
-// whose matrix is on the host and used once.  It follows the argument block in
-// the kernel's arguments; a launch that passes a device pointer leaves it
-// unread.
+// A pass's matrices (or phase table) carried by the launch itself, behind the
+// argument block, for a pass whose matrix is on the host and used once.
+constexpr int kMatArgMaxD = 3;      // largest block dimension that comes this way
 struct MatArg {
     static constexpr std::size_t kBytes = 1024;   // a dense 3-qubit gate, or a 6-qubit phase table, in complex128
     alignas(8) unsigned char b[kBytes];
