@@ -403,7 +403,9 @@ cast_status path_cost_get(const char *key, cast_dtype dt, double *value);
  * apply_circuit (path 0: a launch plus max(algorithmic bytes / rate, flops /
  * rate) per pass) or apply_circuit_blocked (path 1: ordinary passes the same
  * way, a segment one read and write of the state plus its gates' in-tile
- * costs).  Host only. */
+ * costs).  Path 0 prices a launch for every pass; where passes share launches
+ * (tile_groups) apply_circuit takes less, so with path 1 close behind path 0 or
+ * ahead of it only timing both tells which is faster.  Host only. */
 cast_status predict_ms(const cast_fused *f, int n, cast_dtype dt, int path, double *ms);
 
 /* Fuses the circuit (fixed gates, as fuse_circuit) at every size limit

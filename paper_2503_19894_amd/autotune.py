@@ -154,6 +154,14 @@ def stream_rate(buf, nbytes, reps=5):
     return 2.0 * nbytes / (best * 1e-3) / 1e9
 
 
+def gate_slope(points):
+    """(ms per gate, ms at no gate) of the line through two (gates, ms) points;
+    None if more gates took no longer, which measures nothing."""
+    (m0, t0), (m1, t1) = points
+    slope = (t1 - t0) / (m1 - m0)
+    return (slope, t0 - slope * m0) if slope > 0 else None
+
+
 def path_costs(n, dtype, log):
     """Rates the path planner prices plans with (measured on 2^n states):
     algorithmic GB/s of each pass kernel, the matrix cores' GFLOP/s by block
@@ -193,14 +201,17 @@ def path_costs(n, dtype, log):
     small = cast.StateVector(12, dtype=dtype)
     fc = cast.FusedCircuit(12, gate_sweep("haar", 2, (10, 11), seed=1) * 1, k_max=2)
     out["launch_ms"] = float(np.median(_timed_passes(small, fc, reps=7)))
-    # segments: m gates of block dimension d on the low qubits, one segment
+    # segments: m gates of block dimension d, one segment; blocks on the low
+    # qubits, diagonal gates anywhere (on the low qubits alone they would all
+    # be multiplied into one phase table), in and out of the tile, and more of
+    # them (the first few dozen hide behind the tile's loads and stores)
     seg = {}
     for d in (0, 1, 2, 3):
         pts = []
-        for m in (4, 24):
+        for m in (4, 24) if d else (40, 200):
             gates = []
             for i in range(m):
-                qs = tuple(sorted(rng.permutation(8)[:max(d, 1) + (1 if d == 0 else 0)]))
+                qs = tuple(sorted(int(q) for q in rng.permutation(8 if d else n)[:d if d else 2]))
                 if d == 0:
                     gates.append(Gate("unitary", qs, matrix=np.diag(np.exp(1j * rng.uniform(0.1, 6, 1 << len(qs))))))
                 else:
@@ -213,9 +224,11 @@ def path_costs(n, dtype, log):
             t = min(float(sv.apply_circuit_blocked_timed(fc)[0]) for _ in range(3))
             pts.append((len(fc), t))
         if len(pts) == 2 and pts[1][0] > pts[0][0]:
-            (m0, t0), (m1, t1) = pts
-            b = (t1 - t0) / (m1 - m0)
-            seg[d] = (max(b, 1e-4) * 2.0 ** (30 - n), t0 - b * m0)
+            fit = gate_slope(pts)
+            if fit is None:
+                log(f"  seg_gate{d}: no slope in {pts}, left as it was")
+                continue
+            seg[d] = (fit[0] * 2.0 ** (30 - n), fit[1])
     for d, (per_gate, _) in seg.items():
         out[f"seg_gate{d}"] = per_gate
     base = [a for _, a in seg.values() if a > 0]
