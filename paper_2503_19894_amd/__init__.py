@@ -195,55 +195,28 @@ def std_matrix(name, params=()):
     return out[:2 * D * D].reshape(D, D, 2).copy()
 
 
-#: cast_gate as a numpy record (GateArray fills whole columns)
-_GATE_REC = np.dtype({"names": [f for f, _ in cast_gate._fields_],
-                      "formats": [np.int32, (np.int32, 6), np.uintp, np.int32, np.float64, np.int32],
-                      "offsets": [getattr(cast_gate, f).offset for f, _ in cast_gate._fields_],
-                      "itemsize": ctypes.sizeof(cast_gate)})
-
-
-def _int32(values):
-    """int(v) of each value as a C int array; like a ctypes field, it keeps the
-    low 32 bits."""
-    try:
-        a = np.array(values)
-    except ValueError:
-        a = None
-    if a is None or a.dtype != np.int64 or a.ndim != 1:   # floats, texts, integers past 64 bits, nested values
-        a = np.array([int(v) & 0xffffffff for v in values], dtype=np.int64)
-    return a.astype(np.int32)
-
-
 class GateArray:
     """cast_gate[] for a list of gate records (keeps matrices alive)."""
 
     def __init__(self, gates):
-        n = len(gates)
-        rec = np.zeros(max(1, n), dtype=_GATE_REC)
-        self._keep = [rec]
-        k, qubits, matrix, param, coeff, generator = [], [], [], [], [], []
-        std = {}   # addresses of this list's standard matrices, by name and angles
-        for g in gates:
-            q, p = g.qubits, int(getattr(g, "param", -1))
-            kq = len(q)
-            if kq > 6:
-                raise IndexError("a gate record holds at most six qubits")
-            if not -0x80000000 <= p < 0x80000000:
-                p = int(_int32([p])[0])
-            k.append(kq)
-            qubits.extend(q)
-            qubits.extend((0,) * (6 - kq))
-            param.append(p)
-            coeff.append(float(getattr(g, "coeff", 1.0)))
-            if p >= 0:
-                generator.append(_GEN[g.name])
-                matrix.append(0)
+        self.n = len(gates)
+        self.arr = (cast_gate * max(1, self.n))()
+        self._keep = []
+        std = {}   # this list's standard matrices by name and angles
+        for cg, g in zip(self.arr, gates):
+            cg.k = len(g.qubits)
+            qubits = cg.qubits
+            for j, q in enumerate(g.qubits):
+                qubits[j] = int(q)
+            cg.param_id = int(getattr(g, "param", -1))
+            cg.param_coeff = float(getattr(g, "coeff", 1.0))
+            if cg.param_id >= 0:
+                cg.generator = _GEN[g.name]
                 continue
-            generator.append(0)
             if g.name == "unitary":
                 m = np.ascontiguousarray(np.asarray(g.matrix, dtype=np.complex128)).view(np.float64).copy()
                 self._keep.append(m)
-                matrix.append(m.ctypes.data)
+                cg.matrix = _dptr(m)
                 continue
             try:
                 key = (g.name, tuple(g.params))
@@ -253,38 +226,26 @@ class GateArray:
             if hit is None:
                 m = std_matrix(g.name, g.params)
                 self._keep.append(m)
-                hit = m.ctypes.data
+                hit = _dptr(m)
                 if key is not None:
                     std[key] = hit
-            matrix.append(hit)
-        if n:
-            rec["k"], rec["param_id"], rec["param_coeff"] = k, param, coeff
-            rec["qubits"] = _int32(qubits).reshape(n, 6)
-            rec["matrix"], rec["generator"] = matrix, generator
-        self.arr = (cast_gate * max(1, n)).from_buffer(rec)
-        self.n = n
-
-
-_TERM_REC = np.dtype([("coeff", np.float64), ("xmask", np.uint64), ("zmask", np.uint64)])
+            cg.matrix = hit
 
 
 def pauli_terms(terms):
     """cast_pauli_term[] from records with .coeff and .ops = ((qubit, 'X'|'Y'|'Z'), ...)."""
-    coeff, xmask, zmask = [], [], []
-    for t in terms:
+    arr = (cast_pauli_term * max(1, len(terms)))()
+    for a, t in zip(arr, terms):
         x = z = 0
         for q, p in t.ops:
             if p in "XY":
                 x |= 1 << q
             if p in "YZ":
                 z |= 1 << q
-        coeff.append(float(t.coeff))
-        xmask.append(int(x) & 0xffffffffffffffff)   # (qubits may be numpy integers)
-        zmask.append(int(z) & 0xffffffffffffffff)
-    rec = np.zeros(max(1, len(terms)), dtype=_TERM_REC)
-    if len(terms):
-        rec["coeff"], rec["xmask"], rec["zmask"] = coeff, xmask, zmask
-    return (cast_pauli_term * len(rec)).from_buffer(rec)
+        a.coeff = float(t.coeff)
+        a.xmask = x
+        a.zmask = z
+    return arr
 
 
 def fusion_options(k_max=5, opcount_cap=0.0, zero_tol=1e-14, one_tol=1e-14, agglomerative=True,
