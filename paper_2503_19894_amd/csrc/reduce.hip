@@ -4,7 +4,8 @@
 // letter), so (P psi)[y ^ x] = i^{|x&z|} (-1)^{|z&y|} psi[y] and
 //   <a|P|b> = i^{|x&z|} * S(x, z),  S(x, z) = sum_y conj(a[y^x]) (-1)^{|z&y|} b[y].
 // k_pauli_inner computes S of one string between two states, k_expval the
-// weighted sum of many strings on one state; both accumulate products in FP64
+// weighted sum of many strings on one state, k_expval_flip that of strings with
+// one x mask; all accumulate products in FP64
 // (complex64 inputs are promoted per product).  Reduction order is fixed
 // (grid-stride partials, wave shuffles, LDS tree, then one finishing block),
 // so results are bitwise reproducible for a given n.
@@ -369,7 +370,6 @@ struct ExpPlan {
     uint64_t need[kExpPasses];   // qubits the pass's x masks flip
     uint8_t pass_of[kExpGroups];
     size_t used = 0;             // partial sums queued so far
-    bool first = true;
 
     // window w = T - #{q in need: q >= w} of a tile holding `q`, or -1
     int window(uint64_t q) const {
@@ -476,6 +476,115 @@ struct ExpPlan {
 
 }  // namespace
 
+// Strings that share one x mask: the state is streamed once.  Both of a pair
+// (y, y ^ x) give the same value, so a lane takes the one with bit hb clear, the
+// highest of x, and reads both; if x lies within a wave's amplitudes (below bit
+// 6) every lane takes its own, whose partner is in the same lines.
+//   Bound: HBM, one read of the state.
+//   For a single string, and for strings whose partner lies in no tile: there
+//   k_expval reads the state twice, the second time once for each parity of
+//   |x & z|, and its 3 KiB of arguments cost a small state 1 us.
+//   Split: J items per lane in flight on 2048 workgroups; full sweeps in
+//   complex128, 16 bytes per lane each, are as fast with one on 1024 (27 qubits,
+//   409 us; four: 435 where the partner is read too), in complex64 they are not
+//   (429; four: 240).
+//   Measured: one string that flips all of 27 qubits, complex64, 204 us (k_expval
+//   453, each amplitude with its partner 383); two with different parities 210
+//   (610).
+constexpr int kFlipTerms = 16, kFlipBlocks = 2048;
+struct FlipArgs {
+    double c[kFlipTerms];
+    uint64_t z[kFlipTerms];
+    uint32_t odd;           // bit m: Im
+    int count, hb;          // hb: -1: every amplitude
+};
+
+template <typename R, int J>
+__global__ void __launch_bounds__(kRedThreads) k_expval_flip(const R *__restrict__ psi_r, uint64_t items, uint64_t x,
+                                                            FlipArgs a, double *__restrict__ partial) {
+    using V = typename AmpR<R>::T;
+    const V *psi = reinterpret_cast<const V *>(psi_r);
+    const uint64_t stride = (uint64_t)gridDim.x * kRedThreads;
+    const uint64_t low = a.hb < 0 ? ~0ull : (1ull << a.hb) - 1;
+    const double c0 = a.c[0];
+    const uint64_t z0 = a.z[0];
+    double e = 0.0;
+    for (uint64_t i0 = (uint64_t)blockIdx.x * kRedThreads + threadIdx.x; i0 < items; i0 += J * stride) {
+        V u[J], w[J];
+        uint64_t y[J];
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const uint64_t i = i0 + j * stride;
+            y[j] = ((i & ~low) << 1) | (i & low);
+            u[j].x = u[j].y = w[j].x = w[j].y = 0;
+            if (i < items) {
+                u[j] = psi[y[j]];
+                w[j] = x == 0 ? u[j] : psi[y[j] ^ x];
+            }
+        }
+#pragma unroll
+        for (int j = 0; j < J; ++j) {
+            const double ur = u[j].x, ui = u[j].y, wr = w[j].x, wi = w[j].y;
+            const double re = wr * ur + wi * ui, im = wr * ui - wi * ur;
+            e = fma(flip_sign(c0, (uint32_t)__popcll(z0 & y[j])), a.odd & 1u ? im : re, e);
+            for (int m = 1; m < a.count; ++m)
+                e = fma(flip_sign(a.c[m], (uint32_t)__popcll(a.z[m] & y[j])), (a.odd >> m) & 1u ? im : re, e);
+        }
+    }
+    __shared__ double red[kRedThreads / 64];
+    e = wave_sum(e);
+    if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = e;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        double t = 0.0;
+        for (int i = 0; i < kRedThreads / 64; ++i) t += red[i];
+        partial[blockIdx.x] = t;
+    }
+}
+
+// i^{|x&z|} S with S = Re, or i Im for an odd power
+static double real_coeff(const cast_pauli_term &t) {
+    const int pw = __builtin_popcountll(t.xmask & t.zmask) & 3;
+    return pw == 1 || pw == 2 ? -t.coeff : t.coeff;
+}
+
+static cast_status expval_flip(const void *psi, int n, cast_dtype dt, const cast_pauli_term *terms, size_t n_terms,
+                               double *scratch, double *dev_out, hipStream_t s) {
+    const uint64_t x = terms[0].xmask;
+    const bool pairs = x >> 6, four = pairs || dt == CAST_C64;
+    const uint64_t items = 1ull << (pairs ? n - 1 : n);
+    const uint32_t blocks = (uint32_t)std::min<uint64_t>(four ? kFlipBlocks : kFlipBlocks / 2,
+                                                         (items + 4 * kRedThreads - 1) / (4 * kRedThreads));
+    size_t used = 0;
+    auto fold = [&](double *out) {
+        hipLaunchKernelGGL(k_finish, dim3(1), dim3(kRedThreads), 0, s, scratch, (int)used, 1, out);
+        return reduce_error();
+    };
+    for (size_t t = 0; t < n_terms; t += kFlipTerms) {
+        if (used + blocks > kReduceScratch) {   // into its first entry
+            if (cast_status rc = fold(scratch)) return rc;
+            used = 1;
+        }
+        FlipArgs a{};
+        a.count = (int)std::min<size_t>(kFlipTerms, n_terms - t);
+        a.hb = pairs ? 63 - __builtin_clzll(x) : -1;
+        for (int m = 0; m < a.count; ++m) {
+            const cast_pauli_term &p = terms[t + m];
+            a.c[m] = pairs ? 2.0 * real_coeff(p) : real_coeff(p);
+            a.z[m] = p.zmask;
+            a.odd |= (uint32_t)(__builtin_popcountll(p.xmask & p.zmask) & 1) << m;
+        }
+        auto launch = [&](auto kernel, auto *state) {
+            hipLaunchKernelGGL(kernel, dim3(blocks), dim3(kRedThreads), 0, s, state, items, x, a, scratch + used);
+        };
+        if (dt == CAST_C128) launch(four ? k_expval_flip<double, 4> : k_expval_flip<double, 1>, (const double *)psi);
+        else launch(four ? k_expval_flip<float, 4> : k_expval_flip<float, 1>, (const float *)psi);
+        if (cast_status rc = reduce_error()) return rc;
+        used += blocks;
+    }
+    return fold(dev_out);
+}
+
 cast_status expval_sum(const void *psi, int n, cast_dtype dt, const cast_pauli_term *terms, size_t n_terms,
                        uint16_t *order, double *scratch, double *dev_out, hipStream_t s) {
     ExpPlan pl;
@@ -488,6 +597,9 @@ cast_status expval_sum(const void *psi, int n, cast_dtype dt, const cast_pauli_t
     pl.wmin = std::min(dt == CAST_C64 && pl.T == 12 ? 4 : 3, n);
     pl.scratch = scratch;
     pl.s = s;
+    if (std::all_of(terms, terms + n_terms, [&](const cast_pauli_term &t) { return t.xmask == terms[0].xmask; }) &&
+        (n_terms == 1 || pl.window(terms[0].xmask) < 0))
+        return expval_flip(psi, n, dt, terms, n_terms, scratch, dev_out, s);
     for (size_t i = 0; i < n_terms; ++i) order[i] = (uint16_t)i;
     auto odd_of = [&](size_t i) { return __builtin_popcountll(terms[i].xmask & terms[i].zmask) & 1; };
     // by x mask, the diagonal terms last (they fit every pass), then by parity
@@ -516,9 +628,7 @@ cast_status expval_sum(const void *psi, int n, cast_dtype dt, const cast_pauli_t
         G.t0 = pl.nt;
         for (; k < n_terms && pl.nt < kExpTerms && terms[order[k]].xmask == x && odd_of(order[k]) == odd; ++k) {
             const cast_pauli_term &t = terms[order[k]];
-            // i^{|x&z|} S with S = Re, or i Im for an odd power
-            const int pw = __builtin_popcountll(t.xmask & t.zmask) & 3;
-            pl.a.term[pl.nt++] = ExpTerm{pw == 1 || pw == 2 ? -t.coeff : t.coeff, t.zmask, 0, 0};
+            pl.a.term[pl.nt++] = ExpTerm{real_coeff(t), t.zmask, 0, 0};
         }
         G.t1 = pl.nt;
     }
