@@ -66,18 +66,15 @@ __device__ __forceinline__ void cmac(V &acc, R mre, R mim, const V &v) {
 // pointer, argument block) of a launch that has one (Arg...: MatArg or nothing;
 // in every launch, read or not, it costs the runtime the copy of 1 KiB more of
 // arguments: 35 two-qubit gates on 8 qubits, a launch each, 155 us instead of
-// 147).  In the read-only address space uniform reads stay scalar loads on
-// either; blocks of 16 and more dimensions never come as a MatArg and keep an
-// ordinary pointer, with which the compiler holds less of the matrix in registers.
-template <int D, typename Args, typename... Arg, typename R>
+// 147).  Of the arguments uniform reads are scalar loads, as of the restricted
+// pointer.
+template <typename Args, typename... Arg, typename R>
 __device__ __forceinline__ auto pass_mats(const R *__restrict__ mat) {
-    typedef const __attribute__((address_space(4))) R *P;
     if constexpr (sizeof...(Arg) != 0) {
         static_assert(sizeof(Args) % 8 == 0 && alignof(Args) == 8, "MatArg follows the argument block");
         typedef const __attribute__((address_space(4))) char *B;
+        typedef const __attribute__((address_space(4))) R *P;
         return (P)((B)__builtin_amdgcn_kernarg_segment_ptr() + 16 + sizeof(Args));
-    } else if constexpr (D <= kMatArgMaxD) {
-        return (P)(uintptr_t)mat;
     } else {
         return mat;
     }
@@ -134,7 +131,7 @@ __device__ __forceinline__ void direct_item(uint64_t i, uint32_t nblk, int cl, u
 template <int D, typename R, int IPT, bool NT, typename... Arg>
 __global__ void __launch_bounds__(256) k_direct(R *__restrict__ psi_r, const R *__restrict__ dmat,
                                                 PassArgs a, Arg...) {
-    const auto mat = pass_mats<D, PassArgs, Arg...>(dmat);
+    const auto mat = pass_mats<PassArgs, Arg...>(dmat);
     using V = typename Amp<R>::T;
     constexpr int N = 1 << D;
     V *psi = reinterpret_cast<V *>(psi_r);
@@ -230,14 +227,15 @@ __device__ __forceinline__ uint64_t xcd_spread(uint64_t it) {
 
 template <typename R, int U, bool LDS_TABLE, typename... Arg>
 __global__ void __launch_bounds__(256) k_diag(R *__restrict__ psi_r, const R *__restrict__ dmat, DiagArgs a, Arg...) {
-    const auto table = pass_mats<0, DiagArgs, Arg...>(dmat);
+    const auto table = pass_mats<DiagArgs, Arg...>(dmat);
     using V = typename Amp<R>::T;
     constexpr int S = sizeof(V) == 16 ? 0 : 1;   // log2(amplitudes per 16-byte chunk)
     constexpr int A = 1 << S;
     // phases: staged in LDS, or read straight from the (L1-resident) table
     __shared__ V tab_lds[LDS_TABLE ? 64 : 1];
     auto phase = [&](uint32_t j) {
-        if (LDS_TABLE) return tab_lds[j];
+        if constexpr (LDS_TABLE) return tab_lds[j];
+        else if constexpr (sizeof...(Arg) == 0) return reinterpret_cast<const V *>(table)[j];
         V t;
         t.x = table[2 * j];
         t.y = table[2 * j + 1];
@@ -370,7 +368,7 @@ __device__ __forceinline__ uint64_t tile_chunk_addr(uint32_t c, uint64_t tbase, 
 template <int D, typename R, bool UNI, bool TWOBUF, typename... Arg>
 __global__ void __launch_bounds__(256) k_tile(R *__restrict__ psi_r, const R *__restrict__ dmat,
                                               PassArgs a, Arg...) {
-    const auto mat = pass_mats<D, PassArgs, Arg...>(dmat);
+    const auto mat = pass_mats<PassArgs, Arg...>(dmat);
     using V = typename Amp<R>::T;
     constexpr int N = 1 << D;
     constexpr int S = sizeof(V) == 16 ? 0 : 1;   // log2(amplitudes per 16-byte chunk)
