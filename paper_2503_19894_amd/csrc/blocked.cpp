@@ -494,11 +494,13 @@ cast_status check(const cast_sv *sv) {
 // kernel times at 12 to 26 qubits:
 //   a pass    3.8 (direct, diagonal) to 6.5 (through LDS) on any small state,
 //             then its bytes at 5.4 TB/s or its products at 60 / 120 TFLOP/s;
-//   a group   5 + the longer of the state's read and write at 5.2 TB/s and
-//             its operations, + 0.3 of the shorter (up to 256 tiles, a
-//             compute unit has one: their sum, tile by tile at 0.1 TB/s, and
-//             operations but for the matrix cores' take 1.2 as long).  An
-//             operation occupies a
+//   a group   5 (8 with tiles of 2^8 of a larger state, on 256 lanes: a
+//             9-qubit Fourier transform fused to 6 qubits took 44.0 grouped
+//             by 2^8, complex64, and takes 41.5 by 2^9) + the longer of the
+//             state's read and write at 5.2 TB/s and its operations, + 0.3 of
+//             the shorter (up to 256 tiles, a compute unit has one: their
+//             sum, tile by tile at 0.1 TB/s, and operations but for the
+//             matrix cores' take 1.2 as long).  An operation occupies a
 //             compute unit for, per tile of 2^12 amplitudes: a table 0.3,
 //             d = 1 0.7, d = 2 0.8, d = 3 1.1, and per tile of any size 0.1;
 //             d = 4 / 5 3.0 / 5.3 (complex64: 1.5 / 2.8, matrix cores); never
@@ -553,6 +555,7 @@ std::vector<Span> plan_groups(const Schedule &sc, const std::vector<PassPlan> &P
     const Tuning &tu = tuning();
     static const double op_us[] = {0.3, 0.7, 0.8, 1.1, 3.0, 5.3}, least_us[] = {0.8, 0.8, 0.8, 0.8, 1.6, 2.6};
     const double tiles = std::ldexp(1.0, sc.n - tb), rounds = std::max(1.0, tiles / 256);
+    const double base = tb == 8 && sc.n > 8 ? 8.0 : 5.0;
     double op[6];   // of an operation of dimension d, but for a run's tables
     for (int d = 0; d < 6; ++d) op[d] = op_us[d] * std::ldexp(1.0, tb - 12);
     const double mem = 2 * std::ldexp((double)amp_bytes(sc.dt), sc.n) / 5.2e6;
@@ -565,7 +568,7 @@ std::vector<Span> plan_groups(const Schedule &sc, const std::vector<PassPlan> &P
     double sep = 0, ops = 0;            // their own launches, and as operations of a tile
     auto close = [&](size_t b) {
         if (a < b) {
-            const double grp = tiles <= 256 ? 5.0 + lone + ops : 5.0 + std::max(mem, ops) + 0.3 * std::min(mem, ops);
+            const double grp = base + (tiles <= 256 ? lone + ops : std::max(mem, ops) + 0.3 * std::min(mem, ops));
             if (live > 1 && grp < sep) {
                 out.push_back(Span{a, b, need, true});
                 *us += grp;

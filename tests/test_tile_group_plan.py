@@ -79,3 +79,12 @@ def test_matrix_core_knobs(dtype, knob, value, kept_out):
     finally:
         cast.set_tuning(knob, old, dtype)
     assert grouped() == before
+
+
+@pytest.mark.parametrize("dtype", [torch.complex128, torch.complex64], ids=["c128", "c64"])
+def test_tiles_of_256_lanes_cost_more(dtype):
+    """A 9-qubit Fourier transform shares a launch in one tile of 2^9
+    amplitudes, not in two of 2^8 on workgroups of 256 lanes."""
+    fc = cast.FusedCircuit(9, qft(9), k_max=6)
+    launches = fc.launches(dtype)
+    assert {x["tile_bits"] for x in launches} == {0, 9}, launches
