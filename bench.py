@@ -762,11 +762,30 @@ def host_description():
     return {"cpu_model": model, "logical_cpus": os.cpu_count(), "mem_total_gib": round(mem / 2**20, 1)}
 
 
+def run_case_profile(name, passes=3):
+    """One case of perf/cases.py as it runs by default: a pass to warm up, then
+    `passes` between the region markers."""
+    import torch
+
+    import perf.cases as cases
+
+    case = next(c for c in cases.listed() if c["name"] == name)
+    state = cases.prepare(case, 0)
+    cases.run(state)
+    region_marker()
+    for _ in range(passes):
+        cases.run(state)
+    region_marker()
+    torch.cuda.synchronize()
+    return {"case": name, "passes": passes}
+
+
 PROFILES = os.path.join(os.path.dirname(os.path.abspath(__file__)), "profiles")
 CSRC = os.path.join(os.path.dirname(os.path.abspath(__file__)), "paper_2503_19894_amd", "csrc")
 # kernel name prefix -> the source file that defines it
 KERNEL_FILES = (("k_diag_run", "diagrun.hip"), ("k_blocked", "blocked.hip"), ("k_batch", "batch_kernels.hip"),
                 ("k_pauli", "reduce.hip"), ("k_apply_pauli", "reduce.hip"), ("k_finish", "reduce.hip"),
+                ("k_expval", "reduce.hip"),
                 ("k_stream", "stream.hip"), ("k_", "apply.hip"))
 
 
@@ -937,6 +956,8 @@ def main():
     ap.add_argument("--no-tfim", action="store_true")
     ap.add_argument("--tfim-only", action="store_true", help="only the mixed-size TFIM batch")
     ap.add_argument("--dense-only", action="store_true", help="only the 32-qubit dense circuit")
+    ap.add_argument("--case-profile", metavar="NAME",
+                    help="only passes of one case of perf/cases.py (a profiled command)")
     ap.add_argument("--calibrate-copy", action="store_true",
                     help="first run one device copy of exactly 1 GiB (reference for HBM byte counters)")
     ap.add_argument("--summarize-kernel-trace", nargs="+", metavar="STATS_CSV COMMAND [NAME_FILTER]")
@@ -985,6 +1006,9 @@ def main():
         dst.copy_(src)
         torch.cuda.synchronize()
         del src, dst
+    if args.case_profile:
+        print(json.dumps(run_case_profile(args.case_profile)), flush=True)
+        return
     import paper_2503_19894_amd as cast
 
     for dt in (torch.complex64, torch.complex128):

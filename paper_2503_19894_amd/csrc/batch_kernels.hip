@@ -745,7 +745,7 @@ template <typename R>
 __global__ void __launch_bounds__(256, 3) k_batch_step(BatchDev d, int s) {
     __shared__ double red[4];
     const uint64_t r = find_rec(cptr(d.recs), cptr(d.step_rec)[s], cptr(d.step_rec)[s + 1], blockIdx.x);
-    CPtr<BatchRec> rec = cptr(d.recs) + r;   // by pointer: its qhi[] is indexed at run time
+    CPtr<BatchRec> rec = cptr(d.recs) + r;   // by pointer: its bit[] is indexed at run time
     run_item<R>(d, rec, blockIdx.x - rec->item0, red);
 }
 
@@ -786,7 +786,7 @@ __global__ void __launch_bounds__(256) k_batch_persistent(BatchDev d, uint64_t t
             const int s = (int)lo;
             const uint64_t x = item - cptr(d.step_item)[s];
             const uint64_t r = find_rec(cptr(d.recs), cptr(d.step_rec)[s], cptr(d.step_rec)[s + 1], x);
-            CPtr<BatchRec> rec = cptr(d.recs) + r;   // by pointer: its qhi[] is indexed at run time
+            CPtr<BatchRec> rec = cptr(d.recs) + r;   // by pointer: its bit[] is indexed at run time
             if (threadIdx.x == 0) {
                 unsigned long long *done = &counters[(2 + rec->inst) * kCounterStride];
                 if (pend && pend_inst != rec->inst) {

@@ -335,8 +335,9 @@ __device__ __forceinline__ void mfma_in_tile(typename Cx<R>::T *tile, const BlkG
 // compute unit where both fit (23 qubits, complex64, two 4-qubit gates: 44 us
 // against 53 with one of 1024), else one of 1024.  (Two workgroups that read
 // the matrices from global memory ran in step, both loading, then both
-// multiplying.)  Seven 4- and 5-qubit gates on 26 qubits keep the matrix cores
-// busy for 0.6 of the launch's 2.03 ms (complex128) and 1.04 ms (complex64).
+// multiplying.)  In a 21-qubit random circuit, complex128, the matrix cores are
+// busy for 0.43 of the cycles of the launches with one workgroup, 0.15 of the
+// shorter ones with two.
 // NB: 16-byte chunks per lane of the tile, 0: any number (tiles of small
 // states).  Fixed, so that the wait for a tile's loads need not also wait for
 // the stores of the tile before, issued after them.
