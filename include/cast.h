@@ -288,7 +288,7 @@ cast_status stream_scale(void *data, size_t bytes, double factor, int chunks_per
  * segments of one gate run as the ordinary passes of apply_circuit.  The
  * result equals apply_circuit's up to rounding.  The grouping is built on
  * first use for the state's dtype with the "blocked_tile_bits" knob
- * (log2 amplitudes per tile; 2^tile_bits amplitudes must fit 128 KiB) and
+ * (log2 amplitudes per tile; 2^tile_bits amplitudes must fit 64 KiB) and
  * cached in the fused list; device memory for it is owned by the list.
  * Queued on the state's stream; not thread-safe on one fused list. */
 cast_status apply_circuit_blocked(cast_sv *sv, const cast_fused *f);
